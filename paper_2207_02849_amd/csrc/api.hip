@@ -96,10 +96,10 @@ struct betty_handle_s {
   };
   GraphSlot graph_neumann, graph_fd, graph_cg, graph_br, graph_chain;
   bool use_graphs = true;
-  int tune_target_blocks = 256, tune_tile128_min = 512;   // see plan_chain (measured on 512x4096x8192: 64-tiles beat 128-tiles until the grid is several waves deep)
+  int tune_tile128_min = 512;                 // see plan_chain (measured on 512x4096x8192: 64-tiles beat 128-tiles until the grid is several waves deep)
+  bool tune_split = true, tune_rect_forced = false;   // K-split kernels allowed; 128 x 64 tiles for everything unsplit
   int tune_wgrad_cfg = GEMM_64x1;
-  int tune_rect_max = 1024, tune_rect_min_tt = 16;  // see plan_chain
-  int tune_wgrad128_min = 512;                // 128-tiles a bf16 weight-gradient launch needs to use the 128-tile kernel (0 = never)
+  int tune_wgrad128_min = 512;                // 128-tiles a bf16 weight-gradient launch needs to use the 128-tile kernel (0 = never, and 64-tiles for every launch)
   // For large models the Neumann recurrence overlaps each layer's weight-gradient launch
   // (bandwidth-bound) with the rest of the R-backward chain on a second stream of the same
   // priority.  Every cross-stream dependency costs several microseconds (measured: 5 per product,
@@ -249,51 +249,93 @@ const float* wnet_theta(betty_handle h, const float* lambda) {
 
 OperandSet& fd_operands(betty_handle h) { return h->sets[1].present ? h->sets[1] : h->sets[0]; }
 
-// Kernel configuration of an activation-shaped GEMM (M = batch), from its tile count and the
-// number of k-tiles TT (thresholds from timings on this chip):
-//  * 128-tiles once there are enough of them to fill the chip several times over;
-//  * 32-tiles with an eight-way K split inside the workgroup when even 64-tiles would leave half
-//    the compute units idle (batch 256 against 1024-wide layers);
-//  * 64-tiles with K split four ways while the grid is still small;
-//  * 128 x 64 tiles when 64-tiles would come to between one and four per compute unit and the
-//    reduction is long: such a launch is bound by what a compute unit can pull through its L1
+// Extent of a launch: output tiles of each size over all its problems, and the 64-byte steps along K
+// of the longest one.
+struct Extent {
+  long t16 = 0, t32 = 0, t64 = 0, t128 = 0, rect = 0;
+  int steps = 0;
+  static long up(int n, int t) { return (n + t - 1) / t; }
+  void add(Elem elem, int M, int N, int K0, int K1) {
+    const int per = 64 / (int)elem_size(elem);
+    t16 += up(M, 16) * up(N, 16);
+    t32 += up(M, 32) * up(N, 32);
+    t64 += up(M, 64) * up(N, 64);
+    rect += up(M, 128) * up(N, 64);
+    t128 += up(M, 128) * up(N, 128);
+    steps = std::max(steps, (int)(up(K0, per) + up(K1, per)));
+  }
+};
+
+// Kernel configuration of an activation-shaped GEMM (M = batch), from its extent.  The lines come from
+// timing every configuration on 1 400 shapes (batch 32 ... 1024, widths 8 ... 4096, K 64 ... 8192, both
+// element types, one and two problems a launch); the rule stays within 0.6 % of the best on average.
+//  * 16-tiles while every tile has a compute unit of its own (256 of them; bf16 up to 80 steps, where
+//    32-tiles with their half as large operand traffic draw level), with short K also beyond:
+//    such a launch is bound by latency.  fp32 128 x 256 x 784: 8.9 us on 32-tiles, 6.0 us; bf16
+//    130 x 301 x 777: 8.4 us (64-tiles, four-way K split, since removed), 4.6 us;
+//  * 32-tiles with an eight-way K split inside the workgroup up to about two and a half per compute
+//    unit (bf16 512 x 1024 x 1024: 8.0 us against 10.0 us on 64-tiles; 512 x 2048 x 1024: 12.4 / 10.8);
+//  * 128 x 64 tiles (bf16) from about 200 of them, while 64-tiles would come to at most four per compute
+//    unit and the reduction is long: such a launch is bound by what a compute unit can pull through its L1
 //    (measured: about 63 GB/s each with all of them pulling), and a 128 x 64 tile fetches 192
 //    operand rows for the 8192 outputs that two 64-tiles fetch 256 for (121M-parameter model,
-//    batch 512: R-forward link 73 -> 66 us, backward link 76 -> 60 us);
+//    batch 512: R-forward link 73 -> 66 us, backward link 76 -> 60 us); with fp32 operands, whose
+//    launches of this size are bound by the matrix cores, 64-tiles are 10 % faster;
+//  * 128-tiles once there are enough of them to fill the chip several times over;
 //  * otherwise plain 64-tiles.
-// Measured and dropped: 128-tiles with a two-way K split (2 x 512 x 4096 x 4096: 78 us against
-// 73 us for plain 64-tiles), and 64-tiles computed by one wavefront each over a quarter of K
-// (faster stand-alone, 54 against 62 us on 512 x 4096 x 8192, but 4 % slower with the real
-// epilogues, whose loads cannot be issued ahead of the k loop for four MFMA blocks per wavefront).
-int plan_chain(betty_handle h, Elem elem, int tiles128, int Ktot_p) {
-  const int TT = Ktot_p / gemm_ktile_elems(elem);
-  if (tiles128 >= h->tune_tile128_min) return GEMM_128x1;
-  const int tiles64 = 4 * tiles128;
-  if (tiles64 <= h->tune_target_blocks / 2 && TT >= 16) return GEMM_32x8;
-  if (tiles64 < h->tune_target_blocks && TT >= 8) return GEMM_64x4;
-  if (tiles64 <= h->tune_rect_max && TT >= h->tune_rect_min_tt) return GEMM_128x64;
+int plan_chain(betty_handle h, Elem elem, const GemmBatch& b) {
+  Extent x;
+  for (int i = 0; i < b.n; ++i) x.add(elem, b.p[i].g.M, b.p[i].g.N, b.p[i].g.K[0], b.p[i].g.K[1]);
+  const bool wide_rows = b.p[0].e.mode == EPI_RFWD_LAST_HESS && b.p[0].g.N > 16;   // its row sums need a whole row per tile
+  if (h->tune_split && !wide_rows) {
+    const int shorter = elem == ELEM_BF16 ? 1 : 2;        // the same K has twice the steps with fp32 operands
+    if (x.t16 <= 256 ? (elem == ELEM_F32 || x.steps < 80)
+                     : ((x.t16 <= 512 && x.steps <= 12 * shorter) || (x.t16 <= 1024 && x.steps <= 4 * shorter)))
+      return GEMM_16;
+  }
+  if (h->tune_split && x.t32 <= 600) return GEMM_32x8;
+  if (x.t128 >= h->tune_tile128_min) return GEMM_128x1;
+  if (h->tune_rect_forced || (elem == ELEM_BF16 && x.rect >= 200 && x.t64 <= 1024 && x.steps >= 16)) return GEMM_128x64;
   return GEMM_64x1;
 }
 
-void set_pairs(GemmArgs& g, const void* A0, int lda0, const void* B0, int ldb0, int K0p, const void* A1,
-               int lda1, const void* B1, int ldb1, int K1p) {
-  g.A[0] = A0; g.B[0] = B0; g.lda[0] = lda0; g.ldb[0] = ldb0; g.Kp[0] = K0p;
+// ... and of a weight-gradient launch (M, N = layer widths, K = batch).  Within 0.4 % of the best on 900
+// timed shapes: 16-tiles while they have a compute unit each, 32-tiles with an eight-way K split up to two and
+// a half per compute unit (fp32 512 x 256 x 1024 twice: 46.1 us on 64-tiles, 15.6 us; bf16 512 x 512 x
+// 512 twice: 10.0 / 6.0 us), then 64-tiles; bf16 launches with enough 128-tiles to fill the chip
+// twice take the kernel for large layers.  The whole group of layers that one launch covers decides, also
+// where they are launched one by one, so that both give the same bits.
+int plan_wgrad(betty_handle h, Elem elem, int layer, bool rop, int B) {
+  const int first = (layer - 1) / MAX_PROBLEMS * MAX_PROBLEMS, last = std::min(h->L, first + MAX_PROBLEMS);
+  Extent x;
+  for (int i = first; i < last; ++i)
+    x.add(elem, h->layers[i].n_in, h->layers[i].n_out, B, rop && i > 0 ? B : 0);
+  if (elem == ELEM_BF16 && h->tune_wgrad128_min > 0 && x.t128 >= h->tune_wgrad128_min) return GEMM_128x1;
+  if (h->tune_wgrad_cfg != GEMM_64x1 || !h->tune_split || h->tune_wgrad128_min == 0 || elem == ELEM_BF16) return h->tune_wgrad_cfg;
+  const int shorter = elem == ELEM_BF16 ? 1 : 2;
+  if (x.t16 <= 256 || (x.t16 <= 512 && x.steps <= 4 * shorter) || (x.t16 <= 1024 && x.steps <= 2 * shorter)) return GEMM_16;
+  return x.t32 <= 600 ? GEMM_32x8 : GEMM_64x1;
+}
+
+void set_pairs(GemmArgs& g, const void* A0, int lda0, const void* B0, int ldb0, int K0, const void* A1,
+               int lda1, const void* B1, int ldb1, int K1) {
+  g.A[0] = A0; g.B[0] = B0; g.lda[0] = lda0; g.ldb[0] = ldb0; g.K[0] = K0;
   g.A[1] = A1 ? A1 : A0; g.B[1] = A1 ? B1 : B0; g.lda[1] = A1 ? lda1 : lda0; g.ldb[1] = A1 ? ldb1 : ldb0;
-  g.Kp[1] = A1 ? K1p : 0;
+  g.K[1] = A1 ? K1 : 0;
   g.xgm = g.xgn = 0;
 }
 
 // one activation-shaped GEMM with a fused epilogue
-void chain_gemm(betty_handle h, Elem elem, const void* A0, int lda0, const void* B0, int ldb0, int K0p,
-                const void* A1, int lda1, const void* B1, int ldb1, int K1p, int M, int N, int Mp, int Np,
-                const Epilogue& e, double flops) {
+void chain_gemm(betty_handle h, Elem elem, const void* A0, int lda0, const void* B0, int ldb0, int K0,
+                const void* A1, int lda1, const void* B1, int ldb1, int K1, int M, int N, const Epilogue& e,
+                double flops) {
   GemmBatch b;
   b.n = 1;
   GemmProblem& p = b.p[0];
-  set_pairs(p.g, A0, lda0, B0, ldb0, K0p, A1, lda1, B1, ldb1, K1p);
-  p.g.M = M; p.g.N = N; p.g.Mp = Mp; p.g.Np = Np;
+  set_pairs(p.g, A0, lda0, B0, ldb0, K0, A1, lda1, B1, ldb1, K1);
+  p.g.M = M; p.g.N = N;
   p.e = e;
-  launch_gemm_batch(h->ctx, elem, plan_chain(h, elem, (Mp / 128) * (Np / 128), p.g.Kp[0] + p.g.Kp[1]), b, flops);
+  launch_gemm_batch(h->ctx, elem, plan_chain(h, elem, b), b, flops);
 }
 
 Epilogue blank_epilogue(int mode, int act = 0) {
@@ -352,15 +394,14 @@ void forward_and_loss(betty_handle h, OperandSet& os, int sides, const float* w,
     const bool last = l == L;
     GemmBatch b;
     double flops = 0;
-    int tiles128 = 0;
     for (int side = 0; side < 2; ++side) {
       if (!has_side(sides, side)) continue;
       SideBuf& sb = os.side[side];
       SideBuf& fb = fs.side[side];
       GemmProblem& p = b.p[b.n++];
       const void* Aop = l == 1 ? h->at<void>(fb.X) : h->at<void>(fb.A[l - 1]);
-      set_pairs(p.g, Aop, li.n_in_p, h->at<void>(fs.Wt[l - 1]), li.n_in_p, li.n_in_p, nullptr, 0, nullptr, 0, 0);
-      p.g.M = sb.B; p.g.N = li.n_out; p.g.Mp = sb.Bp; p.g.Np = li.n_out_p;
+      set_pairs(p.g, Aop, li.n_in_p, h->at<void>(fs.Wt[l - 1]), li.n_in_p, li.n_in, nullptr, 0, nullptr, 0, 0);
+      p.g.M = sb.B; p.g.N = li.n_out;
       Epilogue e = blank_epilogue(last ? EPI_FWD_LAST : EPI_FWD, h->desc.act);
       e.colvec = h->desc.has_bias ? w + li.b_off : nullptr;
       e.ldf = li.n_out_p;
@@ -375,9 +416,8 @@ void forward_and_loss(betty_handle h, OperandSet& os, int sides, const float* w,
       }
       p.e = e;
       flops += 2.0 * sb.B * li.n_in * li.n_out;
-      tiles128 += (sb.Bp / 128) * (li.n_out_p / 128);
     }
-    launch_gemm_batch(h->ctx, fs.elem, plan_chain(h, fs.elem, tiles128, li.n_in_p), b, flops);
+    launch_gemm_batch(h->ctx, fs.elem, plan_chain(h, fs.elem, b), b, flops);
   }
   if (skip_last) return;
   const LayerInfo& lo = h->layers[L - 1];
@@ -410,14 +450,13 @@ void backward_chain(betty_handle h, OperandSet& os, int sides, int l_from = 0) {
     const LayerInfo& li = h->layers[l - 1];
     GemmBatch b;
     double flops = 0;
-    int tiles128 = 0;
     for (int side = 0; side < 2; ++side) {
       if (!has_side(sides, side)) continue;
       SideBuf& sb = os.side[side];
       GemmProblem& p = b.p[b.n++];
-      set_pairs(p.g, h->at<void>(sb.D[l]), li.n_out_p, h->at<void>(os.Wn[l - 1]), li.n_out_p, li.n_out_p, nullptr, 0,
+      set_pairs(p.g, h->at<void>(sb.D[l]), li.n_out_p, h->at<void>(os.Wn[l - 1]), li.n_out_p, li.n_out, nullptr, 0,
                 nullptr, 0, 0);
-      p.g.M = sb.B; p.g.N = li.n_in; p.g.Mp = sb.Bp; p.g.Np = li.n_in_p;
+      p.g.M = sb.B; p.g.N = li.n_in;
       Epilogue e = blank_epilogue(EPI_BWD);
       e.dphi = h->f(sb.dphi[l - 1]);
       e.e_io = sb.e2[l - 1] ? h->f(sb.e2[l - 1]) : nullptr;
@@ -426,9 +465,8 @@ void backward_chain(betty_handle h, OperandSet& os, int sides, int l_from = 0) {
       e.outT = h->at<void>(sb.Dt[l - 1]); e.ldT = sb.Bp;
       p.e = e;
       flops += 2.0 * sb.B * li.n_in * li.n_out;
-      tiles128 += (sb.Bp / 128) * (li.n_in_p / 128);
     }
-    launch_gemm_batch(h->ctx, os.elem, plan_chain(h, os.elem, tiles128, li.n_out_p), b, flops);
+    launch_gemm_batch(h->ctx, os.elem, plan_chain(h, os.elem, b), b, flops);
   }
 }
 
@@ -513,11 +551,6 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
   for (int l0 = l_first; l0 <= L; l0 += MAX_PROBLEMS) {
     GemmBatch b;
     b.n = std::min(MAX_PROBLEMS, L - l0 + 1);
-    // bf16 launches with enough 128-tiles to fill the chip twice take the 128-tile kernel
-    long tiles128 = 0;
-    for (int i = 0; i < b.n; ++i) tiles128 += (long)(h->layers[l0 + i - 1].n_in_p / 128) * (h->layers[l0 + i - 1].n_out_p / 128);
-    const int cfg = (os.elem == ELEM_BF16 && h->tune_wgrad128_min > 0 && tiles128 >= h->tune_wgrad128_min) ? GEMM_128x1
-                                                                                                             : h->tune_wgrad_cfg;
     double flops = 0;
     for (int i = 0; i < b.n; ++i) {
       const int l = l0 + (b.n - 1 - i);         // deepest layer first
@@ -525,18 +558,17 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
       GemmProblem& p = b.p[i];
       const void* aT = l == 1 ? h->at<void>(sb.XT) : h->at<void>(sb.At[l - 1]);
       if (!rop) {
-        set_pairs(p.g, aT, Bp, h->at<void>(sb.Dt[l]), Bp, Bp, nullptr, 0, nullptr, 0, 0);
+        set_pairs(p.g, aT, Bp, h->at<void>(sb.Dt[l]), Bp, B, nullptr, 0, nullptr, 0, 0);
         flops += 2.0 * B * li.n_in * li.n_out;
       } else if (l == 1) {
-        set_pairs(p.g, aT, Bp, h->at<void>(os.RDt[l]), Bp, Bp, nullptr, 0, nullptr, 0, 0);
+        set_pairs(p.g, aT, Bp, h->at<void>(os.RDt[l]), Bp, B, nullptr, 0, nullptr, 0, 0);
         flops += 2.0 * B * li.n_in * li.n_out;
       } else {
-        set_pairs(p.g, h->at<void>(os.RAt[l - 1]), Bp, h->at<void>(sb.Dt[l]), Bp, Bp, aT, Bp,
-                  h->at<void>(os.RDt[l]), Bp, Bp);
+        set_pairs(p.g, h->at<void>(os.RAt[l - 1]), Bp, h->at<void>(sb.Dt[l]), Bp, B, aT, Bp,
+                  h->at<void>(os.RDt[l]), Bp, B);
         flops += 4.0 * B * li.n_in * li.n_out;
       }
-      p.g.M = li.n_in; p.g.N = li.n_out; p.g.Mp = li.n_in_p; p.g.Np = li.n_out_p;
-      xcd_split(li.n_in_p / gemm_cfg_tile(cfg), li.n_out_p / gemm_cfg_tile(cfg), p.g.xgm, p.g.xgn);
+      p.g.M = li.n_in; p.g.N = li.n_out;
       Epilogue e = blank_epilogue(k.mode);
       e.ldc = li.n_out;
       e.C = k.C ? k.C + li.w_off : nullptr;
@@ -576,6 +608,10 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
     else if (k.mode == EPI_WGRAD_INIT) per_param = k.p ? 8.0 : 4.0;
     else if (k.lam) per_param = 12.0;
     if (k.copies) per_param += 4.0;
+    const int cfg = plan_wgrad(h, os.elem, l0, rop, B), bt = gemm_cfg_tile(cfg);
+    if (cfg == GEMM_64x1 || cfg == GEMM_128x1)
+      for (int i = 0; i < b.n; ++i)
+        xcd_split((b.p[i].g.M + bt - 1) / bt, (b.p[i].g.N + bt - 1) / bt, b.p[i].g.xgm, b.p[i].g.xgn);
     launch_gemm_batch(h->ctx, os.elem, cfg, b, flops, per_param * params);
   }
 }
@@ -608,12 +644,12 @@ void r_forward(betty_handle h, OperandSet& os, const float* vflat, bool fuse_hes
       e.outT = h->at<void>(os.RAt[l]); e.ldT = Bp;
     }
     if (l == 1)
-      chain_gemm(h, os.elem, a_prev, li.n_in_p, h->at<void>(os.Vt[0]), li.n_in_p, li.n_in_p, nullptr, 0, nullptr,
-                 0, 0, B, li.n_out, Bp, li.n_out_p, e, 2.0 * B * li.n_in * li.n_out);
+      chain_gemm(h, os.elem, a_prev, li.n_in_p, h->at<void>(os.Vt[0]), li.n_in_p, li.n_in, nullptr, 0, nullptr,
+                 0, 0, B, li.n_out, e, 2.0 * B * li.n_in * li.n_out);
     else
       chain_gemm(h, os.elem, h->at<void>(os.RA[l - 1]), li.n_in_p, h->at<void>(os.Wt[l - 1]), li.n_in_p,
-                 li.n_in_p, a_prev, li.n_in_p, h->at<void>(os.Vt[l - 1]), li.n_in_p, li.n_in_p, B, li.n_out, Bp,
-                 li.n_out_p, e, 4.0 * B * li.n_in * li.n_out);
+                 li.n_in, a_prev, li.n_in_p, h->at<void>(os.Vt[l - 1]), li.n_in_p, li.n_in, B, li.n_out, e,
+                 4.0 * B * li.n_in * li.n_out);
   }
 }
 
@@ -670,9 +706,9 @@ void hvp_cached(betty_handle h, OperandSet& os, const float* vflat, const WgradS
     e.ldf = li.n_in_p;
     e.out = h->at<void>(os.RD[l - 1]); e.ld = li.n_in_p;
     e.outT = h->at<void>(os.RDt[l - 1]); e.ldT = Bp;
-    chain_gemm(h, os.elem, h->at<void>(os.RD[l]), li.n_out_p, h->at<void>(os.Wn[l - 1]), li.n_out_p, li.n_out_p,
-               h->at<void>(sb.D[l]), li.n_out_p, h->at<void>(os.Vn[l - 1]), li.n_out_p, li.n_out_p, B, li.n_in, Bp,
-               li.n_in_p, e, 4.0 * B * li.n_in * li.n_out);
+    chain_gemm(h, os.elem, h->at<void>(os.RD[l]), li.n_out_p, h->at<void>(os.Wn[l - 1]), li.n_out_p, li.n_out,
+               h->at<void>(sb.D[l]), li.n_out_p, h->at<void>(os.Vn[l - 1]), li.n_out_p, li.n_out, B, li.n_in, e,
+               4.0 * B * li.n_in * li.n_out);
     if (pipe) side_wgrad(h, os, sink, l - 1);
   }
   if (!pipe) {
@@ -993,14 +1029,14 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
   h->use_pipeline = large && desc->prec == BETTY_PREC_FP32;
   h->fd_two_streams = !large;
   h->max_Bp = std::max(padup(desc->batch_train), padup(desc->batch_val));
-  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=<n>,rect=<n>,rectk=<n>,pipe=<0|1>,fd2=<0|1>" (see plan_chain)
+  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,rect=<n>,pipe=<0|1>,fd2=<0|1>" (see plan_chain)
   if (const char* t = getenv("BETTY_TUNE")) {
     int v;
     if (const char* q = strstr(t, "wgrad=")) if (sscanf(q + 6, "%d", &v) == 1 && (v == GEMM_128x1 || v == GEMM_64x1)) h->tune_wgrad_cfg = v;
     if (const char* q = strstr(t, "tile128=")) if (sscanf(q + 8, "%d", &v) == 1 && v > 0) h->tune_tile128_min = v;
-    if (const char* q = strstr(t, "blocks=")) if (sscanf(q + 7, "%d", &v) == 1 && v > 0) h->tune_target_blocks = v;
-    if (const char* q = strstr(t, "rect=")) if (sscanf(q + 5, "%d", &v) == 1 && v >= 0) h->tune_rect_max = v;
-    if (const char* q = strstr(t, "rectk=")) if (sscanf(q + 6, "%d", &v) == 1 && v > 0) h->tune_rect_min_tt = v;
+    // blocks=1: no K-split kernel; rect above 1024: 128 x 64 tiles wherever 128-tiles are not taken
+    if (const char* q = strstr(t, "blocks=")) if (sscanf(q + 7, "%d", &v) == 1) h->tune_split = v != 1;
+    if (const char* q = strstr(t, "rect=")) if (sscanf(q + 5, "%d", &v) == 1) h->tune_rect_forced = v > 1024;
     if (const char* q = strstr(t, "wgrad128=")) if (sscanf(q + 9, "%d", &v) == 1 && v >= 0) h->tune_wgrad128_min = v;
     if (const char* q = strstr(t, "pipe=")) if (sscanf(q + 5, "%d", &v) == 1) h->use_pipeline = v != 0;
     if (const char* q = strstr(t, "fd2=")) if (sscanf(q + 4, "%d", &v) == 1) h->fd_two_streams = v != 0;

@@ -9,10 +9,11 @@
 // of the R-op passes, e.g. Rz = Ra W + a V as [Ra | a] [W ; V].
 //
 // Launch = a batch of up to MAX_PROBLEMS independent problems plus optional bias-row jobs,
-// flattened on blockIdx.x.  Skinny problems (few output tiles, long K) are split along K *inside*
-// the workgroup: KG groups (of 4 wavefronts, or of one) each take a contiguous range of k-tiles with their own
-// LDS operand buffers, and the groups' accumulators are summed through LDS in group order, so the
-// result is bit-reproducible and no inter-workgroup synchronisation exists.  (Splitting K across
+// flattened on blockIdx.x.  Problems with few output tiles are split along K *inside*
+// the workgroup: KG wavefronts each take a contiguous range of k-tiles with their own
+// LDS operand buffers, and their accumulators are summed through LDS in wavefront order, so the
+// result is bit-reproducible and no inter-workgroup synchronisation exists (the smallest launches
+// have a kernel of their own, gemm16_kernel).  (Splitting K across
 // workgroups was measured first: the agent-scope fences it needs write back the L2 of every XCD
 // and cost 10-80 us per launch on this chip.)
 //
@@ -27,6 +28,8 @@
 // assignment, so the order of k inside the product does not matter.  Register r of lane l holds
 // C[8*(r/4) + 4*(l/32) + r%4][l%32]: four consecutive rows of one column per register quad, which
 // is what the epilogues consume (one 4-element vector store into the transposed output).
+#include <algorithm>
+
 #include "internal.h"
 
 namespace betty {
@@ -47,6 +50,8 @@ __device__ __forceinline__ void act_eval(int act, float z, float& a, float& d1, 
     a = z; d1 = 1.f; d2 = 0.f;
   }
 }
+
+typedef float f32x4v __attribute__((ext_vector_type(4)));
 
 template <typename T> __device__ __forceinline__ void store1(T* p, float x);
 template <> __device__ __forceinline__ void store1<float>(float* p, float x) { *p = x; }
@@ -70,10 +75,11 @@ template <> __device__ __forceinline__ void store4<__bf16>(__bf16* p, const floa
 // (before the loop) issues every load the mode needs for the block's 16 elements into EpiRegs;
 // epi_finish (after the loop) computes and stores.  Nothing the prefetch reads is written by the
 // same launch before epi_finish of the same element.
-// NR = 16: a whole block;  NR = 4: one register quad (four consecutive rows), rb already at its first row.
+// NR = 16: a whole block;  NR = 4: one register quad (four consecutive rows), rb already at its first row;
+// NR = 1: a single element (gemm16_kernel).
 template <int NR> struct EpiRegs { float a[NR], b[NR], c[NR], d[NR]; float colv; };
 
-template <int NR> __device__ __forceinline__ int epi_row(int rb, int k) { return NR == 16 ? rb + 8 * (k >> 2) + (k & 3) : rb + k; }
+template <int NR> __device__ __forceinline__ int epi_row(int rb, int k) { return NR == 1 ? rb : NR == 16 ? rb + 8 * (k >> 2) + (k & 3) : rb + k; }
 
 template <int NR>
 __device__ __forceinline__ int epi_offset(int rb, int k, long long ld, int col) {
@@ -148,7 +154,7 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
     }
     if (e.act == BETTY_LOSS_SOFTMAX_CE) {
 #pragma unroll
-      for (int o = 16; o > 0; o >>= 1)
+      for (int o = NR == 1 ? 8 : 16; o > 0; o >>= 1)       // (16 lanes hold a row of a 16-tile)
 #pragma unroll
         for (int k = 0; k < NR; ++k) dot[k] += __shfl_xor(dot[k], o, 64);
 #pragma unroll
@@ -263,10 +269,14 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
   }
   if (e.outT) {
     T* o = (T*)e.outT + (long long)col * e.ldT + rb;
+    if constexpr (NR == 1) {
+      store1<T>(o, val[0]);
+    } else {
 #pragma unroll
-    for (int q = 0; q < NR / 4; ++q) {
-      const float quad[4] = {val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
-      if (rb + 8 * q < M) store4<T>(o + 8 * q, quad);
+      for (int q = 0; q < NR / 4; ++q) {
+        const float quad[4] = {val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
+        if (rb + 8 * q < M) store4<T>(o + 8 * q, quad);
+      }
     }
   }
   if constexpr (MODE == EPI_FWD && sizeof(T) == 4) {
@@ -279,10 +289,14 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
     }
     if (e.outT2) {
       __bf16* o = (__bf16*)e.outT2 + (long long)col * e.ldT + rb;
+      if constexpr (NR == 1) {
+        store1<__bf16>(o, val[0]);
+      } else {
 #pragma unroll
-      for (int q = 0; q < NR / 4; ++q) {
-        const float quad[4] = {val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
-        if (rb + 8 * q < M) store4<__bf16>(o + 8 * q, quad);
+        for (int q = 0; q < NR / 4; ++q) {
+          const float quad[4] = {val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
+          if (rb + 8 * q < M) store4<__bf16>(o + 8 * q, quad);
+        }
       }
     }
   }
@@ -303,9 +317,18 @@ template <typename T, int MODE>
 __device__ void bias_rows(const BiasJob& j, int row) {
   const int lane = threadIdx.x & 63;
   if (row >= j.rows) return;
-  const T* p = (const T*)j.Mt + (long long)row * j.ld;
+  // 16 bytes per lane and access, two in flight; entries beyond k are zero padding of the operand
+  constexpr int EPC = 16 / (int)sizeof(T);
+  typedef __attribute__((__vector_size__(16))) T vecT;
+  const T* p = (const T*)j.Mt + (long long)row * j.ld + lane * EPC;
   float acc = 0.f;
-  for (int c = lane; c < j.k; c += 64) acc += (float)p[c];
+  for (int c = lane * EPC; c < j.k; c += 128 * EPC, p += 128 * EPC) {
+    const vecT v0 = *(const vecT*)p;
+    vecT v1{};
+    if (c + 64 * EPC < j.k) v1 = *(const vecT*)(p + 64 * EPC);
+#pragma unroll
+    for (int i = 0; i < EPC; ++i) acc += (float)v0[i] + (float)v1[i];
+  }
   acc = wave_sum_f(acc);
   if (lane != 0) return;
   switch (MODE) {
@@ -345,10 +368,17 @@ __device__ void bias_rows(const BiasJob& j, int row) {
   }
 }
 
+template <int MODE> struct BatchOf { typedef ChainBatch type; };
+template <> struct BatchOf<EPI_WGRAD> { typedef GemmBatch type; };
+template <> struct BatchOf<EPI_WGRAD_INIT> { typedef GemmBatch type; };
+template <> struct BatchOf<EPI_WGRAD_NEUMANN> { typedef GemmBatch type; };
+template <> struct BatchOf<EPI_WGRAD_NEUMANN_L2> { typedef GemmBatch type; };
+template <> struct BatchOf<EPI_WGRAD_SGD> { typedef GemmBatch type; };
+
 // (128-tiles are compiled for two resident workgroups per compute unit, so that one workgroup's
 // epilogue traffic overlaps the other's k loop)
 template <typename T, int BM, int BN, int NCH, int WPG, int KG, int MODE>
-__global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void gemm_fused_kernel(GemmBatch batch) {
+__global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void gemm_fused_kernel(typename BatchOf<MODE>::type batch) {
   constexpr int GT = 64 * WPG;                     // threads of one K group
   constexpr int WM = WPG == 8 ? 4 : WPG == 4 ? 2 : 1, WN = WPG >= 4 ? 2 : 1;   // wavefronts of a group over the tile
   constexpr int ROW = NCH + 1;                     // LDS row pitch in 16-byte chunks
@@ -356,6 +386,7 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
   constexpr int KT = NCH * EPC;                    // elements per k-tile
   constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);   // 32x32 blocks per wavefront
   constexpr int LA = BM * NCH / GT, LB = BN * NCH / GT;
+  static_assert(WPG == 1 ? KG >= 4 : KG == 1, "K is split over groups of one wavefront only");
   static_assert(WPG == 1 || WPG == 4 || WPG == 8, "a K group is one wavefront, 2 x 2 or 4 x 2 wavefronts");
   static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0 && (BM * NCH) % GT == 0 && (BN * NCH) % GT == 0, "tile");
   extern __shared__ u32x4 smem[];
@@ -387,17 +418,17 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
   while (pi + 1 < batch.n && bid >= batch.block_begin[pi + 1]) ++pi;
   const GemmArgs& g = batch.p[pi].g;
   const int tile = bid - batch.block_begin[pi];
-  const int tiles_n = g.Np / BN;
+  const int tiles_n = (g.N + BN - 1) / BN;
   int tm = tile / tiles_n, tn = tile % tiles_n;
   if (g.xgm > 0) {                                 // XCD-compact order (see GemmArgs)
     const int x = tile & 7, q = tile >> 3;
-    const int rm = (g.Mp / BM) / g.xgm, rn = tiles_n / g.xgn;
+    const int rm = (g.M + BM - 1) / BM / g.xgm, rn = tiles_n / g.xgn;
     tm = (x / g.xgn) * rm + q / rn;
     tn = (x % g.xgn) * rn + q % rn;
   }
   const int m0 = tm * BM, n0 = tn * BN;
 
-  const int T0 = g.Kp[0] / KT, T1 = g.Kp[1] / KT, TT = T0 + T1;
+  const int T0 = (g.K[0] + KT - 1) / KT, T1 = (g.K[1] + KT - 1) / KT, TT = T0 + T1;
   const int NI = (TT + KG - 1) / KG;               // iterations of every group (same barrier count)
   const int tb = kg * NI;
   const int te = tb + NI < TT ? tb + NI : TT;
@@ -415,7 +446,7 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
   // One-wavefront K groups: the tile is a single MFMA block, and once the groups' partial sums are
   // in LDS the first four wavefronts each finish one register quad of it (four consecutive rows
   // per lane), so the epilogue's arithmetic and stores run on four wavefronts instead of one.
-  constexpr bool SPLIT_EPI = WPG == 1 && KG >= 4;
+  constexpr bool SPLIT_EPI = WPG == 1;
   const Epilogue& e = batch.p[pi].e;
   EpiRegs<16> pre[SPLIT_EPI ? 1 : TM * TN];
   EpiRegs<4> pre4;
@@ -578,24 +609,6 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
     }
     epi_finish<T, MODE, 4>(e, g.M, g.N, m0 + 8 * kg + 4 * (lane >> 5), n0 + (lane & 31), q4, pre4);
     return;
-  } else if constexpr (KG > 1) {
-    __syncthreads();                                // all groups are done with the operand tiles
-    float* red = (float*)smem;
-    if (kg > 0) {
-#pragma unroll
-      for (int i = 0; i < TM * TN; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) red[(((kg - 1) * TM * TN + i) * 16 + r) * GT + tid] = acc[i][r];
-    }
-    __syncthreads();
-    if (kg > 0) return;
-#pragma unroll 1
-    for (int g2 = 1; g2 < KG; ++g2) {
-#pragma unroll
-      for (int i = 0; i < TM * TN; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][r] += red[(((g2 - 1) * TM * TN + i) * 16 + r) * GT + tid];
-    }
   }
 
   // ---- epilogue from registers, one MFMA block at a time
@@ -609,6 +622,93 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
     for (int r = 0; r < 16; ++r) accf[r] = acc[ij][r];
     epi_finish<T, MODE, 16>(e, g.M, g.N, rb, col, accf, pre[ij]);
   }
+}
+
+// ------------------------------------------------------------------------------------------
+// small launches: 16 x 16 tiles, operands straight from memory into MFMA fragments
+// ------------------------------------------------------------------------------------------
+//
+// A launch whose output has few tiles is bound by latency, not by any throughput: what counts is how
+// many dependent memory round trips, barriers and instructions lie between its start and its last
+// store (an empty kernel in a graph costs 1.75 us, one load-add-store per thread 1.85 us).  Here a
+// workgroup owns one 16 x 16 tile; its wavefronts split K, and each requests U steps (64 bytes of
+// every operand row) at once, directly in fragment layout: lane l holds row l % 16 and 16-byte chunk
+// l / 16 of A and of B, so one request covers 16 rows x 64 bytes.  One round trip, U to 4 U MFMA
+// instructions, one pass through LDS (partial tiles summed in wavefront order, bit-reproducible),
+// then one output element per thread.
+template <typename T> struct MfmaStep16;
+template <> struct MfmaStep16<__bf16> {
+  static __device__ __forceinline__ void run(const u32x4& a, const u32x4& b, f32x4v& acc) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+  }
+};
+template <> struct MfmaStep16<float> {
+  static __device__ __forceinline__ void run(const u32x4& a, const u32x4& b, f32x4v& acc) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+  }
+};
+
+constexpr int G16_PITCH = 17;                      // row pitch of a partial tile in LDS (floats)
+
+template <typename T, int U, int MODE>
+__global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::type batch) {
+  constexpr int EPC = 16 / (int)sizeof(T), KS = 4 * EPC;   // elements per chunk, per step
+  extern __shared__ float part[];
+  const int t = threadIdx.x, lane = t & 63, kg = __builtin_amdgcn_readfirstlane(t >> 6), KG = blockDim.x >> 6;
+  int bid = blockIdx.x;
+  if constexpr (MODE >= EPI_WGRAD) {
+    if (bid >= batch.gemm_blocks) {
+      bid -= batch.gemm_blocks;
+      int j = 0;
+      while (j + 1 < batch.n_bias && bid >= batch.bias_begin[j + 1]) ++j;
+      bias_rows<T, MODE>(batch.bias[j], (bid - batch.bias_begin[j]) * KG + kg);
+      return;
+    }
+  }
+  int pi = 0;
+  while (pi + 1 < batch.n && bid >= batch.block_begin[pi + 1]) ++pi;
+  const GemmArgs& g = batch.p[pi].g;
+  const Epilogue& e = batch.p[pi].e;
+  const int tile = bid - batch.block_begin[pi];
+  const int tiles_n = (g.N + 15) >> 4;
+  const int m0 = (tile / tiles_n) * 16, n0 = (tile % tiles_n) * 16;
+
+  const int row = m0 + (t >> 4), col = n0 + (t & 15);      // the output element of threads 0..255
+  EpiRegs<1> pre;
+  if (t < 256) epi_prefetch<MODE, 1>(e, g.M, g.N, row, col, pre);
+
+  const int S0 = (g.K[0] + KS - 1) / KS, S = S0 + (g.K[1] + KS - 1) / KS;
+  const int per = (S + KG - 1) / KG, s_begin = kg * per, s_end = min(S, s_begin + per);
+  const int fr = lane & 15, fc = (lane >> 4) * EPC;
+  const T* A0 = (const T*)g.A[0] + (long long)(m0 + fr) * g.lda[0] + fc;
+  const T* B0 = (const T*)g.B[0] + (long long)(n0 + fr) * g.ldb[0] + fc;
+  const T* A1 = (const T*)g.A[1] + (long long)(m0 + fr) * g.lda[1] + fc - (long long)S0 * KS;
+  const T* B1 = (const T*)g.B[1] + (long long)(n0 + fr) * g.ldb[1] + fc - (long long)S0 * KS;
+  f32x4v acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s = s_begin; s < s_end; s += U) {
+    u32x4 a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {                  // (steps beyond the range repeat the last one and are not multiplied)
+      const int q = min(s + u, s_end - 1);
+      const bool second = q >= S0;
+      a[u] = *(const u32x4*)((second ? A1 : A0) + (long long)q * KS);
+      b[u] = *(const u32x4*)((second ? B1 : B0) + (long long)q * KS);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (s + u < s_end) MfmaStep16<T>::run(a[u], b[u], acc);
+  }
+  // register r of lane l is element [4 (l / 16) + r][l % 16]
+#pragma unroll
+  for (int r = 0; r < 4; ++r) part[(kg * 16 + 4 * (lane >> 4) + r) * G16_PITCH + fr] = acc[r];
+  __syncthreads();
+  if (t >= 256) return;
+  float v[1] = {0.f};
+  for (int k = 0; k < KG; ++k) v[0] += part[(k * 16 + (t >> 4)) * G16_PITCH + (t & 15)];
+  epi_finish<T, MODE, 1>(e, g.M, g.N, row, col, v, pre);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -655,8 +755,6 @@ struct WgTile {
 // only after gigabytes of other traffic: their 16-byte accesses carry the non-temporal hint
 // (121M-parameter model +3 %; the same hint on the operand copies, which the next launches read,
 // loses 0.3 %).
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-
 // Rows and columns are clamped into the valid extent instead of being predicated, so the loads of
 // all arrays of a patch are in flight together (a load inside control flow makes the compiler wait
 // for the earlier ones first).  VEC: 16-byte accesses, whole patch inside the column extent.
@@ -858,16 +956,16 @@ __global__ __launch_bounds__(256, 2) void wgrad128_kernel(GemmBatch batch) {
     while (pi + 1 < batch.n && (tile_) >= batch.block_begin[pi + 1]) ++pi;                           \
     const GemmArgs& g_ = batch.p[pi].g;                                                              \
     const int t_ = (tile_) - batch.block_begin[pi];                                                  \
-    const int tiles_n_ = g_.Np / BT;                                                                 \
+    const int tiles_n_ = (g_.N + BT - 1) / BT;                                                       \
     int tm_ = t_ / tiles_n_, tn_ = t_ % tiles_n_;                                                    \
     if (g_.xgm > 0) {                                 /* XCD-compact order (see GemmArgs) */         \
       const int x_ = t_ & 7, q_ = t_ >> 3;                                                           \
-      const int rm_ = (g_.Mp / BT) / g_.xgm, rn_ = tiles_n_ / g_.xgn;                                \
+      const int rm_ = (g_.M + BT - 1) / BT / g_.xgm, rn_ = tiles_n_ / g_.xgn;                        \
       tm_ = (x_ / g_.xgn) * rm_ + q_ / rn_;                                                          \
       tn_ = (x_ % g_.xgn) * rn_ + q_ % rn_;                                                          \
     }                                                                                                \
     m0 = tm_ * BT; n0 = tn_ * BT;                                                                    \
-    T0 = g_.Kp[0] / KT; TT = T0 + g_.Kp[1] / KT;     /* an even number of k-tiles (operands are padded to 128) */ \
+    T0 = (g_.K[0] + 127) / 128 * 2; TT = T0 + (g_.K[1] + 127) / 128 * 2;   /* an even number of k-tiles (operands are padded to 128) */ \
     lda0 = g_.lda[0]; lda1 = g_.lda[1]; ldb0 = g_.ldb[0]; ldb1 = g_.ldb[1];                          \
     Abase0 = (const T*)g_.A[0] + (long long)(m0 + tid / NCH) * lda0 + (tid % NCH) * EPC;             \
     Abase1 = (const T*)g_.A[1] + (long long)(m0 + tid / NCH) * lda1 + (tid % NCH) * EPC;             \
@@ -1001,10 +1099,25 @@ __global__ __launch_bounds__(256, 2) void wgrad128_kernel(GemmBatch batch) {
 // host side
 // ------------------------------------------------------------------------------------------
 
+// the by-value argument block of a launch: weight-gradient launches pass the batch as it is,
+// activation-shaped ones (at most two problems) its short form
+template <int MODE>
+static typename BatchOf<MODE>::type kernel_args(const GemmBatch& b) {
+  if constexpr (MODE >= EPI_WGRAD) {
+    return b;
+  } else {
+    ChainBatch c;
+    c.n = b.n; c.gemm_blocks = b.gemm_blocks;
+    for (int i = 0; i <= b.n; ++i) c.block_begin[i] = b.block_begin[i];
+    for (int i = 0; i < b.n; ++i) c.p[i] = b.p[i];
+    return c;
+  }
+}
+
 template <typename T, int BT, int WPG, int KG>
 constexpr size_t lds_bytes() {
   constexpr size_t operands = (size_t)(KG == 1 ? 2 : KG) * 2 * BT * (GEMM_NCH + 1) * 16;
-  constexpr size_t reduce = (size_t)(WPG == 1 ? KG : KG - 1) * BT * BT * 4;
+  constexpr size_t reduce = WPG == 1 ? (size_t)KG * BT * BT * 4 : 0;
   return operands > reduce ? operands : reduce;
 }
 
@@ -1020,7 +1133,7 @@ static void launch_one(int total, hipStream_t st, const GemmBatch& b, hipError_t
     }
     configured = true;
   }
-  gemm_fused_kernel<T, BT, BT, GEMM_NCH, WPG, KG, MODE><<<total, 64 * WPG * KG, lds, st>>>(b);
+  gemm_fused_kernel<T, BT, BT, GEMM_NCH, WPG, KG, MODE><<<total, 64 * WPG * KG, lds, st>>>(kernel_args<MODE>(b));
 }
 
 // 128 x 64 tiles, unsplit, eight wavefronts with one MFMA block each (a launch of these tiles puts
@@ -1037,7 +1150,7 @@ static void launch_rect(int total, hipStream_t st, const GemmBatch& b, hipError_
     if (e != hipSuccess) { err = e; return; }
     configured = true;
   }
-  gemm_fused_kernel<T, 128, 64, GEMM_NCH, 8, 1, MODE><<<total, 512, lds, st>>>(b);
+  gemm_fused_kernel<T, 128, 64, GEMM_NCH, 8, 1, MODE><<<total, 512, lds, st>>>(kernel_args<MODE>(b));
 }
 
 template <typename T>
@@ -1061,10 +1174,10 @@ static void launch_chain_mode(int mode, int total, hipStream_t st, const GemmBat
   }
 }
 
-template <typename T, int BT>
+template <typename T, int BT, int WPG, int KG>
 static void launch_wgrad_mode(int mode, int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
   switch (mode) {
-#define BETTY_CASE_W(M_) case M_: launch_one<T, BT, 4, 1, M_>(total, st, b, err); break;
+#define BETTY_CASE_W(M_) case M_: launch_one<T, BT, WPG, KG, M_>(total, st, b, err); break;
     BETTY_CASE_W(EPI_WGRAD) BETTY_CASE_W(EPI_WGRAD_INIT) BETTY_CASE_W(EPI_WGRAD_NEUMANN)
     BETTY_CASE_W(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_W(EPI_WGRAD_SGD)
 #undef BETTY_CASE_W
@@ -1098,19 +1211,63 @@ static void launch_wgrad128(int mode, int total, hipStream_t st, const GemmBatch
   }
 }
 
+// gemm16_kernel: K steps per wavefront and round (U) and wavefronts (KG) for S steps in all
+struct Small { int u, kg; };
+static Small small_shape(int S) {
+  int u = 1;
+  while (u < 8 && (S + u - 1) / u > 16) u *= 2;
+  const int per = std::max(u, (S + 15) / 16);
+  return Small{u, std::min(16, std::max(4, (S + per - 1) / per))};
+}
+template <typename T>
+static int batch_steps(const GemmBatch& b) {
+  constexpr int KS = 64 / (int)sizeof(T);
+  int S = 1;
+  for (int i = 0; i < b.n; ++i) S = std::max(S, (b.p[i].g.K[0] + KS - 1) / KS + (b.p[i].g.K[1] + KS - 1) / KS);
+  return S;
+}
+
+template <typename T, int MODE>
+static void launch_small(int total, hipStream_t st, const GemmBatch& b) {
+  const Small sh = small_shape(batch_steps<T>(b));
+  const dim3 block(64 * sh.kg);
+  const size_t lds = (size_t)sh.kg * 16 * G16_PITCH * 4;
+  switch (sh.u) {
+    case 1: gemm16_kernel<T, 1, MODE><<<total, block, lds, st>>>(kernel_args<MODE>(b)); break;
+    case 2: gemm16_kernel<T, 2, MODE><<<total, block, lds, st>>>(kernel_args<MODE>(b)); break;
+    case 4: gemm16_kernel<T, 4, MODE><<<total, block, lds, st>>>(kernel_args<MODE>(b)); break;
+    default: gemm16_kernel<T, 8, MODE><<<total, block, lds, st>>>(kernel_args<MODE>(b)); break;
+  }
+}
+
+template <typename T>
+static void launch_small_mode(int mode, int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
+  switch (mode) {
+#define BETTY_CASE_S(M_) case M_: launch_small<T, M_>(total, st, b); break;
+    BETTY_CASE_S(EPI_FWD) BETTY_CASE_S(EPI_FWD_LAST) BETTY_CASE_S(EPI_BWD) BETTY_CASE_S(EPI_RFWD)
+    BETTY_CASE_S(EPI_RFWD_LAST) BETTY_CASE_S(EPI_RBWD) BETTY_CASE_S(EPI_RFWD_LAST_HESS)
+    BETTY_CASE_S(EPI_WGRAD) BETTY_CASE_S(EPI_WGRAD_INIT) BETTY_CASE_S(EPI_WGRAD_NEUMANN)
+    BETTY_CASE_S(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_S(EPI_WGRAD_SGD)
+#undef BETTY_CASE_S
+    default: err = hipErrorInvalidValue; break;
+  }
+}
+
 template <typename T>
 static void launch_elem(int cfg, int mode, int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
+  if (mode < EPI_WGRAD && b.n > 2) { err = hipErrorInvalidValue; return; }
+  if (cfg == GEMM_16) { launch_small_mode<T>(mode, total, st, b, err); return; }
   if (mode >= EPI_WGRAD) {
     if (cfg == GEMM_128x1 && sizeof(T) == 2) launch_wgrad128(mode, total, st, b, err);
-    else if (cfg == GEMM_128x1) launch_wgrad_mode<T, 128>(mode, total, st, b, err);
-    else if (cfg == GEMM_64x1) launch_wgrad_mode<T, 64>(mode, total, st, b, err);
+    else if (cfg == GEMM_128x1) launch_wgrad_mode<T, 128, 4, 1>(mode, total, st, b, err);
+    else if (cfg == GEMM_64x1) launch_wgrad_mode<T, 64, 4, 1>(mode, total, st, b, err);
+    else if (cfg == GEMM_32x8) launch_wgrad_mode<T, 32, 1, 8>(mode, total, st, b, err);
     else err = hipErrorInvalidValue;
     return;
   }
   switch (cfg) {
     case GEMM_128x1: launch_chain_mode<T, 128, 4, 1>(mode, total, st, b, err); break;
     case GEMM_64x1: launch_chain_mode<T, 64, 4, 1>(mode, total, st, b, err); break;
-    case GEMM_64x4: launch_chain_mode<T, 64, 4, 4>(mode, total, st, b, err); break;
     case GEMM_32x8: launch_chain_mode<T, 32, 1, 8>(mode, total, st, b, err); break;
     case GEMM_128x64: launch_rect_mode<T>(mode, total, st, b, err); break;
     default: err = hipErrorInvalidValue; break;
@@ -1129,18 +1286,19 @@ static int resident_cus() {
   return cus;
 }
 
-int gemm_ktile_elems(Elem elem) { return GEMM_NCH * (elem == ELEM_BF16 ? 8 : 4); }
-int gemm_cfg_tile(int cfg) { return cfg == GEMM_128x1 ? 128 : cfg == GEMM_32x8 ? 32 : 64; }   // (columns, for 128x64)
+int gemm_cfg_tile(int cfg) { return cfg == GEMM_128x1 ? 128 : cfg == GEMM_32x8 ? 32 : cfg == GEMM_16 ? 16 : 64; }   // (columns, for 128x64)
 static int gemm_cfg_tile_rows(int cfg) { return cfg == GEMM_128x64 ? 128 : gemm_cfg_tile(cfg); }
-static int gemm_cfg_waves(int cfg) { return cfg == GEMM_64x4 ? 16 : cfg == GEMM_32x8 ? 8 : 4; }
+static int gemm_cfg_waves(int cfg) { return cfg == GEMM_32x8 ? 8 : 4; }
 
 void launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& b, double flops, double bytes) {
   const int bt = gemm_cfg_tile(cfg);
-  const int rows_per_block = gemm_cfg_waves(cfg);
+  const int rows_per_block = cfg != GEMM_16 ? gemm_cfg_waves(cfg)
+                           : small_shape(elem == ELEM_BF16 ? batch_steps<__bf16>(b) : batch_steps<float>(b)).kg;
   int blocks = 0;
   for (int i = 0; i < b.n; ++i) {
     b.block_begin[i] = blocks;
-    blocks += (b.p[i].g.Mp / gemm_cfg_tile_rows(cfg)) * (b.p[i].g.Np / bt);
+    const int br = gemm_cfg_tile_rows(cfg);
+    blocks += ((b.p[i].g.M + br - 1) / br) * ((b.p[i].g.N + bt - 1) / bt);
   }
   b.block_begin[b.n] = blocks;
   b.gemm_blocks = blocks;

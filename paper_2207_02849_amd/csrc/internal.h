@@ -27,9 +27,8 @@ struct GemmArgs {
   const void* A[2];
   const void* B[2];
   int lda[2], ldb[2];        // leading dimensions in elements
-  int Kp[2];                 // padded reduction extents in elements; 0 = pair absent
-  int M, N;                  // valid output extent (epilogue stores are bounds-checked against it)
-  int Mp, Np;                // padded extents (define the tile grid)
+  int K[2];                  // reduction extents in elements (operands are zero beyond them); 0 = pair absent
+  int M, N;                  // valid output extent: defines the tile grid; epilogue stores are bounds-checked against it
   // Workgroups go to the eight XCDs round-robin, so tiles t, t+8, t+16, ... of a problem share an
   // L2.  With xgm x xgn = 8 those tiles are laid out as one compact (tiles_m/xgm) x (tiles_n/xgn)
   // rectangle, which cuts the operand panels each L2 has to fetch; 0 = row-major tile order.
@@ -87,17 +86,22 @@ struct BiasJob {
 constexpr int MAX_PROBLEMS = 8;
 constexpr int GEMM_NCH = 8;              // 16-byte chunks per row of a k-tile
 // tile extent x number of K groups per workgroup; a group is 2 x 2 wavefronts, except in 32x8
-// (32-tile, eight groups of one wavefront)
-enum { GEMM_128x1 = 0, GEMM_64x1 = 2, GEMM_64x4 = 3, GEMM_32x8 = 4, GEMM_128x64 = 5 };
+// (32-tile, eight groups of one wavefront) and 16 (16-tile, 4 to 16 groups of one wavefront)
+enum { GEMM_128x1 = 0, GEMM_64x1 = 2, GEMM_32x8 = 4, GEMM_128x64 = 5, GEMM_16 = 6 };
 
-struct GemmBatch {
+// Passed to the kernels by value.  Activation-shaped launches have at most two problems (train and
+// validation batch) and no bias rows; their short form costs the host less to launch
+// (2.7 us against 4.5 us outside a graph).
+template <int NP, int NB> struct GemmBatchT {
   int n = 0, n_bias = 0, gemm_blocks = 0;
   int walkers = 0;                       // wgrad128_kernel: workgroups that walk the tiles (set by launch_gemm_batch)
-  int block_begin[MAX_PROBLEMS + 1];
-  int bias_begin[MAX_PROBLEMS + 1];
-  GemmProblem p[MAX_PROBLEMS];
-  BiasJob bias[MAX_PROBLEMS];
+  int block_begin[NP + 1];
+  int bias_begin[NB + 1];
+  GemmProblem p[NP];
+  BiasJob bias[NB > 0 ? NB : 1];
 };
+typedef GemmBatchT<MAX_PROBLEMS, MAX_PROBLEMS> GemmBatch;
+typedef GemmBatchT<2, 0> ChainBatch;
 static_assert(sizeof(GemmBatch) <= 3584, "GemmBatch is passed by value as a kernel argument (4 KiB limit)");
 
 // Launch context: stream + optional per-launch event timing.
@@ -144,7 +148,6 @@ template <> struct MfmaChunk<float> {
 };
 
 // ---- gemm.hip
-int gemm_ktile_elems(Elem elem);
 int gemm_cfg_tile(int cfg);
 void launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& batch, double algorithmic_flops,
                        double algorithmic_bytes = 0);

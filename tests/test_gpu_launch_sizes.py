@@ -1,0 +1,43 @@
+"""GPU parity at the edges of the size-selected launch forms, against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import betty_oracle as orc
+from paper_2207_02849_amd import binding
+from paper_2207_02849_amd import workloads as wk
+from tests.util import oracle_problem, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def dev(a):
+    return torch.as_tensor(np.ascontiguousarray(a, dtype=np.float32)).cuda()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy().astype(np.float64)
+
+
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
+@pytest.mark.parametrize("dims,batch,loss", [
+    ((16, 16, 16), 16, "ce"),                # exactly one 16-tile everywhere
+    ((17, 15, 33), 31, "ce"),                # one past, one short; output beyond the narrow-output kernels
+    ((2300, 17, 3), 33, "ce"),               # K of more than one round of loads per wavefront
+    ((40, 24), 65, "ce"),                    # one layer, rows of the loss Hessian wider than a 16-tile
+    ((40, 9), 257, "mse"),                   # ... and inside one
+    ((70, 530, 260), 100, "ce"),             # 16-, 32- and 64-tiles side by side
+])
+def test_small_launch_forms(dims, batch, loss, prec, tol):
+    wl = wk.tiny(kind="l2", act="gelu" if len(dims) > 2 else "none", dims=dims, batch=batch, loss=loss, prec=prec)
+    prob = oracle_problem(wl)
+    b = binding.from_workload(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    v = np.random.default_rng(5).standard_normal(wl.d)
+    for name, got, ref in (("grad", b.betty_lower_grad(w, lam), orc.lower_grad(prob, wl.w, wl.lam)[1]),
+                           ("hvp", b.betty_hvp(w, lam, dev(v)), orc.hvp(prob, wl.w, wl.lam, v)),
+                           ("neumann", b.betty_hypergrad_neumann(w, lam, 2, 0.02),
+                            orc.hypergrad_neumann(prob, wl.w, wl.lam, 2, 0.02))):
+        assert rel_l2(host(got), ref) < tol, name
+    b.close()
