@@ -73,6 +73,8 @@ def load_library():
         getattr(lib, name).restype = C.c_size_t
     lib.betty_bind.argtypes = [vp, vp, C.c_size_t, vp]
     lib.betty_bind.restype = C.c_int
+    lib.betty_run_on.argtypes = [vp, vp]
+    lib.betty_run_on.restype = C.c_int
     lib.betty_set_batches.argtypes = [vp, Batch, Batch]
     lib.betty_set_batches.restype = C.c_int
     lib.betty_lower_grad.argtypes = [vp, f32p, f32p, f32p, f32p]
@@ -138,35 +140,49 @@ class Betty:
         self.batch_train, self.batch_val = batch_train, batch_val
         nbytes = self.lib.betty_workspace_bytes(self.h)
         self._keep = []
+        self._index = self.device.index if self.device.index is not None else torch.cuda.current_device()
+        self._own = bind and stream is None
         if not bind:
             self.workspace = None
-            self.stream = torch.cuda.current_stream(self.device) if stream is None else stream
+            self._stream = torch.cuda.current_stream(self.device) if stream is None else stream
             return
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
-        # The library captures repeated calls into HIP graphs and overlaps launches on a second stream;
-        # neither is possible on the legacy default stream, so without an explicit stream the handle
-        # gets one of its own (default priority).  Whenever the handle's stream is not the caller's
-        # current torch stream, every call is ordered against that stream with events, before and after.
+        # Without an explicit stream the handle follows the caller: every call runs on the torch stream
+        # that is current at the time, behind the handle's earlier calls (waiting for another stream
+        # costs tens of microseconds a call, so none is involved as long as the current stream stays the
+        # same).  It also has a stream of its own (default priority); whoever asks for it through
+        # `stream` finds it ordered behind the calls made so far.
+        # With an explicit stream the calls run on that stream, ordered with events against the caller's
+        # current torch stream, before and after, where the two differ.
         # Handles that work together (betty_hypergrad_chain3) must share a stream: pass the first one's.
-        self.stream = torch.cuda.Stream(self.device) if stream is None else stream
+        self._stream = torch.cuda.Stream(self.device) if stream is None else stream
         cur = torch.cuda.current_stream(self.device)
-        if cur.cuda_stream != self.stream.cuda_stream:
-            self.stream.wait_stream(cur)
-        self._check(self.lib.betty_bind(self.h, self.workspace.data_ptr(), nbytes, self.stream.cuda_stream))
-        self._keep = []
+        if cur.cuda_stream != self._stream.cuda_stream:
+            self._stream.wait_stream(cur)
+        self._check(self.lib.betty_bind(self.h, self.workspace.data_ptr(), nbytes, self._stream.cuda_stream))
+
+    @property
+    def stream(self):
+        if self._own and self.h.value:
+            self._check(self.lib.betty_run_on(self.h, self._stream.cuda_stream))
+        return self._stream
 
     def _check(self, st):
         if st != OK:
             raise BettyError(st, self.lib.betty_last_error(self.h).decode())
 
     def _call(self, fn, *args):
+        if self._own:
+            st = self.lib.betty_run_on(self.h, torch._C._cuda_getCurrentRawStream(self._index))
+            self._check(st or fn(self.h, *args))
+            return
         cur = torch.cuda.current_stream(self.device)
-        foreign = cur.cuda_stream != self.stream.cuda_stream
+        foreign = cur.cuda_stream != self._stream.cuda_stream
         if foreign:
-            self.stream.wait_stream(cur)
-        st = fn(self.h, *args)
+            self._stream.wait_stream(cur)
+        st = self.lib.betty_run_on(self.h, self._stream.cuda_stream) or fn(self.h, *args)
         if foreign:
-            cur.wait_stream(self.stream)
+            cur.wait_stream(self._stream)
         self._check(st)
 
     def close(self):
@@ -222,7 +238,8 @@ class Betty:
         tr = Batch(_ptr(X_tr, torch.float32, self.batch_train * n0),
                    _ptr(y_tr, torch.int32, self.batch_train) if y_tr is not None else None,
                    _ptr(t_tr, torch.float32, self.batch_train * nL) if t_tr is not None else None)
-        self._call(lambda h, *a: self.lib.betty_hvp_static(h, tr, self.stream.cuda_stream, *a),
+        stream = torch.cuda.current_stream(self.device) if self._own else self._stream
+        self._call(lambda h, *a: self.lib.betty_hvp_static(h, tr, stream.cuda_stream, *a),
                    _ptr(w, torch.float32, self.d), _ptr(lam, torch.float32, self.n_hyper),
                    _ptr(v, torch.float32, self.d), _ptr(Hv, torch.float32, self.d))
         return Hv

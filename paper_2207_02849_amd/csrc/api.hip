@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
+#include <initializer_list>
 #include <new>
 #include <cstring>
 #include <mutex>
@@ -76,25 +77,39 @@ struct betty_handle_s {
   char* ws = nullptr;
   size_t ws_need = 0;
   bool bound = false, batches = false;
-  unsigned long long epoch = 0;   // process-wide unique stamp of the last betty_bind / betty_set_batches
-  betty_batch batch[2]{};
+  unsigned long long epoch = 0;   // process-wide unique stamp of the last betty_bind
   OperandSet sets[2];        // [0]: element type of desc.prec; [1]: fp32 set for finite differences when prec is bf16
   OperandSet fd_minus;       // fp32, train side only: the evaluation at w - eps v, which runs beside the one at w + eps v
   size_t vec_g = 0, vec_v = 0, vec_p = 0, vec_Hv = 0, vec_wpm = 0, vec_Gm = 0;
   size_t vec_wpm2 = 0, vec_g2 = 0;   // the second evaluation's perturbed point and anchor distance
   size_t partials = 0, scalars = 0;
+  size_t labels = 0;         // Labels[2]: train, validation
   size_t logrho = 0;         // proximal cost: log(rho_j) per parameter (a large negative value where rho_j = 0)
-  // a hypergradient call repeated with the same arguments is replayed from a captured HIP graph
+  // A call repeated with the same arguments is replayed from a captured HIP graph.  Each kind of call
+  // keeps the graphs of its last few argument sets: results that a caller lets the allocator place
+  // alternate between a few addresses.
+  struct CallKey {
+    const void* ptr[6] = {};
+    int k[2] = {-1, -1};
+    float f[4] = {};
+    unsigned long long other_epoch = 0;       // the three-level chain: the binding of its other handle
+    bool operator==(const CallKey& o) const {
+      return !memcmp(ptr, o.ptr, sizeof ptr) && !memcmp(k, o.k, sizeof k) && !memcmp(f, o.f, sizeof f) && other_epoch == o.other_epoch;
+    }
+  };
   struct GraphSlot {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    const void* w = nullptr; const void* lam = nullptr; const void* u = nullptr; void* out = nullptr;
-    int K = -1; float alpha = 0.f, eps = 0.f;
-    int K2 = -1; float alpha2 = 0.f; const void* other = nullptr;   // second level of the three-level chain
-    unsigned long long other_epoch = 0;                             // ... and the state of its handle when recorded
-    int seen = 0;
+    CallKey key;
+    unsigned long long used = 0;              // 0: empty
   };
-  GraphSlot graph_neumann, graph_fd, graph_cg, graph_br, graph_chain;
+  enum { CALL_NEUMANN, CALL_FD, CALL_CG, CALL_BEST_RESPONSE, CALL_CHAIN, CALL_HVP, CALL_LOWER, CALL_UPPER, CALL_MIXED, CALL_SGD, CALL_KINDS };
+  static constexpr int SLOTS = 4;
+  GraphSlot graphs[CALL_KINDS][SLOTS];
+  unsigned long long graph_clock = 0;
+  hipStream_t capture_stream = nullptr;       // sequences are recorded here and replayed on ctx.stream
+  hipStream_t bound_stream = nullptr;         // betty_bind; ctx.stream is where the calls run (betty_run_on)
+  hipEvent_t order_event = nullptr;
   bool use_graphs = true;
   int tune_tile128_min = 512;                 // see plan_chain (measured on 512x4096x8192: 64-tiles beat 128-tiles until the grid is several waves deep)
   bool tune_split = true, tune_rect_forced = false;   // K-split kernels allowed; 128 x 64 tiles for everything unsplit
@@ -140,14 +155,16 @@ struct Planner {
   }
 };
 
-void plan_side(betty_handle h, Planner& pl, SideBuf& sb, Elem elem, int B, bool lower) {
+void plan_side(betty_handle h, Planner& pl, SideBuf& sb, Elem elem, int B, bool lower, bool inputs = true) {
   const int L = h->L;
   const size_t es = elem_size(elem);
   sb.B = B;
   sb.Bp = padup(B);
   const size_t Bp = sb.Bp;
-  sb.X = pl.take(Bp * h->layers[0].n_in_p * es);
-  sb.XT = pl.take((size_t)h->layers[0].n_in_p * Bp * es);
+  if (inputs) {
+    sb.X = pl.take(Bp * h->layers[0].n_in_p * es);
+    sb.XT = pl.take((size_t)h->layers[0].n_in_p * Bp * es);
+  }
   sb.A.assign(L + 1, 0); sb.At.assign(L + 1, 0); sb.D.assign(L + 1, 0); sb.Dt.assign(L + 1, 0);
   sb.dphi.assign(L + 1, 0); sb.e2.assign(L + 1, 0);
   for (int l = 1; l <= L; ++l) {
@@ -186,7 +203,7 @@ void plan_set(betty_handle h, Planner& pl, OperandSet& os, Elem elem, bool secon
   const size_t es = elem_size(elem);
   os.elem = elem;
   os.present = true;
-  plan_side(h, pl, os.side[0], elem, h->desc.batch_train, true);
+  plan_side(h, pl, os.side[0], elem, h->desc.batch_train, true, scope != SET_TRAIN_ONLY);
   os.Wn.assign(L, 0); os.Wt.assign(L, 0); os.Vn.assign(L, 0); os.Vt.assign(L, 0);
   for (int i = 0; i < L; ++i) {
     const size_t m = (size_t)h->layers[i].n_in_p * h->layers[i].n_out_p * es;
@@ -216,6 +233,8 @@ void plan_set(betty_handle h, Planner& pl, OperandSet& os, Elem elem, bool secon
   }
 }
 
+OperandSet& fd_operands(betty_handle h) { return h->sets[1].present ? h->sets[1] : h->sets[0]; }
+
 void plan(betty_handle h) {
   Planner pl;
   const Elem main_elem = h->desc.prec == BETTY_PREC_BF16_FP32ACC ? ELEM_BF16 : ELEM_F32;
@@ -226,12 +245,15 @@ void plan(betty_handle h) {
   h->vec_wpm = pl.take(vb); h->vec_Gm = pl.take(vb);
   if (h->fd_two_streams) {
     plan_set(h, pl, h->fd_minus, ELEM_F32, false, SET_TRAIN_ONLY);
+    h->fd_minus.side[0].X = fd_operands(h).side[0].X;      // the same inputs
+    h->fd_minus.side[0].XT = fd_operands(h).side[0].XT;
     h->vec_wpm2 = pl.take(vb);
     if (h->desc.hp == BETTY_HP_PROXIMAL) h->vec_g2 = pl.take(vb);
   }
   if (h->desc.hp == BETTY_HP_PROXIMAL) h->logrho = pl.take(vb);
   h->partials = pl.take(1024 * 8);
   h->scalars = pl.take(256);
+  h->labels = pl.take(2 * sizeof(Labels));
   h->ws_need = pl.off;
 }
 
@@ -246,8 +268,6 @@ const float* diag_log(betty_handle h, const float* lambda) {
 const float* wnet_theta(betty_handle h, const float* lambda) {
   return h->desc.hp == BETTY_HP_REWEIGHT_NET ? lambda : nullptr;
 }
-
-OperandSet& fd_operands(betty_handle h) { return h->sets[1].present ? h->sets[1] : h->sets[0]; }
 
 // Extent of a launch: output tiles of each size over all its problems, and the 64-byte steps along K
 // of the longest one.
@@ -348,14 +368,14 @@ Epilogue blank_epilogue(int mode, int act = 0) {
 
 // operand copies of a flat parameter-shaped vector: per layer, as stored (n_in x n_out) and
 // transposed; all layers in one launch (eight per launch)
-void make_shadows(betty_handle h, OperandSet& os, const float* flat, float scale,
-                  std::vector<size_t>* N, std::vector<size_t>* T, std::vector<size_t>* T32 = nullptr) {
+void make_shadows(betty_handle h, OperandSet& os, const float* flat, std::vector<size_t>* N,
+                  std::vector<size_t>* T, std::vector<size_t>* T32 = nullptr) {
   for (int i0 = 0; i0 < h->L; i0 += MAX_PROBLEMS) {
     ConvertBatch b;
     b.n = std::min(MAX_PROBLEMS, h->L - i0);
     for (int k = 0; k < b.n; ++k) {
       const LayerInfo& li = h->layers[i0 + k];
-      b.j[k] = ConvertJob{flat + li.w_off, li.n_out, scale, li.n_in, li.n_out,
+      b.j[k] = ConvertJob{flat + li.w_off, li.n_out, li.n_in, li.n_out,
                           N ? h->at<void>((*N)[i0 + k]) : nullptr, li.n_out_p,
                           T ? h->at<void>((*T)[i0 + k]) : nullptr, li.n_in_p};
       if (T32) b.j[k].outT32 = h->f((*T32)[i0 + k]);
@@ -375,7 +395,7 @@ bool hybrid_forward(betty_handle h, const OperandSet& os) {
 // operand copies of the parameters w for everything that follows
 void make_weight_operands(betty_handle h, OperandSet& os, const float* w) {
   // (with the fp32 forward of ReLU networks the same launch also leaves the fp32 transposed copies)
-  make_shadows(h, os, w, 1.f, &os.Wn, &os.Wt, hybrid_forward(h, os) ? &h->sets[1].Wt : nullptr);
+  make_shadows(h, os, w, &os.Wn, &os.Wt, hybrid_forward(h, os) ? &h->sets[1].Wt : nullptr);
 }
 
 // Which batches a pass covers: the train (lower) side, the validation (upper) side, or both in
@@ -431,7 +451,7 @@ void forward_and_loss(betty_handle h, OperandSet& os, int sides, const float* w,
     a.reweight = (side == 0 && h->desc.hp == BETTY_HP_REWEIGHT_NET) ? 1 : 0;
     a.hidden = h->desc.wnet_hidden;
     a.Z = h->f(sb.ZL); a.ldz = lo.n_out_p;
-    a.y = h->batch[side].y; a.target = h->batch[side].target; a.C = lo.n_out;
+    a.labels = h->at<Labels>(h->labels) + side; a.C = lo.n_out;
     a.theta = theta;
     a.omega_fixed = side == 0 ? omega_fixed : nullptr;
     a.rows = sb.B; a.inv_batch = 1.0f / (float)sb.B;
@@ -491,7 +511,7 @@ void forward_backward(betty_handle h, OperandSet& os, int sides, const float* w,
     SideBuf& sb = os.side[side];
     LastGradSide& d = a.side[a.n_sides++];
     d.A = h->at<void>(sb.A[L - 1]); d.lda = lo.n_in_p;
-    d.y = h->batch[side].y; d.target = h->batch[side].target;
+    d.labels = h->at<Labels>(h->labels) + side;
     d.omega_fixed = side == 0 ? omega_fixed : nullptr;
     d.ZL = h->f(sb.ZL); d.P = h->f(sb.P); d.ldz = lo.n_out_p;
     d.ell = h->f(sb.ell); d.s = h->f(sb.s); d.omega = h->f(sb.omega); d.dsig = h->f(sb.dsig);
@@ -770,7 +790,7 @@ void mixed_reweight_seq(betty_handle h, OperandSet& os, const float* lam, const 
   const int L = h->L;
   const LayerInfo& lo = h->layers[L - 1];
   // c_i is linear in the direction, so the scale is applied once, to the final sum over samples
-  if (!copies_current) make_shadows(h, os, qflat, 1.f, nullptr, &os.Vt);   // else os.Vt already holds qflat
+  if (!copies_current) make_shadows(h, os, qflat, nullptr, &os.Vt);   // else os.Vt already holds qflat
   if (L >= 2 && lo.n_out <= LAST_ROP_MAX_C) {
     // narrow output layer: the last product and the directional derivative in one vector kernel
     r_forward(h, os, qflat, false, L - 1);
@@ -780,12 +800,12 @@ void mixed_reweight_seq(betty_handle h, OperandSet& os, const float* lam, const 
     a.cbias = h->desc.has_bias ? qflat + lo.b_off : nullptr;
     a.P = h->f(sb.P); a.ldp = lo.n_out_p;
     a.B = sb.B; a.n_in = lo.n_in; a.n_in_p = lo.n_in_p; a.C = lo.n_out; a.loss = h->desc.loss;
-    a.cvec = h->f(os.cvec); a.y = h->batch[0].y; a.Z = h->f(sb.ZL); a.target = h->batch[0].target;
+    a.cvec = h->f(os.cvec); a.labels = h->at<Labels>(h->labels); a.Z = h->f(sb.ZL);
     launch_last_layer_rop(h->ctx, os.elem, a);
   } else {
     r_forward(h, os, qflat);
-    launch_loss_directional_rows(h->ctx, h->desc.loss, h->f(sb.P), h->f(sb.ZL), h->batch[0].y,
-                                 h->batch[0].target, h->f(os.Rz[L]), lo.n_out_p, sb.B, lo.n_out, h->f(os.cvec));
+    launch_loss_directional_rows(h->ctx, h->desc.loss, h->f(sb.P), h->f(sb.ZL), h->at<Labels>(h->labels),
+                                 h->f(os.Rz[L]), lo.n_out_p, sb.B, lo.n_out, h->f(os.cvec));
   }
   launch_wnet_theta_vjp(h->ctx, h->f(sb.ell), h->f(sb.dsig), h->f(os.cvec), lam, h->desc.wnet_hidden, sb.B,
                         scale / (float)sb.B, out);
@@ -858,56 +878,83 @@ static void drop_graph(betty_handle_s::GraphSlot& g) {
 }
 
 static void drop_graphs(betty_handle h) {
-  drop_graph(h->graph_neumann); drop_graph(h->graph_fd); drop_graph(h->graph_cg); drop_graph(h->graph_br);
-  drop_graph(h->graph_chain);
+  for (auto& kind : h->graphs)
+    for (auto& g : kind) drop_graph(g);
 }
 
-// Runs `body` (which only enqueues kernels on the bound stream) directly the first time a given
+// Moves the handle's work to another stream, behind everything it has enqueued so far.
+static hipError_t move_to_stream(betty_handle h, hipStream_t to) {
+  if (h->ctx.stream == to) return hipSuccess;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t e = hipSuccess;
+  if (hipStreamIsCapturing(to, &cap) != hipSuccess) (void)hipGetLastError();
+  if (cap == hipStreamCaptureStatusNone) {          // (a stream being captured cannot wait for work outside its graph)
+    if (!h->order_event) e = hipEventCreateWithFlags(&h->order_event, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(h->order_event, h->ctx.stream);
+    if (e == hipSuccess) e = hipStreamWaitEvent(to, h->order_event, 0);
+  }
+  if (e == hipSuccess) h->ctx.stream = to;
+  return e;
+}
+
+// Runs `body` (which only enqueues kernels on ctx.stream) directly the first time a given
 // argument set is seen, captures it into a graph the second time, and replays the graph from then
 // on.  Any capture failure switches graphs off for the handle and runs the body directly.
 template <typename Body>
-static betty_status run_cached(betty_handle h, betty_handle_s::GraphSlot& g, const void* w, const void* lam,
-                               const void* u, void* out, int K, float alpha, float eps, Body body,
-                               int K2 = -1, float alpha2 = 0.f, const void* other = nullptr,
-                               unsigned long long other_epoch = 0) {
-  const bool eligible = h->use_graphs && !h->ctx.profiling && h->ctx.stream != nullptr;
-  if (!eligible) { body(); return finish(h); }
-  const bool same = g.seen > 0 && g.w == w && g.lam == lam && g.u == u && g.out == out && g.K == K &&
-                    g.alpha == alpha && g.eps == eps && g.K2 == K2 && g.alpha2 == alpha2 && g.other == other &&
-                    g.other_epoch == other_epoch;
-  if (same && g.exec) {
-    if (hipGraphLaunch(g.exec, h->ctx.stream) != hipSuccess) return fail(h, BETTY_EDEVICE, "hipGraphLaunch failed");
-    return BETTY_OK;
+static betty_status run_cached(betty_handle h, int kind, const betty_handle_s::CallKey& key, Body body) {
+  if (!h->use_graphs || h->ctx.profiling) { body(); return finish(h); }
+  betty_handle_s::GraphSlot* g = nullptr;
+  betty_handle_s::GraphSlot* oldest = &h->graphs[kind][0];
+  for (auto& s : h->graphs[kind]) {
+    if (s.used && s.key == key) g = &s;
+    if (s.used < oldest->used) oldest = &s;
   }
-  if (!same) {
-    drop_graph(g);
-    g.w = w; g.lam = lam; g.u = u; g.out = out; g.K = K; g.alpha = alpha; g.eps = eps; g.seen = 1;
-    g.K2 = K2; g.alpha2 = alpha2; g.other = other; g.other_epoch = other_epoch;
+  if (!g) {
+    drop_graph(*oldest);
+    oldest->key = key;
+    oldest->used = ++h->graph_clock;
     body();
     return finish(h);
   }
-  if (hipStreamBeginCapture(h->ctx.stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-    (void)hipGetLastError();
-    h->use_graphs = false;
+  g->used = ++h->graph_clock;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(h->ctx.stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();                        // the caller is recording a graph of its own
     body();
     return finish(h);
   }
-  body();
-  hipGraph_t graph = nullptr;
-  const hipError_t e_end = hipStreamEndCapture(h->ctx.stream, &graph);
-  hipGraphExec_t exec = nullptr;
-  if (e_end != hipSuccess || h->ctx.first_error != hipSuccess || !graph ||
-      hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) {
-    (void)hipGetLastError();
-    if (graph) (void)hipGraphDestroy(graph);
-    h->ctx.first_error = hipSuccess;
-    h->use_graphs = false;
-    body();                     // nothing ran during the failed capture
-    return finish(h);
+  if (!g->exec) {
+    const hipStream_t run = h->ctx.stream;
+    hipError_t e = hipSuccess;
+    if (!h->capture_stream) e = hipStreamCreateWithFlags(&h->capture_stream, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipStreamBeginCapture(h->capture_stream, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+      h->ctx.stream = h->capture_stream;
+      body();
+      h->ctx.stream = run;
+      e = hipStreamEndCapture(h->capture_stream, &g->graph);
+    }
+    if (e == hipSuccess) e = h->ctx.first_error;
+    if (e == hipSuccess) e = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      drop_graph(*g);
+      h->ctx.first_error = hipSuccess;
+      h->use_graphs = false;
+      body();                                       // nothing ran during the failed capture
+      return finish(h);
+    }
   }
-  g.graph = graph; g.exec = exec;
-  if (hipGraphLaunch(g.exec, h->ctx.stream) != hipSuccess) return fail(h, BETTY_EDEVICE, "hipGraphLaunch failed");
+  if (hipGraphLaunch(g->exec, h->ctx.stream) != hipSuccess) return fail(h, BETTY_EDEVICE, "hipGraphLaunch failed");
   return BETTY_OK;
+}
+
+static betty_handle_s::CallKey call_key(std::initializer_list<const void*> ptr, int K = -1, std::initializer_list<float> f = {}) {
+  betty_handle_s::CallKey key;
+  std::copy(ptr.begin(), ptr.end(), key.ptr);
+  std::copy(f.begin(), f.end(), key.f);
+  key.k[0] = K;
+  return key;
 }
 
 static betty_status check_hyper_args(betty_handle h, const float* w, const float* lambda, int K, float alpha,
@@ -938,7 +985,7 @@ static void neumann_seq(betty_handle h, const float* w, const float* lambda, con
   // written by whichever launch produces that sum
   if (u_or_null) {
     if (need_lower) prepare_lower(h, os, w, lambda);
-    if (K > 0 || rw) make_shadows(h, os, u_or_null, 1.f, &os.Vn, &os.Vt);
+    if (K > 0 || rw) make_shadows(h, os, u_or_null, &os.Vn, &os.Vt);
   } else {
     // g = grad_w L_U lands in vec_v, with its operand copies for the first product
     WgradSink init{EPI_WGRAD_INIT, nullptr, nullptr, nullptr, h->f(h->vec_v), nullptr, 0.f, K > 0 || rw};
@@ -1050,6 +1097,8 @@ void betty_destroy(betty_handle h) {
   if (!h) return;
   drop_graphs(h);
   release_side_stream(h);
+  if (h->capture_stream) (void)hipStreamDestroy(h->capture_stream);
+  if (h->order_event) (void)hipEventDestroy(h->order_event);
   for (auto& r : h->ctx.recs) { (void)hipEventDestroy(r.e0); (void)hipEventDestroy(r.e1); }
   delete h;
 }
@@ -1065,7 +1114,7 @@ betty_status betty_bind(betty_handle h, void* workspace, size_t bytes, void* hip
   if (((uintptr_t)workspace) & 255) return fail(h, BETTY_EALIGN, "workspace is not 256-byte aligned");
   if (bytes < h->ws_need) return fail(h, BETTY_EWORKSPACE, "workspace has %zu bytes, %zu needed", bytes, h->ws_need);
   h->ws = (char*)workspace;
-  h->ctx.stream = (hipStream_t)hip_stream;
+  h->ctx.stream = h->bound_stream = (hipStream_t)hip_stream;
   if (!h->side_stream && hip_stream != nullptr) {
     // second stream (default priority) and the events that order it against the bound stream
     bool ok = hipStreamCreateWithFlags(&h->side_stream, hipStreamNonBlocking) == hipSuccess;
@@ -1083,6 +1132,32 @@ betty_status betty_bind(betty_handle h, void* workspace, size_t bytes, void* hip
   return finish(h);
 }
 
+betty_status betty_run_on(betty_handle h, void* hip_stream) {
+  if (!h) return BETTY_ENULL;
+  if (!h->bound) return BETTY_OK;
+  const hipError_t e = move_to_stream(h, (hipStream_t)hip_stream);
+  return e == hipSuccess ? BETTY_OK : fail(h, BETTY_EDEVICE, "HIP error: %s", hipGetErrorString(e));
+}
+
+// X of the first n batches (train, validation) into every operand set that reads it, and the places of
+// the labels, in one launch
+static void convert_inputs(betty_handle h, const betty_batch* b, int n) {
+  const LayerInfo& l0 = h->layers[0];
+  ConvertBatch cb;
+  cb.n = n;
+  for (int s = 0; s < n; ++s) {
+    const SideBuf& sb = h->sets[0].side[s];
+    cb.j[s] = ConvertJob{b[s].x, l0.n_in, sb.B, l0.n_in, h->at<void>(sb.X), l0.n_in_p, h->at<void>(sb.XT), sb.Bp};
+    if (h->sets[1].present) {
+      cb.j[s].out32 = h->f(h->sets[1].side[s].X);
+      cb.j[s].outT32 = h->f(h->sets[1].side[s].XT);
+    }
+  }
+  cb.table = h->at<Labels>(h->labels);
+  for (int s = 0; s < 2; ++s) cb.labels[s] = Labels{b[s < n ? s : 0].y, b[s < n ? s : 0].target};
+  launch_convert_batch(h->ctx, h->sets[0].elem, cb);
+}
+
 betty_status betty_set_batches(betty_handle h, betty_batch train, betty_batch val) {
   if (!h) return BETTY_ENULL;
   if (!h->bound) return fail(h, BETTY_EWORKSPACE, "no workspace bound (call betty_bind)");
@@ -1092,25 +1167,7 @@ betty_status betty_set_batches(betty_handle h, betty_batch train, betty_batch va
     if (h->desc.loss == BETTY_LOSS_SOFTMAX_CE) CHECK(check_vec(h, b[s].y, s ? "val.y" : "train.y"));
     else CHECK(check_vec(h, b[s].target, s ? "val.target" : "train.target"));
   }
-  drop_graphs(h);
-  h->epoch = next_epoch();
-  h->batch[0] = train;
-  h->batch[1] = val;
-  const LayerInfo& l0 = h->layers[0];
-  for (int k = 0; k < 2; ++k) {
-    OperandSet& os = h->sets[k];
-    if (!os.present) continue;
-    for (int s = 0; s < 2; ++s) {
-      SideBuf& sb = os.side[s];
-      launch_convert_dual(h->ctx, os.elem, b[s].x, l0.n_in, 1.f, sb.B, l0.n_in, h->at<void>(sb.X), l0.n_in_p,
-                          h->at<void>(sb.XT), sb.Bp);
-    }
-  }
-  if (h->fd_minus.present) {
-    SideBuf& sb = h->fd_minus.side[0];
-    launch_convert_dual(h->ctx, ELEM_F32, b[0].x, l0.n_in, 1.f, sb.B, l0.n_in, h->at<void>(sb.X), l0.n_in_p,
-                        h->at<void>(sb.XT), sb.Bp);
-  }
+  convert_inputs(h, b, 2);
   h->batches = true;
   return finish(h);
 }
@@ -1122,10 +1179,11 @@ betty_status betty_lower_grad(betty_handle h, const float* w, const float* lambd
   if (loss_or_null) CHECK(check_vec(h, loss_or_null, "loss"));
   if (overlaps(grad_w, h->d * 4, w, h->d * 4) || overlaps(grad_w, h->d * 4, lambda, h->n_hyper * 4))
     return fail(h, BETTY_EINVAL, "grad_w overlaps an input");
-  OperandSet& os = h->sets[0];
-  make_weight_operands(h, os, w);
-  lower_grad_seq(h, os, w, lambda, grad_w, loss_or_null);
-  return finish(h);
+  return run_cached(h, h->CALL_LOWER, call_key({w, lambda, grad_w, loss_or_null}), [=]() {
+    OperandSet& os = h->sets[0];
+    make_weight_operands(h, os, w);
+    lower_grad_seq(h, os, w, lambda, grad_w, loss_or_null);
+  });
 }
 
 betty_status betty_upper_grad(betty_handle h, const float* w, float* grad_w, float* loss_or_null) {
@@ -1133,11 +1191,12 @@ betty_status betty_upper_grad(betty_handle h, const float* w, float* grad_w, flo
   CHECK(check_vec(h, w, "w")); CHECK(check_vec(h, grad_w, "grad_w"));
   if (loss_or_null) CHECK(check_vec(h, loss_or_null, "loss"));
   if (overlaps(grad_w, h->d * 4, w, h->d * 4)) return fail(h, BETTY_EINVAL, "grad_w overlaps w");
-  OperandSet& os = h->sets[0];
-  make_weight_operands(h, os, w);
-  WgradSink k{EPI_WGRAD, grad_w, nullptr, nullptr, nullptr, nullptr, 0.f, false};
-  upper_grad_seq(h, os, w, nullptr, false, k, loss_or_null);
-  return finish(h);
+  return run_cached(h, h->CALL_UPPER, call_key({w, grad_w, loss_or_null}), [=]() {
+    OperandSet& os = h->sets[0];
+    make_weight_operands(h, os, w);
+    WgradSink k{EPI_WGRAD, grad_w, nullptr, nullptr, nullptr, nullptr, 0.f, false};
+    upper_grad_seq(h, os, w, nullptr, false, k, loss_or_null);
+  });
 }
 
 static betty_status check_hvp_args(betty_handle h, const float* w, const float* lambda, const float* v, float* Hv) {
@@ -1155,7 +1214,7 @@ static void hvp_seq(betty_handle h, const float* w, const float* lambda, const f
   OperandSet& os = h->sets[0];
   make_weight_operands(h, os, w);
   prepare_lower(h, os, w, lambda);
-  make_shadows(h, os, v, 1.f, &os.Vn, &os.Vt);
+  make_shadows(h, os, v, &os.Vn, &os.Vt);
   const float* dl = diag_log(h, lambda);
   WgradSink k{EPI_WGRAD, Hv, dl, dl ? v : nullptr, nullptr, nullptr, 0.f, false};
   hvp_cached(h, os, v, k);
@@ -1164,8 +1223,7 @@ static void hvp_seq(betty_handle h, const float* w, const float* lambda, const f
 betty_status betty_hvp(betty_handle h, const float* w, const float* lambda, const float* v, float* Hv) {
   CHECK(check_ready(h));
   CHECK(check_hvp_args(h, w, lambda, v, Hv));
-  hvp_seq(h, w, lambda, v, Hv);
-  return finish(h);
+  return run_cached(h, h->CALL_HVP, call_key({w, lambda, v, Hv}), [=]() { hvp_seq(h, w, lambda, v, Hv); });
 }
 
 // ---- the same product for callers that cannot allocate device memory ----------------------
@@ -1209,29 +1267,15 @@ betty_status betty_hvp_static(betty_handle h, betty_batch train, void* hip_strea
   char* const ws0 = h->ws;
   const hipStream_t st0 = h->ctx.stream;
   const bool prof0 = h->ctx.profiling;
-  const betty_batch b0 = h->batch[0], b1 = h->batch[1];
   h->ws = base;
   h->ctx.stream = (hipStream_t)hip_stream;
   h->ctx.profiling = false;                         // (event creation allocates)
-  h->batch[0] = train;
-  h->batch[1] = train;
   init_workspace(h);                                // the array keeps the last call's contents
-  OperandSet& os = h->sets[0];
-  const LayerInfo& l0 = h->layers[0];
-  SideBuf& sb = os.side[0];
-  launch_convert_dual(h->ctx, os.elem, train.x, l0.n_in, 1.f, sb.B, l0.n_in, h->at<void>(sb.X), l0.n_in_p,
-                      h->at<void>(sb.XT), sb.Bp);
-  if (hybrid_forward(h, os)) {                      // the fp32 forward of ReLU networks reads its own copy of X
-    SideBuf& fb = h->sets[1].side[0];
-    launch_convert_dual(h->ctx, ELEM_F32, train.x, l0.n_in, 1.f, fb.B, l0.n_in, h->at<void>(fb.X), l0.n_in_p,
-                        h->at<void>(fb.XT), fb.Bp);
-  }
+  convert_inputs(h, &train, 1);
   hvp_seq(h, w, lambda, v, Hv);
   h->ws = ws0;
   h->ctx.stream = st0;
   h->ctx.profiling = prof0;
-  h->batch[0] = b0;
-  h->batch[1] = b1;
   return finish(h);
 }
 
@@ -1250,18 +1294,19 @@ betty_status betty_mixed_vjp(betty_handle h, const float* w, const float* lambda
     launch_mixed_prox(h->ctx, h->f(h->logrho), q, 1.f, out, h->d);
     return finish(h);
   }
-  OperandSet& os = h->sets[0];
-  make_weight_operands(h, os, w);
-  forward_and_loss(h, os, SIDE_TRAIN, w, lambda);
-  mixed_reweight_seq(h, os, lambda, q, 1.f, out);
-  return finish(h);
+  return run_cached(h, h->CALL_MIXED, call_key({w, lambda, q, out}), [=]() {
+    OperandSet& os = h->sets[0];
+    make_weight_operands(h, os, w);
+    forward_and_loss(h, os, SIDE_TRAIN, w, lambda);
+    mixed_reweight_seq(h, os, lambda, q, 1.f, out);
+  });
 }
 
 betty_status betty_hypergrad_neumann(betty_handle h, const float* w, const float* lambda, int K, float alpha,
                                      float* dlambda) {
   CHECK(check_hyper_args(h, w, lambda, K, alpha, dlambda));
   auto body = [=]() { neumann_seq(h, w, lambda, nullptr, K, alpha, dlambda); };
-  return run_cached(h, h->graph_neumann, w, lambda, nullptr, dlambda, K, alpha, 0.f, body);
+  return run_cached(h, h->CALL_NEUMANN, call_key({w, lambda, dlambda}, K, {alpha}), body);
 }
 
 betty_status betty_best_response_neumann(betty_handle h, const float* w, const float* lambda, const float* u, int K,
@@ -1270,7 +1315,7 @@ betty_status betty_best_response_neumann(betty_handle h, const float* w, const f
   CHECK(check_vec(h, u, "u"));
   if (overlaps(out, h->n_hyper * 4, u, h->d * 4)) return fail(h, BETTY_EINVAL, "out overlaps u");
   auto body = [=]() { neumann_seq(h, w, lambda, u, K, alpha, out); };
-  return run_cached(h, h->graph_br, w, lambda, u, out, K, alpha, 0.f, body);
+  return run_cached(h, h->CALL_BEST_RESPONSE, call_key({w, lambda, u, out}, K, {alpha}), body);
 }
 
 betty_status betty_hypergrad_chain3(betty_handle hp, betty_handle hf, const float* w, const float* theta,
@@ -1281,7 +1326,7 @@ betty_status betty_hypergrad_chain3(betty_handle hp, betty_handle hf, const floa
   if (check_ready(hf) != BETTY_OK) return fail(hp, BETTY_EWORKSPACE, "finetune handle: %s", hf->err.c_str());
   if (hf->desc.hp != BETTY_HP_PROXIMAL) return fail(hp, BETTY_EINVAL, "the finetune handle must be BETTY_HP_PROXIMAL");
   if (hf->d != hp->d) return fail(hp, BETTY_ESHAPE, "finetune handle has %zu parameters, pretrain handle %zu", hf->d, hp->d);
-  if (hf->ctx.stream != hp->ctx.stream) return fail(hp, BETTY_EINVAL, "both handles must be bound to the same stream");
+  if (hf->bound_stream != hp->bound_stream) return fail(hp, BETTY_EINVAL, "both handles must be bound to the same stream");
   CHECK(check_vec(hp, v, "v"));
   if (K_ft < 0) return fail(hp, BETTY_EINVAL, "K_finetune must be >= 0 (got %d)", K_ft);
   if (!std::isfinite(alpha_ft)) return fail(hp, BETTY_EINVAL, "alpha_finetune must be finite");
@@ -1289,20 +1334,26 @@ betty_status betty_hypergrad_chain3(betty_handle hp, betty_handle hf, const floa
   // rightmost factor first: u = (dv* / dw) grad_v L_U(v) on the finetuning problem (anchor w),
   // kept in that handle's workspace; then (dw* / dtheta) u on the pretraining problem
   if (hf->ctx.profiling) return fail(hp, BETTY_EINVAL, "switch per-launch timing off on the finetune handle first");
+  if (const hipError_t e = move_to_stream(hf, hp->ctx.stream); e != hipSuccess)
+    return fail(hp, BETTY_EDEVICE, "HIP error: %s", hipGetErrorString(e));
   auto body = [=]() {
     float* u = hf->f(hf->vec_g);
+    const hipStream_t own = hf->ctx.stream;
+    hf->ctx.stream = hp->ctx.stream;                  // (the recording stream while the sequence is captured)
     neumann_seq(hf, v, w, nullptr, K_ft, alpha_ft, u);
+    hf->ctx.stream = own;
     if (hf->ctx.first_error != hipSuccess) {          // reported through the pretrain handle
       if (hp->ctx.first_error == hipSuccess) hp->ctx.first_error = hf->ctx.first_error;
       hf->ctx.first_error = hipSuccess;
     }
     neumann_seq(hp, w, theta, u, K_pre, alpha_pre, dtheta);
   };
-  // repeated identical calls replay one captured graph that spans both handles (same stream); the
-  // finetune handle's workspace and batches are part of what the graph has recorded, so its stamp
-  // is part of the key
-  return run_cached(hp, hp->graph_chain, w, theta, v, dtheta, K_pre, alpha_pre, 0.f, body, K_ft, alpha_ft, hf,
-                    hf->epoch);
+  // repeated identical calls replay one captured graph that spans both handles; the finetune handle's
+  // workspace is part of what the graph has recorded, so its binding is part of the key
+  auto key = call_key({w, theta, v, dtheta, hf}, K_pre, {alpha_pre, alpha_ft});
+  key.k[1] = K_ft;
+  key.other_epoch = hf->epoch;
+  return run_cached(hp, hp->CALL_CHAIN, key, body);
 }
 
 betty_status betty_hypergrad_fd(betty_handle h, const float* w, const float* lambda, int K, float alpha,
@@ -1386,7 +1437,7 @@ betty_status betty_hypergrad_fd(betty_handle h, const float* w, const float* lam
                             h->desc.wnet_hidden, sb.B, 1.0f / (float)sb.B, dlambda);
     }
   };
-  return run_cached(h, h->graph_fd, w, lambda, nullptr, dlambda, K, alpha, eps_scale, body);
+  return run_cached(h, h->CALL_FD, call_key({w, lambda, dlambda}, K, {alpha, eps_scale}), body);
 }
 
 betty_status betty_hypergrad_cg(betty_handle h, const float* w, const float* lambda, int K, float* dlambda) {
@@ -1406,7 +1457,7 @@ betty_status betty_hypergrad_cg(betty_handle h, const float* w, const float* lam
     for (int k = 0; k < K; ++k) {
       float* rs = sc + (k & 1);
       float* rs_new = sc + ((k + 1) & 1);
-      make_shadows(h, os, d, 1.f, &os.Vn, &os.Vt);
+      make_shadows(h, os, d, &os.Vn, &os.Vt);
       WgradSink hd{EPI_WGRAD, Hd, dl, dl ? d : nullptr, nullptr, nullptr, 0.f, false};
       hvp_cached(h, os, d, hd);
       launch_dot(h->ctx, d, Hd, h->d, partials, sc + 2);
@@ -1417,7 +1468,7 @@ betty_status betty_hypergrad_cg(betty_handle h, const float* w, const float* lam
     else if (rw) mixed_reweight_seq(h, os, lambda, q, 1.f, dlambda);
     else launch_mixed_prox(h->ctx, h->f(h->logrho), q, 1.f, dlambda, h->d);
   };
-  return run_cached(h, h->graph_cg, w, lambda, nullptr, dlambda, K, 0.f, -1.f, body);
+  return run_cached(h, h->CALL_CG, call_key({w, lambda, dlambda}, K), body);
 }
 
 betty_status betty_lower_sgd_step(betty_handle h, float* w, const float* lambda, float* momentum, float lr, float mu,
@@ -1430,30 +1481,31 @@ betty_status betty_lower_sgd_step(betty_handle h, float* w, const float* lambda,
   if (overlaps(w, h->d * 4, momentum, h->d * 4) || overlaps(w, h->d * 4, lambda, h->n_hyper * 4) ||
       overlaps(momentum, h->d * 4, lambda, h->n_hyper * 4))
     return fail(h, BETTY_EINVAL, "w, momentum and lambda must not overlap");
-  OperandSet& os = h->sets[0];
-  const bool prox = h->desc.hp == BETTY_HP_PROXIMAL;
-  const float* dl = diag_log(h, lambda);
-  make_weight_operands(h, os, w);
-  forward_backward(h, os, SIDE_TRAIN, w, wnet_theta(h, lambda));
-  if (loss_or_null) {                      // the cost at the w before the step
-    float* add = nullptr;
-    if (dl) {
-      const float* x = w;
-      if (prox) {
-        launch_diff(h->ctx, w, lambda, h->f(h->vec_g), h->d);
-        x = h->f(h->vec_g);
+  return run_cached(h, h->CALL_SGD, call_key({w, lambda, momentum, loss_or_null}, -1, {lr, mu, weight_decay}), [=]() {
+    OperandSet& os = h->sets[0];
+    const bool prox = h->desc.hp == BETTY_HP_PROXIMAL;
+    const float* dl = diag_log(h, lambda);
+    make_weight_operands(h, os, w);
+    forward_backward(h, os, SIDE_TRAIN, w, wnet_theta(h, lambda));
+    if (loss_or_null) {                      // the cost at the w before the step
+      float* add = nullptr;
+      if (dl) {
+        const float* x = w;
+        if (prox) {
+          launch_diff(h->ctx, w, lambda, h->f(h->vec_g), h->d);
+          x = h->f(h->vec_g);
+        }
+        add = h->f(h->scalars) + 8;
+        launch_l2_cost(h->ctx, dl, x, h->d, h->at<double>(h->partials), add);
       }
-      add = h->f(h->scalars) + 8;
-      launch_l2_cost(h->ctx, dl, x, h->d, h->at<double>(h->partials), add);
+      launch_weighted_loss_sum(h->ctx, h->f(os.side[0].s), h->f(os.side[0].ell), os.side[0].B, add, loss_or_null);
     }
-    launch_weighted_loss_sum(h->ctx, h->f(os.side[0].s), h->f(os.side[0].ell), os.side[0].B, add, loss_or_null);
-  }
-  // momentum and parameters are updated in the epilogue of the weight-gradient launch
-  // (the proximal term pulls towards the anchor: the epilogue subtracts it from w in that term)
-  WgradSink k{EPI_WGRAD_SGD, nullptr, dl, prox ? lambda : nullptr, momentum, w, lr, false};
-  k.beta = mu; k.gamma = weight_decay;
-  wgrad_batch(h, os, 0, false, k);
-  return finish(h);
+    // momentum and parameters are updated in the epilogue of the weight-gradient launch
+    // (the proximal term pulls towards the anchor: the epilogue subtracts it from w in that term)
+    WgradSink k{EPI_WGRAD_SGD, nullptr, dl, prox ? lambda : nullptr, momentum, w, lr, false};
+    k.beta = mu; k.gamma = weight_decay;
+    wgrad_batch(h, os, 0, false, k);
+  });
 }
 
 betty_status betty_upper_adam_step(betty_handle h, float* lambda, const float* dlambda, float* m, float* v, int t,

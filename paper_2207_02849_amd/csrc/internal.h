@@ -153,26 +153,31 @@ void launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& batch, double al
                        double algorithmic_bytes = 0);
 
 // ---- kernels.hip : operand conversion -----------------------------------------------------
-// out (row-major [rows_p][ld]) and outT ([cols_p][ldT]) = convert(scale * src[r * lds + c]); either may be null
+// Where the labels or targets of a batch are: kept in the workspace and read by the kernels, so that a
+// recorded launch sequence stays valid when another batch is registered.
+struct Labels { const int32_t* y; const float* target; };
+
+// out ([rows][ld], operand type), outT ([cols][ldT], operand type), out32, outT32 (the same in fp32) =
+// convert(src[r * lds + c]); each may be null
 struct ConvertJob {
-  const float* src; long long lds; float scale; int rows, cols;
+  const float* src; long long lds; int rows, cols;
   void* out; int ld; void* outT; int ldT;
-  float* outT32 = nullptr;    // optional further transposed copy in fp32 (same ldT)
+  float* out32 = nullptr; float* outT32 = nullptr;
 };
 struct ConvertBatch {
   int n = 0;
   int block_begin[MAX_PROBLEMS + 1];
   ConvertJob j[MAX_PROBLEMS];
+  Labels* table = nullptr;     // the launch also writes labels[0], labels[1] to table[0], table[1] if given
+  Labels labels[2];
 };
 void launch_convert_batch(Ctx&, Elem, ConvertBatch&);
-void launch_convert_dual(Ctx&, Elem, const float* src, long long lds, float scale, int rows,
-                         int cols, void* out, int ld, void* outT, int ldT);
 
 // ---- kernels.hip : loss rows ---------------------------------------------------------------
 struct LossArgs {
   int loss, reweight, hidden;
   const float* Z; long long ldz;        // logits [rows][ldz]
-  const int32_t* y; const float* target; int C;
+  const Labels* labels; int C;
   const float* theta;                   // weight net (reweight only)
   const float* omega_fixed;             // reweight only: use these weights instead of R(l_i; theta)
   int rows; float inv_batch;
@@ -202,8 +207,8 @@ struct LastRopArgs {
   int B, n_in, n_in_p, C, loss;
   // Directional form (cvec non-null): only c_i = <dl_i/dz, Rz_L,i> per sample leaves the kernel
   // (the per-sample directional derivative of the loss, for the reweighting mixed term);
-  // y / (Z, target) give dl/dz for cross-entropy / squared error.
-  float* cvec; const int32_t* y; const float* Z; const float* target;
+  // labels / (Z, targets) give dl/dz for cross-entropy / squared error.
+  float* cvec; const Labels* labels; const float* Z;
 };
 constexpr int LAST_ROP_MAX_C = 16;
 void launch_last_layer_rop(Ctx&, Elem, const LastRopArgs&);
@@ -214,7 +219,7 @@ void launch_last_layer_rop(Ctx&, Elem, const LastRopArgs&);
 // is given), for up to two batches (train, validation) in one launch.
 struct LastGradSide {
   const void* A; int lda;                        // a_{L-1} [B][lda], operand type
-  const int32_t* y; const float* target;         // labels, or targets [B][C]
+  const Labels* labels;                          // labels, or targets [B][C]
   const float* omega_fixed;                      // sample weights to use instead of the weight net, or null
   float* ZL; float* P; int ldz;                  // out: logits, softmax probabilities, fp32 [B][ldz]
   float* ell; float* s; float* omega;            // out: per-sample loss, scale, weight
@@ -236,8 +241,7 @@ void launch_last_layer_grad(Ctx&, Elem, const LastGradArgs&);
 void launch_loss_hessian_rows(Ctx&, Elem, int loss, const float* P, const float* Rz, long long ld,
                               const float* s, int rows, int C, void* D, int ldD, void* Dt, int ldDt);
 // c_i = < dl_i/dz, Rz_i >
-void launch_loss_directional_rows(Ctx&, int loss, const float* P, const float* Z, const int32_t* y,
-                                  const float* target, const float* Rz, long long ld, int rows,
+void launch_loss_directional_rows(Ctx&, int loss, const float* P, const float* Z, const Labels* labels, const float* Rz, long long ld, int rows,
                                   int C, float* c);
 // out = -(1/B) sum_i c_i dR(l_i; theta)/dtheta
 void launch_wnet_theta_vjp(Ctx&, const float* ell, const float* dsig, const float* c,

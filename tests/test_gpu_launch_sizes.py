@@ -41,3 +41,34 @@ def test_small_launch_forms(dims, batch, loss, prec, tol):
                             orc.hypergrad_neumann(prob, wl.w, wl.lam, 2, 0.02))):
         assert rel_l2(host(got), ref) < tol, name
     b.close()
+
+
+def test_recorded_calls_follow_streams_and_batches():
+    """A handle without an explicit stream runs on the caller's current stream; recorded sequences
+    survive a move to another stream and new batches (labels included), and one argument set does
+    not push out another."""
+    wl, wl2 = (wk.tiny(kind="reweight", dims=(40, 30, 5), batch=33, hidden=9, seed=s) for s in (0, 1))
+    batches = [dict(X_tr=dev(x.X_tr), X_val=dev(x.X_val), y_tr=torch.as_tensor(x.y_tr).int().cuda(),
+                    y_val=torch.as_tensor(x.y_val).int().cuda()) for x in (wl, wl2)]
+    b = binding.from_workload(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    outs = [torch.empty(b.n_hyper, device="cuda") for _ in range(2)]
+    other = torch.cuda.Stream()
+    ref = [orc.hypergrad_neumann(oracle_problem(x), wl.w, wl.lam, 3, 0.05) for x in (wl, wl2)]
+    for rep in range(4):
+        for batch, want in zip(batches, ref):
+            b.set_batches(**batch)
+            for out in outs:
+                if rep % 2:
+                    other.wait_stream(torch.cuda.current_stream())
+                    with torch.cuda.stream(other):
+                        b.betty_hypergrad_neumann(w, lam, 3, 0.05, out=out)
+                    torch.cuda.current_stream().wait_stream(other)
+                else:
+                    b.betty_hypergrad_neumann(w, lam, 3, 0.05, out=out)
+                assert rel_l2(host(out), want) < 1e-4
+                out.zero_()
+    out = b.betty_hypergrad_neumann(w, lam, 3, 0.05)
+    b.stream.synchronize()                       # the handle's own stream is ordered behind the call
+    assert rel_l2(out.cpu().numpy(), ref[1]) < 1e-4
+    b.close()
