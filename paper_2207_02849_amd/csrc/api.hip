@@ -61,6 +61,15 @@ struct OperandSet {
   std::vector<size_t> Vn2, Vt2;               // second set of direction copies (pipelined recurrence; main set only)
   std::vector<size_t> RA, RAt, RD, RDt, Rz;   // R-op quantities (train side only)
   size_t cvec = 0;
+  // The Neumann series in sample space (main set of the costs without a per-parameter diagonal).  Per layer,
+  // over pairs of train samples: G = a a^T (+ 1 for the bias), E = delta delta^T, M = a Ra^T, N = delta R delta^T,
+  // and against the validation samples Gx, Ex; all as A operands (EPI_GRAM).  AS = a V + c and DS = delta V^T
+  // (fp32) for the current partial sum, Ag and Dg for the vector the series is applied to; the sums of
+  // R a and R delta over the steps (proximal cost).
+  bool samples = false;
+  int ldG = 0, ldGx = 0;
+  std::vector<size_t> G, E, M, N, Gx, Ex, AS, DS, Ag, Dg, sumRA, sumRD;
+  size_t RA1 = 0, RA1t = 0;   // second place for R a_1, which a step's update writes while it is still being read
 };
 
 }  // namespace
@@ -124,6 +133,11 @@ struct betty_handle_s {
   std::vector<hipEvent_t> fork_events;        // one per layer
   hipEvent_t join_event = nullptr;
   bool use_pipeline = false;
+  // Optimiser steps with bf16 operands keep one grouping of the sums along K, whatever kernel the launch
+  // rule picks elsewhere: activations and deltas are rounded to bf16 after every layer, so another grouping
+  // sends a training run down another trajectory (up to 3e-3 in the momentum after a step or three).
+  bool fixed_grouping = false;
+  int tune_samples = -1;                      // sample-space series: 0 never, 1 wherever it exists, -1 by size
   // Finite differences: the gradient evaluations at w + eps v and w - eps v are independent and run
   // side by side on the two streams when one of them alone leaves part of the chip idle
   // (measured: -10 % per hypergradient at 1M parameters, -1 % at 5M, +0.5 % at 116M, where each
@@ -231,6 +245,37 @@ void plan_set(betty_handle h, Planner& pl, OperandSet& os, Elem elem, bool secon
     os.RDt[l] = pl.take(np * Bp * es);
     os.Rz[l] = pl.take(Bp * np * 4);
   }
+  if (h->desc.hp == BETTY_HP_L2_DECAY) return;
+  os.samples = true;
+  const int width = elem == ELEM_BF16 ? 2 : 1;              // value and remainder (GemmArgs::split)
+  os.ldG = (int)Bp * width;
+  os.ldGx = os.side[1].Bp * width;
+  for (auto* v : {&os.G, &os.E, &os.M, &os.N, &os.Gx, &os.Ex, &os.AS, &os.DS, &os.Ag, &os.Dg}) v->assign(L + 1, 0);
+  for (int l = 1; l <= L; ++l) {
+    const size_t np = h->layers[l - 1].n_out_p, ip = h->layers[l - 1].n_in_p;
+    os.G[l] = pl.take(Bp * os.ldG * es);
+    os.Gx[l] = pl.take(Bp * os.ldGx * es);
+    os.AS[l] = pl.take(Bp * np * 4);
+    os.Ag[l] = pl.take(Bp * np * 4);
+    if (l == 1) continue;
+    os.E[l] = pl.take(Bp * os.ldG * es);
+    os.M[l] = pl.take(Bp * os.ldG * es);
+    os.N[l] = pl.take(Bp * os.ldG * es);
+    os.Ex[l] = pl.take(Bp * os.ldGx * es);
+    os.DS[l] = pl.take(Bp * ip * 4);
+    os.Dg[l] = pl.take(Bp * ip * 4);
+  }
+  if (L >= 2) {
+    const size_t n1 = h->layers[0].n_out_p;
+    os.RA1 = pl.take(Bp * n1 * es); os.RA1t = pl.take(n1 * Bp * es);
+  }
+  if (h->desc.hp != BETTY_HP_PROXIMAL) return;
+  os.sumRA.assign(L + 1, 0); os.sumRD.assign(L + 1, 0);
+  for (int l = 1; l <= L; ++l) {
+    const size_t np = h->layers[l - 1].n_out_p;
+    os.sumRD[l] = pl.take(np * Bp * 4);
+    if (l < L) os.sumRA[l] = pl.take(np * Bp * 4);
+  }
 }
 
 OperandSet& fd_operands(betty_handle h) { return h->sets[1].present ? h->sets[1] : h->sets[0]; }
@@ -303,7 +348,23 @@ struct Extent {
 //    launches of this size are bound by the matrix cores, 64-tiles are 10 % faster;
 //  * 128-tiles once there are enough of them to fill the chip several times over;
 //  * otherwise plain 64-tiles.
-int plan_chain(betty_handle h, Elem elem, const GemmBatch& b) {
+int plan_chain(betty_handle h, Elem elem, GemmBatch& b) {
+  if (h->fixed_grouping && elem == ELEM_BF16) {
+    // eight, four or one contiguous ranges of 64-element k-tiles of the padded extent; the unsplit kernels
+    // all sum in the same order
+    long tiles = 0;
+    int TT = 0;
+    for (int i = 0; i < b.n; ++i) {
+      GemmArgs& g = b.p[i].g;
+      g.K[0] = padup(g.K[0]);
+      tiles += 4L * (padup(g.M) / 128) * (padup(g.N) / 128);
+      TT = std::max(TT, g.K[0] / 64);
+    }
+    if (tiles >= 4L * h->tune_tile128_min) return GEMM_128x1;
+    if (tiles <= 128 && TT >= 16) return GEMM_32x8;
+    if (tiles < 256 && TT >= 8) return GEMM_32x4;
+    return tiles <= 1024 && TT >= 16 ? GEMM_128x64 : GEMM_64x1;
+  }
   Extent x;
   for (int i = 0; i < b.n; ++i) x.add(elem, b.p[i].g.M, b.p[i].g.N, b.p[i].g.K[0], b.p[i].g.K[1]);
   const bool wide_rows = b.p[0].e.mode == EPI_RFWD_LAST_HESS && b.p[0].g.N > 16;   // its row sums need a whole row per tile
@@ -343,6 +404,7 @@ void set_pairs(GemmArgs& g, const void* A0, int lda0, const void* B0, int ldb0, 
   g.A[1] = A1 ? A1 : A0; g.B[1] = A1 ? B1 : B0; g.lda[1] = A1 ? lda1 : lda0; g.ldb[1] = A1 ? ldb1 : ldb0;
   g.K[1] = A1 ? K1 : 0;
   g.xgm = g.xgn = 0;
+  g.split = 0;
 }
 
 // one activation-shaped GEMM with a fused epilogue
@@ -547,6 +609,10 @@ void xcd_split(int tiles_m, int tiles_n, int& gm, int& gn) {
   }
 }
 
+// the proximal cost's share of the series' recurrence V <- g + beta V - alpha (...) in layer l
+bool anchored(betty_handle h, int l) { return h->desc.hp == BETTY_HP_PROXIMAL && !(h->desc.prox_skip_last && l == h->L); }
+float series_beta(betty_handle h, int l, float alpha) { return anchored(h, l) ? 1.f - 2.f * alpha * h->desc.prox_rho : 1.f; }
+
 // What the grouped weight-gradient launch does with its result.
 struct WgradSink {
   int mode;                 // EPI_WGRAD / EPI_WGRAD_INIT / EPI_WGRAD_NEUMANN
@@ -557,6 +623,7 @@ struct WgradSink {
   bool copies;              // also write the operand copies of the new v
   bool second_set = false;  // ... into the second set of direction copies (the first is still being read)
   float beta = 0.f, gamma = 0.f;   // EPI_WGRAD_SGD: momentum factor and plain weight decay
+  int K = 0;                // EPI_WGRAD_SCALED: steps of the series
 };
 // (aggregate initialisation in the callers lists the fields up to `copies`)
 
@@ -597,6 +664,12 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
       e.v = k.v ? k.v + li.w_off : nullptr;
       e.p = k.p ? k.p + li.w_off : nullptr;
       e.alpha = k.alpha; e.beta = k.beta; e.gamma = k.gamma;
+      if (k.mode == EPI_WGRAD_SCALED) {
+        const float beta = series_beta(h, l, k.alpha);
+        e.beta = 1.f;
+        for (int j = 0; j < k.K; ++j) e.beta = 1.f + beta * e.beta;
+        e.gamma = anchored(h, l) ? 2.f * h->desc.prox_rho * k.alpha : 0.f;
+      }
       if (k.copies) {
         e.out = h->at<void>(VN[l - 1]); e.ld = li.n_out_p;
         e.outT = h->at<void>(VT[l - 1]); e.ldT = li.n_in_p;
@@ -611,7 +684,7 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
         j.x = k.x ? k.x + li.b_off : nullptr;
         j.v = k.v ? k.v + li.b_off : nullptr;
         j.p = k.p ? k.p + li.b_off : nullptr;
-        j.alpha = k.alpha; j.beta = k.beta; j.gamma = k.gamma;
+        j.alpha = e.alpha; j.beta = e.beta; j.gamma = e.gamma;
       }
     }
     double params = 0;
@@ -625,6 +698,7 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
     if (k.mode == EPI_WGRAD_NEUMANN) per_param = 8.0 + 4.0 + (k.lam ? 4.0 : 0.0);
     else if (k.mode == EPI_WGRAD_NEUMANN_L2) per_param = 16.0 + 4.0;
     else if (k.mode == EPI_WGRAD_SGD) per_param = 16.0 + (k.lam ? 4.0 : 0.0);
+    else if (k.mode == EPI_WGRAD_SCALED) per_param = 8.0;
     else if (k.mode == EPI_WGRAD_INIT) per_param = k.p ? 8.0 : 4.0;
     else if (k.lam) per_param = 12.0;
     if (k.copies) per_param += 4.0;
@@ -968,12 +1042,343 @@ static betty_status check_hyper_args(betty_handle h, const float* w, const float
   return BETTY_OK;
 }
 
+// ---- the Neumann series in sample space ----------------------------------------------------------
+//
+// Without a per-parameter diagonal (reweighting cost; the proximal cost has one constant per layer) the
+// Hessian of the batch acts through its samples: per layer H V = Ra^T delta + a^T R delta (+ 2 rho V), and
+// what the next product needs of V are only a V and delta V^T.  Both follow from V's own recurrence
+// V <- g + beta V - alpha (Ra^T delta + a^T R delta), beta = 1 - 2 alpha rho, through matrices over pairs of
+// samples:
+//   AS = a V + c          <-  Ag + beta AS - alpha [ (a Ra^T) delta + (a a^T + 1) R delta ]
+//   DS = delta V^T        <-  Dg + beta DS - alpha [ (delta R delta^T) a + (delta delta^T) Ra ]
+// so no parameter-sized vector is formed, read or written between the steps, the links of the R-op chains
+// carry half the reduction (the direction's half is AS, DS), and layer 1 has no link at all (R a_0 = 0).
+// Per layer and step 10 B^2 (n_in + n_out) operations with bf16 operands (6 with fp32) take the place of
+// 8 B n_in n_out and of the parameter-sized traffic (121M-parameter model, batch 512: 5.88 -> 3.80 ms per
+// hypergradient; 2000 x 4 - 700, batch 100: 837 -> 478 us).  AS and DS stay fp32, the operands are those the
+// parameter-sized products would take; the matrices over samples are kept as value + remainder with bf16
+// operands, since their entries share a large common part whose rounding would not cancel.
+struct SampleLaunch {
+  betty_handle h;
+  OperandSet& os;
+  GemmBatch b;
+  double flops = 0;
+  int mode;
+  SampleLaunch(betty_handle h_, OperandSet& os_, int mode_) : h(h_), os(os_), mode(mode_) {}
+  GemmProblem& add(int M, int N, int Ktot) {
+    if (b.n == MAX_SAMPLE_PROBLEMS) flush();
+    GemmProblem& p = b.p[b.n++];
+    p.e = blank_epilogue(mode);
+    p.g.M = M; p.g.N = N;
+    flops += 2.0 * M * N * Ktot;
+    return p;
+  }
+  // C = A B^T + gamma over pairs of samples; A [rows][ld], B [cols][ld]
+  void gram(const void* A, int lda, const void* B, int ldb, int rows, int cols, int K, float gamma, size_t out, int ldo) {
+    GemmProblem& p = add(rows, cols, K);
+    set_pairs(p.g, A, lda, B, ldb, K, nullptr, 0, nullptr, 0, 0);
+    p.e.gamma = gamma;
+    p.e.out = h->at<void>(out); p.e.ld = ldo;
+  }
+  void flush() {
+    if (b.n == 0) return;
+    launch_gemm_batch(h->ctx, os.elem, plan_chain(h, os.elem, b), b, flops);
+    b = GemmBatch();
+    flops = 0;
+  }
+};
+
+bool use_samples(betty_handle h, int K) {
+  const OperandSet& os = h->sets[0];
+  if (!os.samples || h->tune_samples == 0 || (K == 0 && h->desc.hp != BETTY_HP_REWEIGHT_NET)) return false;
+  if (h->tune_samples == 1) return true;
+  // Microseconds a step saves: the operations of either form at the rates that launches of this kind
+  // reach, the parameter-sized traffic, and the launch of layer 1's link.  (Taken against timings of 83
+  // models, batch 32 ... 700: wrong by no more than 5 % of a call anywhere.)
+  const double B = h->desc.batch_train, rate = os.elem == ELEM_BF16 ? 150e6 : 60e6;
+  const double per_pair = os.elem == ELEM_BF16 ? 10.0 : 6.0;
+  double saved = 2.0;
+  for (int i = 0; i < h->L; ++i) {
+    const double n_in = h->layers[i].n_in, n_out = h->layers[i].n_out;
+    saved += (i == 0 ? 4.0 : 8.0) * B * n_in * n_out / rate + 16.0 * n_in * n_out / 2e6;
+    saved -= i == 0 ? (per_pair - 4.0) * B * B * n_out / rate : per_pair * B * B * (n_in + n_out) / rate;
+  }
+  return saved > 0;
+}
+
+// what the train side's activations a_{l-1} are called
+const void* act_rows(betty_handle h, OperandSet& os, int side, int l) { return l == 1 ? h->at<void>(os.side[side].X) : h->at<void>(os.side[side].A[l - 1]); }
+const void* act_cols(betty_handle h, OperandSet& os, int side, int l) { return l == 1 ? h->at<void>(os.side[side].XT) : h->at<void>(os.side[side].At[l - 1]); }
+
+// epilogue of a SAMPLE problem that leaves a V + c (or delta V^T) in `to`; for layer 1 of a deeper network R a_1 too
+void sample_sum(betty_handle h, OperandSet& os, GemmProblem& p, size_t to, int ldf, bool first_layer) {
+  p.e.f0 = h->f(to);
+  p.e.ldf = ldf;
+  if (!first_layer || h->L < 2) return;
+  p.e.dphi = h->f(os.side[0].dphi[1]);
+  p.e.out = h->at<void>(os.RA1); p.e.ld = ldf;
+  p.e.outT = h->at<void>(os.RA1t); p.e.ldT = os.side[0].Bp;
+}
+void next_RA1(OperandSet& os) { std::swap(os.RA[1], os.RA1); std::swap(os.RAt[1], os.RA1t); }
+
+
+
+// Ag, Dg from the validation batch (u = grad_w L_U = a_val^T delta_val) or from the dense vector u, and the
+// matrices that stay the same over the steps
+void samples_begin(betty_handle h, OperandSet& os, const float* u_or_null, bool steps) {
+  SideBuf& sb = os.side[0];
+  SideBuf& vb = os.side[1];
+  const int L = h->L, B = sb.B;
+  const float one = h->desc.has_bias ? 1.f : 0.f;
+  SampleLaunch gram(h, os, EPI_GRAM);
+  for (int l = 1; l <= L; ++l) {
+    const LayerInfo& li = h->layers[l - 1];
+    const void* a = act_rows(h, os, 0, l);
+    const void* D = h->at<void>(sb.D[l]);
+    if (!u_or_null) {
+      gram.gram(a, li.n_in_p, act_rows(h, os, 1, l), li.n_in_p, B, vb.B, li.n_in, one, os.Gx[l], os.ldGx);
+      if (l > 1 && steps) gram.gram(D, li.n_out_p, h->at<void>(vb.D[l]), li.n_out_p, B, vb.B, li.n_out, 0.f, os.Ex[l], os.ldGx);
+    }
+    if (!steps) continue;
+    gram.gram(a, li.n_in_p, a, li.n_in_p, B, B, li.n_in, one, os.G[l], os.ldG);
+    if (l > 1) gram.gram(D, li.n_out_p, D, li.n_out_p, B, B, li.n_out, 0.f, os.E[l], os.ldG);
+  }
+  gram.flush();
+  SampleLaunch sum(h, os, EPI_SAMPLE);
+  for (int l = 1; l <= L; ++l) {
+    const LayerInfo& li = h->layers[l - 1];
+    GemmProblem& p = sum.add(B, li.n_out, u_or_null ? li.n_in : vb.B);
+    if (u_or_null) {
+      set_pairs(p.g, act_rows(h, os, 0, l), li.n_in_p, h->at<void>(os.Vt[l - 1]), li.n_in_p, li.n_in, nullptr, 0, nullptr, 0, 0);
+      p.e.colvec = h->desc.has_bias ? u_or_null + li.b_off : nullptr;
+    } else {
+      set_pairs(p.g, h->at<void>(os.Gx[l]), os.ldGx, h->at<void>(vb.Dt[l]), vb.Bp, vb.B, nullptr, 0, nullptr, 0, 0);
+      p.g.split = os.elem == ELEM_BF16;
+    }
+    p.e.alpha = -1.f;
+    sample_sum(h, os, p, os.Ag[l], li.n_out_p, l == 1);
+    if (l == 1 || !steps) continue;
+    GemmProblem& q = sum.add(B, li.n_in, u_or_null ? li.n_out : vb.B);
+    if (u_or_null) {
+      set_pairs(q.g, h->at<void>(sb.D[l]), li.n_out_p, h->at<void>(os.Vn[l - 1]), li.n_out_p, li.n_out, nullptr, 0, nullptr, 0, 0);
+    } else {
+      set_pairs(q.g, h->at<void>(os.Ex[l]), os.ldGx, act_cols(h, os, 1, l), vb.Bp, vb.B, nullptr, 0, nullptr, 0, 0);
+      q.g.split = os.elem == ELEM_BF16;
+    }
+    q.e.alpha = -1.f;
+    sample_sum(h, os, q, os.Dg[l], li.n_in_p, false);
+  }
+  sum.flush();
+  if (L >= 2) next_RA1(os);
+}
+
+// R-forward links 2 ... upto with a V + c given (in AS, layer 1's Ra_1 with it)
+void samples_r_forward(betty_handle h, OperandSet& os, const std::vector<size_t>& AS, int upto) {
+  SideBuf& sb = os.side[0];
+  for (int l = 2; l <= upto; ++l) {
+    const LayerInfo& li = h->layers[l - 1];
+    const bool last = l == h->L;
+    Epilogue e = blank_epilogue(last ? EPI_RFWD_LAST : EPI_RFWD);
+    e.e = h->f(AS[l]);
+    e.f0 = h->f(os.Rz[l]);
+    e.ldf = li.n_out_p;
+    if (!last) {
+      e.dphi = h->f(sb.dphi[l]);
+      e.out = h->at<void>(os.RA[l]); e.ld = li.n_out_p;
+      e.outT = h->at<void>(os.RAt[l]); e.ldT = sb.Bp;
+    }
+    chain_gemm(h, os.elem, h->at<void>(os.RA[l - 1]), li.n_in_p, h->at<void>(os.Wt[l - 1]), li.n_in_p, li.n_in,
+               nullptr, 0, nullptr, 0, 0, sb.B, li.n_out, e, 2.0 * sb.B * li.n_in * li.n_out);
+  }
+}
+
+// the narrow output layer of the R-op passes with a V + c and delta V^T given
+LastRopArgs samples_last_args(betty_handle h, OperandSet& os, const std::vector<size_t>& AS) {
+  SideBuf& sb = os.side[0];
+  const int L = h->L;
+  const LayerInfo& lo = h->layers[L - 1];
+  LastRopArgs a{};
+  a.RA = h->at<void>(os.RA[L - 1]); a.lda = lo.n_in_p;
+  a.Wt = h->at<void>(os.Wt[L - 1]); a.ldt = lo.n_in_p;
+  a.Wn = h->at<void>(os.Wn[L - 1]); a.ldn = lo.n_out_p;
+  a.AS = h->f(AS[L]); a.ldas = lo.n_out_p;
+  a.P = h->f(sb.P); a.ldp = lo.n_out_p;
+  a.B = sb.B; a.n_in = lo.n_in; a.n_in_p = lo.n_in_p; a.C = lo.n_out; a.loss = h->desc.loss;
+  return a;
+}
+
+// The R-op chains along the current partial sum, and the matrices that its update takes (if one follows).
+// `last` (reweighting cost): only a V is needed afterwards, for the mixed term.
+void samples_chains(betty_handle h, OperandSet& os, bool first, bool update, bool last) {
+  SideBuf& sb = os.side[0];
+  const int L = h->L, B = sb.B, Bp = sb.Bp;
+  const std::vector<size_t>& AS = first ? os.Ag : os.AS;
+  const std::vector<size_t>& DS = first ? os.Dg : os.DS;
+  const LayerInfo& lo = h->layers[L - 1];
+  const bool narrow = L >= 2 && lo.n_out <= LAST_ROP_MAX_C;
+  samples_r_forward(h, os, AS, narrow ? L - 1 : L);
+  auto rz = [&](int l) { return h->f(l == 1 ? AS[1] : os.Rz[l]); };
+  if (narrow) {
+    LastRopArgs a = samples_last_args(h, os, AS);
+    a.DS = h->f(DS[L]);
+    a.s = h->f(sb.s);
+    a.DL = h->at<void>(sb.D[L]); a.ldd = lo.n_out_p;
+    a.dphi = h->f(sb.dphi[L - 1]); a.e2 = sb.e2[L - 1] ? h->f(sb.e2[L - 1]) : nullptr;
+    a.Rz = rz(L - 1); a.ldf = lo.n_in_p;
+    a.RDL = h->at<void>(os.RD[L]); a.RDLt = h->at<void>(os.RDt[L]); a.ldRDLt = Bp;
+    a.RD = h->at<void>(os.RD[L - 1]); a.ldRD = lo.n_in_p; a.RDt = h->at<void>(os.RDt[L - 1]); a.ldRDt = Bp;
+    launch_last_layer_rop(h->ctx, os.elem, a);
+  } else {
+    launch_loss_hessian_rows(h->ctx, os.elem, h->desc.loss, h->f(sb.P), rz(L), lo.n_out_p, h->f(sb.s), B, lo.n_out,
+                             h->at<void>(os.RD[L]), lo.n_out_p, h->at<void>(os.RDt[L]), Bp);
+  }
+  // M and N of the update: ready once their R a and R delta are, so they ride along in the links of the
+  // R-backward chain where those leave the chip room, the rest in a launch of their own
+  SampleLaunch grams(h, os, EPI_GRAM);
+  auto want = [&](int l) {
+    const LayerInfo& li = h->layers[l - 1];
+    if (!update) return;
+    grams.gram(h->at<void>(sb.A[l - 1]), li.n_in_p, h->at<void>(os.RA[l - 1]), li.n_in_p, B, B, li.n_in, 0.f, os.M[l], os.ldG);
+    if (!last) grams.gram(h->at<void>(sb.D[l]), li.n_out_p, h->at<void>(os.RD[l]), li.n_out_p, B, B, li.n_out, 0.f, os.N[l], os.ldG);
+  };
+  if (narrow) want(L);
+  for (int l = narrow ? L - 1 : L; l >= 2; --l) {
+    want(l);
+    const LayerInfo& li = h->layers[l - 1];
+    GemmBatch b;
+    b.n = 1;
+    GemmProblem& p = b.p[0];
+    set_pairs(p.g, h->at<void>(os.RD[l]), li.n_out_p, h->at<void>(os.Wn[l - 1]), li.n_out_p, li.n_out, nullptr, 0, nullptr, 0, 0);
+    p.g.M = B; p.g.N = li.n_in;
+    Epilogue& e = p.e;
+    e = blank_epilogue(EPI_RBWD);
+    e.e_io = h->f(DS[l]);
+    e.dphi = h->f(sb.dphi[l - 1]);
+    e.e = sb.e2[l - 1] ? h->f(sb.e2[l - 1]) : nullptr;
+    e.Rz = rz(l - 1);
+    e.ldf = li.n_in_p;
+    e.out = h->at<void>(os.RD[l - 1]); e.ld = li.n_in_p;
+    e.outT = h->at<void>(os.RDt[l - 1]); e.ldT = Bp;
+    double flops = 2.0 * B * li.n_in * li.n_out;
+    long tiles = Extent::up(B, 32) * Extent::up(li.n_in, 32);
+    while (grams.b.n > 0 && b.n < MAX_CHAIN_PROBLEMS) {
+      const GemmProblem& g = grams.b.p[grams.b.n - 1];
+      tiles += Extent::up(g.g.M, 32) * Extent::up(g.g.N, 32);
+      if (tiles > 512) break;
+      b.p[b.n++] = g;
+      flops += 2.0 * g.g.M * g.g.N * g.g.K[0];
+      grams.flops -= 2.0 * g.g.M * g.g.N * g.g.K[0];
+      --grams.b.n;
+    }
+    launch_gemm_batch(h->ctx, os.elem, plan_chain(h, os.elem, b), b, flops);
+  }
+  grams.flush();
+}
+
+// The update of the partial sum after its chains.
+void samples_update(betty_handle h, OperandSet& os, bool first, bool last, float alpha) {
+  SideBuf& sb = os.side[0];
+  const int L = h->L, B = sb.B, Bp = sb.Bp;
+  const std::vector<size_t>& AS = first ? os.Ag : os.AS;
+  const std::vector<size_t>& DS = first ? os.Dg : os.DS;
+  SampleLaunch sum(h, os, EPI_SAMPLE);
+  for (int l = 1; l <= L; ++l) {
+    const LayerInfo& li = h->layers[l - 1];
+    const float beta = series_beta(h, l, alpha);
+    GemmProblem& p = sum.add(B, li.n_out, (l == 1 ? 1 : 2) * B);
+    if (l == 1) set_pairs(p.g, h->at<void>(os.G[l]), os.ldG, h->at<void>(os.RDt[l]), Bp, B, nullptr, 0, nullptr, 0, 0);
+    else set_pairs(p.g, h->at<void>(os.M[l]), os.ldG, h->at<void>(sb.Dt[l]), Bp, B, h->at<void>(os.G[l]), os.ldG,
+                   h->at<void>(os.RDt[l]), Bp, B);
+    p.g.split = os.elem == ELEM_BF16;
+    p.e.alpha = alpha; p.e.beta = beta;
+    p.e.e = h->f(AS[l]); p.e.Rz = h->f(os.Ag[l]);
+    sample_sum(h, os, p, os.AS[l], li.n_out_p, l == 1);
+    if (l == 1 || last) continue;
+    GemmProblem& q = sum.add(B, li.n_in, 2 * B);
+    set_pairs(q.g, h->at<void>(os.N[l]), os.ldG, act_cols(h, os, 0, l), Bp, B, h->at<void>(os.E[l]), os.ldG,
+              h->at<void>(os.RAt[l - 1]), Bp, B);
+    q.g.split = os.elem == ELEM_BF16;
+    q.e.alpha = alpha; q.e.beta = beta;
+    q.e.e = h->f(DS[l]); q.e.Rz = h->f(os.Dg[l]);
+    sample_sum(h, os, q, os.DS[l], li.n_in_p, false);
+  }
+  sum.flush();
+  if (L >= 2) next_RA1(os);
+}
+
+// Proximal cost: sum_k beta^(K-1-k) (Ra, R delta) of the steps; after the last one it stands in RAt, RDt.
+void samples_accumulate(betty_handle h, OperandSet& os, bool first, bool last, float alpha) {
+  const size_t Bp = os.side[0].Bp;
+  AccumulateBatch b;
+  b.first = first; b.last = last;
+  auto add = [&](size_t r, size_t sum, float beta, int rows) {
+    if (b.n == MAX_PROBLEMS) { launch_accumulate(h->ctx, os.elem, b); b.n = 0; }
+    b.j[b.n++] = AccumulateJob{h->at<void>(r), h->f(sum), beta, rows * Bp};
+  };
+  for (int l = 1; l <= h->L; ++l) {
+    add(os.RDt[l], os.sumRD[l], series_beta(h, l, alpha), h->layers[l - 1].n_out_p);
+    if (l < h->L) add(os.RAt[l], os.sumRA[l], series_beta(h, l + 1, alpha), h->layers[l - 1].n_out_p);
+  }
+  launch_accumulate(h->ctx, os.elem, b);
+}
+
+void neumann_samples_seq(betty_handle h, const float* w, const float* lambda, const float* u_or_null, int K, float alpha,
+                         float* out) {
+  OperandSet& os = h->sets[0];
+  const bool rw = h->desc.hp == BETTY_HP_REWEIGHT_NET;
+  const int L = h->L;
+  const LayerInfo& lo = h->layers[L - 1];
+  make_weight_operands(h, os, w);
+  if (u_or_null) {
+    prepare_lower(h, os, w, lambda);
+    make_shadows(h, os, u_or_null, &os.Vn, &os.Vt);
+  } else {
+    forward_backward(h, os, SIDE_BOTH, w, wnet_theta(h, lambda));
+  }
+  samples_begin(h, os, u_or_null, K > 0);
+  for (int k = 0; k < K; ++k) {
+    const bool last = k + 1 == K;
+    const bool update = rw || !last;
+    samples_chains(h, os, k == 0, update, last);
+    if (!rw) samples_accumulate(h, os, k == 0, last, alpha);
+    if (update) samples_update(h, os, k == 0, last, alpha);
+  }
+  SideBuf& sb = os.side[0];
+  if (rw) {
+    // the mixed term is one more R-forward along the final sum
+    const std::vector<size_t>& AS = K > 0 ? os.AS : os.Ag;
+    const bool narrow = L >= 2 && lo.n_out <= LAST_ROP_MAX_C;
+    samples_r_forward(h, os, AS, narrow ? L - 1 : L);
+    if (narrow) {
+      LastRopArgs a = samples_last_args(h, os, AS);
+      a.cvec = h->f(os.cvec); a.labels = h->at<Labels>(h->labels); a.Z = h->f(sb.ZL);
+      launch_last_layer_rop(h->ctx, os.elem, a);
+    } else {
+      launch_loss_directional_rows(h->ctx, h->desc.loss, h->f(sb.P), h->f(sb.ZL), h->at<Labels>(h->labels),
+                                   h->f(L == 1 ? AS[1] : os.Rz[L]), lo.n_out_p, sb.B, lo.n_out, h->f(os.cvec));
+    }
+    launch_wnet_theta_vjp(h->ctx, h->f(sb.ell), h->f(sb.dsig), h->f(os.cvec), lambda, h->desc.wnet_hidden, sb.B,
+                          alpha / (float)sb.B, out);
+    return;
+  }
+  // proximal cost: d(anchor) = 2 rho alpha s with s = (sum_j beta^j) g - alpha sum_k beta^(K-1-k) (Ra^T delta + a^T R delta)_k
+  const float* g = u_or_null;
+  if (!g) {
+    wgrad_batch(h, os, 1, false, WgradSink{EPI_WGRAD, h->f(h->vec_v), nullptr, nullptr, nullptr, nullptr, 0.f, false});
+    g = h->f(h->vec_v);
+  }
+  WgradSink fin{EPI_WGRAD_SCALED, out, nullptr, g, nullptr, nullptr, alpha, false};
+  fin.K = K;
+  wgrad_batch(h, os, 0, true, fin);
+}
+
 // out = (dw* / dlambda) u by the K-step Neumann series and the mixed VJP; u = grad_w L_U(w) on the
 // validation batch when u_or_null is null.  Only enqueues launches on the handle's stream.
 // The partial sum is carried in nested form, s <- g + (I - alpha H) s from s = g: after K steps
 // s = sum_{j<=K} (I - alpha H)^j g, with one parameter-sized state vector to read and write per step.
 static void neumann_seq(betty_handle h, const float* w, const float* lambda, const float* u_or_null, int K,
                         float alpha, float* out) {
+  if (use_samples(h, K)) { neumann_samples_seq(h, w, lambda, u_or_null, K, alpha, out); return; }
   OperandSet& os = h->sets[0];
   const bool l2 = h->desc.hp == BETTY_HP_L2_DECAY, rw = h->desc.hp == BETTY_HP_REWEIGHT_NET;
   const float* dl = diag_log(h, lambda);
@@ -1076,7 +1481,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
   h->use_pipeline = large && desc->prec == BETTY_PREC_FP32;
   h->fd_two_streams = !large;
   h->max_Bp = std::max(padup(desc->batch_train), padup(desc->batch_val));
-  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,rect=<n>,pipe=<0|1>,fd2=<0|1>" (see plan_chain)
+  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>" (see plan_chain)
   if (const char* t = getenv("BETTY_TUNE")) {
     int v;
     if (const char* q = strstr(t, "wgrad=")) if (sscanf(q + 6, "%d", &v) == 1 && (v == GEMM_128x1 || v == GEMM_64x1)) h->tune_wgrad_cfg = v;
@@ -1086,6 +1491,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
     if (const char* q = strstr(t, "rect=")) if (sscanf(q + 5, "%d", &v) == 1) h->tune_rect_forced = v > 1024;
     if (const char* q = strstr(t, "wgrad128=")) if (sscanf(q + 9, "%d", &v) == 1 && v >= 0) h->tune_wgrad128_min = v;
     if (const char* q = strstr(t, "pipe=")) if (sscanf(q + 5, "%d", &v) == 1) h->use_pipeline = v != 0;
+    if (const char* q = strstr(t, "samples=")) if (sscanf(q + 8, "%d", &v) == 1) h->tune_samples = v != 0;
     if (const char* q = strstr(t, "fd2=")) if (sscanf(q + 4, "%d", &v) == 1) h->fd_two_streams = v != 0;
   }
   plan(h);
@@ -1486,7 +1892,9 @@ betty_status betty_lower_sgd_step(betty_handle h, float* w, const float* lambda,
     const bool prox = h->desc.hp == BETTY_HP_PROXIMAL;
     const float* dl = diag_log(h, lambda);
     make_weight_operands(h, os, w);
+    h->fixed_grouping = true;
     forward_backward(h, os, SIDE_TRAIN, w, wnet_theta(h, lambda));
+    h->fixed_grouping = false;
     if (loss_or_null) {                      // the cost at the w before the step
       float* add = nullptr;
       if (dl) {

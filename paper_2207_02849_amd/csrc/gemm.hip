@@ -29,6 +29,7 @@
 // C[8*(r/4) + 4*(l/32) + r%4][l%32]: four consecutive rows of one column per register quad, which
 // is what the epilogues consume (one 4-element vector store into the transposed output).
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -98,12 +99,13 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
       const bool ok = colok && row < M;
       R.a[k] = (ok && e.dphi) ? e.dphi[epi_offset<NR>(rb, k, e.ldf, col)] : 0.f;
       R.b[k] = ok ? e.e[row] : 0.f;
+      R.c[k] = (ok && e.e_io) ? e.e_io[epi_offset<NR>(rb, k, e.ldf, col)] : 0.f;
     }
     return;
   }
-  if (col >= N || rb >= M) return;
+  if (MODE == EPI_GRAM || (MODE == EPI_RBWD && e.mode == EPI_GRAM) || col >= N || rb >= M) return;
   const long long ldx = MODE >= EPI_WGRAD ? e.ldc : e.ldf;
-  if constexpr (MODE == EPI_FWD || MODE == EPI_FWD_LAST || MODE == EPI_RFWD || MODE == EPI_RFWD_LAST)
+  if constexpr (MODE == EPI_SAMPLE || MODE == EPI_FWD || MODE == EPI_FWD_LAST || MODE == EPI_RFWD || MODE == EPI_RFWD_LAST)
     R.colv = e.colvec ? e.colvec[col] : 0.f;
 #pragma unroll
   for (int k = 0; k < NR; ++k) {
@@ -114,7 +116,15 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
       R.b[k] = (ok && e.e_io) ? e.e_io[o] : 0.f;
     } else if constexpr (MODE == EPI_RFWD) {
       R.a[k] = ok ? e.dphi[o] : 0.f;
+      R.b[k] = (ok && e.e) ? e.e[o] : 0.f;
+    } else if constexpr (MODE == EPI_RFWD_LAST) {
+      R.b[k] = (ok && e.e) ? e.e[o] : 0.f;
+    } else if constexpr (MODE == EPI_SAMPLE) {
+      R.a[k] = (ok && e.dphi) ? e.dphi[o] : 0.f;
+      R.b[k] = (ok && e.e) ? e.e[o] : 0.f;
+      R.c[k] = (ok && e.Rz) ? e.Rz[o] : 0.f;
     } else if constexpr (MODE == EPI_RBWD) {
+      R.d[k] = (ok && e.e_io) ? e.e_io[o] : 0.f;
       R.a[k] = ok ? e.dphi[o] : 0.f;
       R.b[k] = (ok && e.e) ? e.e[o] : 0.f;
       R.c[k] = (ok && e.e) ? e.Rz[o] : 0.f;
@@ -130,11 +140,32 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
       R.b[k] = ok ? e.v[o] : 0.f;                         // g
       R.c[k] = ok ? e.lam[o] : 0.f;
       R.d[k] = ok ? e.x[o] : 0.f;                         // w
+    } else if constexpr (MODE == EPI_WGRAD_SCALED) {
+      R.a[k] = ok ? e.x[o] : 0.f;
     } else if constexpr (MODE == EPI_WGRAD_SGD) {
       R.a[k] = ok ? e.v[o] : 0.f;
       R.b[k] = ok ? e.p[o] : 0.f;
       R.c[k] = (ok && e.lam) ? e.lam[o] : 0.f;
       R.d[k] = (ok && e.x) ? e.x[o] : 0.f;
+    }
+  }
+}
+
+// a matrix over pairs of samples: fp32 as it is, bf16 as value and remainder (GemmArgs::split)
+template <typename T, int NR>
+__device__ __forceinline__ void epi_gram(const Epilogue& e, int M, int rb, int col, const float (&acc)[NR]) {
+  T* o = (T*)e.out;
+#pragma unroll
+  for (int k = 0; k < NR; ++k) {
+    if (epi_row<NR>(rb, k) >= M) continue;
+    const float x = acc[k] + e.gamma;
+    const long long at = (long long)epi_row<NR>(rb, k) * e.ld;
+    if constexpr (sizeof(T) == 4) {
+      o[at + col] = x;
+    } else {
+      const T hi = (T)x;
+      o[at + (col >> 6) * 128 + (col & 63)] = hi;
+      o[at + (col >> 6) * 128 + (col & 63) + 64] = (T)(x - (float)hi);
     }
   }
 }
@@ -149,7 +180,7 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
     float rz[NR], dot[NR];
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
-      rz[k] = colok ? acc[k] + R.colv : 0.f;
+      rz[k] = colok ? acc[k] + (R.colv + R.c[k]) : 0.f;
       dot[k] = R.a[k] * rz[k];
     }
     if (e.act == BETTY_LOSS_SOFTMAX_CE) {
@@ -165,6 +196,7 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
     }
   }
   if (col >= N || rb >= M) return;
+  if (MODE == EPI_GRAM || (MODE == EPI_RBWD && e.mode == EPI_GRAM)) { epi_gram<T, NR>(e, M, rb, col, acc); return; }
   const long long ldx = MODE >= EPI_WGRAD ? e.ldc : e.ldf;
   bool ok[NR];
   int of[NR];
@@ -187,10 +219,22 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
       for (int k = 0; k < NR; ++k)
         if (ok[k]) e.d2_out[of[k]] = d2[k];
     }
-  } else if constexpr (MODE == EPI_FWD_LAST || MODE == EPI_RFWD_LAST) {
+  } else if constexpr (MODE == EPI_SAMPLE) {
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const float sn = R.c[k] + (e.beta * R.b[k] - e.alpha * acc[k]) + R.colv;
+      if (ok[k]) e.f0[of[k]] = sn;
+      val[k] = R.a[k] * sn;
+    }
+  } else if constexpr (MODE == EPI_FWD_LAST) {
 #pragma unroll
     for (int k = 0; k < NR; ++k)
       if (ok[k]) e.f0[of[k]] = acc[k] + R.colv;
+    return;
+  } else if constexpr (MODE == EPI_RFWD_LAST) {
+#pragma unroll
+    for (int k = 0; k < NR; ++k)
+      if (ok[k]) e.f0[of[k]] = acc[k] + (R.colv + R.b[k]);
     return;
   } else if constexpr (MODE == EPI_BWD) {
     if (e.e_io) {
@@ -203,12 +247,12 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
   } else if constexpr (MODE == EPI_RFWD) {
 #pragma unroll
     for (int k = 0; k < NR; ++k)
-      if (ok[k]) e.f0[of[k]] = acc[k] + R.colv;
+      if (ok[k]) e.f0[of[k]] = acc[k] + (R.colv + R.b[k]);
 #pragma unroll
-    for (int k = 0; k < NR; ++k) val[k] = R.a[k] * (acc[k] + R.colv);
+    for (int k = 0; k < NR; ++k) val[k] = R.a[k] * (acc[k] + (R.colv + R.b[k]));
   } else if constexpr (MODE == EPI_RBWD) {
 #pragma unroll
-    for (int k = 0; k < NR; ++k) val[k] = acc[k] * R.a[k] + R.b[k] * R.c[k];
+    for (int k = 0; k < NR; ++k) val[k] = (acc[k] + R.d[k]) * R.a[k] + R.b[k] * R.c[k];
   } else if constexpr (MODE == EPI_WGRAD) {            // C = acc (+ 2 e^lam x)
     if (e.lam) {
 #pragma unroll
@@ -236,6 +280,11 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
 #pragma unroll
     for (int k = 0; k < NR; ++k)
       if (ok[k]) e.p[of[k]] = val[k];
+  } else if constexpr (MODE == EPI_WGRAD_SCALED) {
+#pragma unroll
+    for (int k = 0; k < NR; ++k)
+      if (ok[k]) e.C[of[k]] = e.gamma * (e.beta * R.a[k] - e.alpha * acc[k]);
+    return;
   } else if constexpr (MODE == EPI_WGRAD_SGD) {          // lower optimiser step: momentum SGD in place
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
@@ -349,6 +398,9 @@ __device__ void bias_rows(const BiasJob& j, int row) {
       j.p[row] = j.v[row] + (so - j.alpha * hs);
       break;
     }
+    case EPI_WGRAD_SCALED:
+      j.C[row] = j.gamma * (j.beta * j.x[row] - j.alpha * acc);
+      break;
     case EPI_WGRAD_SGD: {
       const float wo = j.p[row];
       float gk = acc + j.gamma * wo;
@@ -368,12 +420,10 @@ __device__ void bias_rows(const BiasJob& j, int row) {
   }
 }
 
-template <int MODE> struct BatchOf { typedef ChainBatch type; };
-template <> struct BatchOf<EPI_WGRAD> { typedef GemmBatch type; };
-template <> struct BatchOf<EPI_WGRAD_INIT> { typedef GemmBatch type; };
-template <> struct BatchOf<EPI_WGRAD_NEUMANN> { typedef GemmBatch type; };
-template <> struct BatchOf<EPI_WGRAD_NEUMANN_L2> { typedef GemmBatch type; };
-template <> struct BatchOf<EPI_WGRAD_SGD> { typedef GemmBatch type; };
+template <int MODE> struct BatchOf {
+  typedef std::conditional_t<(MODE >= EPI_WGRAD), WgradBatch,
+                             std::conditional_t<(MODE == EPI_GRAM || MODE == EPI_SAMPLE), SampleBatch, ChainBatch>> type;
+};
 
 // (128-tiles are compiled for two resident workgroups per compute unit, so that one workgroup's
 // epilogue traffic overlaps the other's k loop)
@@ -428,7 +478,8 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
   }
   const int m0 = tm * BM, n0 = tn * BN;
 
-  const int T0 = (g.K[0] + KT - 1) / KT, T1 = (g.K[1] + KT - 1) / KT, TT = T0 + T1;
+  const int sp = g.split;                          // (see GemmArgs::split)
+  const int T0 = (g.K[0] + KT - 1) / KT << sp, T1 = (g.K[1] + KT - 1) / KT << sp, TT = T0 + T1;
   const int NI = (TT + KG - 1) / KG;               // iterations of every group (same barrier count)
   const int tb = kg * NI;
   const int te = tb + NI < TT ? tb + NI : TT;
@@ -487,7 +538,7 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
     const bool second_ = (t_) >= T0;                                                                 \
     const int tt_ = second_ ? (t_) - T0 : (t_);                                                      \
     const T* Ab_ = (second_ ? Abase1 : Abase0) + (long long)tt_ * KT;                                \
-    const T* Bb_ = (second_ ? Bbase1 : Bbase0) + (long long)tt_ * KT;                                \
+    const T* Bb_ = (second_ ? Bbase1 : Bbase0) + (long long)(tt_ >> sp) * KT;                        \
     const long long lda_ = (second_ ? lda1 : lda0) * (GT / NCH);                                    \
     const long long ldb_ = (second_ ? ldb1 : ldb0) * (GT / NCH);                                    \
     _Pragma("unroll") for (int i_ = 0; i_ < LA; ++i_) RA_[i_] = *(const u32x4*)(Ab_ + i_ * lda_);    \
@@ -680,13 +731,15 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
   EpiRegs<1> pre;
   if (t < 256) epi_prefetch<MODE, 1>(e, g.M, g.N, row, col, pre);
 
-  const int S0 = (g.K[0] + KS - 1) / KS, S = S0 + (g.K[1] + KS - 1) / KS;
+  const bool sp = g.split;
+  const int S0 = sp ? (g.K[0] + 63) / 64 * 4 : (g.K[0] + KS - 1) / KS;
+  const int S = S0 + (sp ? (g.K[1] + 63) / 64 * 4 : (g.K[1] + KS - 1) / KS);
   const int per = (S + KG - 1) / KG, s_begin = kg * per, s_end = min(S, s_begin + per);
   const int fr = lane & 15, fc = (lane >> 4) * EPC;
   const T* A0 = (const T*)g.A[0] + (long long)(m0 + fr) * g.lda[0] + fc;
   const T* B0 = (const T*)g.B[0] + (long long)(n0 + fr) * g.ldb[0] + fc;
-  const T* A1 = (const T*)g.A[1] + (long long)(m0 + fr) * g.lda[1] + fc - (long long)S0 * KS;
-  const T* B1 = (const T*)g.B[1] + (long long)(n0 + fr) * g.ldb[1] + fc - (long long)S0 * KS;
+  const T* A1 = (const T*)g.A[1] + (long long)(m0 + fr) * g.lda[1] + fc;
+  const T* B1 = (const T*)g.B[1] + (long long)(n0 + fr) * g.ldb[1] + fc;
   f32x4v acc = {0.f, 0.f, 0.f, 0.f};
   for (int s = s_begin; s < s_end; s += U) {
     u32x4 a[U], b[U];
@@ -694,8 +747,9 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
     for (int u = 0; u < U; ++u) {                  // (steps beyond the range repeat the last one and are not multiplied)
       const int q = min(s + u, s_end - 1);
       const bool second = q >= S0;
-      a[u] = *(const u32x4*)((second ? A1 : A0) + (long long)q * KS);
-      b[u] = *(const u32x4*)((second ? B1 : B0) + (long long)q * KS);
+      const int qa = second ? q - S0 : q, qb = sp ? (qa >> 2 << 1) | (qa & 1) : qa;   // two steps of value, two of remainder
+      a[u] = *(const u32x4*)((second ? A1 : A0) + (long long)qa * KS);
+      b[u] = *(const u32x4*)((second ? B1 : B0) + (long long)qb * KS);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -728,7 +782,7 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
 
 template <int MODE, bool LAM> constexpr int wg_narr() {
   return MODE == EPI_WGRAD ? (LAM ? 2 : 0) : MODE == EPI_WGRAD_INIT ? 0 : MODE == EPI_WGRAD_NEUMANN ? (LAM ? 3 : 2)
-       : MODE == EPI_WGRAD_SGD ? (LAM ? 4 : 2) : 4;
+       : MODE == EPI_WGRAD_SGD ? (LAM ? 4 : 2) : MODE == EPI_WGRAD_SCALED ? 1 : 4;
 }
 template <int MODE, bool LAM> constexpr int wg_nreg() { return wg_narr<MODE, LAM>() > 0 ? wg_narr<MODE, LAM>() : 1; }
 
@@ -827,6 +881,8 @@ __device__ __forceinline__ void wg_finish(const WgTile& w, int pass, int pr, int
         val[i][j] = LAM ? a + 2.f * expf(I0[i][j]) * I1[i][j] : a;
       } else if constexpr (MODE == EPI_WGRAD_INIT) {
         val[i][j] = a;
+      } else if constexpr (MODE == EPI_WGRAD_SCALED) {     // I0 = x
+        val[i][j] = w.gamma * (w.beta * I0[i][j] - w.alpha * a);
       } else if constexpr (MODE == EPI_WGRAD_NEUMANN) {    // I0 = s, I1 = g, I2 = lam
         float h = a;
         if constexpr (LAM) h += 2.f * expf(I2[i][j]) * I0[i][j];
@@ -843,7 +899,7 @@ __device__ __forceinline__ void wg_finish(const WgTile& w, int pass, int pr, int
         val2[i][j] = I1[i][j] - w.alpha * mk;
       }
     }
-  if constexpr (MODE == EPI_WGRAD || MODE == EPI_WGRAD_NEUMANN_L2) {
+  if constexpr (MODE == EPI_WGRAD || MODE == EPI_WGRAD_NEUMANN_L2 || MODE == EPI_WGRAD_SCALED) {
     store_patch<VEC>(w.C, w.ldc, row0, col0, w.M, w.N, val);
     return;
   } else if constexpr (MODE == EPI_WGRAD_SGD) {
@@ -921,7 +977,7 @@ __device__ __forceinline__ void wg_epilogue(const WgTile& w, int pr, int pc, int
 }
 
 template <int MODE, bool LAM>
-__global__ __launch_bounds__(256, 2) void wgrad128_kernel(GemmBatch batch) {
+__global__ __launch_bounds__(256, 2) void wgrad128_kernel(WgradBatch batch) {
   typedef __bf16 T;
   constexpr int BT = WG_BT, NCH = GEMM_NCH, ROW = NCH + 1, EPC = 8, KT = NCH * EPC, GT = 256;
   constexpr int LA = BT * NCH / GT;
@@ -1028,6 +1084,7 @@ __global__ __launch_bounds__(256, 2) void wgrad128_kernel(GemmBatch batch) {
     if constexpr (MODE == EPI_WGRAD) { w.src[0] = e.lam; w.src[1] = e.x; w.src[2] = e.lam; w.src[3] = e.lam; }
     else if constexpr (MODE == EPI_WGRAD_NEUMANN) { w.src[0] = e.x; w.src[1] = e.v; w.src[2] = e.lam; w.src[3] = e.x; }
     else if constexpr (MODE == EPI_WGRAD_NEUMANN_L2) { w.src[0] = e.p; w.src[1] = e.v; w.src[2] = e.lam; w.src[3] = e.x; }
+    else if constexpr (MODE == EPI_WGRAD_SCALED) { w.src[0] = e.x; w.src[1] = w.src[2] = w.src[3] = e.x; }
     else if constexpr (MODE == EPI_WGRAD_SGD) { w.src[0] = e.v; w.src[1] = e.p; w.src[2] = e.lam; w.src[3] = e.x ? e.x : e.p; }
     else { w.src[0] = w.src[1] = w.src[2] = w.src[3] = nullptr; }
     // 16-byte accesses need every flat vector of the tile aligned and the tile inside the columns
@@ -1099,20 +1156,20 @@ __global__ __launch_bounds__(256, 2) void wgrad128_kernel(GemmBatch batch) {
 // host side
 // ------------------------------------------------------------------------------------------
 
-// the by-value argument block of a launch: weight-gradient launches pass the batch as it is,
-// activation-shaped ones (at most two problems) its short form
+// the by-value argument block of a launch, cut to its kind
 template <int MODE>
 static typename BatchOf<MODE>::type kernel_args(const GemmBatch& b) {
+  typename BatchOf<MODE>::type c;
+  c.n = b.n; c.n_bias = b.n_bias; c.gemm_blocks = b.gemm_blocks; c.walkers = b.walkers;
+  for (int i = 0; i <= b.n; ++i) c.block_begin[i] = b.block_begin[i];
+  for (int i = 0; i < b.n; ++i) c.p[i] = b.p[i];
   if constexpr (MODE >= EPI_WGRAD) {
-    return b;
-  } else {
-    ChainBatch c;
-    c.n = b.n; c.gemm_blocks = b.gemm_blocks;
-    for (int i = 0; i <= b.n; ++i) c.block_begin[i] = b.block_begin[i];
-    for (int i = 0; i < b.n; ++i) c.p[i] = b.p[i];
-    return c;
+    for (int i = 0; i <= b.n_bias; ++i) c.bias_begin[i] = b.bias_begin[i];
+    for (int i = 0; i < b.n_bias; ++i) c.bias[i] = b.bias[i];
   }
+  return c;
 }
+static int max_problems(int mode) { return mode >= EPI_WGRAD ? MAX_PROBLEMS : mode >= EPI_GRAM ? MAX_SAMPLE_PROBLEMS : MAX_CHAIN_PROBLEMS; }
 
 template <typename T, int BT, int WPG, int KG>
 constexpr size_t lds_bytes() {
@@ -1158,7 +1215,7 @@ static void launch_rect_mode(int mode, int total, hipStream_t st, const GemmBatc
   switch (mode) {
 #define BETTY_CASE_R(M_) case M_: launch_rect<T, M_>(total, st, b, err); break;
     BETTY_CASE_R(EPI_FWD) BETTY_CASE_R(EPI_FWD_LAST) BETTY_CASE_R(EPI_BWD) BETTY_CASE_R(EPI_RFWD)
-    BETTY_CASE_R(EPI_RFWD_LAST) BETTY_CASE_R(EPI_RBWD) BETTY_CASE_R(EPI_RFWD_LAST_HESS)
+    BETTY_CASE_R(EPI_RFWD_LAST) BETTY_CASE_R(EPI_RBWD) BETTY_CASE_R(EPI_RFWD_LAST_HESS) BETTY_CASE_R(EPI_GRAM) BETTY_CASE_R(EPI_SAMPLE)
 #undef BETTY_CASE_R
     default: err = hipErrorInvalidValue; break;
   }
@@ -1169,7 +1226,7 @@ static void launch_chain_mode(int mode, int total, hipStream_t st, const GemmBat
   switch (mode) {
 #define BETTY_CASE(M_) case M_: launch_one<T, BT, WPG, KG, M_>(total, st, b, err); break;
     BETTY_CASE(EPI_FWD) BETTY_CASE(EPI_FWD_LAST) BETTY_CASE(EPI_BWD) BETTY_CASE(EPI_RFWD)
-    BETTY_CASE(EPI_RFWD_LAST) BETTY_CASE(EPI_RBWD) BETTY_CASE(EPI_RFWD_LAST_HESS)
+    BETTY_CASE(EPI_RFWD_LAST) BETTY_CASE(EPI_RBWD) BETTY_CASE(EPI_RFWD_LAST_HESS) BETTY_CASE(EPI_GRAM) BETTY_CASE(EPI_SAMPLE)
     default: err = hipErrorInvalidValue; break;
   }
 }
@@ -1179,7 +1236,7 @@ static void launch_wgrad_mode(int mode, int total, hipStream_t st, const GemmBat
   switch (mode) {
 #define BETTY_CASE_W(M_) case M_: launch_one<T, BT, WPG, KG, M_>(total, st, b, err); break;
     BETTY_CASE_W(EPI_WGRAD) BETTY_CASE_W(EPI_WGRAD_INIT) BETTY_CASE_W(EPI_WGRAD_NEUMANN)
-    BETTY_CASE_W(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_W(EPI_WGRAD_SGD)
+    BETTY_CASE_W(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_W(EPI_WGRAD_SGD) BETTY_CASE_W(EPI_WGRAD_SCALED)
 #undef BETTY_CASE_W
     default: err = hipErrorInvalidValue; break;
   }
@@ -1195,7 +1252,7 @@ static void launch_wgrad128_one(int total, hipStream_t st, const GemmBatch& b, h
     if (e != hipSuccess) { err = e; return; }
     configured = true;
   }
-  wgrad128_kernel<MODE, LAM><<<total - b.gemm_blocks + b.walkers, 256, WG_LDS, st>>>(b);
+  wgrad128_kernel<MODE, LAM><<<total - b.gemm_blocks + b.walkers, 256, WG_LDS, st>>>(kernel_args<MODE>(b));
 }
 
 // bf16 weight-gradient launches on 128-tiles; the L2-decay term (lam) is the same for every problem of a batch
@@ -1206,6 +1263,7 @@ static void launch_wgrad128(int mode, int total, hipStream_t st, const GemmBatch
     BETTY_CASE_W(EPI_WGRAD) BETTY_CASE_W(EPI_WGRAD_NEUMANN) BETTY_CASE_W(EPI_WGRAD_SGD)
 #undef BETTY_CASE_W
     case EPI_WGRAD_INIT: launch_wgrad128_one<EPI_WGRAD_INIT, false>(total, st, b, err); break;
+    case EPI_WGRAD_SCALED: launch_wgrad128_one<EPI_WGRAD_SCALED, false>(total, st, b, err); break;
     case EPI_WGRAD_NEUMANN_L2: launch_wgrad128_one<EPI_WGRAD_NEUMANN_L2, true>(total, st, b, err); break;
     default: err = hipErrorInvalidValue; break;
   }
@@ -1223,7 +1281,7 @@ template <typename T>
 static int batch_steps(const GemmBatch& b) {
   constexpr int KS = 64 / (int)sizeof(T);
   int S = 1;
-  for (int i = 0; i < b.n; ++i) S = std::max(S, (b.p[i].g.K[0] + KS - 1) / KS + (b.p[i].g.K[1] + KS - 1) / KS);
+  for (int i = 0; i < b.n; ++i) S = std::max(S, ((b.p[i].g.K[0] + KS - 1) / KS + (b.p[i].g.K[1] + KS - 1) / KS) << b.p[i].g.split);
   return S;
 }
 
@@ -1245,9 +1303,9 @@ static void launch_small_mode(int mode, int total, hipStream_t st, const GemmBat
   switch (mode) {
 #define BETTY_CASE_S(M_) case M_: launch_small<T, M_>(total, st, b); break;
     BETTY_CASE_S(EPI_FWD) BETTY_CASE_S(EPI_FWD_LAST) BETTY_CASE_S(EPI_BWD) BETTY_CASE_S(EPI_RFWD)
-    BETTY_CASE_S(EPI_RFWD_LAST) BETTY_CASE_S(EPI_RBWD) BETTY_CASE_S(EPI_RFWD_LAST_HESS)
+    BETTY_CASE_S(EPI_RFWD_LAST) BETTY_CASE_S(EPI_RBWD) BETTY_CASE_S(EPI_RFWD_LAST_HESS) BETTY_CASE_S(EPI_GRAM) BETTY_CASE_S(EPI_SAMPLE)
     BETTY_CASE_S(EPI_WGRAD) BETTY_CASE_S(EPI_WGRAD_INIT) BETTY_CASE_S(EPI_WGRAD_NEUMANN)
-    BETTY_CASE_S(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_S(EPI_WGRAD_SGD)
+    BETTY_CASE_S(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_S(EPI_WGRAD_SGD) BETTY_CASE_S(EPI_WGRAD_SCALED)
 #undef BETTY_CASE_S
     default: err = hipErrorInvalidValue; break;
   }
@@ -1255,7 +1313,7 @@ static void launch_small_mode(int mode, int total, hipStream_t st, const GemmBat
 
 template <typename T>
 static void launch_elem(int cfg, int mode, int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
-  if (mode < EPI_WGRAD && b.n > 2) { err = hipErrorInvalidValue; return; }
+  if (b.n > max_problems(mode)) { err = hipErrorInvalidValue; return; }
   if (cfg == GEMM_16) { launch_small_mode<T>(mode, total, st, b, err); return; }
   if (mode >= EPI_WGRAD) {
     if (cfg == GEMM_128x1 && sizeof(T) == 2) launch_wgrad128(mode, total, st, b, err);
@@ -1269,6 +1327,12 @@ static void launch_elem(int cfg, int mode, int total, hipStream_t st, const Gemm
     case GEMM_128x1: launch_chain_mode<T, 128, 4, 1>(mode, total, st, b, err); break;
     case GEMM_64x1: launch_chain_mode<T, 64, 4, 1>(mode, total, st, b, err); break;
     case GEMM_32x8: launch_chain_mode<T, 32, 1, 8>(mode, total, st, b, err); break;
+    case GEMM_32x4:                                  // first-order passes of optimiser steps only (plan_chain)
+      if (mode == EPI_FWD) launch_one<T, 32, 1, 4, EPI_FWD>(total, st, b, err);
+      else if (mode == EPI_FWD_LAST) launch_one<T, 32, 1, 4, EPI_FWD_LAST>(total, st, b, err);
+      else if (mode == EPI_BWD) launch_one<T, 32, 1, 4, EPI_BWD>(total, st, b, err);
+      else err = hipErrorInvalidValue;
+      break;
     case GEMM_128x64: launch_rect_mode<T>(mode, total, st, b, err); break;
     default: err = hipErrorInvalidValue; break;
   }
@@ -1286,7 +1350,7 @@ static int resident_cus() {
   return cus;
 }
 
-int gemm_cfg_tile(int cfg) { return cfg == GEMM_128x1 ? 128 : cfg == GEMM_32x8 ? 32 : cfg == GEMM_16 ? 16 : 64; }   // (columns, for 128x64)
+int gemm_cfg_tile(int cfg) { return cfg == GEMM_128x1 ? 128 : (cfg == GEMM_32x8 || cfg == GEMM_32x4) ? 32 : cfg == GEMM_16 ? 16 : 64; }   // (columns, for 128x64)
 static int gemm_cfg_tile_rows(int cfg) { return cfg == GEMM_128x64 ? 128 : gemm_cfg_tile(cfg); }
 static int gemm_cfg_waves(int cfg) { return cfg == GEMM_32x8 ? 8 : 4; }
 

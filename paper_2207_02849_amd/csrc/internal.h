@@ -28,6 +28,9 @@ struct GemmArgs {
   const void* B[2];
   int lda[2], ldb[2];        // leading dimensions in elements
   int K[2];                  // reduction extents in elements (operands are zero beyond them); 0 = pair absent
+  // A holds bf16 value and remainder (EPI_GRAM): every 64 elements of K are followed by the 64 remainders,
+  // both multiplied with the same 64 elements of B
+  int split;
   int M, N;                  // valid output extent: defines the tile grid; epilogue stores are bounds-checked against it
   // Workgroups go to the eight XCDs round-robin, so tiles t, t+8, t+16, ... of a problem share an
   // L2.  With xgm x xgn = 8 those tiles are laid out as one compact (tiles_m/xgm) x (tiles_n/xgn)
@@ -40,15 +43,21 @@ enum EpiMode {
   EPI_FWD = 1,             // z = acc + bias; out = phi(z); dphi_out = phi'(z); d2_out = phi''(z)
   EPI_FWD_LAST,          // f0 = acc + bias                       (logits)
   EPI_BWD,               // out = acc * dphi; e_io = acc * e_io   (delta of the layer below)
-  EPI_RFWD,              // f0 = rz = acc + cbias; out = dphi * rz
-  EPI_RFWD_LAST,         // f0 = acc + cbias
-  EPI_RBWD,              // out = acc * dphi + e * Rz
+  EPI_RFWD,              // f0 = rz = acc + cbias (+ e); out = dphi * rz
+  EPI_RFWD_LAST,         // f0 = acc + cbias (+ e)
+  EPI_RBWD,              // out = (acc (+ e_io)) * dphi + e * Rz;  problems of mode GRAM may share the launch
   // Last layer of the R-forward with the loss Hessian applied in place (outputs of at most 32
-  // columns, so that one MFMA block holds whole rows): rz = acc + cbias;
+  // columns, so that one MFMA block holds whole rows): rz = acc + cbias (+ e_io);
   // out = e[row] * (dphi .* rz - dphi * <dphi, rz>_row) for softmax cross-entropy (dphi = the
   // softmax probabilities, e = the per-sample scale), out = 2 e[row] rz for the squared error;
   // `act` carries the loss kind.
   EPI_RFWD_LAST_HESS,
+  // The series in sample space (see neumann_samples_seq):
+  //  GRAM    out = acc + gamma: a matrix over pairs of samples as the A operand of a later product; with bf16
+  //          operands as value + remainder (GemmArgs::split), which carries 16 bits of it
+  //  SAMPLE  f0 = s = g + beta x - alpha acc + colvec  (g = Rz, x = e, each may be null);
+  //          out, outT = dphi .* s when asked for
+  EPI_GRAM, EPI_SAMPLE,
   EPI_WGRAD,             // C = acc (+ 2 exp(lam) x)                       flat parameter layout
   EPI_WGRAD_INIT,        // v = acc (and p = acc when p is given); out = operand copies
   // One step of the Neumann partial sum in nested form, s_{j+1} = g + (I - alpha H) s_j with s_0 = g
@@ -57,22 +66,30 @@ enum EpiMode {
   // operand copies of the new s.
   EPI_WGRAD_NEUMANN,
   EPI_WGRAD_NEUMANN_L2,  // last step for L2 decay: s read from p, new s kept in registers, C = -2 exp(lam) x (alpha s)
+  EPI_WGRAD_SCALED,      // C = gamma (beta x - alpha acc)
   EPI_WGRAD_SGD          // g = acc (+ 2 exp(lam) p) + gamma p; v <- beta v + g; p <- p - alpha v  (p = w, v = momentum)
 };
 
 struct Epilogue {
   int mode, act;
   const float* colvec;                   // per-column addend (bias or bias direction), may be null
-  float* f0;                             // fp32 [row * ldf + col]
-  float* dphi_out; float* d2_out;
-  const float* dphi; float* e_io; const float* e; const float* Rz;
-  long long ldf;
   void* out; int ld;                     // operand-typed, row-major [row][col]
-  void* outT; int ldT;                   // operand-typed, transposed [col][row]
-  void* out2; void* outT2;               // EPI_FWD only: further copies of `out` in bf16 (same ld, ldT), or null
-  float* C; long long ldc;               // fp32 row-major (flat parameter slice for the WGRAD modes)
-  const float* lam; const float* x;      // same indexing as C
-  float* v; float* p; float alpha, beta, gamma;
+  int ldT; void* outT;                   // operand-typed, transposed [col][row]
+  union {
+    struct {                             // activation-shaped modes
+      float* f0;                         // fp32 [row * ldf + col]
+      float* dphi_out; float* d2_out;
+      const float* dphi; float* e_io; const float* e; const float* Rz;
+      long long ldf;
+      void* out2; void* outT2;           // EPI_FWD only: further copies of `out` in bf16 (same ld, ldT), or null
+    };
+    struct {                             // parameter-shaped modes
+      float* C; long long ldc;           // fp32 row-major (flat parameter slice)
+      const float* lam; const float* x;  // same indexing as C
+      float* v; float* p;
+    };
+  };
+  float alpha, beta, gamma;
 };
 
 struct GemmProblem { GemmArgs g; Epilogue e; };
@@ -85,13 +102,13 @@ struct BiasJob {
 
 constexpr int MAX_PROBLEMS = 8;
 constexpr int GEMM_NCH = 8;              // 16-byte chunks per row of a k-tile
-// tile extent x number of K groups per workgroup; a group is 2 x 2 wavefronts, except in 32x8
-// (32-tile, eight groups of one wavefront) and 16 (16-tile, 4 to 16 groups of one wavefront)
-enum { GEMM_128x1 = 0, GEMM_64x1 = 2, GEMM_32x8 = 4, GEMM_128x64 = 5, GEMM_16 = 6 };
+// tile extent x number of K groups per workgroup; a group is 2 x 2 wavefronts, except in 32x8 and 32x4
+// (32-tile, groups of one wavefront) and 16 (16-tile, 4 to 16 groups of one wavefront)
+enum { GEMM_128x1 = 0, GEMM_64x1 = 2, GEMM_32x8 = 4, GEMM_128x64 = 5, GEMM_16 = 6, GEMM_32x4 = 7 };
 
-// Passed to the kernels by value.  Activation-shaped launches have at most two problems (train and
-// validation batch) and no bias rows; their short form costs the host less to launch
-// (2.7 us against 4.5 us outside a graph).
+// Assembled on the host and passed to the kernels by value, in a form cut to the kind of launch.
+// Activation-shaped launches have few problems (train and validation batch; a link of the R-backward chain
+// with matrices over samples, mode GRAM, beside it) and no bias rows; their short form costs the host less to launch (2.7 us against 4.5 us outside a graph).
 template <int NP, int NB> struct GemmBatchT {
   int n = 0, n_bias = 0, gemm_blocks = 0;
   int walkers = 0;                       // wgrad128_kernel: workgroups that walk the tiles (set by launch_gemm_batch)
@@ -100,9 +117,12 @@ template <int NP, int NB> struct GemmBatchT {
   GemmProblem p[NP];
   BiasJob bias[NB > 0 ? NB : 1];
 };
-typedef GemmBatchT<MAX_PROBLEMS, MAX_PROBLEMS> GemmBatch;
-typedef GemmBatchT<2, 0> ChainBatch;
-static_assert(sizeof(GemmBatch) <= 3584, "GemmBatch is passed by value as a kernel argument (4 KiB limit)");
+constexpr int MAX_SAMPLE_PROBLEMS = 16, MAX_CHAIN_PROBLEMS = 4;
+typedef GemmBatchT<MAX_SAMPLE_PROBLEMS, MAX_PROBLEMS> GemmBatch;
+typedef GemmBatchT<MAX_PROBLEMS, MAX_PROBLEMS> WgradBatch;
+typedef GemmBatchT<MAX_SAMPLE_PROBLEMS, 0> SampleBatch;
+typedef GemmBatchT<MAX_CHAIN_PROBLEMS, 0> ChainBatch;
+static_assert(sizeof(WgradBatch) <= 3840 && sizeof(SampleBatch) <= 3840, "passed by value as kernel arguments (4 KiB limit)");
 
 // Launch context: stream + optional per-launch event timing.
 struct ProfRec { int kind; double flops, bytes; hipEvent_t e0, e1; float ms; };
@@ -173,6 +193,12 @@ struct ConvertBatch {
 };
 void launch_convert_batch(Ctx&, Elem, ConvertBatch&);
 
+// Weighted sum over the steps of the series: sum = beta sum + r (sum = r on the first step); on the last step
+// the result goes back to r in the operand type.  n elements each, a multiple of 8.
+struct AccumulateJob { void* r; float* sum; float beta; size_t n; };
+struct AccumulateBatch { int n = 0; int block_begin[MAX_PROBLEMS + 1]; AccumulateJob j[MAX_PROBLEMS]; bool first, last; };
+void launch_accumulate(Ctx&, Elem, AccumulateBatch&);
+
 // ---- kernels.hip : loss rows ---------------------------------------------------------------
 struct LossArgs {
   int loss, reweight, hidden;
@@ -199,6 +225,9 @@ struct LastRopArgs {
   const void* Wt; const void* Vt; int ldt;              // W_L, V_L as [n_out_p][n_in_p]
   const void* Wn; const void* Vn; int ldn;              // W_L, V_L as [n_in_p][n_out_p]
   const float* cbias;                                   // bias direction of the last layer, or null
+  // Direction products formed elsewhere (the series in sample space): AS = a_{L-1} V_L + c_L [B][ldas] and
+  // DS = delta_L V_L^T [B][ldf] instead of A, Vt, Vn and cbias; null otherwise
+  const float* AS; int ldas; const float* DS;
   const float* P; const float* s; int ldp;              // softmax probabilities [B][ldp], per-sample scale
   const void* DL; int ldd;                              // delta_L [B][ldd], operand type
   const float* dphi; const float* e2; const float* Rz; int ldf;   // layer L-1, fp32 [B][ldf]; e2 may be null

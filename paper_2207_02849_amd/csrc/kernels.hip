@@ -162,6 +162,43 @@ void launch_convert_batch(Ctx& ctx, Elem elem, ConvertBatch& b) {
   else convert_batch_kernel<float><<<blocks, 256, 0, ctx.stream>>>(b);
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void accumulate_kernel(AccumulateBatch b) {
+  int bid = blockIdx.x, ji = 0;
+  while (ji + 1 < b.n && bid >= b.block_begin[ji + 1]) ++ji;
+  const AccumulateJob& j = b.j[ji];
+  const size_t i = ((size_t)(bid - b.block_begin[ji]) * 256 + threadIdx.x) * 8;
+  if (i >= j.n) return;
+  typedef __attribute__((__vector_size__(8 * sizeof(T)))) T vecT;
+  vecT r = *(const vecT*)((const T*)j.r + i);
+  float s[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) s[k] = (b.first ? 0.f : j.beta * j.sum[i + k]) + (float)r[k];
+  if (b.last) {
+#pragma unroll
+    for (int k = 0; k < 8; ++k) r[k] = from_float<T>(s[k]);
+    *(vecT*)((T*)j.r + i) = r;
+  } else {
+    *(float4*)(j.sum + i) = make_float4(s[0], s[1], s[2], s[3]);
+    *(float4*)(j.sum + i + 4) = make_float4(s[4], s[5], s[6], s[7]);
+  }
+}
+
+void launch_accumulate(Ctx& ctx, Elem elem, AccumulateBatch& b) {
+  int blocks = 0;
+  double bytes = 0;
+  for (int i = 0; i < b.n; ++i) {
+    b.block_begin[i] = blocks;
+    blocks += (int)((b.j[i].n / 8 + 255) / 256);
+    bytes += (double)b.j[i].n * (8.0 + elem_size(elem));
+  }
+  b.block_begin[b.n] = blocks;
+  if (blocks <= 0) return;
+  Launch l(ctx, BETTY_K_VECTOR, 0, bytes);
+  if (elem == ELEM_BF16) accumulate_kernel<__bf16><<<blocks, 256, 0, ctx.stream>>>(b);
+  else accumulate_kernel<float><<<blocks, 256, 0, ctx.stream>>>(b);
+}
+
 // ------------------------------------------------------------------------------------------
 // row-wise loss kernels: one wavefront per sample
 // ------------------------------------------------------------------------------------------
@@ -336,19 +373,20 @@ __global__ __launch_bounds__(1024) void last_layer_rop_kernel(LastRopArgs a) {
   const int j = jb + lane;
   const bool j_ok = jb_ok && lane < 32 && j < j_end;
   u32x4 w3[CP / (2 * EPC)], v3[CP / (2 * EPC)];
-  float dphi3[S], e23[S], rz3[S];
+  float dphi3[S], e23[S], rz3[S], ds3[S];
 #pragma unroll
   for (int p = 0; p < CP / (2 * EPC); ++p) { w3[p] = zero; v3[p] = zero; }
 #pragma unroll
-  for (int ss = 0; ss < S; ++ss) { dphi3[ss] = 0.f; e23[ss] = 0.f; rz3[ss] = 0.f; }
+  for (int ss = 0; ss < S; ++ss) { dphi3[ss] = 0.f; e23[ss] = 0.f; rz3[ss] = 0.f; ds3[ss] = 0.f; }
   if (jb_ok) {
     const int jr = jb + row;                                // < n_in_p: rows beyond n_in are zero padding
     const T* wr = (const T*)a.Wn + (long long)jr * a.ldn + half * EPC;
-    const T* vr = (const T*)a.Vn + (long long)jr * a.ldn + half * EPC;
 #pragma unroll
-    for (int p = 0; p < CP / (2 * EPC); ++p) {
-      w3[p] = *(const u32x4*)(wr + p * 2 * EPC);
-      v3[p] = *(const u32x4*)(vr + p * 2 * EPC);
+    for (int p = 0; p < CP / (2 * EPC); ++p) w3[p] = *(const u32x4*)(wr + p * 2 * EPC);
+    if (a.Vn) {
+      const T* vr = (const T*)a.Vn + (long long)jr * a.ldn + half * EPC;
+#pragma unroll
+      for (int p = 0; p < CP / (2 * EPC); ++p) v3[p] = *(const u32x4*)(vr + p * 2 * EPC);
     }
   }
   if (j_ok) {
@@ -358,6 +396,7 @@ __global__ __launch_bounds__(1024) void last_layer_rop_kernel(LastRopArgs a) {
         const long long f = (long long)(i0 + ss) * a.ldf + j;
         dphi3[ss] = a.dphi[f];
         if (a.e2) { e23[ss] = a.e2[f]; rz3[ss] = a.Rz[f]; }
+        if (a.DS) ds3[ss] = a.DS[f];
       }
   }
   float p2 = 0.f, s2 = 0.f, cb2 = 0.f;
@@ -369,6 +408,7 @@ __global__ __launch_bounds__(1024) void last_layer_rop_kernel(LastRopArgs a) {
     if (c < a.C && i < a.B) {
       if (a.loss == BETTY_LOSS_SOFTMAX_CE) p2 = a.P[(long long)i * a.ldp + c];
       if (a.cbias) cb2 = a.cbias[c];
+      if (a.AS) cb2 = a.AS[(long long)i * a.ldas + c];
       if (!a.cvec) {
         s2 = a.s[i];
         d2 = ((const T*)a.DL)[(long long)i * a.ldd + c];
@@ -397,7 +437,7 @@ __global__ __launch_bounds__(1024) void last_layer_rop_kernel(LastRopArgs a) {
         for (int u = 0; u < U; ++u)
           if (p0 + u < p_end) {
             r8[u] = *(const u32x4*)(ra + (p0 + u) * 2 * EPC);
-            a8[u] = *(const u32x4*)(av + (p0 + u) * 2 * EPC);
+            if (a.Vt) a8[u] = *(const u32x4*)(av + (p0 + u) * 2 * EPC);
           }
       }
       if (b_ok) {
@@ -405,13 +445,13 @@ __global__ __launch_bounds__(1024) void last_layer_rop_kernel(LastRopArgs a) {
         for (int u = 0; u < U; ++u)
           if (p0 + u < p_end) {
             w8[u] = *(const u32x4*)(w + (p0 + u) * 2 * EPC);
-            v8[u] = *(const u32x4*)(v + (p0 + u) * 2 * EPC);
+            if (a.Vt) v8[u] = *(const u32x4*)(v + (p0 + u) * 2 * EPC);
           }
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {                         // all-zero chunks add nothing
         MfmaChunk<T>::run(r8[u], w8[u], acc);
-        MfmaChunk<T>::run(a8[u], v8[u], acc);
+        if (a.Vt) MfmaChunk<T>::run(a8[u], v8[u], acc);
       }
     }
     // registers 0..3 of lanes 0..15 hold samples 0..3 of class `lane`
@@ -488,7 +528,7 @@ __global__ __launch_bounds__(1024) void last_layer_rop_kernel(LastRopArgs a) {
         const int ii = i0 + ss;
         float o = 0.f;
         if (ii < a.B) {
-          o = acc[ss] * dphi3[ss] + e23[ss] * rz3[ss];
+          o = (acc[ss] + ds3[ss]) * dphi3[ss] + e23[ss] * rz3[ss];
           ((T*)a.RD)[(long long)ii * a.ldRD + j] = from_float<T>(o);
         }
         out[ss] = o;                                       // rows beyond the batch: zero padding

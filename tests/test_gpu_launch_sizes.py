@@ -72,3 +72,35 @@ def test_recorded_calls_follow_streams_and_batches():
     b.stream.synchronize()                       # the handle's own stream is ordered behind the call
     assert rel_l2(out.cpu().numpy(), ref[1]) < 1e-4
     b.close()
+
+
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
+@pytest.mark.parametrize("kind,dims,batch,act", [
+    ("reweight", (40, 33), 65, "none"),                          # one layer: no link at all
+    ("reweight", (40, 9), 20, "none"),                           # ... with a narrow output
+    ("reweight", (300, 200, 150, 10), 130, "relu"),              # narrow output; batch of two padded 64-groups and a bit
+    ("reweight", (70, 200, 90, 20), 64, "gelu"),                 # wide output
+    ("proximal", (30, 31, 32, 33, 34, 35, 36, 37, 38, 5), 40, "gelu"),   # more layers than a launch has problems
+    ("proximal", (300, 150, 10), 129, "gelu"),
+    ("proximal", (33, 130, 40), 7, "none"),
+])
+def test_series_in_sample_space(kind, dims, batch, act, prec, tol, monkeypatch):
+    """Costs without a per-parameter diagonal carry the Neumann series over pairs of samples; forced on here,
+    from the validation gradient and from a dense vector, against the oracle and (where a family of
+    inputs is outside the tolerance in either form) no worse than the parameter-sized form."""
+    wl = wk.tiny(kind=kind, act=act, dims=dims, batch=batch, prec=prec, hidden=20, prox_skip_last=len(dims) > 3, prox_rho=0.3)
+    prob = oracle_problem(wl)
+    u = orc.lower_grad(prob, wl.w, wl.lam)[1].astype(np.float32)
+    err = {}
+    for form in (0, 1):
+        monkeypatch.setenv("BETTY_TUNE", f"samples={form}")
+        b = binding.from_workload(wl)
+        w, lam = dev(wl.w), dev(wl.lam)
+        for K in (0, 1, 4):
+            err[form, K] = max(
+                rel_l2(host(b.betty_hypergrad_neumann(w, lam, K, 0.05)), orc.hypergrad_neumann(prob, wl.w, wl.lam, K, 0.05)),
+                rel_l2(host(b.betty_best_response_neumann(w, lam, dev(u), K, 0.05)),
+                       orc.best_response_neumann(prob, wl.w, wl.lam, u.astype(np.float64), K, 0.05)))
+        b.close()
+    for K in (0, 1, 4):
+        assert err[1, K] < max(tol, 1.5 * err[0, K]), (K, err)
