@@ -392,7 +392,7 @@ int plan_wgrad(betty_handle h, Elem elem, int layer, bool rop, int B) {
   for (int i = first; i < last; ++i)
     x.add(elem, h->layers[i].n_in, h->layers[i].n_out, B, rop && i > 0 ? B : 0);
   if (elem == ELEM_BF16 && h->tune_wgrad128_min > 0 && x.t128 >= h->tune_wgrad128_min) return GEMM_128x1;
-  if (h->tune_wgrad_cfg != GEMM_64x1 || !h->tune_split || h->tune_wgrad128_min == 0 || elem == ELEM_BF16) return h->tune_wgrad_cfg;
+  if (h->tune_wgrad_cfg != GEMM_64x1 || !h->tune_split || h->tune_wgrad128_min == 0) return h->tune_wgrad_cfg;
   const int shorter = elem == ELEM_BF16 ? 1 : 2;
   if (x.t16 <= 256 || (x.t16 <= 512 && x.steps <= 4 * shorter) || (x.t16 <= 1024 && x.steps <= 2 * shorter)) return GEMM_16;
   return x.t32 <= 600 ? GEMM_32x8 : GEMM_64x1;
