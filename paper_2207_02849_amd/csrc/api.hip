@@ -89,9 +89,10 @@ struct betty_handle_s {
   unsigned long long epoch = 0;   // process-wide unique stamp of the last betty_bind
   OperandSet sets[2];        // [0]: element type of desc.prec; [1]: fp32 set for finite differences when prec is bf16
   OperandSet fd_minus;       // fp32, train side only: the evaluation at w - eps v, which runs beside the one at w + eps v
-  size_t vec_g = 0, vec_v = 0, vec_p = 0, vec_Hv = 0, vec_wpm = 0, vec_Gm = 0;
-  size_t vec_wpm2 = 0, vec_g2 = 0;   // the second evaluation's perturbed point and anchor distance
+  size_t vec_g = 0, vec_v = 0, vec_p = 0, vec_Hv = 0;
+  size_t bias_pm[2] = {0, 0};        // biases of the two perturbed points (flat layout; only the bias slices are used)
   size_t partials = 0, scalars = 0;
+  size_t sums = 0;           // what the weight-gradient launches sum up beside their results (Epilogue::partial)
   size_t labels = 0;         // Labels[2]: train, validation
   size_t logrho = 0;         // proximal cost: log(rho_j) per parameter (a large negative value where rho_j = 0)
   // A call repeated with the same arguments is replayed from a captured HIP graph.  Each kind of call
@@ -137,12 +138,12 @@ struct betty_handle_s {
   // rule picks elsewhere: activations and deltas are rounded to bf16 after every layer, so another grouping
   // sends a training run down another trajectory (up to 3e-3 in the momentum after a step or three).
   bool fixed_grouping = false;
+  bool as_pair = false;                       // choose kernels for single passes as if two shared the launch
   int tune_samples = -1;                      // sample-space series: 0 never, 1 wherever it exists, -1 by size
-  // Finite differences: the gradient evaluations at w + eps v and w - eps v are independent and run
-  // side by side on the two streams when one of them alone leaves part of the chip idle
-  // (measured: -10 % per hypergradient at 1M parameters, -1 % at 5M, +0.5 % at 116M, where each
-  // evaluation is bandwidth-bound already), so below the same 32M-parameter mark.
-  bool fd_two_streams = false;
+  // Finite differences: the passes at w + eps v and w - eps v share their launches, with weight operands
+  // for both points; above 32M parameters, where either alone fills the chip, they follow each other on one
+  // set of weight operands.  Same kernels on the same data: not a bit differs.
+  bool fd_paired = false;
 
   template <typename T = void> T* at(size_t off) const { return (T*)(ws + off); }
   float* f(size_t off) const { return (float*)(ws + off); }
@@ -169,7 +170,24 @@ struct Planner {
   }
 };
 
-void plan_side(betty_handle h, Planner& pl, SideBuf& sb, Elem elem, int B, bool lower, bool inputs = true) {
+// Extent of a launch: output tiles of each size over all its problems, and the 64-byte steps along K
+// of the longest one.
+struct Extent {
+  long t16 = 0, t32 = 0, t64 = 0, t128 = 0, rect = 0;
+  int steps = 0;
+  static long up(int n, int t) { return (n + t - 1) / t; }
+  void add(Elem elem, int M, int N, int K0, int K1) {
+    const int per = 64 / (int)elem_size(elem);
+    t16 += up(M, 16) * up(N, 16);
+    t32 += up(M, 32) * up(N, 32);
+    t64 += up(M, 64) * up(N, 64);
+    rect += up(M, 128) * up(N, 64);
+    t128 += up(M, 128) * up(N, 128);
+    steps = std::max(steps, (int)(up(K0, per) + up(K1, per)));
+  }
+};
+
+void plan_side(betty_handle h, Planner& pl, SideBuf& sb, Elem elem, int B, bool curvature, bool inputs = true) {
   const int L = h->L;
   const size_t es = elem_size(elem);
   sb.B = B;
@@ -187,7 +205,7 @@ void plan_side(betty_handle h, Planner& pl, SideBuf& sb, Elem elem, int B, bool 
       sb.A[l] = pl.take(Bp * np * es);
       sb.At[l] = pl.take(np * Bp * es);
       sb.dphi[l] = pl.take(Bp * np * 4);
-      if (lower && h->desc.act == BETTY_ACT_GELU_ERF) sb.e2[l] = pl.take(Bp * np * 4);
+      if (curvature && h->desc.act == BETTY_ACT_GELU_ERF) sb.e2[l] = pl.take(Bp * np * 4);
     }
     sb.D[l] = pl.take(Bp * np * es);
     sb.Dt[l] = pl.take(np * Bp * es);
@@ -210,14 +228,17 @@ void plan_side(betty_handle h, Planner& pl, SideBuf& sb, Elem elem, int B, bool 
 //  SET_FIRST_ORDER   what first-order gradients on both batches touch (the fp32 set that serves the
 //                    finite-difference variant and the fp32 forward of ReLU networks beside bf16 operands)
 //  SET_TRAIN_ONLY    just what a gradient of the lower cost on the train batch touches
-enum SetScope { SET_FULL, SET_FIRST_ORDER, SET_TRAIN_ONLY };
+//  SET_ACTIVATIONS   the same without weight operands
+enum SetScope { SET_FULL, SET_FIRST_ORDER, SET_TRAIN_ONLY, SET_ACTIVATIONS };
 
 void plan_set(betty_handle h, Planner& pl, OperandSet& os, Elem elem, bool second_direction_set, SetScope scope) {
   const int L = h->L;
   const size_t es = elem_size(elem);
   os.elem = elem;
   os.present = true;
-  plan_side(h, pl, os.side[0], elem, h->desc.batch_train, true, scope != SET_TRAIN_ONLY);
+  const bool inputs = scope == SET_FULL || scope == SET_FIRST_ORDER;
+  plan_side(h, pl, os.side[0], elem, h->desc.batch_train, scope == SET_FULL, inputs);
+  if (scope == SET_ACTIVATIONS) return;
   os.Wn.assign(L, 0); os.Wt.assign(L, 0); os.Vn.assign(L, 0); os.Vt.assign(L, 0);
   for (int i = 0; i < L; ++i) {
     const size_t m = (size_t)h->layers[i].n_in_p * h->layers[i].n_out_p * es;
@@ -287,14 +308,16 @@ void plan(betty_handle h) {
   if (main_elem == ELEM_BF16) plan_set(h, pl, h->sets[1], ELEM_F32, false, SET_FIRST_ORDER);
   const size_t vb = h->d * 4;
   h->vec_g = pl.take(vb); h->vec_v = pl.take(vb); h->vec_p = pl.take(vb); h->vec_Hv = pl.take(vb);
-  h->vec_wpm = pl.take(vb); h->vec_Gm = pl.take(vb);
-  if (h->fd_two_streams) {
-    plan_set(h, pl, h->fd_minus, ELEM_F32, false, SET_TRAIN_ONLY);
-    h->fd_minus.side[0].X = fd_operands(h).side[0].X;      // the same inputs
-    h->fd_minus.side[0].XT = fd_operands(h).side[0].XT;
-    h->vec_wpm2 = pl.take(vb);
-    if (h->desc.hp == BETTY_HP_PROXIMAL) h->vec_g2 = pl.take(vb);
-  }
+  if (h->desc.has_bias) { h->bias_pm[0] = pl.take(vb); h->bias_pm[1] = pl.take(vb); }
+  size_t n_sums = 4096;      // one per finishing wavefront of at most 64-tiles (16-tiles: at most 1024 of them) and per bias
+  for (const LayerInfo& li : h->layers) n_sums += 4 * (size_t)Extent::up(li.n_in, 64) * Extent::up(li.n_out, 64) + li.n_out + 4096;
+  h->sums = pl.take(n_sums * 4);
+  // the second perturbed point of a central difference: activations and deltas of its own, weights of its
+  // own where both points go through the same launches
+  plan_set(h, pl, h->fd_minus, ELEM_F32, false, h->fd_paired ? SET_TRAIN_ONLY : SET_ACTIVATIONS);
+  h->fd_minus.side[0].X = fd_operands(h).side[0].X;      // the same inputs
+  h->fd_minus.side[0].XT = fd_operands(h).side[0].XT;
+  if (!h->fd_paired) { h->fd_minus.Wn = fd_operands(h).Wn; h->fd_minus.Wt = fd_operands(h).Wt; }
   if (h->desc.hp == BETTY_HP_PROXIMAL) h->logrho = pl.take(vb);
   h->partials = pl.take(1024 * 8);
   h->scalars = pl.take(256);
@@ -313,23 +336,6 @@ const float* diag_log(betty_handle h, const float* lambda) {
 const float* wnet_theta(betty_handle h, const float* lambda) {
   return h->desc.hp == BETTY_HP_REWEIGHT_NET ? lambda : nullptr;
 }
-
-// Extent of a launch: output tiles of each size over all its problems, and the 64-byte steps along K
-// of the longest one.
-struct Extent {
-  long t16 = 0, t32 = 0, t64 = 0, t128 = 0, rect = 0;
-  int steps = 0;
-  static long up(int n, int t) { return (n + t - 1) / t; }
-  void add(Elem elem, int M, int N, int K0, int K1) {
-    const int per = 64 / (int)elem_size(elem);
-    t16 += up(M, 16) * up(N, 16);
-    t32 += up(M, 32) * up(N, 32);
-    t64 += up(M, 64) * up(N, 64);
-    rect += up(M, 128) * up(N, 64);
-    t128 += up(M, 128) * up(N, 128);
-    steps = std::max(steps, (int)(up(K0, per) + up(K1, per)));
-  }
-};
 
 // Kernel configuration of an activation-shaped GEMM (M = batch), from its extent.  The lines come from
 // timing every configuration on 1 400 shapes (batch 32 ... 1024, widths 8 ... 4096, K 64 ... 8192, both
@@ -366,7 +372,8 @@ int plan_chain(betty_handle h, Elem elem, GemmBatch& b) {
     return tiles <= 1024 && TT >= 16 ? GEMM_128x64 : GEMM_64x1;
   }
   Extent x;
-  for (int i = 0; i < b.n; ++i) x.add(elem, b.p[i].g.M, b.p[i].g.N, b.p[i].g.K[0], b.p[i].g.K[1]);
+  for (int r = 0; r < (h->as_pair && b.n == 1 ? 2 : 1); ++r)
+    for (int i = 0; i < b.n; ++i) x.add(elem, b.p[i].g.M, b.p[i].g.N, b.p[i].g.K[0], b.p[i].g.K[1]);
   const bool wide_rows = b.p[0].e.mode == EPI_RFWD_LAST_HESS && b.p[0].g.N > 16;   // its row sums need a whole row per tile
   if (h->tune_split && !wide_rows) {
     const int shorter = elem == ELEM_BF16 ? 1 : 2;        // the same K has twice the steps with fp32 operands
@@ -386,11 +393,11 @@ int plan_chain(betty_handle h, Elem elem, GemmBatch& b) {
 // 512 twice: 10.0 / 6.0 us), then 64-tiles; bf16 launches with enough 128-tiles to fill the chip
 // twice take the kernel for large layers.  The whole group of layers that one launch covers decides, also
 // where they are launched one by one, so that both give the same bits.
-int plan_wgrad(betty_handle h, Elem elem, int layer, bool rop, int B) {
+int plan_wgrad(betty_handle h, Elem elem, int layer, bool rop, bool two, int B) {
   const int first = (layer - 1) / MAX_PROBLEMS * MAX_PROBLEMS, last = std::min(h->L, first + MAX_PROBLEMS);
   Extent x;
   for (int i = first; i < last; ++i)
-    x.add(elem, h->layers[i].n_in, h->layers[i].n_out, B, rop && i > 0 ? B : 0);
+    x.add(elem, h->layers[i].n_in, h->layers[i].n_out, B, two || (rop && i > 0) ? B : 0);
   if (elem == ELEM_BF16 && h->tune_wgrad128_min > 0 && x.t128 >= h->tune_wgrad128_min) return GEMM_128x1;
   if (h->tune_wgrad_cfg != GEMM_64x1 || !h->tune_split || h->tune_wgrad128_min == 0) return h->tune_wgrad_cfg;
   const int shorter = elem == ELEM_BF16 ? 1 : 2;
@@ -460,38 +467,53 @@ void make_weight_operands(betty_handle h, OperandSet& os, const float* w) {
   make_shadows(h, os, w, &os.Wn, &os.Wt, hybrid_forward(h, os) ? &h->sets[1].Wt : nullptr);
 }
 
-// Which batches a pass covers: the train (lower) side, the validation (upper) side, or both in
-// the same launches (same weights, two independent problems per launch).
-enum { SIDE_TRAIN = 1, SIDE_VAL = 2, SIDE_BOTH = 3 };
-inline bool has_side(int mask, int side) { return (mask >> side) & 1; }
+// One first-order pass over a batch.  Up to two of them share their launches: the train and the
+// validation batch at the same weights, or the two perturbed points of a central difference.
+struct Pass {
+  OperandSet* os;                   // weights and buffers
+  int side;                         // 0 = train (lower cost), 1 = validation (upper cost)
+  const float* w;                   // flat parameters, for the biases
+  const float* theta = nullptr;     // weight net (train side of the reweighting cost)
+  const float* omega_fixed = nullptr;   // sample weights to use instead of it
+  float sign = 1.f;                 // -1: output delta, and with it every delta, with the opposite sign
+  bool curvature = false;           // also phi'' and (delta W^T) phi'', for forward-over-reverse passes
+  size_t ell = 0, omega = 0, dsig = 0;  // other places for the per-sample values (0: the side's own)
+};
+Pass train_pass(betty_handle h, OperandSet& os, const float* w, const float* lam, bool curvature) {
+  Pass p{&os, 0, w};
+  p.theta = wnet_theta(h, lam);
+  p.curvature = curvature;
+  return p;
+}
+Pass val_pass(OperandSet& os, const float* w) { return Pass{&os, 1, w}; }
 
-// a_l, phi'(z_l) (and phi'' on the lower side), logits, per-sample loss, output delta
-void forward_and_loss(betty_handle h, OperandSet& os, int sides, const float* w, const float* theta,
-                      const float* omega_fixed = nullptr, bool skip_last = false) {
+// a_l, phi'(z_l) (phi''), logits, per-sample loss, output delta
+void forward_and_loss(betty_handle h, const Pass* ps, int n, bool skip_last = false) {
   const int L = h->L;
-  const bool hybrid = hybrid_forward(h, os);
-  OperandSet& fs = hybrid ? h->sets[1] : os;          // operands of the forward products
+  const bool hybrid = hybrid_forward(h, *ps[0].os);
+  const Elem elem = hybrid ? ELEM_F32 : ps[0].os->elem;     // operands of the forward products
   for (int l = 1; l <= (skip_last ? L - 1 : L); ++l) {
     const LayerInfo& li = h->layers[l - 1];
     const bool last = l == L;
     GemmBatch b;
     double flops = 0;
-    for (int side = 0; side < 2; ++side) {
-      if (!has_side(sides, side)) continue;
-      SideBuf& sb = os.side[side];
-      SideBuf& fb = fs.side[side];
+    for (int i = 0; i < n; ++i) {
+      const Pass& ps_i = ps[i];
+      OperandSet& fs = hybrid ? h->sets[1] : *ps_i.os;
+      SideBuf& sb = ps_i.os->side[ps_i.side];
+      SideBuf& fb = fs.side[ps_i.side];
       GemmProblem& p = b.p[b.n++];
       const void* Aop = l == 1 ? h->at<void>(fb.X) : h->at<void>(fb.A[l - 1]);
       set_pairs(p.g, Aop, li.n_in_p, h->at<void>(fs.Wt[l - 1]), li.n_in_p, li.n_in, nullptr, 0, nullptr, 0, 0);
       p.g.M = sb.B; p.g.N = li.n_out;
       Epilogue e = blank_epilogue(last ? EPI_FWD_LAST : EPI_FWD, h->desc.act);
-      e.colvec = h->desc.has_bias ? w + li.b_off : nullptr;
+      e.colvec = h->desc.has_bias ? ps_i.w + li.b_off : nullptr;
       e.ldf = li.n_out_p;
       if (last) {
         e.f0 = h->f(sb.ZL);
       } else {
         e.dphi_out = h->f(sb.dphi[l]);
-        e.d2_out = sb.e2[l] ? h->f(sb.e2[l]) : nullptr;
+        e.d2_out = ps_i.curvature && sb.e2[l] ? h->f(sb.e2[l]) : nullptr;
         e.out = h->at<void>(fb.A[l]); e.ld = li.n_out_p;
         e.outT = hybrid ? nullptr : h->at<void>(fb.At[l]); e.ldT = sb.Bp;
         if (hybrid) { e.out2 = h->at<void>(sb.A[l]); e.outT2 = h->at<void>(sb.At[l]); }
@@ -499,98 +521,99 @@ void forward_and_loss(betty_handle h, OperandSet& os, int sides, const float* w,
       p.e = e;
       flops += 2.0 * sb.B * li.n_in * li.n_out;
     }
-    launch_gemm_batch(h->ctx, fs.elem, plan_chain(h, fs.elem, b), b, flops);
+    launch_gemm_batch(h->ctx, elem, plan_chain(h, elem, b), b, flops);
   }
   if (skip_last) return;
   const LayerInfo& lo = h->layers[L - 1];
   LossBatch lb;
-  for (int side = 0; side < 2; ++side) {
-    if (!has_side(sides, side)) continue;
-    SideBuf& sb = os.side[side];
+  for (int i = 0; i < n; ++i) {
+    SideBuf& sb = ps[i].os->side[ps[i].side];
     LossArgs& a = lb.a[lb.n++];
     a = LossArgs{};
     a.loss = h->desc.loss;
-    a.reweight = (side == 0 && h->desc.hp == BETTY_HP_REWEIGHT_NET) ? 1 : 0;
+    a.reweight = (ps[i].side == 0 && h->desc.hp == BETTY_HP_REWEIGHT_NET) ? 1 : 0;
     a.hidden = h->desc.wnet_hidden;
     a.Z = h->f(sb.ZL); a.ldz = lo.n_out_p;
-    a.labels = h->at<Labels>(h->labels) + side; a.C = lo.n_out;
-    a.theta = theta;
-    a.omega_fixed = side == 0 ? omega_fixed : nullptr;
-    a.rows = sb.B; a.inv_batch = 1.0f / (float)sb.B;
-    a.ell = h->f(sb.ell); a.s = h->f(sb.s); a.omega = h->f(sb.omega); a.dsig = h->f(sb.dsig);
+    a.labels = h->at<Labels>(h->labels) + ps[i].side; a.C = lo.n_out;
+    a.theta = ps[i].theta;
+    a.omega_fixed = ps[i].omega_fixed;
+    a.rows = sb.B; a.inv_batch = ps[i].sign / (float)sb.B;
+    a.ell = h->f(ps[i].ell ? ps[i].ell : sb.ell); a.s = h->f(sb.s);
+    a.omega = h->f(ps[i].omega ? ps[i].omega : sb.omega); a.dsig = h->f(ps[i].dsig ? ps[i].dsig : sb.dsig);
     a.P = h->f(sb.P);
     a.D = h->at<void>(sb.D[L]); a.ldD = lo.n_out_p;
     a.Dt = h->at<void>(sb.Dt[L]); a.ldDt = sb.Bp;
   }
-  launch_loss_rows(h->ctx, os.elem, lb);
+  launch_loss_rows(h->ctx, ps[0].os->elem, lb);
 }
 
-// delta_l for every layer below the output (and (delta W^T) phi'' on the lower side)
-void backward_chain(betty_handle h, OperandSet& os, int sides, int l_from = 0) {
+// delta_l for every layer below the output (and (delta W^T) phi'')
+void backward_chain(betty_handle h, const Pass* ps, int n, int l_from = 0) {
   const int L = h->L;
+  const Elem elem = ps[0].os->elem;
   for (int l = l_from > 0 ? l_from : L; l >= 2; --l) {
     const LayerInfo& li = h->layers[l - 1];
     GemmBatch b;
     double flops = 0;
-    for (int side = 0; side < 2; ++side) {
-      if (!has_side(sides, side)) continue;
-      SideBuf& sb = os.side[side];
+    for (int i = 0; i < n; ++i) {
+      SideBuf& sb = ps[i].os->side[ps[i].side];
       GemmProblem& p = b.p[b.n++];
-      set_pairs(p.g, h->at<void>(sb.D[l]), li.n_out_p, h->at<void>(os.Wn[l - 1]), li.n_out_p, li.n_out, nullptr, 0,
+      set_pairs(p.g, h->at<void>(sb.D[l]), li.n_out_p, h->at<void>(ps[i].os->Wn[l - 1]), li.n_out_p, li.n_out, nullptr, 0,
                 nullptr, 0, 0);
       p.g.M = sb.B; p.g.N = li.n_in;
       Epilogue e = blank_epilogue(EPI_BWD);
       e.dphi = h->f(sb.dphi[l - 1]);
-      e.e_io = sb.e2[l - 1] ? h->f(sb.e2[l - 1]) : nullptr;
+      e.e_io = ps[i].curvature && sb.e2[l - 1] ? h->f(sb.e2[l - 1]) : nullptr;
       e.ldf = li.n_in_p;
       e.out = h->at<void>(sb.D[l - 1]); e.ld = li.n_in_p;
       e.outT = h->at<void>(sb.Dt[l - 1]); e.ldT = sb.Bp;
       p.e = e;
       flops += 2.0 * sb.B * li.n_in * li.n_out;
     }
-    launch_gemm_batch(h->ctx, os.elem, plan_chain(h, os.elem, b), b, flops);
+    launch_gemm_batch(h->ctx, elem, plan_chain(h, elem, b), b, flops);
   }
 }
 
 // Forward pass, loss and backward chain.  A narrow output layer (see LastGradArgs) goes through
 // one vector kernel that produces the logits, the loss quantities and delta_{L-1}.
-void forward_backward(betty_handle h, OperandSet& os, int sides, const float* w, const float* theta,
-                      const float* omega_fixed = nullptr) {
+void forward_backward(betty_handle h, const Pass* ps, int n) {
   const int L = h->L;
   const LayerInfo& lo = h->layers[L - 1];
   // (also with the fp32 forward of ReLU networks: the output layer has no mask to protect, and the
   // operand-type copy of a_{L-1} exists either way)
   const bool narrow = L >= 2 && lo.n_out <= LAST_ROP_MAX_C;
   if (!narrow) {
-    forward_and_loss(h, os, sides, w, theta, omega_fixed);
-    backward_chain(h, os, sides);
+    forward_and_loss(h, ps, n);
+    backward_chain(h, ps, n);
     return;
   }
-  forward_and_loss(h, os, sides, w, theta, omega_fixed, true);
+  forward_and_loss(h, ps, n, true);
   LastGradArgs a{};
-  for (int side = 0; side < 2; ++side) {
-    if (!has_side(sides, side)) continue;
-    SideBuf& sb = os.side[side];
+  for (int i = 0; i < n; ++i) {
+    SideBuf& sb = ps[i].os->side[ps[i].side];
     LastGradSide& d = a.side[a.n_sides++];
     d.A = h->at<void>(sb.A[L - 1]); d.lda = lo.n_in_p;
-    d.labels = h->at<Labels>(h->labels) + side;
-    d.omega_fixed = side == 0 ? omega_fixed : nullptr;
+    d.labels = h->at<Labels>(h->labels) + ps[i].side;
+    d.omega_fixed = ps[i].omega_fixed;
     d.ZL = h->f(sb.ZL); d.P = h->f(sb.P); d.ldz = lo.n_out_p;
-    d.ell = h->f(sb.ell); d.s = h->f(sb.s); d.omega = h->f(sb.omega); d.dsig = h->f(sb.dsig);
+    d.ell = h->f(ps[i].ell ? ps[i].ell : sb.ell); d.s = h->f(sb.s);
+    d.omega = h->f(ps[i].omega ? ps[i].omega : sb.omega); d.dsig = h->f(ps[i].dsig ? ps[i].dsig : sb.dsig);
     d.DL = h->at<void>(sb.D[L]); d.DLt = h->at<void>(sb.Dt[L]); d.ldd = lo.n_out_p; d.ldDLt = sb.Bp;
-    d.dphi = h->f(sb.dphi[L - 1]); d.e2 = sb.e2[L - 1] ? h->f(sb.e2[L - 1]) : nullptr; d.ldf = lo.n_in_p;
+    d.dphi = h->f(sb.dphi[L - 1]);
+    d.e2 = ps[i].curvature && sb.e2[L - 1] ? h->f(sb.e2[L - 1]) : nullptr; d.ldf = lo.n_in_p;
     d.D = h->at<void>(sb.D[L - 1]); d.ldD = lo.n_in_p; d.Dt = h->at<void>(sb.Dt[L - 1]); d.ldDt = sb.Bp;
+    d.Wt = h->at<void>(ps[i].os->Wt[L - 1]); d.Wn = h->at<void>(ps[i].os->Wn[L - 1]);
+    d.bias = h->desc.has_bias ? ps[i].w + lo.b_off : nullptr;
     d.B = sb.B;
-    d.reweight = (side == 0 && h->desc.hp == BETTY_HP_REWEIGHT_NET) ? 1 : 0;
-    d.inv_batch = 1.0f / (float)sb.B;
+    d.reweight = (ps[i].side == 0 && h->desc.hp == BETTY_HP_REWEIGHT_NET) ? 1 : 0;
+    d.inv_batch = ps[i].sign / (float)sb.B;
+    if (ps[i].theta) a.theta = ps[i].theta;
   }
-  a.Wt = h->at<void>(os.Wt[L - 1]); a.ldt = lo.n_in_p;
-  a.Wn = h->at<void>(os.Wn[L - 1]); a.ldn = lo.n_out_p;
-  a.bias = h->desc.has_bias ? w + lo.b_off : nullptr;
-  a.theta = theta; a.hidden = h->desc.wnet_hidden;
+  a.ldt = lo.n_in_p; a.ldn = lo.n_out_p;
+  a.hidden = h->desc.wnet_hidden;
   a.n_in = lo.n_in; a.n_in_p = lo.n_in_p; a.C = lo.n_out; a.loss = h->desc.loss;
-  launch_last_layer_grad(h->ctx, os.elem, a);
-  backward_chain(h, os, sides, L - 1);
+  launch_last_layer_grad(h->ctx, ps[0].os->elem, a);
+  backward_chain(h, ps, n, L - 1);
 }
 
 // Split of a tile grid over the eight XCDs (see GemmArgs::xgm): the factorisation gm x gn = 8 that
@@ -624,6 +647,10 @@ struct WgradSink {
   bool second_set = false;  // ... into the second set of direction copies (the first is still being read)
   float beta = 0.f, gamma = 0.f;   // EPI_WGRAD_SGD: momentum factor and plain weight decay
   int K = 0;                // EPI_WGRAD_SCALED: steps of the series
+  const float* eps = nullptr;      // EPI_WGRAD_FD
+  OperandSet* minus = nullptr;     // the second perturbed point: its products are added (its deltas carry the sign)
+  bool sum_p = false;
+  int* sums = nullptr;             // non-null: the launch leaves its sums in vec partials, their number here
 };
 // (aggregate initialisation in the callers lists the fields up to `copies`)
 
@@ -644,7 +671,12 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
       const LayerInfo& li = h->layers[l - 1];
       GemmProblem& p = b.p[i];
       const void* aT = l == 1 ? h->at<void>(sb.XT) : h->at<void>(sb.At[l - 1]);
-      if (!rop) {
+      if (k.minus) {
+        SideBuf& mb = k.minus->side[side];
+        set_pairs(p.g, aT, Bp, h->at<void>(sb.Dt[l]), Bp, B, l == 1 ? aT : h->at<void>(mb.At[l - 1]), Bp,
+                  h->at<void>(mb.Dt[l]), Bp, B);
+        flops += 4.0 * B * li.n_in * li.n_out;
+      } else if (!rop) {
         set_pairs(p.g, aT, Bp, h->at<void>(sb.Dt[l]), Bp, B, nullptr, 0, nullptr, 0, 0);
         flops += 2.0 * B * li.n_in * li.n_out;
       } else if (l == 1) {
@@ -674,9 +706,13 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
         e.out = h->at<void>(VN[l - 1]); e.ld = li.n_out_p;
         e.outT = h->at<void>(VT[l - 1]); e.ldT = li.n_in_p;
       }
+      e.eps = k.eps; e.sum_p = k.sum_p;
       p.e = e;
       if (h->desc.has_bias) {
         BiasJob& j = b.bias[b.n_bias++];
+        j = BiasJob{};
+        j.Mt2 = k.minus ? h->at<void>(k.minus->side[side].Dt[l]) : nullptr;
+        j.eps = k.eps; j.sum_p = k.sum_p;
         j.Mt = rop ? h->at<void>(os.RDt[l]) : h->at<void>(sb.Dt[l]);
         j.ld = Bp; j.rows = li.n_out; j.k = B; j.mode = k.mode;
         j.C = k.C ? k.C + li.b_off : nullptr;
@@ -699,14 +735,18 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
     else if (k.mode == EPI_WGRAD_NEUMANN_L2) per_param = 16.0 + 4.0;
     else if (k.mode == EPI_WGRAD_SGD) per_param = 16.0 + (k.lam ? 4.0 : 0.0);
     else if (k.mode == EPI_WGRAD_SCALED) per_param = 8.0;
+    else if (k.mode == EPI_WGRAD_FD) per_param = 16.0 + (k.lam ? 4.0 : 0.0);
+    else if (k.mode == EPI_WGRAD_FD_LAST) per_param = 16.0 + (k.x ? 4.0 : 0.0);
     else if (k.mode == EPI_WGRAD_INIT) per_param = k.p ? 8.0 : 4.0;
     else if (k.lam) per_param = 12.0;
     if (k.copies) per_param += 4.0;
-    const int cfg = plan_wgrad(h, os.elem, l0, rop, B), bt = gemm_cfg_tile(cfg);
+    const int cfg = plan_wgrad(h, os.elem, l0, rop, k.minus != nullptr, B), bt = gemm_cfg_tile(cfg);
     if (cfg == GEMM_64x1 || cfg == GEMM_128x1)
       for (int i = 0; i < b.n; ++i)
         xcd_split((b.p[i].g.M + bt - 1) / bt, (b.p[i].g.N + bt - 1) / bt, b.p[i].g.xgm, b.p[i].g.xgn);
-    launch_gemm_batch(h->ctx, os.elem, cfg, b, flops, per_param * params);
+    const int n = launch_gemm_batch(h->ctx, os.elem, cfg, b, flops, per_param * params,
+                                    k.sums ? h->f(h->sums) + *k.sums : nullptr);
+    if (k.sums) *k.sums += n;
   }
 }
 
@@ -816,28 +856,18 @@ void hvp_cached(betty_handle h, OperandSet& os, const float* vflat, const WgradS
 }
 
 // full first-order gradient of the lower cost at w (operand copies of w already made)
-void lower_grad_seq(betty_handle h, OperandSet& os, const float* w, const float* lam, float* grad,
-                    float* loss_or_null, const float* omega_fixed = nullptr, float* dist_or_null = nullptr) {
+void lower_grad_seq(betty_handle h, OperandSet& os, const float* w, const float* lam, float* grad, float* loss_or_null) {
   const float* dl = diag_log(h, lam);
-  // what the diagonal term multiplies: w itself, or its distance to the anchor (kept in vec_g
-  // unless the caller names another place)
-  const float* x = w;
-  if (h->desc.hp == BETTY_HP_PROXIMAL) {
-    float* dist = dist_or_null ? dist_or_null : h->f(h->vec_g);
-    launch_diff(h->ctx, w, lam, dist, h->d);
-    x = dist;
-  }
-  forward_backward(h, os, SIDE_TRAIN, w, wnet_theta(h, lam), omega_fixed);
-  WgradSink k{EPI_WGRAD, grad, dl, dl ? x : nullptr, nullptr, nullptr, 0.f, false};
+  const Pass ps = train_pass(h, os, w, lam, false);
+  forward_backward(h, &ps, 1);
+  // the diagonal term multiplies w itself or its distance to the anchor; its cost is summed on the way
+  int n = 0;
+  WgradSink k{EPI_WGRAD, grad, dl, dl ? w : nullptr, nullptr, nullptr, 0.f, false};
+  if (h->desc.hp == BETTY_HP_PROXIMAL) k.p = const_cast<float*>(lam);
+  if (dl && loss_or_null) k.sums = &n;
   wgrad_batch(h, os, 0, false, k);
-  if (loss_or_null) {
-    float* add = nullptr;
-    if (dl) {
-      add = h->f(h->scalars) + 8;
-      launch_l2_cost(h->ctx, dl, x, h->d, h->at<double>(h->partials), add);
-    }
-    launch_weighted_loss_sum(h->ctx, h->f(os.side[0].s), h->f(os.side[0].ell), os.side[0].B, add, loss_or_null);
-  }
+  if (loss_or_null)
+    launch_weighted_loss_sum(h->ctx, h->f(os.side[0].s), h->f(os.side[0].ell), os.side[0].B, h->f(h->sums), n, loss_or_null);
 }
 
 // gradient of the upper cost on the validation batch; the result goes where `sink` says.  With
@@ -845,16 +875,18 @@ void lower_grad_seq(betty_handle h, OperandSet& os, const float* w, const float*
 // R-op passes need (no parameter gradient on that side).
 void upper_grad_seq(betty_handle h, OperandSet& os, const float* w, const float* lam, bool with_lower,
                     const WgradSink& sink, float* loss_or_null) {
-  const int sides = with_lower ? SIDE_BOTH : SIDE_VAL;
-  forward_backward(h, os, sides, w, wnet_theta(h, lam));
+  Pass ps[2] = {val_pass(os, w), val_pass(os, w)};
+  if (with_lower) ps[0] = train_pass(h, os, w, lam, true);
+  forward_backward(h, ps, with_lower ? 2 : 1);
   wgrad_batch(h, os, 1, false, sink);
   if (loss_or_null)
-    launch_weighted_loss_sum(h->ctx, h->f(os.side[1].s), h->f(os.side[1].ell), os.side[1].B, nullptr, loss_or_null);
+    launch_weighted_loss_sum(h->ctx, h->f(os.side[1].s), h->f(os.side[1].ell), os.side[1].B, nullptr, 0, loss_or_null);
 }
 
 // forward/backward cache of the train batch for the R-op passes (no parameter gradient)
 void prepare_lower(betty_handle h, OperandSet& os, const float* w, const float* lam) {
-  forward_backward(h, os, SIDE_TRAIN, w, wnet_theta(h, lam));
+  const Pass ps = train_pass(h, os, w, lam, true);
+  forward_backward(h, &ps, 1);
 }
 
 // out = -(1/B) sum_i c_i dR/dtheta with c_i = <grad_w l_i, scale * qflat>
@@ -881,7 +913,7 @@ void mixed_reweight_seq(betty_handle h, OperandSet& os, const float* lam, const 
     launch_loss_directional_rows(h->ctx, h->desc.loss, h->f(sb.P), h->f(sb.ZL), h->at<Labels>(h->labels),
                                  h->f(os.Rz[L]), lo.n_out_p, sb.B, lo.n_out, h->f(os.cvec));
   }
-  launch_wnet_theta_vjp(h->ctx, h->f(sb.ell), h->f(sb.dsig), h->f(os.cvec), lam, h->desc.wnet_hidden, sb.B,
+  launch_wnet_theta_vjp(h->ctx, h->f(sb.ell), h->f(sb.dsig), h->f(os.cvec), nullptr, nullptr, lam, h->desc.wnet_hidden, sb.B,
                         scale / (float)sb.B, out);
 }
 
@@ -1333,7 +1365,8 @@ void neumann_samples_seq(betty_handle h, const float* w, const float* lambda, co
     prepare_lower(h, os, w, lambda);
     make_shadows(h, os, u_or_null, &os.Vn, &os.Vt);
   } else {
-    forward_backward(h, os, SIDE_BOTH, w, wnet_theta(h, lambda));
+    const Pass ps[2] = {train_pass(h, os, w, lambda, true), val_pass(os, w)};
+    forward_backward(h, ps, 2);
   }
   samples_begin(h, os, u_or_null, K > 0);
   for (int k = 0; k < K; ++k) {
@@ -1357,8 +1390,8 @@ void neumann_samples_seq(betty_handle h, const float* w, const float* lambda, co
       launch_loss_directional_rows(h->ctx, h->desc.loss, h->f(sb.P), h->f(sb.ZL), h->at<Labels>(h->labels),
                                    h->f(L == 1 ? AS[1] : os.Rz[L]), lo.n_out_p, sb.B, lo.n_out, h->f(os.cvec));
     }
-    launch_wnet_theta_vjp(h->ctx, h->f(sb.ell), h->f(sb.dsig), h->f(os.cvec), lambda, h->desc.wnet_hidden, sb.B,
-                          alpha / (float)sb.B, out);
+    launch_wnet_theta_vjp(h->ctx, h->f(sb.ell), h->f(sb.dsig), h->f(os.cvec), nullptr, nullptr, lambda, h->desc.wnet_hidden,
+                          sb.B, alpha / (float)sb.B, out);
     return;
   }
   // proximal cost: d(anchor) = 2 rho alpha s with s = (sum_j beta^j) g - alpha sum_k beta^(K-1-k) (Ra^T delta + a^T R delta)_k
@@ -1479,7 +1512,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
   // 128-tile ones (the two streams contend for the same memory path).
   const bool large = h->d >= ((size_t)32 << 20);
   h->use_pipeline = large && desc->prec == BETTY_PREC_FP32;
-  h->fd_two_streams = !large;
+  h->fd_paired = !large;
   h->max_Bp = std::max(padup(desc->batch_train), padup(desc->batch_val));
   // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>" (see plan_chain)
   if (const char* t = getenv("BETTY_TUNE")) {
@@ -1492,7 +1525,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
     if (const char* q = strstr(t, "wgrad128=")) if (sscanf(q + 9, "%d", &v) == 1 && v >= 0) h->tune_wgrad128_min = v;
     if (const char* q = strstr(t, "pipe=")) if (sscanf(q + 5, "%d", &v) == 1) h->use_pipeline = v != 0;
     if (const char* q = strstr(t, "samples=")) if (sscanf(q + 8, "%d", &v) == 1) h->tune_samples = v != 0;
-    if (const char* q = strstr(t, "fd2=")) if (sscanf(q + 4, "%d", &v) == 1) h->fd_two_streams = v != 0;
+    if (const char* q = strstr(t, "fd2=")) if (sscanf(q + 4, "%d", &v) == 1) h->fd_paired = v != 0;
   }
   plan(h);
   *out = h;
@@ -1703,7 +1736,8 @@ betty_status betty_mixed_vjp(betty_handle h, const float* w, const float* lambda
   return run_cached(h, h->CALL_MIXED, call_key({w, lambda, q, out}), [=]() {
     OperandSet& os = h->sets[0];
     make_weight_operands(h, os, w);
-    forward_and_loss(h, os, SIDE_TRAIN, w, lambda);
+    const Pass ps = train_pass(h, os, w, lambda, false);
+    forward_and_loss(h, &ps, 1);
     mixed_reweight_seq(h, os, lambda, q, 1.f, out);
   });
 }
@@ -1762,87 +1796,104 @@ betty_status betty_hypergrad_chain3(betty_handle hp, betty_handle hf, const floa
   return run_cached(hp, hp->CALL_CHAIN, key, body);
 }
 
+// The two points w +- eps q, q = scale v, as operands: both at once, or the one of `signs` (1 = plus, 2 = minus).
+static void make_perturbed_operands(betty_handle h, const float* w, const float* v, const float* eps, float scale, int signs) {
+  OperandSet* os[2] = {&fd_operands(h), &h->fd_minus};
+  for (int i0 = 0; i0 < h->L; i0 += MAX_PROBLEMS) {
+    PerturbBatch b;
+    b.n = std::min(MAX_PROBLEMS, h->L - i0);
+    b.eps = eps; b.scale = scale; b.signs = signs;
+    for (int k = 0; k < b.n; ++k) {
+      const LayerInfo& li = h->layers[i0 + k];
+      PerturbJob& j = b.j[k];
+      j = PerturbJob{};
+      j.w = w + li.w_off; j.v = v + li.w_off; j.rows = li.n_in; j.cols = li.n_out;
+      j.ld = li.n_out_p; j.ldT = li.n_in_p;
+      if (h->desc.has_bias) { j.b = w + li.b_off; j.bv = v + li.b_off; }
+      for (int s = 0; s < 2; ++s) {
+        j.out[s] = h->f(os[s]->Wn[i0 + k]); j.outT[s] = h->f(os[s]->Wt[i0 + k]);
+        if (h->desc.has_bias) j.bout[s] = h->f(h->bias_pm[s]) + li.b_off;
+      }
+    }
+    launch_perturb(h->ctx, b);
+  }
+}
+
+// Central differences of first-order passes, fp32 operands throughout.  Both perturbed points go through the
+// same launches (or, on large models, one after the other); the deltas of the minus point carry the
+// opposite sign, so one weight-gradient launch over both forms the difference of the data terms in its
+// accumulators and its epilogue takes the step.  The diagonal terms are linear in w: their differences are
+// formed exactly, 2 exp(lambda) v and, in the mixed VJP, -2 exp(lambda) w q.
+static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, float alpha, float eps_scale, float* dlambda) {
+  OperandSet& os = fd_operands(h);
+  OperandSet& om = h->fd_minus;
+  SideBuf& sb = os.side[0];
+  const bool l2 = h->desc.hp == BETTY_HP_L2_DECAY, rw = h->desc.hp == BETTY_HP_REWEIGHT_NET;
+  const float* dl = diag_log(h, lambda);
+  float* v = h->f(h->vec_v); float* p = h->f(h->vec_p); float* eps = h->f(h->scalars) + 1;
+  int sums = 0;
+  make_weight_operands(h, os, w);
+  WgradSink init{EPI_WGRAD_INIT, nullptr, nullptr, nullptr, v, K > 0 ? p : nullptr, 0.f, false};
+  if (K > 0 || rw) init.sums = &sums;
+  const float* omega_bar = nullptr;
+  if (!rw) {
+    upper_grad_seq(h, os, w, nullptr, false, init, nullptr);
+  } else {
+    // the reweighting cost holds its sample weights constant in w: evaluate them (and the loss fed
+    // to the weight net) once at the unperturbed w and keep them for every perturbed pass
+    Pass ps[2] = {train_pass(h, os, w, lambda, false), val_pass(os, w)};
+    ps[0].ell = sb.ell_bar; ps[0].omega = sb.omega_bar; ps[0].dsig = sb.dsig_bar;
+    forward_and_loss(h, ps, 2);
+    backward_chain(h, ps + 1, 1);
+    wgrad_batch(h, os, 1, false, init);
+    omega_bar = h->f(sb.omega_bar);
+  }
+  Pass ps[2] = {Pass{&os, 0, h->f(h->bias_pm[0])}, Pass{&om, 0, h->f(h->bias_pm[1])}};
+  for (Pass& q : ps) q.omega_fixed = omega_bar;
+  ps[1].sign = -1.f;
+  auto both = [&](const float* dir, float scale, auto passes) {
+    launch_fd_eps(h->ctx, h->f(h->sums), sums, eps_scale, scale, eps);
+    h->as_pair = true;
+    if (h->fd_paired) {
+      make_perturbed_operands(h, w, dir, eps, scale, 3);
+      passes(ps, 2);
+    } else {
+      for (int s = 0; s < 2; ++s) {
+        make_perturbed_operands(h, w, dir, eps, scale, 1 << s);
+        passes(ps + s, 1);
+      }
+    }
+    h->as_pair = false;
+  };
+  for (int k = 0; k < K; ++k) {
+    both(v, 1.f, [&](const Pass* q, int n) { forward_backward(h, q, n); });
+    const bool last = k + 1 == K;
+    WgradSink step{last && !rw ? EPI_WGRAD_FD_LAST : EPI_WGRAD_FD, dlambda, dl, last && l2 ? w : nullptr, v, p, alpha, false};
+    step.eps = eps;
+    step.minus = &om;
+    step.sum_p = last;
+    sums = 0;
+    if (!last || rw) step.sums = &sums;
+    wgrad_batch(h, os, 0, false, step);
+  }
+  const float* s = K > 0 ? p : v;
+  if (rw) {
+    // grad_theta L_L(w') = (1/B) sum_i l_i(w') dR(lbar_i)/dtheta, so its central difference along
+    // q = alpha s needs only the per-sample losses at w +- eps q
+    both(s, alpha, [&](const Pass* q, int n) { forward_and_loss(h, q, n); });
+    launch_wnet_theta_vjp(h->ctx, h->f(sb.ell_bar), h->f(sb.dsig_bar), h->f(sb.ell), h->f(om.side[0].ell), eps, lambda,
+                          h->desc.wnet_hidden, sb.B, 1.0f / (float)sb.B, dlambda);
+  } else if (K == 0) {
+    if (l2) launch_mixed_l2(h->ctx, lambda, w, s, alpha, dlambda, h->d);
+    else launch_mixed_prox(h->ctx, h->f(h->logrho), s, alpha, dlambda, h->d);
+  }
+}
+
 betty_status betty_hypergrad_fd(betty_handle h, const float* w, const float* lambda, int K, float alpha,
                                 float eps_scale, float* dlambda) {
   CHECK(check_hyper_args(h, w, lambda, K, alpha, dlambda));
   if (!std::isfinite(eps_scale) || eps_scale <= 0.f) return fail(h, BETTY_EINVAL, "eps_scale must be positive and finite");
-  auto body = [=]() {
-    OperandSet& os = fd_operands(h);
-    SideBuf& sb = os.side[0];
-    const bool l2 = h->desc.hp == BETTY_HP_L2_DECAY, rw = h->desc.hp == BETTY_HP_REWEIGHT_NET;
-    float* v = h->f(h->vec_v); float* p = h->f(h->vec_p); float* Gp = h->f(h->vec_Hv);
-    float* Gm = h->f(h->vec_Gm); float* wpm = h->f(h->vec_wpm); float* wpm2 = h->f(h->vec_wpm2);
-    OperandSet& om = h->fd_minus;
-    float* nrm2 = h->f(h->scalars); float* eps = h->f(h->scalars) + 1;
-    make_weight_operands(h, os, w);
-    WgradSink init{EPI_WGRAD_INIT, nullptr, nullptr, nullptr, v, p, 0.f, false};
-    const float* omega_bar = nullptr;
-    if (!rw) {
-      upper_grad_seq(h, os, w, nullptr, false, init, nullptr);
-    } else {
-      // the reweighting cost holds its sample weights constant in w: evaluate them (and the loss fed
-      // to the weight net) once at the unperturbed w and keep them for every perturbed pass
-      forward_and_loss(h, os, SIDE_BOTH, w, lambda);
-      backward_chain(h, os, SIDE_VAL);
-      wgrad_batch(h, os, 1, false, init);
-      launch_scale_copy(h->ctx, h->f(sb.ell), 1.f, h->f(sb.ell_bar), sb.B);
-      launch_scale_copy(h->ctx, h->f(sb.omega), 1.f, h->f(sb.omega_bar), sb.B);
-      launch_scale_copy(h->ctx, h->f(sb.dsig), 1.f, h->f(sb.dsig_bar), sb.B);
-      omega_bar = h->f(sb.omega_bar);
-    }
-    for (int k = 0; k < K; ++k) {
-      launch_sumsq(h->ctx, v, h->d, h->at<double>(h->partials), nrm2);
-      launch_fd_eps(h->ctx, nrm2, eps_scale, 1.f, eps);
-      // the evaluation at w - eps v goes to the second stream, with operands and scratch of its own
-      hipStream_t main = h->ctx.stream;
-      const bool two = h->fd_minus.present && h->side_stream != nullptr;
-      if (two) {
-        hipError_t e = hipEventRecord(h->fork_events[0], main);
-        if (e == hipSuccess) e = hipStreamWaitEvent(h->side_stream, h->fork_events[0], 0);
-        if (e != hipSuccess && h->ctx.first_error == hipSuccess) h->ctx.first_error = e;
-        h->ctx.stream = h->side_stream;
-        launch_fd_perturb(h->ctx, w, v, eps, -1.f, wpm2, h->d);
-        make_weight_operands(h, om, wpm2);
-        lower_grad_seq(h, om, wpm2, lambda, Gm, nullptr, omega_bar, h->vec_g2 ? h->f(h->vec_g2) : nullptr);
-        h->ctx.stream = main;
-      }
-      launch_fd_perturb(h->ctx, w, v, eps, +1.f, wpm, h->d);
-      make_weight_operands(h, os, wpm);
-      lower_grad_seq(h, os, wpm, lambda, Gp, nullptr, omega_bar);
-      if (two) {
-        hipError_t e = hipEventRecord(h->join_event, h->side_stream);
-        if (e == hipSuccess) e = hipStreamWaitEvent(main, h->join_event, 0);
-        if (e != hipSuccess && h->ctx.first_error == hipSuccess) h->ctx.first_error = e;
-      } else {
-        launch_fd_perturb(h->ctx, w, v, eps, -1.f, wpm, h->d);
-        make_weight_operands(h, os, wpm);
-        lower_grad_seq(h, os, wpm, lambda, Gm, nullptr, omega_bar);
-      }
-      launch_fd_update(h->ctx, v, p, Gp, Gm, eps, alpha, h->d);
-    }
-    launch_sumsq(h->ctx, p, h->d, h->at<double>(h->partials), nrm2);
-    launch_fd_eps(h->ctx, nrm2, eps_scale, alpha, eps);
-    if (l2) {
-      launch_mixed_l2_fd(h->ctx, lambda, w, p, alpha, eps, dlambda, h->d);
-    } else if (!rw) {
-      // grad_a of the proximal cost is linear in w, so its central difference along q is exact
-      launch_mixed_prox(h->ctx, h->f(h->logrho), p, alpha, dlambda, h->d);
-    } else {
-      // grad_theta L_L(w') = (1/B) sum_i l_i(w') dR(lbar_i)/dtheta, so its central difference along
-      // q = alpha p needs only the per-sample losses at w +- eps q
-      launch_scale_copy(h->ctx, p, alpha, v, h->d);                       // v := q (v is no longer needed)
-      launch_fd_perturb(h->ctx, w, v, eps, +1.f, wpm, h->d);
-      make_weight_operands(h, os, wpm);
-      forward_and_loss(h, os, SIDE_TRAIN, wpm, lambda, omega_bar);
-      launch_scale_copy(h->ctx, h->f(sb.ell), 1.f, h->f(sb.ell_p), sb.B);
-      launch_fd_perturb(h->ctx, w, v, eps, -1.f, wpm, h->d);
-      make_weight_operands(h, os, wpm);
-      forward_and_loss(h, os, SIDE_TRAIN, wpm, lambda, omega_bar);
-      launch_fd_loss_diff(h->ctx, h->f(sb.ell_p), h->f(sb.ell), eps, sb.B, h->f(os.cvec));
-      launch_wnet_theta_vjp(h->ctx, h->f(sb.ell_bar), h->f(sb.dsig_bar), h->f(os.cvec), lambda,
-                            h->desc.wnet_hidden, sb.B, 1.0f / (float)sb.B, dlambda);
-    }
-  };
+  auto body = [=]() { fd_seq(h, w, lambda, K, alpha, eps_scale, dlambda); };
   return run_cached(h, h->CALL_FD, call_key({w, lambda, dlambda}, K, {alpha, eps_scale}), body);
 }
 
@@ -1892,27 +1943,19 @@ betty_status betty_lower_sgd_step(betty_handle h, float* w, const float* lambda,
     const bool prox = h->desc.hp == BETTY_HP_PROXIMAL;
     const float* dl = diag_log(h, lambda);
     make_weight_operands(h, os, w);
+    const Pass ps = train_pass(h, os, w, lambda, false);
     h->fixed_grouping = true;
-    forward_backward(h, os, SIDE_TRAIN, w, wnet_theta(h, lambda));
+    forward_backward(h, &ps, 1);
     h->fixed_grouping = false;
-    if (loss_or_null) {                      // the cost at the w before the step
-      float* add = nullptr;
-      if (dl) {
-        const float* x = w;
-        if (prox) {
-          launch_diff(h->ctx, w, lambda, h->f(h->vec_g), h->d);
-          x = h->f(h->vec_g);
-        }
-        add = h->f(h->scalars) + 8;
-        launch_l2_cost(h->ctx, dl, x, h->d, h->at<double>(h->partials), add);
-      }
-      launch_weighted_loss_sum(h->ctx, h->f(os.side[0].s), h->f(os.side[0].ell), os.side[0].B, add, loss_or_null);
-    }
     // momentum and parameters are updated in the epilogue of the weight-gradient launch
     // (the proximal term pulls towards the anchor: the epilogue subtracts it from w in that term)
     WgradSink k{EPI_WGRAD_SGD, nullptr, dl, prox ? lambda : nullptr, momentum, w, lr, false};
     k.beta = mu; k.gamma = weight_decay;
+    int n = 0;
+    if (dl && loss_or_null) k.sums = &n;
     wgrad_batch(h, os, 0, false, k);
+    if (loss_or_null)                        // the cost at the w before the step
+      launch_weighted_loss_sum(h->ctx, h->f(os.side[0].s), h->f(os.side[0].ell), os.side[0].B, h->f(h->sums), n, loss_or_null);
   });
 }
 

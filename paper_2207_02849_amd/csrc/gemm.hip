@@ -131,6 +131,7 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
     } else if constexpr (MODE == EPI_WGRAD) {
       R.a[k] = (ok && e.lam) ? e.lam[o] : 0.f;
       R.b[k] = (ok && e.lam) ? e.x[o] : 0.f;
+      R.c[k] = (ok && e.lam && e.p) ? e.p[o] : 0.f;
     } else if constexpr (MODE == EPI_WGRAD_NEUMANN) {
       R.a[k] = ok ? e.x[o] : 0.f;                         // s: the partial sum so far
       R.b[k] = ok ? e.v[o] : 0.f;                         // g: the vector the series is applied to
@@ -140,6 +141,11 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
       R.b[k] = ok ? e.v[o] : 0.f;                         // g
       R.c[k] = ok ? e.lam[o] : 0.f;
       R.d[k] = ok ? e.x[o] : 0.f;                         // w
+    } else if constexpr (MODE == EPI_WGRAD_FD || MODE == EPI_WGRAD_FD_LAST) {
+      R.a[k] = ok ? e.v[o] : 0.f;
+      R.b[k] = ok ? e.p[o] : 0.f;
+      R.c[k] = (ok && e.lam) ? e.lam[o] : 0.f;
+      if constexpr (MODE == EPI_WGRAD_FD_LAST) R.d[k] = (ok && e.x) ? e.x[o] : -1.f;
     } else if constexpr (MODE == EPI_WGRAD_SCALED) {
       R.a[k] = ok ? e.x[o] : 0.f;
     } else if constexpr (MODE == EPI_WGRAD_SGD) {
@@ -148,6 +154,18 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
       R.c[k] = (ok && e.lam) ? e.lam[o] : 0.f;
       R.d[k] = (ok && e.x) ? e.x[o] : 0.f;
     }
+  }
+}
+
+// the sums of a launch (Epilogue::partial): one number per finishing wavefront
+template <int MODE> constexpr bool epi_sums() { return MODE == EPI_WGRAD || MODE == EPI_WGRAD_INIT || MODE == EPI_WGRAD_FD || MODE == EPI_WGRAD_SGD; }
+template <int MODE>
+__device__ __forceinline__ void epi_store_sum(const Epilogue& e, int wave, float sum) {
+  if constexpr (epi_sums<MODE>()) {
+    if (!e.partial) return;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if ((threadIdx.x & 63) == 0) e.partial[4 * (size_t)blockIdx.x + wave] = sum;
   }
 }
 
@@ -172,7 +190,7 @@ __device__ __forceinline__ void epi_gram(const Epilogue& e, int M, int rb, int c
 
 template <typename T, int MODE, int NR>
 __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int rb, int col,
-                                           const float (&acc)[NR], const EpiRegs<NR>& R) {
+                                           const float (&acc)[NR], const EpiRegs<NR>& R, float& sum) {
   float val[NR];
   if constexpr (MODE == EPI_RFWD_LAST_HESS) {
     // rows live across the 32 lanes of a half-wavefront (lane % 32 = column): butterfly sums
@@ -256,8 +274,10 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
   } else if constexpr (MODE == EPI_WGRAD) {            // C = acc (+ 2 e^lam x)
     if (e.lam) {
 #pragma unroll
-      for (int k = 0; k < NR; ++k)
-        if (ok[k]) e.C[of[k]] = acc[k] + 2.f * expf(R.a[k]) * R.b[k];
+      for (int k = 0; k < NR; ++k) {
+        const float el = expf(R.a[k]), x = R.b[k] - R.c[k];
+        if (ok[k]) { e.C[of[k]] = acc[k] + 2.f * el * x; sum += el * x * x; }
+      }
     } else {
 #pragma unroll
       for (int k = 0; k < NR; ++k)
@@ -268,7 +288,7 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       val[k] = acc[k];
-      if (ok[k]) { e.v[of[k]] = acc[k]; if (e.p) e.p[of[k]] = acc[k]; }
+      if (ok[k]) { e.v[of[k]] = acc[k]; if (e.p) e.p[of[k]] = acc[k]; sum += acc[k] * acc[k]; }
     }
   } else if constexpr (MODE == EPI_WGRAD_NEUMANN) {    // Hs = acc (+ 2 e^lam s); s <- g + s - alpha Hs
 #pragma unroll
@@ -280,6 +300,21 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
 #pragma unroll
     for (int k = 0; k < NR; ++k)
       if (ok[k]) e.p[of[k]] = val[k];
+  } else if constexpr (MODE == EPI_WGRAD_FD || MODE == EPI_WGRAD_FD_LAST) {
+    const float eps = e.eps[0], scale = eps > 0.f ? 0.5f / eps : 0.f;      // v = 0 has the zero product
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const float el = e.lam ? 2.f * expf(R.c[k]) : 0.f;
+      const float vn = R.a[k] - e.alpha * (acc[k] * scale + el * R.a[k]), pn = R.b[k] + vn;
+      if (!ok[k]) continue;
+      if constexpr (MODE == EPI_WGRAD_FD) {
+        e.v[of[k]] = vn; e.p[of[k]] = pn;
+        sum += e.sum_p ? pn * pn : vn * vn;
+      } else {
+        e.C[of[k]] = -el * R.d[k] * (e.alpha * pn);
+      }
+    }
+    return;
   } else if constexpr (MODE == EPI_WGRAD_SCALED) {
 #pragma unroll
     for (int k = 0; k < NR; ++k)
@@ -289,7 +324,11 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       float gk = acc[k] + e.gamma * R.b[k];
-      if (e.lam) gk += 2.f * expf(R.c[k]) * (R.b[k] - R.d[k]);     // x: anchor of a proximal term
+      if (e.lam) {                                                  // x: anchor of a proximal term
+        const float el = expf(R.c[k]), x = R.b[k] - R.d[k];
+        gk += 2.f * el * x;
+        if (ok[k]) sum += el * x * x;
+      }
       const float mk = e.beta * R.a[k] + gk;
       if (ok[k]) { e.v[of[k]] = mk; e.p[of[k]] = R.b[k] - e.alpha * mk; }
     }
@@ -369,27 +408,35 @@ __device__ void bias_rows(const BiasJob& j, int row) {
   // 16 bytes per lane and access, two in flight; entries beyond k are zero padding of the operand
   constexpr int EPC = 16 / (int)sizeof(T);
   typedef __attribute__((__vector_size__(16))) T vecT;
-  const T* p = (const T*)j.Mt + (long long)row * j.ld + lane * EPC;
   float acc = 0.f;
-  for (int c = lane * EPC; c < j.k; c += 128 * EPC, p += 128 * EPC) {
-    const vecT v0 = *(const vecT*)p;
-    vecT v1{};
-    if (c + 64 * EPC < j.k) v1 = *(const vecT*)(p + 64 * EPC);
+  for (const void* M = j.Mt; M; M = M == j.Mt ? j.Mt2 : nullptr) {
+    const T* p = (const T*)M + (long long)row * j.ld + lane * EPC;
+    for (int c = lane * EPC; c < j.k; c += 128 * EPC, p += 128 * EPC) {
+      const vecT v0 = *(const vecT*)p;
+      vecT v1{};
+      if (c + 64 * EPC < j.k) v1 = *(const vecT*)(p + 64 * EPC);
 #pragma unroll
-    for (int i = 0; i < EPC; ++i) acc += (float)v0[i] + (float)v1[i];
+      for (int i = 0; i < EPC; ++i) acc += (float)v0[i] + (float)v1[i];
+    }
   }
   acc = wave_sum_f(acc);
   if (lane != 0) return;
   switch (MODE) {
     case EPI_WGRAD: {
-      float g = acc;
-      if (j.lam) g += 2.f * expf(j.lam[row]) * j.x[row];
+      float g = acc, sum = 0.f;
+      if (j.lam) {
+        const float el = expf(j.lam[row]), x = j.x[row] - (j.p ? j.p[row] : 0.f);
+        g += 2.f * el * x;
+        sum = el * x * x;
+      }
       j.C[row] = g;
+      if (j.partial) j.partial[row] = sum;
       break;
     }
     case EPI_WGRAD_INIT:
       j.v[row] = acc;
       if (j.p) j.p[row] = acc;
+      if (j.partial) j.partial[row] = acc * acc;
       break;
     case EPI_WGRAD_NEUMANN: {
       const float so = j.x[row];
@@ -398,13 +445,31 @@ __device__ void bias_rows(const BiasJob& j, int row) {
       j.p[row] = j.v[row] + (so - j.alpha * hs);
       break;
     }
+    case EPI_WGRAD_FD:
+    case EPI_WGRAD_FD_LAST: {
+      const float eps = j.eps[0], scale = eps > 0.f ? 0.5f / eps : 0.f;
+      const float el = j.lam ? 2.f * expf(j.lam[row]) : 0.f, vo = j.v[row];
+      const float vn = vo - j.alpha * (acc * scale + el * vo), pn = j.p[row] + vn;
+      if (MODE == EPI_WGRAD_FD) {
+        j.v[row] = vn; j.p[row] = pn;
+        if (j.partial) j.partial[row] = j.sum_p ? pn * pn : vn * vn;
+      } else {
+        j.C[row] = -el * (j.x ? j.x[row] : -1.f) * (j.alpha * pn);
+      }
+      break;
+    }
     case EPI_WGRAD_SCALED:
       j.C[row] = j.gamma * (j.beta * j.x[row] - j.alpha * acc);
       break;
     case EPI_WGRAD_SGD: {
       const float wo = j.p[row];
-      float gk = acc + j.gamma * wo;
-      if (j.lam) gk += 2.f * expf(j.lam[row]) * (wo - (j.x ? j.x[row] : 0.f));
+      float gk = acc + j.gamma * wo, sum = 0.f;
+      if (j.lam) {
+        const float el = expf(j.lam[row]), x = wo - (j.x ? j.x[row] : 0.f);
+        gk += 2.f * el * x;
+        sum = el * x * x;
+      }
+      if (j.partial) j.partial[row] = sum;
       const float mk = j.beta * j.v[row] + gk;
       j.v[row] = mk;
       j.p[row] = wo - j.alpha * mk;
@@ -658,11 +723,14 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
 #pragma unroll
       for (int r = 0; r < 4; ++r) q4[r] += red[((g2 * 16) + 4 * kg + r) * 64 + lane];
     }
-    epi_finish<T, MODE, 4>(e, g.M, g.N, m0 + 8 * kg + 4 * (lane >> 5), n0 + (lane & 31), q4, pre4);
+    float sum = 0.f;
+    epi_finish<T, MODE, 4>(e, g.M, g.N, m0 + 8 * kg + 4 * (lane >> 5), n0 + (lane & 31), q4, pre4, sum);
+    epi_store_sum<MODE>(e, kg, sum);
     return;
   }
 
   // ---- epilogue from registers, one MFMA block at a time
+  float sum = 0.f;
 #pragma unroll
   for (int ij = 0; ij < TM * TN; ++ij) {
     const int rb = m0 + wm * TM * 32 + (ij / TN) * 32 + 4 * (lane >> 5);
@@ -671,8 +739,9 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
     float accf[16];
 #pragma unroll
     for (int r = 0; r < 16; ++r) accf[r] = acc[ij][r];
-    epi_finish<T, MODE, 16>(e, g.M, g.N, rb, col, accf, pre[ij]);
+    epi_finish<T, MODE, 16>(e, g.M, g.N, rb, col, accf, pre[ij], sum);
   }
+  epi_store_sum<MODE>(e, wave, sum);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -762,7 +831,9 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
   if (t >= 256) return;
   float v[1] = {0.f};
   for (int k = 0; k < KG; ++k) v[0] += part[(k * 16 + (t >> 4)) * G16_PITCH + (t & 15)];
-  epi_finish<T, MODE, 1>(e, g.M, g.N, row, col, v, pre);
+  float sum = 0.f;
+  epi_finish<T, MODE, 1>(e, g.M, g.N, row, col, v, pre, sum);
+  epi_store_sum<MODE>(e, kg, sum);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -780,11 +851,12 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
 // leaves through a small LDS staging tile as 16-byte rows.  Two workgroups fit a compute unit, so
 // one streams its epilogue while the other multiplies.
 
-template <int MODE, bool LAM> constexpr int wg_narr() {
-  return MODE == EPI_WGRAD ? (LAM ? 2 : 0) : MODE == EPI_WGRAD_INIT ? 0 : MODE == EPI_WGRAD_NEUMANN ? (LAM ? 3 : 2)
+// LAM: 0 = no diagonal term, 1 = with one, 2 = with one whose x is the distance to an anchor (mode WGRAD)
+template <int MODE, int LAM> constexpr int wg_narr() {
+  return MODE == EPI_WGRAD ? (LAM ? LAM + 1 : 0) : MODE == EPI_WGRAD_INIT ? 0 : MODE == EPI_WGRAD_NEUMANN ? (LAM ? 3 : 2)
        : MODE == EPI_WGRAD_SGD ? (LAM ? 4 : 2) : MODE == EPI_WGRAD_SCALED ? 1 : 4;
 }
-template <int MODE, bool LAM> constexpr int wg_nreg() { return wg_narr<MODE, LAM>() > 0 ? wg_narr<MODE, LAM>() : 1; }
+template <int MODE, int LAM> constexpr int wg_nreg() { return wg_narr<MODE, LAM>() > 0 ? wg_narr<MODE, LAM>() : 1; }
 
 constexpr int WG_BT = 128;                 // tile extent
 constexpr int WG_HP = WG_BT + 8;           // pitch of the fp32 accumulator tile in LDS (floats)
@@ -847,7 +919,7 @@ __device__ __forceinline__ void store_patch(float* __restrict__ p, long long ld,
   }
 }
 
-template <int MODE, bool LAM, bool VEC>
+template <int MODE, int LAM, bool VEC>
 __device__ __forceinline__ void wg_request(const WgTile& w, int pass, int pr, int pc, float (&in)[wg_nreg<MODE, LAM>()][4][4]) {
   constexpr int NARR = wg_narr<MODE, LAM>();
   const int row0 = w.m0 + WG_PASS * pass + 4 * pr, col0 = w.n0 + 4 * pc;
@@ -857,10 +929,13 @@ __device__ __forceinline__ void wg_request(const WgTile& w, int pass, int pr, in
 
 // one pass of 32 rows: accumulators from LDS, the mode's update rule, stores.  Every thread of the
 // workgroup calls it (it contains barriers when the transposed copy is asked for).
-template <int MODE, bool LAM, bool VEC>
+template <int MODE, int LAM, bool VEC>
 __device__ __forceinline__ void wg_finish(const WgTile& w, int pass, int pr, int pc, int tid, const float* hs, __bf16* sT,
-                                          const float (&in)[wg_nreg<MODE, LAM>()][4][4]) {
+                                          const float (&in)[wg_nreg<MODE, LAM>()][4][4], float& sum) {
   constexpr int NR = wg_nreg<MODE, LAM>();
+  // A row's terms are added before the next row's are made: the compiler would keep all 64 of the
+  // tile and spill (gradients with a diagonal term, 10.4M parameters: 88 against 41 us).
+  constexpr bool SUMS = MODE == EPI_WGRAD_INIT || (LAM && (MODE == EPI_WGRAD || MODE == EPI_WGRAD_SGD));
   const int row0 = w.m0 + WG_PASS * pass + 4 * pr, col0 = w.n0 + 4 * pc;
   float acc[4][4], val[4][4], val2[4][4];
 #pragma unroll
@@ -873,14 +948,21 @@ __device__ __forceinline__ void wg_finish(const WgTile& w, int pass, int pr, int
   const float (&I2)[4][4] = in[NR > 2 ? 2 : 0];
   const float (&I3)[4][4] = in[NR > 3 ? 3 : 0];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < 4; ++i) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       const float a = acc[i][j];
-      if constexpr (MODE == EPI_WGRAD) {                   // I0 = lam, I1 = x
-        val[i][j] = LAM ? a + 2.f * expf(I0[i][j]) * I1[i][j] : a;
+      const bool ok = row0 + i < w.M && (VEC || col0 + j < w.N);   // (what the sums count)
+      if constexpr (MODE == EPI_WGRAD) {                   // I0 = lam, I1 = x, I2 = anchor
+        val[i][j] = a;
+        if constexpr (LAM) {
+          const float el = expf(I0[i][j]), x = LAM == 2 ? I1[i][j] - I2[i][j] : I1[i][j];
+          val[i][j] += 2.f * el * x;
+          sum += ok ? el * x * x : 0.f;
+        }
       } else if constexpr (MODE == EPI_WGRAD_INIT) {
         val[i][j] = a;
+        sum += ok ? a * a : 0.f;
       } else if constexpr (MODE == EPI_WGRAD_SCALED) {     // I0 = x
         val[i][j] = w.gamma * (w.beta * I0[i][j] - w.alpha * a);
       } else if constexpr (MODE == EPI_WGRAD_NEUMANN) {    // I0 = s, I1 = g, I2 = lam
@@ -893,12 +975,18 @@ __device__ __forceinline__ void wg_finish(const WgTile& w, int pass, int pr, int
         val[i][j] = -el * I3[i][j] * (w.alpha * sn);
       } else {                                             // SGD: I0 = momentum, I1 = w, I2 = lam, I3 = anchor
         float gk = a + w.gamma * I1[i][j];
-        if constexpr (LAM) gk += 2.f * expf(I2[i][j]) * (I1[i][j] - (w.has_x ? I3[i][j] : 0.f));
+        if constexpr (LAM) {
+          const float el = expf(I2[i][j]), x = I1[i][j] - (w.has_x ? I3[i][j] : 0.f);
+          gk += 2.f * el * x;
+          sum += ok ? el * x * x : 0.f;
+        }
         const float mk = w.beta * I0[i][j] + gk;
         val[i][j] = mk;
         val2[i][j] = I1[i][j] - w.alpha * mk;
       }
     }
+    if constexpr (SUMS) asm volatile("" : "+v"(sum));
+  }
   if constexpr (MODE == EPI_WGRAD || MODE == EPI_WGRAD_NEUMANN_L2 || MODE == EPI_WGRAD_SCALED) {
     store_patch<VEC>(w.C, w.ldc, row0, col0, w.M, w.N, val);
     return;
@@ -958,13 +1046,16 @@ __device__ __forceinline__ void wg_finish(const WgTile& w, int pass, int pr, int
 // one more).  Requesting the whole tile ahead (3, affordable with two input arrays) was measured
 // slower than one pass ahead on the 121M-parameter model: 620 against 576 us per launch.  The final
 // step of the series (four input arrays, once per hypergradient) requests each pass as it gets
-// to it: a second register set would not fit beside the tile walk's state.
-template <int MODE, bool LAM> constexpr int wg_depth() { return MODE == EPI_WGRAD_NEUMANN_L2 ? 0 : 1; }
+// to it: a second register set would not fit beside the tile walk's state.  Nor would it where three
+// or four arrays come with a sum (the anchored gradient, the SGD step of a diagonal cost).
+template <int MODE, int LAM> constexpr int wg_depth() {
+  return MODE == EPI_WGRAD_NEUMANN_L2 || (MODE == EPI_WGRAD && LAM == 2) || (MODE == EPI_WGRAD_SGD && LAM) ? 0 : 1;
+}
 constexpr int WG_NPASS = WG_BT / WG_PASS;
 
-template <int MODE, bool LAM, bool VEC>
+template <int MODE, int LAM, bool VEC>
 __device__ __forceinline__ void wg_epilogue(const WgTile& w, int pr, int pc, int tid, const float* hs, __bf16* sT,
-                                            float (&in)[wg_depth<MODE, LAM>() + 1][wg_nreg<MODE, LAM>()][4][4]) {
+                                            float (&in)[wg_depth<MODE, LAM>() + 1][wg_nreg<MODE, LAM>()][4][4], float& sum) {
   constexpr int DEPTH = wg_depth<MODE, LAM>(), EARLY = DEPTH < 2 ? DEPTH : 2;
   // (with 16-byte accesses the first EARLY passes were requested inside the k loop)
 #pragma unroll
@@ -972,11 +1063,11 @@ __device__ __forceinline__ void wg_epilogue(const WgTile& w, int pr, int pc, int
 #pragma unroll
   for (int pass = 0; pass < WG_NPASS; ++pass) {
     if (pass + DEPTH < WG_NPASS) wg_request<MODE, LAM, VEC>(w, pass + DEPTH, pr, pc, in[(pass + DEPTH) % (DEPTH + 1)]);
-    wg_finish<MODE, LAM, VEC>(w, pass, pr, pc, tid, hs, sT, in[pass % (DEPTH + 1)]);
+    wg_finish<MODE, LAM, VEC>(w, pass, pr, pc, tid, hs, sT, in[pass % (DEPTH + 1)], sum);
   }
 }
 
-template <int MODE, bool LAM>
+template <int MODE, int LAM>
 __global__ __launch_bounds__(256, 2) void wgrad128_kernel(WgradBatch batch) {
   typedef __bf16 T;
   constexpr int BT = WG_BT, NCH = GEMM_NCH, ROW = NCH + 1, EPC = 8, KT = NCH * EPC, GT = 256;
@@ -1069,6 +1160,7 @@ __global__ __launch_bounds__(256, 2) void wgrad128_kernel(WgradBatch batch) {
   float* const hs = (float*)smem;
   __bf16* const sT = (__bf16*)(hs + BT * WG_HP);
   int tile = blockIdx.x;
+  float sum = 0.f;
   BETTY_WG_LOCATE(tile)
   BETTY_WG_GLOAD(ra0, rb0, 0)
   BETTY_WG_GLOAD(ra1, rb1, 1)
@@ -1081,7 +1173,7 @@ __global__ __launch_bounds__(256, 2) void wgrad128_kernel(WgradBatch batch) {
     w.M = batch.p[pi].g.M; w.N = batch.p[pi].g.N; w.m0 = m0; w.n0 = n0;
     w.alpha = e.alpha; w.beta = e.beta; w.gamma = e.gamma;
     w.has_x = e.x != nullptr;
-    if constexpr (MODE == EPI_WGRAD) { w.src[0] = e.lam; w.src[1] = e.x; w.src[2] = e.lam; w.src[3] = e.lam; }
+    if constexpr (MODE == EPI_WGRAD) { w.src[0] = e.lam; w.src[1] = e.x; w.src[2] = e.p; w.src[3] = e.lam; }
     else if constexpr (MODE == EPI_WGRAD_NEUMANN) { w.src[0] = e.x; w.src[1] = e.v; w.src[2] = e.lam; w.src[3] = e.x; }
     else if constexpr (MODE == EPI_WGRAD_NEUMANN_L2) { w.src[0] = e.p; w.src[1] = e.v; w.src[2] = e.lam; w.src[3] = e.x; }
     else if constexpr (MODE == EPI_WGRAD_SCALED) { w.src[0] = e.x; w.src[1] = w.src[2] = w.src[3] = e.x; }
@@ -1136,9 +1228,9 @@ __global__ __launch_bounds__(256, 2) void wgrad128_kernel(WgradBatch batch) {
       BETTY_WG_GLOAD(ra0, rb0, 0)
       BETTY_WG_GLOAD(ra1, rb1, 1)
     }
-    if (vec) wg_epilogue<MODE, LAM, true>(w, pr, pc, tid, hs, sT, in);
-    else wg_epilogue<MODE, LAM, false>(w, pr, pc, tid, hs, sT, in);
-    if (!more) break;
+    if (vec) wg_epilogue<MODE, LAM, true>(w, pr, pc, tid, hs, sT, in, sum);
+    else wg_epilogue<MODE, LAM, false>(w, pr, pc, tid, hs, sT, in, sum);
+    if (!more) { epi_store_sum<MODE>(e, wave, sum); break; }
     __syncthreads();                                // the next k loop writes where this epilogue read
     tile = next;
     if constexpr (!AHEAD) {
@@ -1237,13 +1329,14 @@ static void launch_wgrad_mode(int mode, int total, hipStream_t st, const GemmBat
 #define BETTY_CASE_W(M_) case M_: launch_one<T, BT, WPG, KG, M_>(total, st, b, err); break;
     BETTY_CASE_W(EPI_WGRAD) BETTY_CASE_W(EPI_WGRAD_INIT) BETTY_CASE_W(EPI_WGRAD_NEUMANN)
     BETTY_CASE_W(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_W(EPI_WGRAD_SGD) BETTY_CASE_W(EPI_WGRAD_SCALED)
+    BETTY_CASE_W(EPI_WGRAD_FD) BETTY_CASE_W(EPI_WGRAD_FD_LAST)
 #undef BETTY_CASE_W
     default: err = hipErrorInvalidValue; break;
   }
 }
 #undef BETTY_CASE
 
-template <int MODE, bool LAM>
+template <int MODE, int LAM>
 static void launch_wgrad128_one(int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
   static bool configured = false;
   if (!configured) {
@@ -1259,12 +1352,17 @@ static void launch_wgrad128_one(int total, hipStream_t st, const GemmBatch& b, h
 static void launch_wgrad128(int mode, int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
   const bool lam = b.p[0].e.lam != nullptr;
   switch (mode) {
-#define BETTY_CASE_W(M_) case M_: if (lam) launch_wgrad128_one<M_, true>(total, st, b, err); else launch_wgrad128_one<M_, false>(total, st, b, err); break;
-    BETTY_CASE_W(EPI_WGRAD) BETTY_CASE_W(EPI_WGRAD_NEUMANN) BETTY_CASE_W(EPI_WGRAD_SGD)
+#define BETTY_CASE_W(M_) case M_: if (lam) launch_wgrad128_one<M_, 1>(total, st, b, err); else launch_wgrad128_one<M_, 0>(total, st, b, err); break;
+    case EPI_WGRAD:
+      if (lam && b.p[0].e.p) launch_wgrad128_one<EPI_WGRAD, 2>(total, st, b, err);
+      else if (lam) launch_wgrad128_one<EPI_WGRAD, 1>(total, st, b, err);
+      else launch_wgrad128_one<EPI_WGRAD, 0>(total, st, b, err);
+      break;
+    BETTY_CASE_W(EPI_WGRAD_NEUMANN) BETTY_CASE_W(EPI_WGRAD_SGD)
 #undef BETTY_CASE_W
-    case EPI_WGRAD_INIT: launch_wgrad128_one<EPI_WGRAD_INIT, false>(total, st, b, err); break;
-    case EPI_WGRAD_SCALED: launch_wgrad128_one<EPI_WGRAD_SCALED, false>(total, st, b, err); break;
-    case EPI_WGRAD_NEUMANN_L2: launch_wgrad128_one<EPI_WGRAD_NEUMANN_L2, true>(total, st, b, err); break;
+    case EPI_WGRAD_INIT: launch_wgrad128_one<EPI_WGRAD_INIT, 0>(total, st, b, err); break;
+    case EPI_WGRAD_SCALED: launch_wgrad128_one<EPI_WGRAD_SCALED, 0>(total, st, b, err); break;
+    case EPI_WGRAD_NEUMANN_L2: launch_wgrad128_one<EPI_WGRAD_NEUMANN_L2, 1>(total, st, b, err); break;
     default: err = hipErrorInvalidValue; break;
   }
 }
@@ -1306,6 +1404,7 @@ static void launch_small_mode(int mode, int total, hipStream_t st, const GemmBat
     BETTY_CASE_S(EPI_RFWD_LAST) BETTY_CASE_S(EPI_RBWD) BETTY_CASE_S(EPI_RFWD_LAST_HESS) BETTY_CASE_S(EPI_GRAM) BETTY_CASE_S(EPI_SAMPLE)
     BETTY_CASE_S(EPI_WGRAD) BETTY_CASE_S(EPI_WGRAD_INIT) BETTY_CASE_S(EPI_WGRAD_NEUMANN)
     BETTY_CASE_S(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_S(EPI_WGRAD_SGD) BETTY_CASE_S(EPI_WGRAD_SCALED)
+    BETTY_CASE_S(EPI_WGRAD_FD) BETTY_CASE_S(EPI_WGRAD_FD_LAST)
 #undef BETTY_CASE_S
     default: err = hipErrorInvalidValue; break;
   }
@@ -1354,7 +1453,7 @@ int gemm_cfg_tile(int cfg) { return cfg == GEMM_128x1 ? 128 : (cfg == GEMM_32x8 
 static int gemm_cfg_tile_rows(int cfg) { return cfg == GEMM_128x64 ? 128 : gemm_cfg_tile(cfg); }
 static int gemm_cfg_waves(int cfg) { return cfg == GEMM_32x8 ? 8 : 4; }
 
-void launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& b, double flops, double bytes) {
+int launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& b, double flops, double bytes, float* partial) {
   const int bt = gemm_cfg_tile(cfg);
   const int rows_per_block = cfg != GEMM_16 ? gemm_cfg_waves(cfg)
                            : small_shape(elem == ELEM_BF16 ? batch_steps<__bf16>(b) : batch_steps<float>(b)).kg;
@@ -1374,7 +1473,13 @@ void launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& b, double flops,
   }
   b.bias_begin[b.n_bias] = bias_blocks;
   const int total = blocks + bias_blocks;
-  if (total <= 0) return;
+  if (total <= 0) return 0;
+  int n_partial = 0;
+  if (partial) {
+    n_partial = 4 * (elem == ELEM_BF16 && cfg == GEMM_128x1 ? b.walkers : blocks);
+    for (int i = 0; i < b.n; ++i) b.p[i].e.partial = partial;
+    for (int i = 0; i < b.n_bias; ++i) { b.bias[i].partial = partial + n_partial; n_partial += b.bias[i].rows; }
+  }
   const int mode0 = b.p[0].e.mode;
   const int kind = mode0 == EPI_WGRAD_NEUMANN ? BETTY_K_GEMM_UPDATE
                  : mode0 == EPI_WGRAD_NEUMANN_L2 ? BETTY_K_GEMM_UPDATE_FINAL
@@ -1385,6 +1490,7 @@ void launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& b, double flops,
   if (elem == ELEM_BF16) launch_elem<__bf16>(cfg, b.p[0].e.mode, total, ctx.stream, b, err);
   else launch_elem<float>(cfg, b.p[0].e.mode, total, ctx.stream, b, err);
   if (err != hipSuccess && ctx.first_error == hipSuccess) ctx.first_error = err;
+  return n_partial;
 }
 
 }  // namespace betty

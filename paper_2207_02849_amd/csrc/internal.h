@@ -58,7 +58,7 @@ enum EpiMode {
   //  SAMPLE  f0 = s = g + beta x - alpha acc + colvec  (g = Rz, x = e, each may be null);
   //          out, outT = dphi .* s when asked for
   EPI_GRAM, EPI_SAMPLE,
-  EPI_WGRAD,             // C = acc (+ 2 exp(lam) x)                       flat parameter layout
+  EPI_WGRAD,             // C = acc (+ 2 exp(lam) (x - p))                 flat parameter layout; p (an anchor) may be null
   EPI_WGRAD_INIT,        // v = acc (and p = acc when p is given); out = operand copies
   // One step of the Neumann partial sum in nested form, s_{j+1} = g + (I - alpha H) s_j with s_0 = g
   // (the same sum_{i<=j} (I - alpha H)^i g as the term-by-term recurrence, one state vector instead
@@ -67,6 +67,10 @@ enum EpiMode {
   EPI_WGRAD_NEUMANN,
   EPI_WGRAD_NEUMANN_L2,  // last step for L2 decay: s read from p, new s kept in registers, C = -2 exp(lam) x (alpha s)
   EPI_WGRAD_SCALED,      // C = gamma (beta x - alpha acc)
+  // One step of the finite-difference series, acc = difference of the two perturbed gradients' data terms:
+  // Hv = acc / (2 eps) (+ 2 exp(lam) v);  v <- v - alpha Hv;  p <- p + v.  _LAST: only the mixed VJP leaves,
+  // C = -2 exp(lam) x (alpha p), or 2 exp(lam) (alpha p) without x
+  EPI_WGRAD_FD, EPI_WGRAD_FD_LAST,
   EPI_WGRAD_SGD          // g = acc (+ 2 exp(lam) p) + gamma p; v <- beta v + g; p <- p - alpha v  (p = w, v = momentum)
 };
 
@@ -87,6 +91,11 @@ struct Epilogue {
       float* C; long long ldc;           // fp32 row-major (flat parameter slice)
       const float* lam; const float* x;  // same indexing as C
       float* v; float* p;
+      const float* eps;                  // EPI_WGRAD_FD: device scalar
+      // Sums that leave beside the result, one number per finishing wavefront (4 blockIdx.x + wavefront; bias
+      // rows: BiasJob::partial): WGRAD exp(lam) (x - p)^2, INIT acc^2, FD the new v^2 (or p^2: sum_p).  May be null.
+      float* partial;
+      int sum_p;
     };
   };
   float alpha, beta, gamma;
@@ -97,7 +106,9 @@ struct GemmProblem { GemmArgs g; Epilogue e; };
 // out[row] from sum_k Mt[row][k]: bias-shaped slices of the WGRAD modes
 struct BiasJob {
   const void* Mt; int ld, rows, k, mode;
+  const void* Mt2;                       // a second matrix whose sums are added, or null
   float* C; const float* lam; const float* x; float* v; float* p; float alpha, beta, gamma;
+  const float* eps; float* partial; int sum_p;
 };
 
 constexpr int MAX_PROBLEMS = 8;
@@ -169,8 +180,9 @@ template <> struct MfmaChunk<float> {
 
 // ---- gemm.hip
 int gemm_cfg_tile(int cfg);
-void launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& batch, double algorithmic_flops,
-                       double algorithmic_bytes = 0);
+// `partial` (weight-gradient launches): where their sums go, written into the batch; returns how many there are
+int launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& batch, double algorithmic_flops,
+                      double algorithmic_bytes = 0, float* partial = nullptr);
 
 // ---- kernels.hip : operand conversion -----------------------------------------------------
 // Where the labels or targets of a batch are: kept in the workspace and read by the kernels, so that a
@@ -195,6 +207,18 @@ void launch_convert_batch(Ctx&, Elem, ConvertBatch&);
 
 // Weighted sum over the steps of the series: sum = beta sum + r (sum = r on the first step); on the last step
 // the result goes back to r in the operand type.  n elements each, a multiple of 8.
+// out+, out- = w + e v, w - e v as fp32 GEMM operands (as stored and transposed) with e = eps_scale /
+// (|scale| sqrt(sum of partial)) times scale, and the bias slices as they are; e (without scale) also goes to *eps
+struct PerturbJob {
+  const float* w; const float* v; int rows, cols;
+  float* out[2]; int ld; float* outT[2]; int ldT;
+  const float* b; const float* bv; float* bout[2];       // bias slices (cols entries), or null
+};
+struct PerturbBatch { int n = 0; int block_begin[MAX_PROBLEMS + 1]; PerturbJob j[MAX_PROBLEMS]; const float* eps; float scale; int signs; };
+void launch_perturb(Ctx&, PerturbBatch&);
+// *eps = eps_scale / (|scale| sqrt(sum of n partial)), 0 if that sum is 0
+void launch_fd_eps(Ctx&, const float* partial, int n, float eps_scale, float scale, float* eps);
+
 struct AccumulateJob { void* r; float* sum; float beta; size_t n; };
 struct AccumulateBatch { int n = 0; int block_begin[MAX_PROBLEMS + 1]; AccumulateJob j[MAX_PROBLEMS]; bool first, last; };
 void launch_accumulate(Ctx&, Elem, AccumulateBatch&);
@@ -206,7 +230,7 @@ struct LossArgs {
   const Labels* labels; int C;
   const float* theta;                   // weight net (reweight only)
   const float* omega_fixed;             // reweight only: use these weights instead of R(l_i; theta)
-  int rows; float inv_batch;
+  int rows; float inv_batch;             // (negative: the output delta with the opposite sign)
   float* ell; float* s; float* omega;   // per-sample outputs
   float* dsig;                          // omega_i (1 - omega_i), formed without cancellation (weight net evaluated here only)
   float* P;                             // softmax probabilities [rows][ldz] (CE)
@@ -256,12 +280,13 @@ struct LastGradSide {
   void* DL; void* DLt; int ldd, ldDLt;           // out: delta_L [B][ldd] and [n_out_p][ldDLt]
   const float* dphi; float* e2; int ldf;         // layer L-1, fp32 [B][ldf]
   void* D; int ldD; void* Dt; int ldDt;          // out: delta_{L-1} [B][ldD] and [n_in_p][ldDt]
-  int B, reweight; float inv_batch;
+  const void* Wt; const void* Wn;                // W_L as [n_out_p][n_in_p] and [n_in_p][n_out_p]
+  const float* bias;                             // b_L (fp32), or null
+  int B, reweight; float inv_batch;              // (inv_batch negative: the output delta with the opposite sign)
 };
 struct LastGradArgs {
   LastGradSide side[2]; int n_sides;
-  const void* Wt; int ldt; const void* Wn; int ldn;   // W_L as [n_out_p][n_in_p] and [n_in_p][n_out_p]
-  const float* bias;                                  // b_L (fp32), or null
+  int ldt, ldn;
   const float* theta; int hidden;                     // weight net (sides with reweight set)
   int n_in, n_in_p, C, loss;
 };
@@ -273,16 +298,15 @@ void launch_loss_hessian_rows(Ctx&, Elem, int loss, const float* P, const float*
 void launch_loss_directional_rows(Ctx&, int loss, const float* P, const float* Z, const Labels* labels, const float* Rz, long long ld, int rows,
                                   int C, float* c);
 // out = -(1/B) sum_i c_i dR(l_i; theta)/dtheta
-void launch_wnet_theta_vjp(Ctx&, const float* ell, const float* dsig, const float* c,
+// (c_minus given: c_i = (c_i - c_minus_i) / (2 eps), 0 if eps is 0: losses at two perturbed points)
+void launch_wnet_theta_vjp(Ctx&, const float* ell, const float* dsig, const float* c, const float* c_minus, const float* eps,
                            const float* theta, int hidden, int rows, float inv_batch, float* out);
 
 // ---- kernels.hip : flat parameter-shaped vectors ------------------------------------------
 void launch_fill_zero(Ctx&, void* p, size_t bytes);
-void launch_scale_copy(Ctx&, const float* src, float scale, float* dst, size_t n);
 void launch_mixed_l2(Ctx&, const float* lam, const float* w, const float* p, float alpha, float* out, size_t n);
 // out = 2 exp(logrho) (alpha p): the mixed VJP of the proximal cost into its anchor
 void launch_mixed_prox(Ctx&, const float* logrho, const float* p, float alpha, float* out, size_t n);
-void launch_diff(Ctx&, const float* a, const float* b, float* out, size_t n);        // out = a - b
 void launch_fill_value(Ctx&, float* p, float value, size_t n);
 void launch_sumsq(Ctx&, const float* x, size_t n, double* partials, float* out_scalar);
 void launch_dot(Ctx&, const float* x, const float* y, size_t n, double* partials, float* out_scalar);
@@ -292,17 +316,10 @@ void launch_cg_step(Ctx&, float* q, float* r, const float* d, const float* Hd, c
                     size_t n, double* partials, float* rs_new);
 // d = r + (rs_new / rs) d   (beta = 0 if rs == 0)
 void launch_cg_dir(Ctx&, float* d, const float* r, const float* rs, const float* rs_new, size_t n);
-// c_i = (lp_i - lm_i) / (2 eps)   (0 if eps == 0)
 void launch_adam(Ctx&, float* x, const float* g, float* m, float* v, float lr, float beta1, float beta2, float eps,
                  float bias1, float bias2, size_t n);
-void launch_fd_loss_diff(Ctx&, const float* lp, const float* lm, const float* eps_dev, int rows, float* c);
-void launch_l2_cost(Ctx&, const float* lam, const float* w, size_t n, double* partials, float* out_scalar);
-void launch_weighted_loss_sum(Ctx&, const float* s, const float* ell, int rows, const float* add_or_null, float* out);
-// eps_dev = eps_scale / sqrt(nrm2) (0 if nrm2 == 0);  out = w + sign * eps_dev * scale * v
-void launch_fd_eps(Ctx&, const float* nrm2, float eps_scale, float vscale, float* eps_dev);
-void launch_fd_perturb(Ctx&, const float* w, const float* v, const float* eps_dev, float sign, float* out, size_t n);
-void launch_fd_update(Ctx&, float* v, float* p, const float* Gp, const float* Gm, const float* eps_dev, float alpha, size_t n);
-void launch_mixed_l2_fd(Ctx&, const float* lam, const float* w, const float* p, float alpha, const float* eps_dev, float* out, size_t n);
+// sum_i s_i ell_i (+ the sum of n partial)
+void launch_weighted_loss_sum(Ctx&, const float* s, const float* ell, int rows, const float* partial, int n, float* out);
 void launch_label_noise(Ctx&, const int32_t* y, const uint32_t* words, const int32_t* alt,
                         unsigned long long threshold, int n, int32_t* y_out, uint8_t* mask);
 

@@ -581,7 +581,7 @@ __global__ __launch_bounds__(1024) void last_layer_grad_kernel(LastGradArgs a) {
 #pragma unroll
   for (int ss = 0; ss < S; ++ss) { dphi3[ss] = 0.f; e23[ss] = 0.f; }
   if (jb_ok) {
-    const T* wr = (const T*)a.Wn + (long long)(jb + row) * a.ldn + half * EPC;
+    const T* wr = (const T*)sd.Wn + (long long)(jb + row) * a.ldn + half * EPC;
 #pragma unroll
     for (int p = 0; p < CP / (2 * EPC); ++p) w3[p] = *(const u32x4*)(wr + p * 2 * EPC);
   }
@@ -604,7 +604,7 @@ __global__ __launch_bounds__(1024) void last_layer_grad_kernel(LastGradArgs a) {
     if (i < sd.B) {
       if (a.loss == BETTY_LOSS_SOFTMAX_CE) y2 = lab.y[i];
       else if (c < a.C) t2 = lab.target[(long long)i * a.C + c];
-      if (c < a.C && a.bias) bias2 = a.bias[c];
+      if (c < a.C && sd.bias) bias2 = sd.bias[c];
     }
   }
 
@@ -617,7 +617,7 @@ __global__ __launch_bounds__(1024) void last_layer_grad_kernel(LastGradArgs a) {
     const int pairs = a.n_in_p / (2 * EPC), per = (pairs + NW - 1) / NW;
     const int p_begin = ks * per, p_end = min(pairs, p_begin + per);
     const T* av = (const T*)sd.A + (long long)(i0 + row) * sd.lda + half * EPC;
-    const T* w = (const T*)a.Wt + (long long)row * a.ldt + half * EPC;
+    const T* w = (const T*)sd.Wt + (long long)row * a.ldt + half * EPC;
     for (int p0 = p_begin; p0 < p_end; p0 += U) {
       u32x4 a8[U], w8[U];
 #pragma unroll
@@ -753,15 +753,18 @@ void launch_loss_directional_rows(Ctx& ctx, int loss, const float* P, const floa
 
 // one block per hidden unit (and one for the output bias): fixed-order sums over the samples
 __global__ __launch_bounds__(256) void wnet_theta_vjp_kernel(const float* ell, const float* dsig,
-                                                             const float* cvec, const float* theta, int H,
-                                                             int rows, float inv_batch, float* out) {
+                                                             const float* cvec, const float* cminus, const float* eps,
+                                                             const float* theta, int H, int rows, float inv_batch,
+                                                             float* out) {
   __shared__ float red[4];
   const int j = blockIdx.x;
+  const float e = cminus ? eps[0] : 0.f;
+  auto ci = [&](int i) { return !cminus ? cvec[i] : e > 0.f ? (cvec[i] - cminus[i]) / (2.f * e) : 0.f; };
   float a1 = 0.f, a2 = 0.f, a3 = 0.f;
   if (j < H) {
     const float u1 = theta[j], b1 = theta[H + j], u2 = theta[2 * H + j];
     for (int i = threadIdx.x; i < rows; i += 256) {
-      const float ds = cvec[i] * dsig[i];
+      const float ds = ci(i) * dsig[i];
       const float pre = u1 * ell[i] + b1;
       const float on = pre > 0.f ? 1.f : 0.f;
       a1 += ds * u2 * on * ell[i];
@@ -773,16 +776,16 @@ __global__ __launch_bounds__(256) void wnet_theta_vjp_kernel(const float* ell, c
       out[j] = -inv_batch * a1; out[H + j] = -inv_batch * a2; out[2 * H + j] = -inv_batch * a3;
     }
   } else {
-    for (int i = threadIdx.x; i < rows; i += 256) a1 += cvec[i] * dsig[i];
+    for (int i = threadIdx.x; i < rows; i += 256) a1 += ci(i) * dsig[i];
     a1 = block_sum(a1, red);
     if (threadIdx.x == 0) out[3 * H] = -inv_batch * a1;
   }
 }
 
-void launch_wnet_theta_vjp(Ctx& ctx, const float* ell, const float* dsig, const float* c,
+void launch_wnet_theta_vjp(Ctx& ctx, const float* ell, const float* dsig, const float* c, const float* c_minus, const float* eps,
                            const float* theta, int hidden, int rows, float inv_batch, float* out) {
   Launch l(ctx, BETTY_K_WNET);
-  wnet_theta_vjp_kernel<<<hidden + 1, 256, 0, ctx.stream>>>(ell, dsig, c, theta, hidden, rows, inv_batch, out);
+  wnet_theta_vjp_kernel<<<hidden + 1, 256, 0, ctx.stream>>>(ell, dsig, c, c_minus, eps, theta, hidden, rows, inv_batch, out);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -808,14 +811,6 @@ void launch_fill_zero(Ctx& ctx, void* p, size_t bytes) {
   fill_zero_kernel<<<flat_grid(bytes / 16), 256, 0, ctx.stream>>>((uint4*)p, bytes / 16);
 }
 
-__global__ __launch_bounds__(256) void scale_copy_kernel(const float* src, float scale, float* dst, size_t n) {
-  FLAT_LOOP(i, n) dst[i] = scale * src[i];
-}
-void launch_scale_copy(Ctx& ctx, const float* src, float scale, float* dst, size_t n) {
-  Launch l(ctx, BETTY_K_VECTOR, 0, 8.0 * n);
-  scale_copy_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(src, scale, dst, n);
-}
-
 __global__ __launch_bounds__(256) void mixed_l2_kernel(const float* lam, const float* w, const float* p, float alpha, float* out, size_t n) {
   FLAT_LOOP(i, n) out[i] = -2.f * expf(lam[i]) * w[i] * (alpha * p[i]);
 }
@@ -832,14 +827,6 @@ void launch_mixed_prox(Ctx& ctx, const float* logrho, const float* p, float alph
   mixed_prox_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(logrho, p, alpha, out, n);
 }
 
-__global__ __launch_bounds__(256) void diff_kernel(const float* a, const float* b, float* out, size_t n) {
-  FLAT_LOOP(i, n) out[i] = a[i] - b[i];
-}
-void launch_diff(Ctx& ctx, const float* a, const float* b, float* out, size_t n) {
-  Launch l(ctx, BETTY_K_VECTOR, 0, 12.0 * n);
-  diff_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(a, b, out, n);
-}
-
 __global__ __launch_bounds__(256) void fill_value_kernel(float* p, float value, size_t n) {
   FLAT_LOOP(i, n) p[i] = value;
 }
@@ -852,7 +839,7 @@ void launch_fill_value(Ctx& ctx, float* p, float value, size_t n) {
 // two-stage deterministic reductions: per-block partials, then one block in fixed order
 constexpr int RED_BLOCKS = 1024;
 
-template <int MODE>   // 0: sum x^2   1: sum exp(lam) x^2   2: sum lam x  (lam = second vector)
+template <int MODE>   // 0: sum x^2   2: sum lam x  (lam = second vector)
 __global__ __launch_bounds__(256) void reduce_stage1_kernel(const float* lam, const float* x, size_t n, double* partials) {
   __shared__ double red[4];
   float acc = 0.f;
@@ -860,7 +847,7 @@ __global__ __launch_bounds__(256) void reduce_stage1_kernel(const float* lam, co
   int cnt = 0;
   FLAT_LOOP(i, n) {
     const float xi = x[i];
-    acc += MODE == 0 ? xi * xi : MODE == 1 ? expf(lam[i]) * xi * xi : lam[i] * xi;
+    acc += MODE == 0 ? xi * xi : lam[i] * xi;
     if (++cnt == 64) { dacc += acc; acc = 0.f; cnt = 0; }
   }
   dacc += acc;
@@ -882,7 +869,6 @@ static void launch_reduce(Ctx& ctx, int mode, const float* lam, const float* x, 
   {
     Launch l(ctx, BETTY_K_REDUCE, 0, (mode ? 8.0 : 4.0) * n);
     if (mode == 0) reduce_stage1_kernel<0><<<nb, 256, 0, ctx.stream>>>(lam, x, n, partials);
-    else if (mode == 1) reduce_stage1_kernel<1><<<nb, 256, 0, ctx.stream>>>(lam, x, n, partials);
     else reduce_stage1_kernel<2><<<nb, 256, 0, ctx.stream>>>(lam, x, n, partials);
   }
   {
@@ -892,9 +878,6 @@ static void launch_reduce(Ctx& ctx, int mode, const float* lam, const float* x, 
 }
 void launch_sumsq(Ctx& ctx, const float* x, size_t n, double* partials, float* out) {
   launch_reduce(ctx, 0, nullptr, x, n, partials, out);
-}
-void launch_l2_cost(Ctx& ctx, const float* lam, const float* w, size_t n, double* partials, float* out) {
-  launch_reduce(ctx, 1, lam, w, n, partials, out);
 }
 void launch_dot(Ctx& ctx, const float* x, const float* y, size_t n, double* partials, float* out) {
   launch_reduce(ctx, 2, y, x, n, partials, out);
@@ -970,81 +953,135 @@ void launch_adam(Ctx& ctx, float* x, const float* g, float* m, float* v, float l
   adam_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(x, g, m, v, lr, beta1, beta2, eps, bias1, bias2, n);
 }
 
-__global__ __launch_bounds__(256) void fd_loss_diff_kernel(const float* lp, const float* lm, const float* eps_dev, int rows, float* c) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= rows) return;
-  const float e = eps_dev[0];
-  c[i] = e > 0.f ? (lp[i] - lm[i]) / (2.f * e) : 0.f;
-}
-void launch_fd_loss_diff(Ctx& ctx, const float* lp, const float* lm, const float* eps_dev, int rows, float* c) {
-  if (rows <= 0) return;
-  Launch l(ctx, BETTY_K_OTHER);
-  fd_loss_diff_kernel<<<(rows + 255) / 256, 256, 0, ctx.stream>>>(lp, lm, eps_dev, rows, c);
-}
-
-__global__ __launch_bounds__(256) void weighted_loss_sum_kernel(const float* s, const float* ell, int rows, const float* add, float* out) {
-  __shared__ double red[4];
+// the sums that weight-gradient launches leave behind: one block, fixed order, in double
+__device__ __forceinline__ double sum_partials(const float* p, int n, double* red16) {
   double acc = 0.0;
-  for (int i = threadIdx.x; i < rows; i += 256) acc += (double)s[i] * (double)ell[i];
-  acc = block_sum(acc, red);
-  if (threadIdx.x == 0) out[0] = (float)(acc + (add ? (double)add[0] : 0.0));
+  const int n4 = n / 4;
+  for (int i = threadIdx.x; i < n4; i += 1024) {
+    const float4 x = ((const float4*)p)[i];
+    acc += ((double)x.x + (double)x.y) + ((double)x.z + (double)x.w);
+  }
+  if ((int)threadIdx.x < n - 4 * n4) acc += (double)p[4 * n4 + threadIdx.x];
+  acc = wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) red16[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  double t = 0.0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) t += red16[k];
+  return t;
 }
-void launch_weighted_loss_sum(Ctx& ctx, const float* s, const float* ell, int rows, const float* add, float* out) {
+
+__global__ __launch_bounds__(1024) void weighted_loss_sum_kernel(const float* s, const float* ell, int rows, const float* partial, int n, float* out) {
+  __shared__ double red[16], red2[16];
+  const double cost = sum_partials(partial, n, red2);
+  double acc = 0.0;
+  for (int i = threadIdx.x; i < rows; i += 1024) acc += (double)s[i] * (double)ell[i];
+  acc = wave_sum(acc);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  double t = 0.0;
+  for (int k = 0; k < 16; ++k) t += red[k];
+  out[0] = (float)(t + cost);
+}
+void launch_weighted_loss_sum(Ctx& ctx, const float* s, const float* ell, int rows, const float* partial, int n, float* out) {
   Launch l(ctx, BETTY_K_REDUCE);
-  weighted_loss_sum_kernel<<<1, 256, 0, ctx.stream>>>(s, ell, rows, add, out);
+  weighted_loss_sum_kernel<<<1, 1024, 0, ctx.stream>>>(s, ell, rows, partial, n, out);
 }
 
-__global__ void fd_eps_kernel(const float* nrm2, float eps_scale, float vscale, float* eps_dev) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    const float nrm = sqrtf(nrm2[0]) * fabsf(vscale);
-    eps_dev[0] = nrm > 0.f ? eps_scale / nrm : 0.f;
-  }
+__global__ __launch_bounds__(1024) void fd_eps_kernel(const float* partial, int n, float eps_scale, float scale, float* eps) {
+  __shared__ double red[16];
+  const float nrm = sqrtf((float)sum_partials(partial, n, red)) * fabsf(scale);
+  if (threadIdx.x == 0) eps[0] = nrm > 0.f ? eps_scale / nrm : 0.f;
 }
-void launch_fd_eps(Ctx& ctx, const float* nrm2, float eps_scale, float vscale, float* eps_dev) {
-  Launch l(ctx, BETTY_K_OTHER);
-  fd_eps_kernel<<<1, 64, 0, ctx.stream>>>(nrm2, eps_scale, vscale, eps_dev);
-}
-
-__global__ __launch_bounds__(256) void fd_perturb_kernel(const float* w, const float* v, const float* eps_dev, float sign, float* out, size_t n) {
-  const float e = sign * eps_dev[0];
-  FLAT_LOOP(i, n) out[i] = w[i] + e * v[i];
-}
-void launch_fd_perturb(Ctx& ctx, const float* w, const float* v, const float* eps_dev, float sign, float* out, size_t n) {
-  Launch l(ctx, BETTY_K_VECTOR, 0, 12.0 * n);
-  fd_perturb_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(w, v, eps_dev, sign, out, n);
+void launch_fd_eps(Ctx& ctx, const float* partial, int n, float eps_scale, float scale, float* eps) {
+  Launch l(ctx, BETTY_K_OTHER, 0, 4.0 * n);
+  fd_eps_kernel<<<1, 1024, 0, ctx.stream>>>(partial, n, eps_scale, scale, eps);
 }
 
-__global__ __launch_bounds__(256) void fd_update_kernel(float* v, float* p, const float* Gp, const float* Gm, const float* eps_dev, float alpha, size_t n) {
-  const float e = eps_dev[0];
-  const float k = e > 0.f ? alpha / (2.f * e) : 0.f;     // v = 0 has the zero product
-  FLAT_LOOP(i, n) {
-    const float vn = v[i] - k * (Gp[i] - Gm[i]);
-    v[i] = vn;
-    p[i] += vn;
-  }
-}
-void launch_fd_update(Ctx& ctx, float* v, float* p, const float* Gp, const float* Gm, const float* eps_dev, float alpha, size_t n) {
-  Launch l(ctx, BETTY_K_VECTOR, 0, 24.0 * n);
-  fd_update_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(v, p, Gp, Gm, eps_dev, alpha, n);
-}
-
-// central difference of grad_lambda (e^lam w^2) along q = alpha p, formed in fp64 registers so
-// that the subtraction of the two squares does not lose the signal
-__global__ __launch_bounds__(256) void mixed_l2_fd_kernel(const float* lam, const float* w, const float* p, float alpha, const float* eps_dev, float* out, size_t n) {
-  const double e = (double)eps_dev[0];
-  FLAT_LOOP(i, n) {
-    if (e > 0.0) {
-      const double q = (double)alpha * (double)p[i], wi = (double)w[i], el = exp((double)lam[i]);
-      const double up = wi + e * q, dn = wi - e * q;
-      out[i] = (float)(-(el * up * up - el * dn * dn) / (2.0 * e));
+// The two perturbed points of a central difference, straight into GEMM operands: w and v are read once,
+// 24 bytes a parameter against 48 for two passes of perturbation and conversion each.  64 x 64 tiles as in
+// convert_batch_kernel, all loads of a tile in flight together.
+__global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
+  __shared__ float tile[64][65];
+  int bid = blockIdx.x, ji = 0;
+  while (ji + 1 < b.n && bid >= b.block_begin[ji + 1]) ++ji;
+  const PerturbJob& j = b.j[ji];
+  bid -= b.block_begin[ji];
+  const int tiles_x = (j.cols + 63) / 64;
+  const int c0 = (bid % tiles_x) * 64, r0 = (bid / tiles_x) * 64;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
+  const bool quads = j.cols % 4 == 0 && ((uintptr_t)j.w & 15) == 0 && ((uintptr_t)j.v & 15) == 0;
+  float w[4][4], v[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const long long row = (long long)min(r0 + ty + 16 * i, j.rows - 1) * j.cols;
+    if (quads) {
+      const long long at = row + min(c0 + 4 * tx, j.cols - 4);
+      const float4 a = *(const float4*)(j.w + at), d = *(const float4*)(j.v + at);
+      w[i][0] = a.x; w[i][1] = a.y; w[i][2] = a.z; w[i][3] = a.w;
+      v[i][0] = d.x; v[i][1] = d.y; v[i][2] = d.z; v[i][3] = d.w;
     } else {
-      out[i] = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const long long at = row + min(c0 + 4 * tx + k, j.cols - 1);
+        w[i][k] = j.w[at]; v[i][k] = j.v[at];
+      }
+    }
+  }
+  const float eps = b.eps[0];
+  // biases ride along with the first row of tiles
+  if (j.b && r0 == 0 && threadIdx.x < 64 && c0 + (int)threadIdx.x < j.cols) {
+    const int c = c0 + threadIdx.x;
+    const float bw = j.b[c], bd = b.scale * j.bv[c];
+    if (b.signs & 1) j.bout[0][c] = bw + eps * bd;
+    if (b.signs & 2) j.bout[1][c] = bw - eps * bd;
+  }
+#pragma unroll
+  for (int sg = 0; sg < 2; ++sg) {
+    if (!(b.signs >> sg & 1)) continue;
+    const float e = sg ? -eps : eps;
+    if (sg && (b.signs & 1)) __syncthreads();       // the tile of the other sign is read out
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int rl = ty + 16 * i, r = r0 + rl, c = c0 + 4 * tx;
+      float x[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) { x[k] = w[i][k] + e * (b.scale * v[i][k]); tile[rl][4 * tx + k] = x[k]; }
+      if (r < j.rows) {
+        float* o = j.out[sg] + (long long)r * j.ld + c;      // (ld is a multiple of 128, out 256-byte aligned)
+        if (c + 3 < j.cols) *(float4*)o = make_float4(x[0], x[1], x[2], x[3]);
+        else
+#pragma unroll
+          for (int k = 0; k < 4; ++k) if (c + k < j.cols) o[k] = x[k];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int cl = ty + 16 * i, c = c0 + cl, r = r0 + 4 * tx;
+      if (c >= j.cols) continue;
+      float* o = j.outT[sg] + (long long)c * j.ldT + r;
+      const float x[4] = {tile[4 * tx][cl], tile[4 * tx + 1][cl], tile[4 * tx + 2][cl], tile[4 * tx + 3][cl]};
+      if (r + 3 < j.rows) *(float4*)o = make_float4(x[0], x[1], x[2], x[3]);
+      else
+#pragma unroll
+        for (int k = 0; k < 4; ++k) if (r + k < j.rows) o[k] = x[k];
     }
   }
 }
-void launch_mixed_l2_fd(Ctx& ctx, const float* lam, const float* w, const float* p, float alpha, const float* eps_dev, float* out, size_t n) {
-  Launch l(ctx, BETTY_K_VECTOR, 0, 16.0 * n);
-  mixed_l2_fd_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(lam, w, p, alpha, eps_dev, out, n);
+void launch_perturb(Ctx& ctx, PerturbBatch& b) {
+  int blocks = 0;
+  double params = 0;
+  for (int i = 0; i < b.n; ++i) {
+    b.block_begin[i] = blocks;
+    blocks += ((b.j[i].cols + 63) / 64) * ((b.j[i].rows + 63) / 64);
+    params += (double)b.j[i].rows * b.j[i].cols;
+  }
+  b.block_begin[b.n] = blocks;
+  if (blocks <= 0) return;
+  Launch l(ctx, BETTY_K_SHADOW, 0, (8.0 + 8.0 * ((b.signs & 1) + (b.signs >> 1))) * params);
+  perturb_kernel<<<blocks, 256, 0, ctx.stream>>>(b);
 }
 
 __global__ __launch_bounds__(256) void label_noise_kernel(const int32_t* y, const uint32_t* words, const int32_t* alt,
