@@ -311,7 +311,7 @@ void plan(betty_handle h) {
   if (h->desc.has_bias) { h->bias_pm[0] = pl.take(vb); h->bias_pm[1] = pl.take(vb); }
   size_t n_sums = 4096;      // one per finishing wavefront of at most 64-tiles (16-tiles: at most 1024 of them) and per bias
   for (const LayerInfo& li : h->layers) n_sums += 4 * (size_t)Extent::up(li.n_in, 64) * Extent::up(li.n_out, 64) + li.n_out + 4096;
-  h->sums = pl.take(n_sums * 4);
+  h->sums = pl.take(2 * n_sums * 4);       // (conjugate gradient keeps those of two launches)
   // the second perturbed point of a central difference: activations and deltas of its own, weights of its
   // own where both points go through the same launches
   plan_set(h, pl, h->fd_minus, ELEM_F32, false, h->fd_paired ? SET_TRAIN_ONLY : SET_ACTIVATIONS);
@@ -738,6 +738,7 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
     else if (k.mode == EPI_WGRAD_FD) per_param = 16.0 + (k.lam ? 4.0 : 0.0);
     else if (k.mode == EPI_WGRAD_FD_LAST) per_param = 16.0 + (k.x ? 4.0 : 0.0);
     else if (k.mode == EPI_WGRAD_INIT) per_param = k.p ? 8.0 : 4.0;
+    else if (k.mode == EPI_WGRAD_CG) per_param = k.lam ? 12.0 : 8.0;
     else if (k.lam) per_param = 12.0;
     if (k.copies) per_param += 4.0;
     const int cfg = plan_wgrad(h, os.elem, l0, rop, k.minus != nullptr, B), bt = gemm_cfg_tile(cfg);
@@ -1904,23 +1905,41 @@ betty_status betty_hypergrad_cg(betty_handle h, const float* w, const float* lam
     const bool l2 = h->desc.hp == BETTY_HP_L2_DECAY, rw = h->desc.hp == BETTY_HP_REWEIGHT_NET;
     const float* dl = diag_log(h, lambda);
     float* r = h->f(h->vec_g); float* d = h->f(h->vec_v); float* q = h->f(h->vec_p); float* Hd = h->f(h->vec_Hv);
-    float* sc = h->f(h->scalars);            // sc[0], sc[1]: r.r of the current / next iterate; sc[2]: d.Hd
+    float* sc = h->f(h->scalars);            // sc[0], sc[1]: r.r of the current / next iterate
     double* partials = h->at<double>(h->partials);
     make_weight_operands(h, os, w);
-    WgradSink g_out{EPI_WGRAD, r, nullptr, nullptr, nullptr, nullptr, 0.f, false};
-    upper_grad_seq(h, os, w, lambda, K > 0 || rw, g_out, nullptr);
-    launch_cg_init(h->ctx, r, d, q, h->d);
-    launch_sumsq(h->ctx, r, h->d, partials, sc);
+    int n_rs = 0;
+    WgradSink init{EPI_WGRAD_INIT, nullptr, nullptr, nullptr, r, d, 0.f, K > 0};
+    if (K > 0) init.sums = &n_rs;
+    upper_grad_seq(h, os, w, lambda, K > 0 || rw, init, nullptr);
+    if (K == 0) launch_fill_value(h->ctx, q, 0.f, h->d);
     for (int k = 0; k < K; ++k) {
       float* rs = sc + (k & 1);
       float* rs_new = sc + ((k + 1) & 1);
-      make_shadows(h, os, d, &os.Vn, &os.Vt);
-      WgradSink hd{EPI_WGRAD, Hd, dl, dl ? d : nullptr, nullptr, nullptr, 0.f, false};
+      const bool first = k == 0, last = k + 1 == K;
+      int n_sums = (n_rs + 3) & ~3;
+      const int begin = n_sums;
+      WgradSink hd{EPI_WGRAD_CG, Hd, dl, d, nullptr, nullptr, 0.f, false};
+      hd.sums = &n_sums;
       hvp_cached(h, os, d, hd);
-      launch_dot(h->ctx, d, Hd, h->d, partials, sc + 2);
-      launch_cg_step(h->ctx, q, r, d, Hd, rs, sc + 2, h->d, partials, rs_new);
-      if (k + 1 < K) launch_cg_dir(h->ctx, d, r, rs, rs_new, h->d);
+      CgStep c{q, r, d, Hd, h->d, h->f(h->sums) + begin, n_sums - begin, first ? h->f(h->sums) : nullptr, n_rs, rs, partials};
+      if (last && !rw) { c.lam = dl; c.w = l2 ? w : nullptr; c.out = dlambda; }
+      const int n_partial = launch_cg_step(h->ctx, c);
+      if (last) break;
+      for (int i0 = 0; i0 < h->L; i0 += MAX_PROBLEMS) {
+        CgDirBatch b;
+        b.n = std::min(MAX_PROBLEMS, h->L - i0);
+        b.partials = partials; b.n_partial = n_partial; b.rs = rs; b.rs_new = i0 == 0 ? rs_new : nullptr;
+        for (int i = 0; i < b.n; ++i) {
+          const LayerInfo& li = h->layers[i0 + i];
+          b.j[i] = CgDirJob{r + li.w_off, d + li.w_off, li.n_in, li.n_out, h->at<void>(os.Vn[i0 + i]), li.n_out_p,
+                            h->at<void>(os.Vt[i0 + i]), li.n_in_p, h->desc.has_bias ? r + li.b_off : nullptr,
+                            h->desc.has_bias ? d + li.b_off : nullptr};
+        }
+        launch_cg_dir(h->ctx, os.elem, b);
+      }
     }
+    if (K > 0 && !rw) return;
     if (l2) launch_mixed_l2(h->ctx, lambda, w, q, 1.f, dlambda, h->d);
     else if (rw) mixed_reweight_seq(h, os, lambda, q, 1.f, dlambda);
     else launch_mixed_prox(h->ctx, h->f(h->logrho), q, 1.f, dlambda, h->d);

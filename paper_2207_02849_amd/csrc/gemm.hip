@@ -132,6 +132,9 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
       R.a[k] = (ok && e.lam) ? e.lam[o] : 0.f;
       R.b[k] = (ok && e.lam) ? e.x[o] : 0.f;
       R.c[k] = (ok && e.lam && e.p) ? e.p[o] : 0.f;
+    } else if constexpr (MODE == EPI_WGRAD_CG) {
+      R.a[k] = ok ? e.x[o] : 0.f;
+      R.c[k] = (ok && e.lam) ? e.lam[o] : 0.f;
     } else if constexpr (MODE == EPI_WGRAD_NEUMANN) {
       R.a[k] = ok ? e.x[o] : 0.f;                         // s: the partial sum so far
       R.b[k] = ok ? e.v[o] : 0.f;                         // g: the vector the series is applied to
@@ -158,7 +161,7 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
 }
 
 // the sums of a launch (Epilogue::partial): one number per finishing wavefront
-template <int MODE> constexpr bool epi_sums() { return MODE == EPI_WGRAD || MODE == EPI_WGRAD_INIT || MODE == EPI_WGRAD_FD || MODE == EPI_WGRAD_SGD; }
+template <int MODE> constexpr bool epi_sums() { return MODE == EPI_WGRAD || MODE == EPI_WGRAD_INIT || MODE == EPI_WGRAD_FD || MODE == EPI_WGRAD_SGD || MODE == EPI_WGRAD_CG; }
 template <int MODE>
 __device__ __forceinline__ void epi_store_sum(const Epilogue& e, int wave, float sum) {
   if constexpr (epi_sums<MODE>()) {
@@ -282,6 +285,13 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
 #pragma unroll
       for (int k = 0; k < NR; ++k)
         if (ok[k]) e.C[of[k]] = acc[k];
+    }
+    return;
+  } else if constexpr (MODE == EPI_WGRAD_CG) {
+#pragma unroll
+    for (int k = 0; k < NR; ++k) {
+      const float hx = e.lam ? acc[k] + 2.f * expf(R.c[k]) * R.a[k] : acc[k];
+      if (ok[k]) { e.C[of[k]] = hx; sum += hx * R.a[k]; }
     }
     return;
   } else if constexpr (MODE == EPI_WGRAD_INIT) {       // v = acc (and p = acc if asked); operand copies
@@ -431,6 +441,12 @@ __device__ void bias_rows(const BiasJob& j, int row) {
       }
       j.C[row] = g;
       if (j.partial) j.partial[row] = sum;
+      break;
+    }
+    case EPI_WGRAD_CG: {
+      const float x = j.x[row], hx = j.lam ? acc + 2.f * expf(j.lam[row]) * x : acc;
+      j.C[row] = hx;
+      if (j.partial) j.partial[row] = hx * x;
       break;
     }
     case EPI_WGRAD_INIT:
@@ -853,7 +869,7 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
 
 // LAM: 0 = no diagonal term, 1 = with one, 2 = with one whose x is the distance to an anchor (mode WGRAD)
 template <int MODE, int LAM> constexpr int wg_narr() {
-  return MODE == EPI_WGRAD ? (LAM ? LAM + 1 : 0) : MODE == EPI_WGRAD_INIT ? 0 : MODE == EPI_WGRAD_NEUMANN ? (LAM ? 3 : 2)
+  return MODE == EPI_WGRAD ? (LAM ? LAM + 1 : 0) : MODE == EPI_WGRAD_CG ? LAM + 1 : MODE == EPI_WGRAD_INIT ? 0 : MODE == EPI_WGRAD_NEUMANN ? (LAM ? 3 : 2)
        : MODE == EPI_WGRAD_SGD ? (LAM ? 4 : 2) : MODE == EPI_WGRAD_SCALED ? 1 : 4;
 }
 template <int MODE, int LAM> constexpr int wg_nreg() { return wg_narr<MODE, LAM>() > 0 ? wg_narr<MODE, LAM>() : 1; }
@@ -935,7 +951,7 @@ __device__ __forceinline__ void wg_finish(const WgTile& w, int pass, int pr, int
   constexpr int NR = wg_nreg<MODE, LAM>();
   // A row's terms are added before the next row's are made: the compiler would keep all 64 of the
   // tile and spill (gradients with a diagonal term, 10.4M parameters: 88 against 41 us).
-  constexpr bool SUMS = MODE == EPI_WGRAD_INIT || (LAM && (MODE == EPI_WGRAD || MODE == EPI_WGRAD_SGD));
+  constexpr bool SUMS = MODE == EPI_WGRAD_INIT || MODE == EPI_WGRAD_CG || (LAM && (MODE == EPI_WGRAD || MODE == EPI_WGRAD_SGD));
   const int row0 = w.m0 + WG_PASS * pass + 4 * pr, col0 = w.n0 + 4 * pc;
   float acc[4][4], val[4][4], val2[4][4];
 #pragma unroll
@@ -960,6 +976,10 @@ __device__ __forceinline__ void wg_finish(const WgTile& w, int pass, int pr, int
           val[i][j] += 2.f * el * x;
           sum += ok ? el * x * x : 0.f;
         }
+      } else if constexpr (MODE == EPI_WGRAD_CG) {         // I0 = x, I1 = lam
+        val[i][j] = a;
+        if constexpr (LAM) val[i][j] += 2.f * expf(I1[i][j]) * I0[i][j];
+        sum += ok ? val[i][j] * I0[i][j] : 0.f;
       } else if constexpr (MODE == EPI_WGRAD_INIT) {
         val[i][j] = a;
         sum += ok ? a * a : 0.f;
@@ -987,7 +1007,7 @@ __device__ __forceinline__ void wg_finish(const WgTile& w, int pass, int pr, int
     }
     if constexpr (SUMS) asm volatile("" : "+v"(sum));
   }
-  if constexpr (MODE == EPI_WGRAD || MODE == EPI_WGRAD_NEUMANN_L2 || MODE == EPI_WGRAD_SCALED) {
+  if constexpr (MODE == EPI_WGRAD || MODE == EPI_WGRAD_CG || MODE == EPI_WGRAD_NEUMANN_L2 || MODE == EPI_WGRAD_SCALED) {
     store_patch<VEC>(w.C, w.ldc, row0, col0, w.M, w.N, val);
     return;
   } else if constexpr (MODE == EPI_WGRAD_SGD) {
@@ -1174,6 +1194,7 @@ __global__ __launch_bounds__(256, 2) void wgrad128_kernel(WgradBatch batch) {
     w.alpha = e.alpha; w.beta = e.beta; w.gamma = e.gamma;
     w.has_x = e.x != nullptr;
     if constexpr (MODE == EPI_WGRAD) { w.src[0] = e.lam; w.src[1] = e.x; w.src[2] = e.p; w.src[3] = e.lam; }
+    else if constexpr (MODE == EPI_WGRAD_CG) { w.src[0] = e.x; w.src[1] = e.lam; w.src[2] = w.src[3] = e.x; }
     else if constexpr (MODE == EPI_WGRAD_NEUMANN) { w.src[0] = e.x; w.src[1] = e.v; w.src[2] = e.lam; w.src[3] = e.x; }
     else if constexpr (MODE == EPI_WGRAD_NEUMANN_L2) { w.src[0] = e.p; w.src[1] = e.v; w.src[2] = e.lam; w.src[3] = e.x; }
     else if constexpr (MODE == EPI_WGRAD_SCALED) { w.src[0] = e.x; w.src[1] = w.src[2] = w.src[3] = e.x; }
@@ -1329,7 +1350,7 @@ static void launch_wgrad_mode(int mode, int total, hipStream_t st, const GemmBat
 #define BETTY_CASE_W(M_) case M_: launch_one<T, BT, WPG, KG, M_>(total, st, b, err); break;
     BETTY_CASE_W(EPI_WGRAD) BETTY_CASE_W(EPI_WGRAD_INIT) BETTY_CASE_W(EPI_WGRAD_NEUMANN)
     BETTY_CASE_W(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_W(EPI_WGRAD_SGD) BETTY_CASE_W(EPI_WGRAD_SCALED)
-    BETTY_CASE_W(EPI_WGRAD_FD) BETTY_CASE_W(EPI_WGRAD_FD_LAST)
+    BETTY_CASE_W(EPI_WGRAD_FD) BETTY_CASE_W(EPI_WGRAD_FD_LAST) BETTY_CASE_W(EPI_WGRAD_CG)
 #undef BETTY_CASE_W
     default: err = hipErrorInvalidValue; break;
   }
@@ -1358,7 +1379,7 @@ static void launch_wgrad128(int mode, int total, hipStream_t st, const GemmBatch
       else if (lam) launch_wgrad128_one<EPI_WGRAD, 1>(total, st, b, err);
       else launch_wgrad128_one<EPI_WGRAD, 0>(total, st, b, err);
       break;
-    BETTY_CASE_W(EPI_WGRAD_NEUMANN) BETTY_CASE_W(EPI_WGRAD_SGD)
+    BETTY_CASE_W(EPI_WGRAD_NEUMANN) BETTY_CASE_W(EPI_WGRAD_SGD) BETTY_CASE_W(EPI_WGRAD_CG)
 #undef BETTY_CASE_W
     case EPI_WGRAD_INIT: launch_wgrad128_one<EPI_WGRAD_INIT, 0>(total, st, b, err); break;
     case EPI_WGRAD_SCALED: launch_wgrad128_one<EPI_WGRAD_SCALED, 0>(total, st, b, err); break;
@@ -1404,7 +1425,7 @@ static void launch_small_mode(int mode, int total, hipStream_t st, const GemmBat
     BETTY_CASE_S(EPI_RFWD_LAST) BETTY_CASE_S(EPI_RBWD) BETTY_CASE_S(EPI_RFWD_LAST_HESS) BETTY_CASE_S(EPI_GRAM) BETTY_CASE_S(EPI_SAMPLE)
     BETTY_CASE_S(EPI_WGRAD) BETTY_CASE_S(EPI_WGRAD_INIT) BETTY_CASE_S(EPI_WGRAD_NEUMANN)
     BETTY_CASE_S(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_S(EPI_WGRAD_SGD) BETTY_CASE_S(EPI_WGRAD_SCALED)
-    BETTY_CASE_S(EPI_WGRAD_FD) BETTY_CASE_S(EPI_WGRAD_FD_LAST)
+    BETTY_CASE_S(EPI_WGRAD_FD) BETTY_CASE_S(EPI_WGRAD_FD_LAST) BETTY_CASE_S(EPI_WGRAD_CG)
 #undef BETTY_CASE_S
     default: err = hipErrorInvalidValue; break;
   }

@@ -71,6 +71,7 @@ enum EpiMode {
   // Hv = acc / (2 eps) (+ 2 exp(lam) v);  v <- v - alpha Hv;  p <- p + v.  _LAST: only the mixed VJP leaves,
   // C = -2 exp(lam) x (alpha p), or 2 exp(lam) (alpha p) without x
   EPI_WGRAD_FD, EPI_WGRAD_FD_LAST,
+  EPI_WGRAD_CG,          // C = acc (+ 2 exp(lam) x); the launch's sum is <x, C>
   EPI_WGRAD_SGD          // g = acc (+ 2 exp(lam) p) + gamma p; v <- beta v + g; p <- p - alpha v  (p = w, v = momentum)
 };
 
@@ -308,14 +309,21 @@ void launch_mixed_l2(Ctx&, const float* lam, const float* w, const float* p, flo
 // out = 2 exp(logrho) (alpha p): the mixed VJP of the proximal cost into its anchor
 void launch_mixed_prox(Ctx&, const float* logrho, const float* p, float alpha, float* out, size_t n);
 void launch_fill_value(Ctx&, float* p, float value, size_t n);
-void launch_sumsq(Ctx&, const float* x, size_t n, double* partials, float* out_scalar);
-void launch_dot(Ctx&, const float* x, const float* y, size_t n, double* partials, float* out_scalar);
-// conjugate gradient on device scalars: a = rs / dHd (0 if either is 0); q += a d; r -= a Hd; rs_new = r.r
-void launch_cg_init(Ctx&, const float* r, float* d, float* q, size_t n);
-void launch_cg_step(Ctx&, float* q, float* r, const float* d, const float* Hd, const float* rs, const float* dHd,
-                    size_t n, double* partials, float* rs_new);
-// d = r + (rs_new / rs) d   (beta = 0 if rs == 0)
-void launch_cg_dir(Ctx&, float* d, const float* r, const float* rs, const float* rs_new, size_t n);
+// Conjugate gradient, two launches a step beside the Hessian product Hd (scalars stay on the device):
+//  step  a = rs / <d, Hd> (0 if either is 0);  q += a d (q = a d in the first step);  r -= a Hd; leaves the partial
+//        sums of <r, r>.  In the first step rs is the sum of rs_partial and goes to *rs.  With `out`, the last
+//        step, only q and the mixed VJP leave: out = -2 exp(lam) w q, or 2 exp(lam) q without w
+//  dir   d = r + (rs_new / rs) d (d = r if rs is 0) with rs_new = the partial sums, also to *rs_new; d leaves as GEMM
+//        operands as well
+struct CgStep {
+  float* q; float* r; const float* d; const float* Hd; size_t n;
+  const float* dHd; int n_dHd; const float* rs_partial; int n_rs; float* rs; double* partials;
+  const float* lam; const float* w; float* out;
+};
+struct CgDirJob { const float* r; float* d; int rows, cols; void* out; int ld; void* outT; int ldT; const float* br; float* bd; };
+struct CgDirBatch { int n = 0; int block_begin[MAX_PROBLEMS + 1]; CgDirJob j[MAX_PROBLEMS]; const double* partials; int n_partial; const float* rs; float* rs_new; };
+int launch_cg_step(Ctx&, const CgStep&);       // returns the number of partial sums
+void launch_cg_dir(Ctx&, Elem, CgDirBatch&);
 void launch_adam(Ctx&, float* x, const float* g, float* m, float* v, float lr, float beta1, float beta2, float eps,
                  float bias1, float bias2, size_t n);
 // sum_i s_i ell_i (+ the sum of n partial)

@@ -836,105 +836,6 @@ void launch_fill_value(Ctx& ctx, float* p, float value, size_t n) {
   fill_value_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(p, value, n);
 }
 
-// two-stage deterministic reductions: per-block partials, then one block in fixed order
-constexpr int RED_BLOCKS = 1024;
-
-template <int MODE>   // 0: sum x^2   2: sum lam x  (lam = second vector)
-__global__ __launch_bounds__(256) void reduce_stage1_kernel(const float* lam, const float* x, size_t n, double* partials) {
-  __shared__ double red[4];
-  float acc = 0.f;
-  double dacc = 0.0;
-  int cnt = 0;
-  FLAT_LOOP(i, n) {
-    const float xi = x[i];
-    acc += MODE == 0 ? xi * xi : lam[i] * xi;
-    if (++cnt == 64) { dacc += acc; acc = 0.f; cnt = 0; }
-  }
-  dacc += acc;
-  dacc = block_sum(dacc, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = dacc;
-}
-
-__global__ __launch_bounds__(256) void reduce_stage2_kernel(const double* partials, int nb, float* out) {
-  __shared__ double red[4];
-  double acc = 0.0;
-  for (int i = threadIdx.x; i < nb; i += 256) acc += partials[i];
-  acc = block_sum(acc, red);
-  if (threadIdx.x == 0) out[0] = (float)acc;
-}
-
-static void launch_reduce(Ctx& ctx, int mode, const float* lam, const float* x, size_t n, double* partials, float* out) {
-  unsigned nb = flat_grid(n);
-  if (nb > RED_BLOCKS) nb = RED_BLOCKS;
-  {
-    Launch l(ctx, BETTY_K_REDUCE, 0, (mode ? 8.0 : 4.0) * n);
-    if (mode == 0) reduce_stage1_kernel<0><<<nb, 256, 0, ctx.stream>>>(lam, x, n, partials);
-    else reduce_stage1_kernel<2><<<nb, 256, 0, ctx.stream>>>(lam, x, n, partials);
-  }
-  {
-    Launch l(ctx, BETTY_K_REDUCE);
-    reduce_stage2_kernel<<<1, 256, 0, ctx.stream>>>(partials, (int)nb, out);
-  }
-}
-void launch_sumsq(Ctx& ctx, const float* x, size_t n, double* partials, float* out) {
-  launch_reduce(ctx, 0, nullptr, x, n, partials, out);
-}
-void launch_dot(Ctx& ctx, const float* x, const float* y, size_t n, double* partials, float* out) {
-  launch_reduce(ctx, 2, y, x, n, partials, out);
-}
-
-// ---- conjugate gradient (scalars stay on the device; nothing here reads them on the host)
-__global__ __launch_bounds__(256) void cg_init_kernel(const float* r, float* d, float* q, size_t n) {
-  FLAT_LOOP(i, n) { d[i] = r[i]; q[i] = 0.f; }
-}
-void launch_cg_init(Ctx& ctx, const float* r, float* d, float* q, size_t n) {
-  Launch l(ctx, BETTY_K_VECTOR, 0, 12.0 * n);
-  cg_init_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(r, d, q, n);
-}
-
-__global__ __launch_bounds__(256) void cg_step_kernel(float* q, float* r, const float* d, const float* Hd,
-                                                      const float* rs, const float* dHd, size_t n, double* partials) {
-  __shared__ double red[4];
-  const float num = rs[0], den = dHd[0];
-  const float a = (num != 0.f && den != 0.f) ? num / den : 0.f;
-  float acc = 0.f;
-  double dacc = 0.0;
-  int cnt = 0;
-  FLAT_LOOP(i, n) {
-    q[i] += a * d[i];
-    const float ri = r[i] - a * Hd[i];
-    r[i] = ri;
-    acc += ri * ri;
-    if (++cnt == 64) { dacc += acc; acc = 0.f; cnt = 0; }
-  }
-  dacc += acc;
-  dacc = block_sum(dacc, red);
-  if (threadIdx.x == 0) partials[blockIdx.x] = dacc;
-}
-void launch_cg_step(Ctx& ctx, float* q, float* r, const float* d, const float* Hd, const float* rs, const float* dHd,
-                    size_t n, double* partials, float* rs_new) {
-  unsigned nb = flat_grid(n);
-  if (nb > RED_BLOCKS) nb = RED_BLOCKS;
-  {
-    Launch l(ctx, BETTY_K_VECTOR, 0, 24.0 * n);
-    cg_step_kernel<<<nb, 256, 0, ctx.stream>>>(q, r, d, Hd, rs, dHd, n, partials);
-  }
-  {
-    Launch l(ctx, BETTY_K_REDUCE);
-    reduce_stage2_kernel<<<1, 256, 0, ctx.stream>>>(partials, (int)nb, rs_new);
-  }
-}
-
-__global__ __launch_bounds__(256) void cg_dir_kernel(float* d, const float* r, const float* rs, const float* rs_new, size_t n) {
-  const float den = rs[0];
-  const float beta = den != 0.f ? rs_new[0] / den : 0.f;
-  FLAT_LOOP(i, n) d[i] = r[i] + beta * d[i];
-}
-void launch_cg_dir(Ctx& ctx, float* d, const float* r, const float* rs, const float* rs_new, size_t n) {
-  Launch l(ctx, BETTY_K_VECTOR, 0, 12.0 * n);
-  cg_dir_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(d, r, rs, rs_new, n);
-}
-
 // Adam on the upper parameters: bias1 = 1 - beta1^t, bias2 = 1 - beta2^t are formed on the host
 __global__ __launch_bounds__(256) void adam_kernel(float* x, const float* g, float* m, float* v, float lr, float beta1,
                                                    float beta2, float eps, float bias1, float bias2, size_t n) {
@@ -953,27 +854,28 @@ void launch_adam(Ctx& ctx, float* x, const float* g, float* m, float* v, float l
   adam_kernel<<<flat_grid(n), 256, 0, ctx.stream>>>(x, g, m, v, lr, beta1, beta2, eps, bias1, bias2, n);
 }
 
-// the sums that weight-gradient launches leave behind: one block, fixed order, in double
-__device__ __forceinline__ double sum_partials(const float* p, int n, double* red16) {
+// the sums that weight-gradient launches leave behind (4-number aligned): one block, fixed order, in double
+template <int NT>
+__device__ __forceinline__ double sum_partials(const float* p, int n, double* red) {
   double acc = 0.0;
   const int n4 = n / 4;
-  for (int i = threadIdx.x; i < n4; i += 1024) {
+  for (int i = threadIdx.x; i < n4; i += NT) {
     const float4 x = ((const float4*)p)[i];
     acc += ((double)x.x + (double)x.y) + ((double)x.z + (double)x.w);
   }
   if ((int)threadIdx.x < n - 4 * n4) acc += (double)p[4 * n4 + threadIdx.x];
   acc = wave_sum(acc);
-  if ((threadIdx.x & 63) == 0) red16[threadIdx.x >> 6] = acc;
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
   __syncthreads();
   double t = 0.0;
 #pragma unroll
-  for (int k = 0; k < 16; ++k) t += red16[k];
+  for (int k = 0; k < NT / 64; ++k) t += red[k];
   return t;
 }
 
 __global__ __launch_bounds__(1024) void weighted_loss_sum_kernel(const float* s, const float* ell, int rows, const float* partial, int n, float* out) {
   __shared__ double red[16], red2[16];
-  const double cost = sum_partials(partial, n, red2);
+  const double cost = sum_partials<1024>(partial, n, red2);
   double acc = 0.0;
   for (int i = threadIdx.x; i < rows; i += 1024) acc += (double)s[i] * (double)ell[i];
   acc = wave_sum(acc);
@@ -991,12 +893,145 @@ void launch_weighted_loss_sum(Ctx& ctx, const float* s, const float* ell, int ro
 
 __global__ __launch_bounds__(1024) void fd_eps_kernel(const float* partial, int n, float eps_scale, float scale, float* eps) {
   __shared__ double red[16];
-  const float nrm = sqrtf((float)sum_partials(partial, n, red)) * fabsf(scale);
+  const float nrm = sqrtf((float)sum_partials<1024>(partial, n, red)) * fabsf(scale);
   if (threadIdx.x == 0) eps[0] = nrm > 0.f ? eps_scale / nrm : 0.f;
 }
 void launch_fd_eps(Ctx& ctx, const float* partial, int n, float eps_scale, float scale, float* eps) {
   Launch l(ctx, BETTY_K_OTHER, 0, 4.0 * n);
   fd_eps_kernel<<<1, 1024, 0, ctx.stream>>>(partial, n, eps_scale, scale, eps);
+}
+
+// ---- conjugate gradient (scalars stay on the device; nothing here reads them on the host)
+//
+// Bound by the launches for small problems: every block adds up the partial sums of the launch before
+// it again, in the same order (a few KB out of L2), instead of a launch between that leaves one number, and the
+// new direction leaves as GEMM operands.  Two launches a step where there were six (784 x 10 parameters: 28 -> 19
+// us a step with the Hessian product).
+constexpr int CG_BLOCKS = 1024;
+
+__global__ __launch_bounds__(256) void cg_step_kernel(CgStep c) {
+  __shared__ double red[4], red2[4];
+  const float den = (float)sum_partials<256>(c.dHd, c.n_dHd, red);
+  float num;
+  if (c.rs_partial) {
+    num = (float)sum_partials<256>(c.rs_partial, c.n_rs, red2);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *c.rs = num;
+  } else {
+    num = *c.rs;
+  }
+  const float a = (num != 0.f && den != 0.f) ? num / den : 0.f;
+  if (c.out) {
+    FLAT_LOOP(i, c.n) {
+      const float qi = (c.rs_partial ? 0.f : c.q[i]) + a * c.d[i], el = 2.f * expf(c.lam[i]);
+      c.out[i] = c.w ? -el * c.w[i] * qi : el * qi;
+    }
+    return;
+  }
+  float acc = 0.f;
+  double dacc = 0.0;
+  int cnt = 0;
+  FLAT_LOOP(i, c.n) {
+    c.q[i] = (c.rs_partial ? 0.f : c.q[i]) + a * c.d[i];
+    const float ri = c.r[i] - a * c.Hd[i];
+    c.r[i] = ri;
+    acc += ri * ri;
+    if (++cnt == 64) { dacc += acc; acc = 0.f; cnt = 0; }
+  }
+  dacc += acc;
+  dacc = block_sum(dacc, red);
+  if (threadIdx.x == 0) c.partials[blockIdx.x] = dacc;
+}
+int launch_cg_step(Ctx& ctx, const CgStep& c) {
+  const unsigned nb = std::min<unsigned>(flat_grid(c.n), CG_BLOCKS);
+  Launch l(ctx, BETTY_K_VECTOR, 0, 24.0 * c.n);
+  cg_step_kernel<<<nb, 256, 0, ctx.stream>>>(c);
+  return (int)nb;
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void cg_dir_kernel(CgDirBatch b) {
+  __shared__ float tile[64][65];
+  __shared__ double red[4];
+  int bid = blockIdx.x, ji = 0;
+  while (ji + 1 < b.n && bid >= b.block_begin[ji + 1]) ++ji;
+  const CgDirJob& j = b.j[ji];
+  bid -= b.block_begin[ji];
+  const int tiles_x = (j.cols + 63) / 64;
+  const int c0 = (bid % tiles_x) * 64, r0 = (bid / tiles_x) * 64;
+  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4, c = c0 + 4 * tx;
+  const bool quads = j.cols % 4 == 0 && ((uintptr_t)j.r & 15) == 0 && ((uintptr_t)j.d & 15) == 0;
+  float r[4][4], d[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const long long row = (long long)min(r0 + ty + 16 * i, j.rows - 1) * j.cols;
+    if (quads) {
+      const long long at = row + min(c, j.cols - 4);
+      const float4 x = *(const float4*)(j.r + at), y = *(const float4*)(j.d + at);
+      r[i][0] = x.x; r[i][1] = x.y; r[i][2] = x.z; r[i][3] = x.w;
+      d[i][0] = y.x; d[i][1] = y.y; d[i][2] = y.z; d[i][3] = y.w;
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const long long at = row + min(c + k, j.cols - 1);
+        r[i][k] = j.r[at]; d[i][k] = j.d[at];
+      }
+    }
+  }
+  const float rs = *b.rs;
+  double acc = 0.0;
+  for (int i = threadIdx.x; i < b.n_partial; i += 256) acc += b.partials[i];
+  const float rs_new = (float)block_sum(acc, red), beta = rs != 0.f ? rs_new / rs : 0.f;
+  if (blockIdx.x == 0 && ji == 0 && threadIdx.x == 0 && b.rs_new) *b.rs_new = rs_new;
+  if (j.bd && r0 == 0 && threadIdx.x < 64 && c0 + (int)threadIdx.x < j.cols) {     // biases: with the first row of tiles
+    const int cb = c0 + threadIdx.x;
+    j.bd[cb] = j.br[cb] + beta * j.bd[cb];
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int rl = ty + 16 * i, row = r0 + rl;
+    float x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) { x[k] = r[i][k] + beta * d[i][k]; tile[rl][4 * tx + k] = x[k]; }
+    if (row >= j.rows) continue;
+    float* o = j.d + (long long)row * j.cols + c;
+    T* p = (T*)j.out + (long long)row * j.ld + c;              // (operands: pitch a multiple of 128, 256-byte aligned)
+    if (c + 3 < j.cols) {
+      if (quads) *(float4*)o = make_float4(x[0], x[1], x[2], x[3]);
+      else
+#pragma unroll
+        for (int k = 0; k < 4; ++k) o[k] = x[k];
+      store_quad<T>(p, x[0], x[1], x[2], x[3]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) if (c + k < j.cols) { o[k] = x[k]; p[k] = from_float<T>(x[k]); }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int cl = ty + 16 * i, cc = c0 + cl, row = r0 + 4 * tx;
+    if (cc >= j.cols || row >= j.rows) continue;
+    T* o = (T*)j.outT + (long long)cc * j.ldT + row;
+    const float x[4] = {tile[4 * tx][cl], tile[4 * tx + 1][cl], tile[4 * tx + 2][cl], tile[4 * tx + 3][cl]};
+    if (row + 3 < j.rows) store_quad<T>(o, x[0], x[1], x[2], x[3]);
+    else
+#pragma unroll
+      for (int k = 0; k < 4; ++k) if (row + k < j.rows) o[k] = from_float<T>(x[k]);
+  }
+}
+void launch_cg_dir(Ctx& ctx, Elem elem, CgDirBatch& b) {
+  int blocks = 0;
+  double params = 0;
+  for (int i = 0; i < b.n; ++i) {
+    b.block_begin[i] = blocks;
+    blocks += ((b.j[i].cols + 63) / 64) * ((b.j[i].rows + 63) / 64);
+    params += (double)b.j[i].rows * b.j[i].cols;
+  }
+  b.block_begin[b.n] = blocks;
+  if (blocks <= 0) return;
+  Launch l(ctx, BETTY_K_VECTOR, 0, (12.0 + 2.0 * elem_size(elem)) * params);
+  if (elem == ELEM_BF16) cg_dir_kernel<__bf16><<<blocks, 256, 0, ctx.stream>>>(b);
+  else cg_dir_kernel<float><<<blocks, 256, 0, ctx.stream>>>(b);
 }
 
 // The two perturbed points of a central difference, straight into GEMM operands: w and v are read once,

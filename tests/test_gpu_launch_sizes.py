@@ -104,3 +104,22 @@ def test_series_in_sample_space(kind, dims, batch, act, prec, tol, monkeypatch):
         b.close()
     for K in (0, 1, 4):
         assert err[1, K] < max(tol, 1.5 * err[0, K]), (K, err)
+
+
+@pytest.mark.parametrize("kind,dims,batch", [
+    ("l2", (65, 3), 40),                     # widths that allow no 16-byte accesses, a second tile of one row
+    ("l2", (64, 64), 100),                   # exactly one tile
+    ("l2", (130, 68), 300),
+    ("proximal", (70, 67), 90),
+    ("reweight", (33, 10), 65),
+])
+def test_conjugate_gradient_steps(kind, dims, batch):
+    """K = 0 (no step), 1 (the first is the last), 2 and 4 steps of the fused vector updates."""
+    wl = wk.tiny(kind=kind, act="none", dims=dims, batch=batch, hidden=20, prox_rho=0.3)
+    prob = oracle_problem(wl)
+    b = binding.from_workload(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    for K in (0, 1, 2, 4):
+        got, ref = host(b.betty_hypergrad_cg(w, lam, K)), orc.hypergrad_cg(prob, wl.w, wl.lam, K)
+        assert np.abs(got).max() == 0 if K == 0 else rel_l2(got, ref) < 1e-4, K
+    b.close()
