@@ -127,7 +127,8 @@ betty_status betty_bind(betty_handle h, void* workspace, size_t bytes, void* hip
 /* Makes the following calls run on this stream instead of the bound one, behind everything the handle has
  * enqueued so far (NULL = the default stream).  A handle that works for callers on several streams is
  * moved to the caller's stream before each call; as long as that does not change this costs nothing.
- * Graphs that the handle has recorded stay valid.  No effect on an unbound handle. */
+ * Graphs that the handle has recorded stay valid.  The stream of the handle's last call must still exist
+ * when it is moved.  No effect on an unbound handle. */
 betty_status betty_run_on(betty_handle h, void* hip_stream);
 
 /* Registers the train (lower) and validation (upper) batches and enqueues the conversion
@@ -215,7 +216,8 @@ betty_status betty_best_response_neumann(betty_handle h, const float* w, const f
  * Both handles must describe the same number of parameters and be bound to the same stream.
  * w, v: d floats; theta, dtheta: betty_num_hyper(h_pretrain) floats; all device pointers.
  * Errors are reported on h_pretrain (betty_last_error).  A call repeated with identical arguments
- * replays one captured graph over both handles; binding either handle discards it.  Per-launch timing must be off on h_finetune. */
+ * replays one captured graph over both handles; binding either handle discards it.  Per-launch
+ * timing must be off on h_finetune. */
 betty_status betty_hypergrad_chain3(betty_handle h_pretrain, betty_handle h_finetune, const float* w,
                                     const float* theta, const float* v, int K_pretrain,
                                     float alpha_pretrain, int K_finetune, float alpha_finetune,

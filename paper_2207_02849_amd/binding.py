@@ -150,7 +150,8 @@ class Betty:
         # Without an explicit stream the handle follows the caller: every call runs on the torch stream
         # that is current at the time, behind the handle's earlier calls (waiting for another stream
         # costs tens of microseconds a call, so none is involved as long as the current stream stays the
-        # same).  It also has a stream of its own (default priority); whoever asks for it through
+        # same; a stream that a call ran on must outlive the handle's next call on another one).  It also
+        # has a stream of its own (default priority); whoever asks for it through
         # `stream` finds it ordered behind the calls made so far.
         # With an explicit stream the calls run on that stream, ordered with events against the caller's
         # current torch stream, before and after, where the two differ.

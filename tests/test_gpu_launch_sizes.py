@@ -123,3 +123,26 @@ def test_conjugate_gradient_steps(kind, dims, batch):
         got, ref = host(b.betty_hypergrad_cg(w, lam, K)), orc.hypergrad_cg(prob, wl.w, wl.lam, K)
         assert np.abs(got).max() == 0 if K == 0 else rel_l2(got, ref) < 1e-4, K
     b.close()
+
+
+@pytest.mark.parametrize("paired", (0, 1))
+@pytest.mark.parametrize("kind,dims,batch", [
+    ("l2", (65, 3), 40),                     # one layer; rows that allow no 16-byte accesses, a second tile of one row
+    ("l2", (64, 64, 20), 64),                # exactly one tile
+    ("l2", (70, 130, 68, 9), 129),           # ragged tiles, batch one past two 64-groups
+    ("proximal", (33, 66, 10), 31),
+    ("reweight", (33, 66, 10), 65),
+])
+def test_finite_difference_forms(kind, dims, batch, paired, monkeypatch):
+    """Both points of a central difference in shared launches, and one after the other."""
+    wl = wk.tiny(kind=kind, act="gelu" if len(dims) > 2 else "none", dims=dims, batch=batch, hidden=20, prox_rho=0.3)
+    prob = oracle_problem(wl)
+    monkeypatch.setenv("BETTY_TUNE", f"fd2={paired}")
+    b = binding.from_workload(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    for K in (0, 1, 3):
+        # the fp32 gradients' rounding (2^-24) over 2 eps |v| = 0.02, times alpha: some 1e-6; reweighting ends in a
+        # difference of losses of order 1 by 0.02 <grad l, q/|q|>: 2^-23 / 0.02 over a projection of some 0.1, 1e-4
+        assert rel_l2(host(b.betty_hypergrad_fd(w, lam, K, 0.05, 0.01)),
+                      orc.hypergrad_fd(prob, wl.w, wl.lam, K, 0.05, 0.01)) < (1e-3 if kind == "reweight" else 1e-4), K
+    b.close()
