@@ -1798,12 +1798,14 @@ betty_status betty_hypergrad_chain3(betty_handle hp, betty_handle hf, const floa
 }
 
 // The two points w +- eps q, q = scale v, as operands: both at once, or the one of `signs` (1 = plus, 2 = minus).
-static void make_perturbed_operands(betty_handle h, const float* w, const float* v, const float* eps, float scale, int signs) {
+static void make_perturbed_operands(betty_handle h, const float* w, const float* v, float* eps, float scale, int signs,
+                                    int sums, float eps_scale) {
   OperandSet* os[2] = {&fd_operands(h), &h->fd_minus};
   for (int i0 = 0; i0 < h->L; i0 += MAX_PROBLEMS) {
     PerturbBatch b;
     b.n = std::min(MAX_PROBLEMS, h->L - i0);
-    b.eps = eps; b.scale = scale; b.signs = signs;
+    b.eps = sums ? nullptr : eps; b.scale = scale; b.signs = signs;
+    b.partial = h->f(h->sums); b.n_partial = sums; b.eps_scale = eps_scale; b.eps_out = eps;
     for (int k = 0; k < b.n; ++k) {
       const LayerInfo& li = h->layers[i0 + k];
       PerturbJob& j = b.j[k];
@@ -1853,14 +1855,18 @@ static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, f
   for (Pass& q : ps) q.omega_fixed = omega_bar;
   ps[1].sign = -1.f;
   auto both = [&](const float* dir, float scale, auto passes) {
-    launch_fd_eps(h->ctx, h->f(h->sums), sums, eps_scale, scale, eps);
+    // Up to 4096 partial sums (16 KB, at most four rounds of loads a thread beside those of the tile) every block of
+    // the perturbation adds them up itself; beyond that a launch of one block forms the step (4.6 us
+    // with 5.3M parameters).  Reweighting step 1023-509-251-10 with one difference: 145.3 -> 143.7 us.
+    const int in_block = sums <= 4096 ? sums : 0;
+    if (!in_block) launch_fd_eps(h->ctx, h->f(h->sums), sums, eps_scale, scale, eps);
     h->as_pair = true;
     if (h->fd_paired) {
-      make_perturbed_operands(h, w, dir, eps, scale, 3);
+      make_perturbed_operands(h, w, dir, eps, scale, 3, in_block, eps_scale);
       passes(ps, 2);
     } else {
       for (int s = 0; s < 2; ++s) {
-        make_perturbed_operands(h, w, dir, eps, scale, 1 << s);
+        make_perturbed_operands(h, w, dir, eps, scale, 1 << s, in_block, eps_scale);
         passes(ps + s, 1);
       }
     }

@@ -215,7 +215,8 @@ struct PerturbJob {
   float* out[2]; int ld; float* outT[2]; int ldT;
   const float* b; const float* bv; float* bout[2];       // bias slices (cols entries), or null
 };
-struct PerturbBatch { int n = 0; int block_begin[MAX_PROBLEMS + 1]; PerturbJob j[MAX_PROBLEMS]; const float* eps; float scale; int signs; };
+struct PerturbBatch { int n = 0; int block_begin[MAX_PROBLEMS + 1]; PerturbJob j[MAX_PROBLEMS]; const float* eps; float scale; int signs;
+  const float* partial; int n_partial; float eps_scale; float* eps_out; };   // eps null: every block forms it from the partial sums
 void launch_perturb(Ctx&, PerturbBatch&);
 // *eps = eps_scale / (|scale| sqrt(sum of n partial)), 0 if that sum is 0
 void launch_fd_eps(Ctx&, const float* partial, int n, float eps_scale, float scale, float* eps);

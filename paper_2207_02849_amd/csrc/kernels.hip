@@ -891,10 +891,14 @@ void launch_weighted_loss_sum(Ctx& ctx, const float* s, const float* ell, int ro
   weighted_loss_sum_kernel<<<1, 1024, 0, ctx.stream>>>(s, ell, rows, partial, n, out);
 }
 
+__device__ __forceinline__ float fd_step(double sumsq, float eps_scale, float scale) {
+  const float nrm = sqrtf((float)sumsq) * fabsf(scale);
+  return nrm > 0.f ? eps_scale / nrm : 0.f;
+}
 __global__ __launch_bounds__(1024) void fd_eps_kernel(const float* partial, int n, float eps_scale, float scale, float* eps) {
   __shared__ double red[16];
-  const float nrm = sqrtf((float)sum_partials<1024>(partial, n, red)) * fabsf(scale);
-  if (threadIdx.x == 0) eps[0] = nrm > 0.f ? eps_scale / nrm : 0.f;
+  const double s = sum_partials<1024>(partial, n, red);
+  if (threadIdx.x == 0) eps[0] = fd_step(s, eps_scale, scale);
 }
 void launch_fd_eps(Ctx& ctx, const float* partial, int n, float eps_scale, float scale, float* eps) {
   Launch l(ctx, BETTY_K_OTHER, 0, 4.0 * n);
@@ -1036,9 +1040,13 @@ void launch_cg_dir(Ctx& ctx, Elem elem, CgDirBatch& b) {
 
 // The two perturbed points of a central difference, straight into GEMM operands: w and v are read once,
 // 24 bytes a parameter against 48 for two passes of perturbation and conversion each.  64 x 64 tiles as in
-// convert_batch_kernel, all loads of a tile in flight together.
+// convert_batch_kernel, all loads of a tile in flight together.  EPS: the step comes out of the partial sums
+// of |v|^2 in every block, in the same order, beside the loads of the tile, instead of a launch between
+// (see fd_seq).
+template <bool EPS>
 __global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
   __shared__ float tile[64][65];
+  __shared__ double red[4];
   int bid = blockIdx.x, ji = 0;
   while (ji + 1 < b.n && bid >= b.block_begin[ji + 1]) ++ji;
   const PerturbJob& j = b.j[ji];
@@ -1064,7 +1072,13 @@ __global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
       }
     }
   }
-  const float eps = b.eps[0];
+  float eps;
+  if constexpr (EPS) {
+    eps = fd_step(sum_partials<256>(b.partial, b.n_partial, red), b.eps_scale, b.scale);
+    if (blockIdx.x == 0 && threadIdx.x == 0) b.eps_out[0] = eps;
+  } else {
+    eps = b.eps[0];
+  }
   // biases ride along with the first row of tiles
   if (j.b && r0 == 0 && threadIdx.x < 64 && c0 + (int)threadIdx.x < j.cols) {
     const int c = c0 + threadIdx.x;
@@ -1116,7 +1130,8 @@ void launch_perturb(Ctx& ctx, PerturbBatch& b) {
   b.block_begin[b.n] = blocks;
   if (blocks <= 0) return;
   Launch l(ctx, BETTY_K_SHADOW, 0, (8.0 + 8.0 * ((b.signs & 1) + (b.signs >> 1))) * params);
-  perturb_kernel<<<blocks, 256, 0, ctx.stream>>>(b);
+  if (b.eps) perturb_kernel<false><<<blocks, 256, 0, ctx.stream>>>(b);
+  else perturb_kernel<true><<<blocks, 256, 0, ctx.stream>>>(b);
 }
 
 __global__ __launch_bounds__(256) void label_noise_kernel(const int32_t* y, const uint32_t* words, const int32_t* alt,
