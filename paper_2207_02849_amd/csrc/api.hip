@@ -1856,8 +1856,8 @@ static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, f
   ps[1].sign = -1.f;
   auto both = [&](const float* dir, float scale, auto passes) {
     // Up to 4096 partial sums (16 KB, at most four rounds of loads a thread beside those of the tile) every block of
-    // the perturbation adds them up itself; beyond that a launch of one block forms the step (4.6 us
-    // with 5.3M parameters).  Reweighting step 1023-509-251-10 with one difference: 145.3 -> 143.7 us.
+    // the perturbation adds them up itself; beyond that a launch of one block forms the step: with
+    // 5.3M parameters and 5 differences both take the same time (1282 and 1281 us).  Reweighting step 1023-509-251-10 with one difference: 145.3 -> 143.7 us.
     const int in_block = sums <= 4096 ? sums : 0;
     if (!in_block) launch_fd_eps(h->ctx, h->f(h->sums), sums, eps_scale, scale, eps);
     h->as_pair = true;
