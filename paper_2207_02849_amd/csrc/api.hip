@@ -96,6 +96,7 @@ struct betty_handle_s {
   size_t partials = 0, scalars = 0;
   size_t sums = 0;           // what the weight-gradient launches sum up beside their results (Epilogue::partial)
   size_t labels = 0;         // Labels[2]: train, validation
+  size_t lin_gram = 0;       // (linear.hip)
   size_t logrho = 0;         // proximal cost: log(rho_j) per parameter (a large negative value where rho_j = 0)
   // A hypergradient call repeated with the same arguments is replayed from a captured HIP graph.  Each kind of call
   // keeps the graphs of its last few argument sets: results that a caller lets the allocator place
@@ -157,6 +158,7 @@ struct betty_handle_s {
   // 1024-512-512-10 36.9 / 35.6, 2048-2048-2048-1000 at 512 181 / 173, 777-301-65-33 at 130 48.3 / 35.3.
   bool fixed_grouping = false;
   bool as_pair = false;                       // choose kernels for single passes as if two shared the launch
+  int tune_linear = -1;                       // one-workgroup kernel for single-layer models: 0 never, 1 wherever it fits, -1 by size
   int tune_samples = -1;                      // sample-space series: 0 never, 1 wherever it exists, -1 by size
   // Finite differences: the passes at w + eps v and w - eps v share their launches, with weight operands
   // for both points; above 32M parameters, where either alone fills the chip, they follow each other on one
@@ -374,6 +376,19 @@ void plan_samples(betty_handle h, Planner& pl, OperandSet& os) {
   }
 }
 
+// Single-layer models with a decay per parameter and fp32 operands that fit one workgroup (linear.hip): a step
+// there takes longer with every output, a launch hardly.  Ridge 64 - 1, batch 512, K = 20: 163 us by launches, 19 us;
+// softmax 200 - 4, batch 128, K = 5: 52 / 38 us (conjugate gradient 84 / 50); 32 - 16, batch 256, K = 5: 52 / 62 us (conjugate
+// gradient, twice the launches: 83 / 70).  (110 problems with 2 to 16 outputs: even at 13 to 16 outputs for the series
+// of a softmax model, half the time or less up to 5.)
+bool use_linear(betty_handle h, bool cg) {
+  const LayerInfo& li = h->layers[0];
+  if (h->L != 1 || h->desc.hp != BETTY_HP_L2_DECAY || h->desc.prec != BETTY_PREC_FP32 || h->tune_linear == 0) return false;
+  const bool mse = h->desc.loss == BETTY_LOSS_MSE;
+  return linear_fits(li.n_in + (h->desc.has_bias ? 1 : 0), li.n_out, h->desc.batch_train, h->desc.batch_val, mse, cg) &&
+         (h->tune_linear == 1 || li.n_out <= (mse || cg ? 16 : 12));
+}
+
 OperandSet& fd_operands(betty_handle h) { return h->sets[1].present ? h->sets[1] : h->sets[0]; }
 
 void plan(betty_handle h) {
@@ -399,6 +414,8 @@ void plan(betty_handle h) {
   for (const LayerInfo& li : h->layers) n_sums += 4 * (size_t)Extent::up(li.n_in, 64) * Extent::up(li.n_out, 64) + li.n_out + 4096;
   h->sums = pl.take(2 * n_sums * sizeof(double));      // (conjugate gradient keeps those of two launches)
   if (plans_samples(h)) plan_samples(h, pl, h->sets[0]);
+  if (h->desc.loss == BETTY_LOSS_MSE && use_linear(h, false))
+    h->lin_gram = pl.take(linear_gram_bytes(h->layers[0].n_in + (h->desc.has_bias ? 1 : 0)));
   h->ws_need = pl.off;
 }
 
@@ -1497,6 +1514,20 @@ void neumann_samples_seq(betty_handle h, const float* w, const float* lambda, co
   wgrad_batch(h, os, 0, true, fin);
 }
 
+void linear_seq(betty_handle h, const float* w, const float* lambda, int K, float alpha, float* out, bool cg) {
+  const LayerInfo& li = h->layers[0];
+  LinearArgs a{};
+  for (int s = 0; s < 2; ++s) {
+    const SideBuf& sb = h->sets[0].side[s];
+    a.X[s] = h->f(sb.X); a.XT[s] = h->f(sb.XT); a.ldxt[s] = sb.Bp; a.B[s] = sb.B;
+  }
+  a.ldx = li.n_in_p; a.n_in = li.n_in; a.C = li.n_out; a.bias = h->desc.has_bias ? 1 : 0;
+  a.labels = h->at<Labels>(h->labels); a.loss = h->desc.loss;
+  a.K = K; a.alpha = alpha; a.w = w; a.lam = lambda; a.out = out;
+  if (h->desc.loss == BETTY_LOSS_MSE && !cg) a.G = h->f(h->lin_gram);
+  launch_linear_hypergrad(h->ctx, a, cg);
+}
+
 // out = (dw* / dlambda) u by the K-step Neumann series and the mixed VJP; u = grad_w L_U(w) on the
 // validation batch when u_or_null is null.  Only enqueues launches on the handle's stream.
 // The partial sum is carried in nested form, s <- g + (I - alpha H) s from s = g: after K steps
@@ -1609,7 +1640,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
   h->use_pipeline = large && desc->prec == BETTY_PREC_FP32;
   h->fd_paired = !large;
   h->max_Bp = std::max(padup(desc->batch_train), padup(desc->batch_val));
-  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>" (see plan_chain)
+  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>,linear=<0|1>" (see plan_chain)
   if (const char* t = getenv("BETTY_TUNE")) {
     int v;
     if (const char* q = strstr(t, "wgrad=")) if (sscanf(q + 6, "%d", &v) == 1 && (v == GEMM_128x1 || v == GEMM_64x1)) h->tune_wgrad_cfg = v;
@@ -1620,6 +1651,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
     if (const char* q = strstr(t, "wgrad128=")) if (sscanf(q + 9, "%d", &v) == 1 && v >= 0) h->tune_wgrad128_min = v;
     if (const char* q = strstr(t, "pipe=")) if (sscanf(q + 5, "%d", &v) == 1) h->use_pipeline = v != 0;
     if (const char* q = strstr(t, "samples=")) if (sscanf(q + 8, "%d", &v) == 1) h->tune_samples = v != 0;
+    if (const char* q = strstr(t, "linear=")) if (sscanf(q + 7, "%d", &v) == 1) h->tune_linear = v != 0;
     if (const char* q = strstr(t, "fd2=")) if (sscanf(q + 4, "%d", &v) == 1) h->fd_paired = v != 0;
   }
   plan(h);
@@ -1840,6 +1872,7 @@ betty_status betty_mixed_vjp(betty_handle h, const float* w, const float* lambda
 betty_status betty_hypergrad_neumann(betty_handle h, const float* w, const float* lambda, int K, float alpha,
                                      float* dlambda) {
   CHECK(check_hyper_args(h, w, lambda, K, alpha, dlambda));
+  if (use_linear(h, false)) { linear_seq(h, w, lambda, K, alpha, dlambda, false); return finish(h); }
   auto body = [=]() { neumann_seq(h, w, lambda, nullptr, K, alpha, dlambda); };
   return run_cached(h, h->CALL_NEUMANN, call_key({w, lambda, dlambda}, K, {alpha}), body);
 }
@@ -2011,6 +2044,7 @@ betty_status betty_hypergrad_fd(betty_handle h, const float* w, const float* lam
 
 betty_status betty_hypergrad_cg(betty_handle h, const float* w, const float* lambda, int K, float* dlambda) {
   CHECK(check_hyper_args(h, w, lambda, K, 0.f, dlambda));
+  if (use_linear(h, true)) { linear_seq(h, w, lambda, K, 0.f, dlambda, true); return finish(h); }
   auto body = [=]() {
     OperandSet& os = h->sets[0];
     const bool l2 = h->desc.hp == BETTY_HP_L2_DECAY, rw = h->desc.hp == BETTY_HP_REWEIGHT_NET;

@@ -342,4 +342,17 @@ void launch_weighted_loss_sum(Ctx&, const float* s, const float* ell, int rows, 
 void launch_label_noise(Ctx&, const int32_t* y, const uint32_t* words, const int32_t* alt,
                         unsigned long long threshold, int n, int32_t* y_out, uint8_t* mask);
 
+// ---- linear.hip : a whole hypergradient of a small single-layer model in one workgroup ----------------
+struct LinearArgs {
+  const float* X[2]; const float* XT[2]; int ldx, ldxt[2];     // train, validation: fp32 operands [B][ldx], [n_in][ldxt]
+  const Labels* labels;                                         // [2]
+  int B[2], n_in, C, bias, loss, K;
+  float alpha;                                                  // (Neumann)
+  const float* w; const float* lam; float* out;
+  float* G;                                                     // squared error: room for X^T X (linear_gram_bytes), or null
+};
+bool linear_fits(int n, int C, int B, int Bv, bool mse, bool cg);   // n: features and bias
+size_t linear_gram_bytes(int n);
+void launch_linear_hypergrad(Ctx&, const LinearArgs&, bool cg);
+
 }  // namespace betty

@@ -1,0 +1,41 @@
+"""The one-workgroup kernel for small single-layer models at the edges of what it takes, against the fp64 oracle."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import betty_oracle as orc
+from paper_2207_02849_amd import binding
+from paper_2207_02849_amd import workloads as wk
+from tests.util import oracle_problem, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+# (features and bias in chunks of 32, batches in chunks of 32 and groups of 16 lanes, 1024 threads)
+@pytest.mark.parametrize("dims,batch,batch_val,loss,bias", [
+    ((1, 1), 1, 1, "mse", True),
+    ((31, 2), 33, 15, "ce", True),            # 32 entries with the bias
+    ((32, 3), 32, 64, "ce", True),            # the bias opens a chunk of its own
+    ((64, 1), 512, 256, "mse", False),        # every thread holds data of the validation batch's columns
+    ((32, 12), 1024, 1000, "ce", False),      # every thread holds a row; the largest softmax model
+    ((1000, 2), 16, 17, "ce", False),         # ... a column
+    ((175, 4), 700, 30, "mse", True),         # G at its largest, a train batch the registers could not hold
+    ((128, 16), 100, 101, "mse", True),       # operand rows end where the bias begins
+])
+def test_small_linear_models(dims, batch, batch_val, loss, bias):
+    wl = wk.tiny(kind="l2", act="none", dims=dims, batch=max(batch, batch_val), loss=loss, prec="fp32")
+    cut = {f: getattr(wl, f)[:n] for f, n in (("X_tr", batch), ("y_tr", batch), ("t_tr", batch), ("X_val", batch_val),
+                                              ("y_val", batch_val), ("t_val", batch_val)) if getattr(wl, f) is not None}
+    d = dims[0] * dims[1] + (dims[1] if bias else 0)
+    wl = dataclasses.replace(wl, has_bias=bias, w=wl.w[:d], lam=wl.lam[:d] + 4.0, **cut)
+    prob = oracle_problem(wl)
+    b = binding.from_workload(wl)
+    w, lam = (torch.as_tensor(np.asarray(a, dtype=np.float32)).cuda() for a in (wl.w, wl.lam))
+    for K in (0, 1, 4):
+        got = b.betty_hypergrad_neumann(w, lam, K, 0.05).cpu().numpy()
+        assert rel_l2(got, orc.hypergrad_neumann(prob, wl.w, wl.lam, K, 0.05)) < 1e-5, ("neumann", K)
+        got = b.betty_hypergrad_cg(w, lam, K).cpu().numpy()
+        assert rel_l2(got, orc.hypergrad_cg(prob, wl.w, wl.lam, K)) < 1e-4, ("cg", K)
+    b.close()
