@@ -529,22 +529,22 @@ Epilogue blank_epilogue(int mode, int act = 0) {
   return e;
 }
 
-// operand copies of a flat parameter-shaped vector: per layer, as stored (n_in x n_out) and
-// transposed; all layers in one launch (eight per launch)
-void make_shadows(betty_handle h, OperandSet& os, const float* flat, std::vector<size_t>* N,
-                  std::vector<size_t>* T, std::vector<size_t>* T32 = nullptr) {
-  for (int i0 = 0; i0 < h->L; i0 += MAX_PROBLEMS) {
-    ConvertBatch b;
-    b.n = std::min(MAX_PROBLEMS, h->L - i0);
-    for (int k = 0; k < b.n; ++k) {
-      const LayerInfo& li = h->layers[i0 + k];
-      b.j[k] = ConvertJob{flat + li.w_off, li.n_out, li.n_in, li.n_out,
-                          N ? h->at<void>((*N)[i0 + k]) : nullptr, li.n_out_p,
-                          T ? h->at<void>((*T)[i0 + k]) : nullptr, li.n_in_p};
-      if (T32) b.j[k].outT32 = h->f((*T32)[i0 + k]);
+// operand copies of a flat parameter-shaped vector: per layer, as stored (n_in x n_out; not for layer 1, where
+// only R-backward and backward links would read it, and there are none) and transposed; sixteen matrices a launch
+struct Shadows { const float* flat; std::vector<size_t>* N; std::vector<size_t>* T; std::vector<size_t>* T32 = nullptr; };
+void make_shadows(betty_handle h, OperandSet& os, std::initializer_list<Shadows> vectors) {
+  ConvertBatch b;
+  for (const Shadows& v : vectors) {
+    for (int i = 0; i < h->L; ++i) {
+      if (b.n == MAX_CONVERTS) { launch_convert_batch(h->ctx, os.elem, b); b.n = 0; }
+      const LayerInfo& li = h->layers[i];
+      ConvertJob& j = b.j[b.n++];
+      j = ConvertJob{v.flat + li.w_off, li.n_out, li.n_in, li.n_out, v.N && i > 0 ? h->at<void>((*v.N)[i]) : nullptr, li.n_out_p,
+                     v.T ? h->at<void>((*v.T)[i]) : nullptr, li.n_in_p};
+      if (v.T32) j.outT32 = h->f((*v.T32)[i]);
     }
-    launch_convert_batch(h->ctx, os.elem, b);
   }
+  launch_convert_batch(h->ctx, os.elem, b);
 }
 
 // A ReLU mask is a discontinuous function of the pre-activation: deciding it from bf16-rounded
@@ -556,9 +556,12 @@ bool hybrid_forward(betty_handle h, const OperandSet& os) {
 }
 
 // operand copies of the parameters w for everything that follows
-void make_weight_operands(betty_handle h, OperandSet& os, const float* w) {
+// and, with v, of a direction for the forward-over-reverse passes
+void make_weight_operands(betty_handle h, OperandSet& os, const float* w, const float* v = nullptr, bool rforward_only = false) {
   // (with the fp32 forward of ReLU networks the same launch also leaves the fp32 transposed copies)
-  make_shadows(h, os, w, &os.Wn, &os.Wt, hybrid_forward(h, os) ? &h->sets[1].Wt : nullptr);
+  const Shadows sw{w, &os.Wn, &os.Wt, hybrid_forward(h, os) ? &h->sets[1].Wt : nullptr};
+  if (v) make_shadows(h, os, {sw, Shadows{v, rforward_only ? nullptr : &os.Vn, &os.Vt}});
+  else make_shadows(h, os, {sw});
 }
 
 // One first-order pass over a batch.  Up to two of them share their launches: the train and the
@@ -659,7 +662,7 @@ void backward_chain(betty_handle h, const Pass* ps, int n, int l_from = 0) {
       e.dphi = h->f(sb.dphi[l - 1]);
       e.e_io = ps[i].curvature && sb.e2[l - 1] ? h->f(sb.e2[l - 1]) : nullptr;
       e.ldf = li.n_in_p;
-      e.out = h->at<void>(sb.D[l - 1]); e.ld = li.n_in_p;
+      e.out = l > 2 ? h->at<void>(sb.D[l - 1]) : nullptr; e.ld = li.n_in_p;      // (delta_1 has no link below it)
       e.outT = h->at<void>(sb.Dt[l - 1]); e.ldT = sb.Bp;
       p.e = e;
       flops += 2.0 * sb.B * li.n_in * li.n_out;
@@ -695,7 +698,7 @@ void forward_backward(betty_handle h, const Pass* ps, int n) {
     d.DL = h->at<void>(sb.D[L]); d.DLt = h->at<void>(sb.Dt[L]); d.ldd = lo.n_out_p; d.ldDLt = sb.Bp;
     d.dphi = h->f(sb.dphi[L - 1]);
     d.e2 = ps[i].curvature && sb.e2[L - 1] ? h->f(sb.e2[L - 1]) : nullptr; d.ldf = lo.n_in_p;
-    d.D = h->at<void>(sb.D[L - 1]); d.ldD = lo.n_in_p; d.Dt = h->at<void>(sb.Dt[L - 1]); d.ldDt = sb.Bp;
+    d.D = L > 2 ? h->at<void>(sb.D[L - 1]) : nullptr; d.ldD = lo.n_in_p; d.Dt = h->at<void>(sb.Dt[L - 1]); d.ldDt = sb.Bp;
     d.Wt = h->at<void>(ps[i].os->Wt[L - 1]); d.Wn = h->at<void>(ps[i].os->Wn[L - 1]);
     d.bias = h->desc.has_bias ? ps[i].w + lo.b_off : nullptr;
     d.B = sb.B;
@@ -806,7 +809,7 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
         e.alpha = (float)(gamma * k.alpha);
       }
       if (k.copies) {
-        e.out = h->at<void>(VN[l - 1]); e.ld = li.n_out_p;
+        e.out = l > 1 ? h->at<void>(VN[l - 1]) : nullptr; e.ld = li.n_out_p;     // (as in make_shadows)
         e.outT = h->at<void>(VT[l - 1]); e.ldT = li.n_in_p;
       }
       e.eps = k.eps; e.sum_p = k.sum_p;
@@ -827,13 +830,14 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
         j.alpha = e.alpha; j.beta = e.beta; j.gamma = e.gamma;
       }
     }
-    double params = 0;
+    double params = 0, copies = 0;
     for (int i = 0; i < b.n; ++i) {
       const LayerInfo& li = h->layers[l0 + i - 1];
       params += (double)li.n_in * li.n_out + (h->desc.has_bias ? li.n_out : 0);
+      copies += (l0 + i > 1 ? 4.0 : 2.0) * li.n_in * li.n_out;
     }
     // algorithmic bytes per parameter of the epilogue's vector work (fp32 vectors 4 B each way,
-    // operand copies 2 x 2 B): Neumann step reads s, g (+ the diagonal), writes s and the copies
+    // operand copies 2 x 2 B, of layer 1 only the transposed one): Neumann step reads s, g (+ the diagonal), writes s and the copies
     double per_param = 4.0;
     if (k.mode == EPI_WGRAD_NEUMANN) per_param = 8.0 + 4.0 + (k.lam ? 4.0 : 0.0);
     else if (k.mode == EPI_WGRAD_NEUMANN_L2) per_param = 16.0 + 4.0;
@@ -844,12 +848,11 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
     else if (k.mode == EPI_WGRAD_INIT) per_param = k.p ? 8.0 : 4.0;
     else if (k.mode == EPI_WGRAD_CG) per_param = k.lam ? 12.0 : 8.0;
     else if (k.lam) per_param = 12.0;
-    if (k.copies) per_param += 4.0;
     const int cfg = plan_wgrad(h, os.elem, l0, rop, k.minus != nullptr, B), bt = gemm_cfg_tile(cfg);
     if (cfg == GEMM_64x1 || cfg == GEMM_128x1)
       for (int i = 0; i < b.n; ++i)
         xcd_split((b.p[i].g.M + bt - 1) / bt, (b.p[i].g.N + bt - 1) / bt, b.p[i].g.xgm, b.p[i].g.xgn);
-    const int n = launch_gemm_batch(h->ctx, os.elem, cfg, b, flops, per_param * params,
+    const int n = launch_gemm_batch(h->ctx, os.elem, cfg, b, flops, per_param * params + (k.copies ? copies : 0.0),
                                     k.sums ? h->at<double>(h->sums) + *k.sums : nullptr);
     if (k.sums) *k.sums += n;
   }
@@ -926,7 +929,7 @@ void hvp_cached(betty_handle h, OperandSet& os, const float* vflat, const WgradS
     a.dphi = h->f(sb.dphi[L - 1]); a.e2 = sb.e2[L - 1] ? h->f(sb.e2[L - 1]) : nullptr;
     a.Rz = h->f(os.Rz[L - 1]); a.ldf = lo.n_in_p;
     a.RDL = h->at<void>(os.RD[L]); a.RDLt = h->at<void>(os.RDt[L]); a.ldRDLt = Bp;
-    a.RD = h->at<void>(os.RD[L - 1]); a.ldRD = lo.n_in_p; a.RDt = h->at<void>(os.RDt[L - 1]); a.ldRDt = Bp;
+    a.RD = L > 2 ? h->at<void>(os.RD[L - 1]) : nullptr; a.ldRD = lo.n_in_p; a.RDt = h->at<void>(os.RDt[L - 1]); a.ldRDt = Bp;
     a.B = B; a.n_in = lo.n_in; a.n_in_p = lo.n_in_p; a.C = lo.n_out; a.loss = h->desc.loss;
     launch_last_layer_rop(h->ctx, os.elem, a);
     if (pipe) { side_wgrad(h, os, sink, L); side_wgrad(h, os, sink, L - 1); }
@@ -943,7 +946,7 @@ void hvp_cached(betty_handle h, OperandSet& os, const float* vflat, const WgradS
     e.e = sb.e2[l - 1] ? h->f(sb.e2[l - 1]) : nullptr;
     e.Rz = h->f(os.Rz[l - 1]);
     e.ldf = li.n_in_p;
-    e.out = h->at<void>(os.RD[l - 1]); e.ld = li.n_in_p;
+    e.out = l > 2 ? h->at<void>(os.RD[l - 1]) : nullptr; e.ld = li.n_in_p;
     e.outT = h->at<void>(os.RDt[l - 1]); e.ldT = Bp;
     chain_gemm(h, os.elem, h->at<void>(os.RD[l]), li.n_out_p, h->at<void>(os.Wn[l - 1]), li.n_out_p, li.n_out,
                h->at<void>(sb.D[l]), li.n_out_p, h->at<void>(os.Vn[l - 1]), li.n_out_p, li.n_out, B, li.n_in, e,
@@ -1001,7 +1004,7 @@ void mixed_reweight_seq(betty_handle h, OperandSet& os, const float* lam, const 
   const int L = h->L;
   const LayerInfo& lo = h->layers[L - 1];
   // c_i is linear in the direction, so the scale is applied once, to the final sum over samples
-  if (!copies_current) make_shadows(h, os, qflat, nullptr, &os.Vt);   // else os.Vt already holds qflat
+  if (!copies_current) make_shadows(h, os, {Shadows{qflat, nullptr, &os.Vt}});   // else os.Vt already holds qflat
   if (L >= 2 && lo.n_out <= LAST_ROP_MAX_C) {
     // narrow output layer: the last product and the directional derivative in one vector kernel
     r_forward(h, os, qflat, false, L - 1);
@@ -1358,7 +1361,7 @@ void samples_chains(betty_handle h, OperandSet& os, bool first, bool update, boo
     a.dphi = h->f(sb.dphi[L - 1]); a.e2 = sb.e2[L - 1] ? h->f(sb.e2[L - 1]) : nullptr;
     a.Rz = rz(L - 1); a.ldf = lo.n_in_p;
     a.RDL = h->at<void>(os.RD[L]); a.RDLt = h->at<void>(os.RDt[L]); a.ldRDLt = Bp;
-    a.RD = h->at<void>(os.RD[L - 1]); a.ldRD = lo.n_in_p; a.RDt = h->at<void>(os.RDt[L - 1]); a.ldRDt = Bp;
+    a.RD = L > 2 ? h->at<void>(os.RD[L - 1]) : nullptr; a.ldRD = lo.n_in_p; a.RDt = h->at<void>(os.RDt[L - 1]); a.ldRDt = Bp;
     launch_last_layer_rop(h->ctx, os.elem, a);
   } else {
     launch_loss_hessian_rows(h->ctx, os.elem, h->desc.loss, h->f(sb.P), rz(L), lo.n_out_p, h->f(sb.s), B, lo.n_out,
@@ -1389,7 +1392,7 @@ void samples_chains(betty_handle h, OperandSet& os, bool first, bool update, boo
     e.e = sb.e2[l - 1] ? h->f(sb.e2[l - 1]) : nullptr;
     e.Rz = rz(l - 1);
     e.ldf = li.n_in_p;
-    e.out = h->at<void>(os.RD[l - 1]); e.ld = li.n_in_p;
+    e.out = l > 2 ? h->at<void>(os.RD[l - 1]) : nullptr; e.ld = li.n_in_p;
     e.outT = h->at<void>(os.RDt[l - 1]); e.ldT = Bp;
     double flops = 2.0 * B * li.n_in * li.n_out;
     long tiles = Extent::up(B, 32) * Extent::up(li.n_in, 32);
@@ -1468,10 +1471,9 @@ void neumann_samples_seq(betty_handle h, const float* w, const float* lambda, co
     const size_t ra;
     ~Home() { if (os.RA[1] != ra) next_RA1(os); }
   } home{os, os.RA[1]};
-  make_weight_operands(h, os, w);
+  make_weight_operands(h, os, w, u_or_null);
   if (u_or_null) {
     prepare_lower(h, os, w, lambda);
-    make_shadows(h, os, u_or_null, &os.Vn, &os.Vt);
   } else {
     const Pass ps[2] = {train_pass(h, os, w, lambda, true), val_pass(os, w)};
     forward_backward(h, ps, 2);
@@ -1544,12 +1546,11 @@ static void neumann_seq(betty_handle h, const float* w, const float* lambda, con
   float* s = h->f(h->vec_p);
   const float* g = u_or_null;
   const bool need_lower = K > 0 || rw;      // forward/backward cache of the train batch
-  make_weight_operands(h, os, w);
+  make_weight_operands(h, os, w, K > 0 || rw ? u_or_null : nullptr);
   // the reweighting mixed term runs one more R-forward along the final sum: its operand copies are
   // written by whichever launch produces that sum
   if (u_or_null) {
     if (need_lower) prepare_lower(h, os, w, lambda);
-    if (K > 0 || rw) make_shadows(h, os, u_or_null, &os.Vn, &os.Vt);
   } else {
     // g = grad_w L_U lands in vec_v, with its operand copies for the first product
     WgradSink init{EPI_WGRAD_INIT, nullptr, nullptr, nullptr, h->f(h->vec_v), nullptr, 0.f, K > 0 || rw};
@@ -1778,9 +1779,8 @@ static betty_status check_hvp_args(betty_handle h, const float* w, const float* 
 // train batch, operand copies of v, the forward-over-reverse passes
 static void hvp_seq(betty_handle h, const float* w, const float* lambda, const float* v, float* Hv) {
   OperandSet& os = h->sets[0];
-  make_weight_operands(h, os, w);
+  make_weight_operands(h, os, w, v);
   prepare_lower(h, os, w, lambda);
-  make_shadows(h, os, v, &os.Vn, &os.Vt);
   const float* dl = diag_log(h, lambda);
   WgradSink k{EPI_WGRAD, Hv, dl, dl ? v : nullptr, nullptr, nullptr, 0.f, false};
   hvp_cached(h, os, v, k);
@@ -1862,10 +1862,10 @@ betty_status betty_mixed_vjp(betty_handle h, const float* w, const float* lambda
   }
   return run_cached(h, h->CALL_MIXED, call_key({w, lambda, q, out}), [=]() {
     OperandSet& os = h->sets[0];
-    make_weight_operands(h, os, w);
+    make_weight_operands(h, os, w, q, true);
     const Pass ps = train_pass(h, os, w, lambda, false);
     forward_and_loss(h, &ps, 1);
-    mixed_reweight_seq(h, os, lambda, q, 1.f, out);
+    mixed_reweight_seq(h, os, lambda, q, 1.f, out, true);
   });
 }
 
@@ -1952,7 +1952,7 @@ static void make_perturbed_operands(betty_handle h, const float* w, const float*
       j.ld = li.n_out_p; j.ldT = li.n_in_p;
       if (h->desc.has_bias) { j.b = w + li.b_off; j.bv = v + li.b_off; }
       for (int s = 0; s < 2; ++s) {
-        j.out[s] = h->f(os[s]->Wn[i0 + k]); j.outT[s] = h->f(os[s]->Wt[i0 + k]);
+        j.out[s] = i0 + k > 0 ? h->f(os[s]->Wn[i0 + k]) : nullptr; j.outT[s] = h->f(os[s]->Wt[i0 + k]);
         if (h->desc.has_bias) j.bout[s] = h->f(h->bias_pm[s]) + li.b_off;
       }
     }
@@ -2077,7 +2077,8 @@ betty_status betty_hypergrad_cg(betty_handle h, const float* w, const float* lam
         b.partials = partials; b.n_partial = n_partial; b.rs = rs; b.rs_new = i0 == 0 ? rs_new : nullptr;
         for (int i = 0; i < b.n; ++i) {
           const LayerInfo& li = h->layers[i0 + i];
-          b.j[i] = CgDirJob{r + li.w_off, d + li.w_off, li.n_in, li.n_out, h->at<void>(os.Vn[i0 + i]), li.n_out_p,
+          b.j[i] = CgDirJob{r + li.w_off, d + li.w_off, li.n_in, li.n_out,
+                             i0 + i > 0 ? h->at<void>(os.Vn[i0 + i]) : nullptr, li.n_out_p,
                             h->at<void>(os.Vt[i0 + i]), li.n_in_p, h->desc.has_bias ? r + li.b_off : nullptr,
                             h->desc.has_bias ? d + li.b_off : nullptr};
         }

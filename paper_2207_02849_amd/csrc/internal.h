@@ -205,10 +205,11 @@ struct ConvertJob {
   void* out; int ld; void* outT; int ldT;
   float* out32 = nullptr; float* outT32 = nullptr;
 };
+constexpr int MAX_CONVERTS = 16;
 struct ConvertBatch {
   int n = 0;
-  int block_begin[MAX_PROBLEMS + 1];
-  ConvertJob j[MAX_PROBLEMS];
+  int block_begin[MAX_CONVERTS + 1];
+  ConvertJob j[MAX_CONVERTS];
   Labels* table = nullptr;     // the launch also writes labels[0], labels[1] to table[0], table[1] if given
   Labels labels[2];
 };
@@ -267,7 +268,7 @@ struct LastRopArgs {
   const void* DL; int ldd;                              // delta_L [B][ldd], operand type
   const float* dphi; const float* e2; const float* Rz; int ldf;   // layer L-1, fp32 [B][ldf]; e2 may be null
   void* RDL; void* RDLt; int ldRDLt;                    // out: R delta_L [B][ldd] and [n_out_p][ldRDLt]
-  void* RD; int ldRD; void* RDt; int ldRDt;             // out: R delta_{L-1} [B][ldRD] and [n_in_p][ldRDt]
+  void* RD; int ldRD; void* RDt; int ldRDt;             // out: R delta_{L-1} [B][ldRD] (or null) and [n_in_p][ldRDt]
   int B, n_in, n_in_p, C, loss;
   // Directional form (cvec non-null): only c_i = <dl_i/dz, Rz_L,i> per sample leaves the kernel
   // (the per-sample directional derivative of the loss, for the reweighting mixed term);
@@ -290,7 +291,7 @@ struct LastGradSide {
   float* dsig;                                   // out: omega (1 - omega) without cancellation (weight net evaluated here only)
   void* DL; void* DLt; int ldd, ldDLt;           // out: delta_L [B][ldd] and [n_out_p][ldDLt]
   const float* dphi; float* e2; int ldf;         // layer L-1, fp32 [B][ldf]
-  void* D; int ldD; void* Dt; int ldDt;          // out: delta_{L-1} [B][ldD] and [n_in_p][ldDt]
+  void* D; int ldD; void* Dt; int ldDt;          // out: delta_{L-1} [B][ldD] (or null) and [n_in_p][ldDt]
   const void* Wt; const void* Wn;                // W_L as [n_out_p][n_in_p] and [n_in_p][n_out_p]
   const float* bias;                             // b_L (fp32), or null
   int B, reweight; float inv_batch;              // (inv_batch negative: the output delta with the opposite sign)

@@ -46,7 +46,7 @@ template <typename T> __device__ __forceinline__ float to_float(T x) { return (f
 
 // ------------------------------------------------------------------------------------------
 // operand conversion: fp32 source -> operand type, row-major and transposed, through a 64x64
-// LDS tile; up to MAX_PROBLEMS matrices per launch
+// LDS tile; up to MAX_CONVERTS matrices per launch
 // ------------------------------------------------------------------------------------------
 
 // four consecutive elements of the operand type as one store
@@ -544,7 +544,7 @@ __global__ __launch_bounds__(1024) void last_layer_rop_kernel(LastRopArgs a) {
         float o = 0.f;
         if (ii < a.B) {
           o = (SAMPLES ? acc[ss] + ds3[ss] : acc[ss]) * dphi3[ss] + e23[ss] * rz3[ss];
-          ((T*)a.RD)[(long long)ii * a.ldRD + j] = from_float<T>(o);
+          if (a.RD) ((T*)a.RD)[(long long)ii * a.ldRD + j] = from_float<T>(o);
         }
         out[ss] = o;                                       // rows beyond the batch: zero padding
       }
@@ -739,7 +739,7 @@ __global__ __launch_bounds__(1024) void last_layer_grad_kernel(LastGradArgs a) {
         float o = 0.f;
         if (ii < sd.B) {
           o = acc[ss] * dphi3[ss];
-          ((T*)sd.D)[(long long)ii * sd.ldD + j] = from_float<T>(o);
+          if (sd.D) ((T*)sd.D)[(long long)ii * sd.ldD + j] = from_float<T>(o);
           if (sd.e2) sd.e2[(long long)ii * sd.ldf + j] = acc[ss] * e23[ss];
         }
         out[ss] = o;
@@ -1026,10 +1026,10 @@ __global__ __launch_bounds__(256) void cg_dir_kernel(CgDirBatch b) {
       else
 #pragma unroll
         for (int k = 0; k < 4; ++k) o[k] = x[k];
-      store_quad<T>(p, x[0], x[1], x[2], x[3]);
+      if (j.out) store_quad<T>(p, x[0], x[1], x[2], x[3]);
     } else {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) if (c + k < j.cols) { o[k] = x[k]; p[k] = from_float<T>(x[k]); }
+      for (int k = 0; k < 4; ++k) if (c + k < j.cols) { o[k] = x[k]; if (j.out) p[k] = from_float<T>(x[k]); }
     }
   }
   __syncthreads();
@@ -1119,7 +1119,7 @@ __global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
       float x[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) { x[k] = w[i][k] + e * (b.scale * v[i][k]); tile[rl][4 * tx + k] = x[k]; }
-      if (r < j.rows) {
+      if (r < j.rows && j.out[sg]) {
         float* o = j.out[sg] + (long long)r * j.ld + c;      // (ld is a multiple of 128, out 256-byte aligned)
         if (c + 3 < j.cols) *(float4*)o = make_float4(x[0], x[1], x[2], x[3]);
         else
