@@ -214,35 +214,77 @@ void launch_accumulate(Ctx& ctx, Elem elem, AccumulateBatch& b) {
 // ------------------------------------------------------------------------------------------
 // row-wise loss kernels: one wavefront per sample
 // ------------------------------------------------------------------------------------------
+//
+// A workgroup owns ROWS samples and COLS of the C columns (16 and 256; 4 and 64 for models of up to 64 outputs,
+// whose launches are bound by latency): each wavefront keeps its row in registers (up to 64 REGS columns), forms the
+// row's sums over all of it (again in every slice of columns: a few KB from L2), writes its slice, and leaves it in LDS,
+// from where the transposed copy goes out four samples a store.  With one wavefront per sample on its own, a store of
+// the transposed copy touched 64 lines for 2 bytes each and every pass over the row waited for
+// memory: 512 x 1000 in bf16 17.3 us, now 7.8, the Hessian's rows 15.3 us, now 5.8; 100 x 10 3.9 us either way (4.9 with 16
+// samples a workgroup).
+constexpr int lr_rows(int regs) { return regs == 1 ? 4 : 16; }
+constexpr int lr_cols(int regs) { return regs == 1 ? 64 : 256; }
+static int lr_regs(int C) { return C <= 64 ? 1 : C <= 256 ? 4 : 16; }
+__host__ __device__ constexpr int lr_up(int n, int m) { return (n + m - 1) / m; }
 
-template <typename T>
-__global__ __launch_bounds__(256) void loss_rows_kernel(LossBatch lb) {
-  const int blocks0 = (lb.a[0].rows + 3) / 4;
+// f(k, c) for the columns c = lane + 64 k of a row that are kept in registers, g(c) for those beyond
+template <int REGS, typename F, typename G>
+__device__ __forceinline__ void row_columns(int lane, int C, F f, G g) {
+#pragma unroll
+  for (int k = 0; k < REGS; ++k)
+    if (lane + 64 * k < C) f(k, lane + 64 * k);
+  if constexpr (REGS == 16)
+    for (int c = lane + 64 * REGS; c < C; c += 64) g(c);
+}
+
+// transposed copy of the tile [column][row] (rows beyond the batch hold zeros: padding of the operand)
+template <int ROWS, int COLS, typename T>
+__device__ __forceinline__ void store_rows_transposed(const T (*tile)[ROWS + 4], T* Dt, int ldDt, int i0, int c0, int C) {
+  __syncthreads();
+  constexpr int Q = ROWS / 4;                      // stores a column
+  const int t = threadIdx.x, c = c0 + t / Q, q = 4 * (t % Q);
+  typedef __attribute__((__vector_size__(4 * sizeof(T)))) T quad;
+  if (t < COLS * Q && c < C) *(quad*)(Dt + (long long)c * ldDt + i0 + q) = *(const quad*)&tile[t / Q][q];
+}
+
+template <typename T, int REGS>
+__global__ __launch_bounds__(64 * lr_rows(REGS)) void loss_rows_kernel(LossBatch lb) {
+  constexpr int ROWS = lr_rows(REGS), COLS = lr_cols(REGS);
+  __shared__ __attribute__((aligned(16))) T tile[COLS][ROWS + 4];
+  const int slices = lr_up(lb.a[0].C, COLS), blocks0 = lr_up(lb.a[0].rows, ROWS) * slices;
   const int which = (lb.n > 1 && (int)blockIdx.x >= blocks0) ? 1 : 0;
   const LossArgs& a = lb.a[which];
-  const int row = ((int)blockIdx.x - (which ? blocks0 : 0)) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (row >= a.rows) return;
+  const int bid = (int)blockIdx.x - (which ? blocks0 : 0), slice = bid % slices, c0 = slice * COLS;
+  const int i0 = bid / slices * ROWS, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, C = a.C;
+  const bool live = i0 + wave < a.rows;
+  const int row = live ? i0 + wave : a.rows - 1;
   const float* z = a.Z + (long long)row * a.ldz;
   const Labels lab = *a.labels;
-  float ell, m = 0.f, sum = 1.f;
+  const bool ce = a.loss == BETTY_LOSS_SOFTMAX_CE;
+  const float* t = ce ? nullptr : lab.target + (long long)row * C;
+  float zr[REGS], ell, m = 0.f, sum = 1.f;
   int y = 0;
-  if (a.loss == BETTY_LOSS_SOFTMAX_CE) {
+#pragma unroll
+  for (int k = 0; k < REGS; ++k) zr[k] = lane + 64 * k < C ? z[lane + 64 * k] : 0.f;
+  if (ce) {
+    // a label outside [0, C) is clamped into the range, for the gather and the one-hot alike
+    y = min(max(lab.y[row], 0), C - 1);
+    const float zy = z[y];                         // integer gather of the label's logit
     m = -INFINITY;
-    for (int c = lane; c < a.C; c += 64) m = fmaxf(m, z[c]);
+    row_columns<REGS>(lane, C, [&](int k, int) { m = fmaxf(m, zr[k]); }, [&](int c) { m = fmaxf(m, z[c]); });
     m = wave_max(m);
     sum = 0.f;
-    for (int c = lane; c < a.C; c += 64) sum += expf(z[c] - m);
+    row_columns<REGS>(lane, C, [&](int k, int) { sum += expf(zr[k] - m); }, [&](int c) { sum += expf(z[c] - m); });
     sum = wave_sum(sum);
-    // a label outside [0, C) is clamped into the range, for the gather and the one-hot alike
-    y = min(max(lab.y[row], 0), a.C - 1);
-    ell = logf(sum) + m - z[y];                  // integer gather of the label's logit
+    ell = logf(sum) + m - zy;
   } else {
-    const float* t = lab.target + (long long)row * a.C;
     float acc = 0.f;
-    for (int c = lane; c < a.C; c += 64) { const float r = z[c] - t[c]; acc += r * r; }
+    row_columns<REGS>(lane, C, [&](int k, int c) { const float r = zr[k] - t[c]; acc += r * r; },
+                [&](int c) { const float r = z[c] - t[c]; acc += r * r; });
     ell = wave_sum(acc);
   }
   float omega = 1.f;
+  const bool first = live && slice == 0 && lane == 0;
   if (a.reweight && a.omega_fixed) {
     omega = a.omega_fixed[row];
   } else if (a.reweight) {
@@ -253,78 +295,105 @@ __global__ __launch_bounds__(256) void loss_rows_kernel(LossBatch lb) {
     part = wave_sum(part) + a.theta[3 * H];
     omega = 1.f / (1.f + expf(-part));
     // sigmoid'(x) = sigmoid(x) sigmoid(-x): no 1 - omega, which loses every digit once omega rounds to 1
-    if (lane == 0 && a.dsig) a.dsig[row] = omega / (1.f + expf(part));
+    if (first && a.dsig) a.dsig[row] = omega / (1.f + expf(part));
   }
   const float s = omega * a.inv_batch;
-  if (lane == 0) { a.ell[row] = ell; a.s[row] = s; a.omega[row] = omega; }
+  if (first) { a.ell[row] = ell; a.s[row] = s; a.omega[row] = omega; }
   T* D = (T*)a.D + (long long)row * a.ldD;
-  T* Dt = (T*)a.Dt + row;
-  if (a.loss == BETTY_LOSS_SOFTMAX_CE) {
-    float* P = a.P + (long long)row * a.ldz;
-    const float inv = 1.f / sum;
-    for (int c = lane; c < a.C; c += 64) {
-      const float p = expf(z[c] - m) * inv;
-      P[c] = p;
-      const T dv = from_float<T>(s * (p - (c == y ? 1.f : 0.f)));
+  float* P = a.P + (long long)row * a.ldz;
+  const float inv = 1.f / sum;
+#pragma unroll
+  for (int k = 0; k < COLS / 64; ++k) {
+    const int c = c0 + lane + 64 * k;
+    T dv = from_float<T>(0.f);
+    if (live && c < C) {
+      const float zc = z[c];
+      if (ce) {
+        const float p = expf(zc - m) * inv;
+        P[c] = p;
+        dv = from_float<T>(s * (p - (c == y ? 1.f : 0.f)));
+      } else {
+        dv = from_float<T>(s * 2.f * (zc - t[c]));
+      }
       D[c] = dv;
-      Dt[(long long)c * a.ldDt] = dv;
     }
-  } else {
-    const float* t = lab.target + (long long)row * a.C;
-    for (int c = lane; c < a.C; c += 64) {
-      const T dv = from_float<T>(s * 2.f * (z[c] - t[c]));
-      D[c] = dv;
-      Dt[(long long)c * a.ldDt] = dv;
-    }
+    tile[lane + 64 * k][wave] = dv;
   }
+  store_rows_transposed<ROWS, COLS, T>(tile, (T*)a.Dt, a.ldDt, i0, c0, C);
 }
 
-void launch_loss_rows(Ctx& ctx, Elem elem, const LossBatch& lb) {
+template <int REGS>
+static void launch_loss_rows_of(hipStream_t st, Elem elem, const LossBatch& lb) {
   int blocks = 0;
-  for (int i = 0; i < lb.n; ++i) blocks += (lb.a[i].rows + 3) / 4;
+  for (int i = 0; i < lb.n; ++i) blocks += lr_up(lb.a[i].rows, lr_rows(REGS)) * lr_up(lb.a[0].C, lr_cols(REGS));
   if (blocks <= 0) return;
+  if (elem == ELEM_BF16) loss_rows_kernel<__bf16, REGS><<<blocks, 64 * lr_rows(REGS), 0, st>>>(lb);
+  else loss_rows_kernel<float, REGS><<<blocks, 64 * lr_rows(REGS), 0, st>>>(lb);
+}
+void launch_loss_rows(Ctx& ctx, Elem elem, const LossBatch& lb) {
+  if (lb.n <= 0) return;
   Launch l(ctx, BETTY_K_LOSS);
-  if (elem == ELEM_BF16) loss_rows_kernel<__bf16><<<blocks, 256, 0, ctx.stream>>>(lb);
-  else loss_rows_kernel<float><<<blocks, 256, 0, ctx.stream>>>(lb);
+  const int regs = lr_regs(lb.a[0].C);
+  if (regs == 1) launch_loss_rows_of<1>(ctx.stream, elem, lb);
+  else if (regs == 4) launch_loss_rows_of<4>(ctx.stream, elem, lb);
+  else launch_loss_rows_of<16>(ctx.stream, elem, lb);
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void loss_hessian_rows_kernel(int loss, const float* P, const float* Rz,
-                                                                long long ld, const float* s, int rows,
-                                                                int C, T* D, int ldD, T* Dt, int ldDt) {
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (row >= rows) return;
+template <typename T, int REGS>
+__global__ __launch_bounds__(64 * lr_rows(REGS)) void loss_hessian_rows_kernel(int loss, const float* P, const float* Rz,
+                                                                               long long ld, const float* s, int rows,
+                                                                               int C, T* D, int ldD, T* Dt, int ldDt) {
+  constexpr int ROWS = lr_rows(REGS), COLS = lr_cols(REGS);
+  __shared__ __attribute__((aligned(16))) T tile[COLS][ROWS + 4];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c0 = blockIdx.y * COLS, i0 = blockIdx.x * ROWS;
+  const bool live = i0 + wave < rows, ce = loss == BETTY_LOSS_SOFTMAX_CE;
+  const int row = live ? i0 + wave : rows - 1;
   const float* rz = Rz + (long long)row * ld;
-  T* o = D + (long long)row * ldD;
-  T* ot = Dt + row;
+  const float* p = P + (long long)row * ld;
   const float si = s[row];
-  if (loss == BETTY_LOSS_SOFTMAX_CE) {
-    const float* p = P + (long long)row * ld;
-    float dot = 0.f;
-    for (int c = lane; c < C; c += 64) dot += p[c] * rz[c];
-    dot = wave_sum(dot);
-    for (int c = lane; c < C; c += 64) {
-      const T v = from_float<T>(si * (p[c] * rz[c] - p[c] * dot));
-      o[c] = v;
-      ot[(long long)c * ldDt] = v;
-    }
-  } else {
-    for (int c = lane; c < C; c += 64) {
-      const T v = from_float<T>(si * 2.f * rz[c]);
-      o[c] = v;
-      ot[(long long)c * ldDt] = v;
-    }
+  float x[COLS / 64], px[COLS / 64], dot = 0.f;
+#pragma unroll
+  for (int k = 0; k < COLS / 64; ++k) {
+    const int c = c0 + lane + 64 * k;
+    x[k] = c < C ? rz[c] : 0.f;
+    px[k] = ce && c < C ? p[c] : 0.f;
   }
+  if (ce) {
+    float pr[REGS], rr[REGS];
+#pragma unroll
+    for (int k = 0; k < REGS; ++k) {
+      const int c = lane + 64 * k;
+      pr[k] = c < C ? p[c] : 0.f; rr[k] = c < C ? rz[c] : 0.f;
+    }
+    row_columns<REGS>(lane, C, [&](int k, int) { dot += pr[k] * rr[k]; }, [&](int c) { dot += p[c] * rz[c]; });
+    dot = wave_sum(dot);
+  }
+#pragma unroll
+  for (int k = 0; k < COLS / 64; ++k) {
+    const int c = c0 + lane + 64 * k;
+    const T v = from_float<T>(!live || c >= C ? 0.f : ce ? si * (px[k] * x[k] - px[k] * dot) : si * 2.f * x[k]);
+    if (live && c < C) D[(long long)row * ldD + c] = v;
+    tile[lane + 64 * k][wave] = v;
+  }
+  store_rows_transposed<ROWS, COLS, T>(tile, Dt, ldDt, i0, c0, C);
 }
 
+template <typename T, int REGS>
+static void launch_loss_hessian_rows_of(hipStream_t st, int loss, const float* P, const float* Rz, long long ld,
+                                        const float* s, int rows, int C, void* D, int ldD, void* Dt, int ldDt) {
+  const dim3 grid(lr_up(rows, lr_rows(REGS)), lr_up(C, lr_cols(REGS)));
+  loss_hessian_rows_kernel<T, REGS><<<grid, 64 * lr_rows(REGS), 0, st>>>(loss, P, Rz, ld, s, rows, C, (T*)D, ldD, (T*)Dt, ldDt);
+}
 void launch_loss_hessian_rows(Ctx& ctx, Elem elem, int loss, const float* P, const float* Rz, long long ld,
                               const float* s, int rows, int C, void* D, int ldD, void* Dt, int ldDt) {
   if (rows <= 0) return;
   Launch l(ctx, BETTY_K_LOSS);
-  if (elem == ELEM_BF16)
-    loss_hessian_rows_kernel<__bf16><<<(rows + 3) / 4, 256, 0, ctx.stream>>>(loss, P, Rz, ld, s, rows, C, (__bf16*)D, ldD, (__bf16*)Dt, ldDt);
-  else
-    loss_hessian_rows_kernel<float><<<(rows + 3) / 4, 256, 0, ctx.stream>>>(loss, P, Rz, ld, s, rows, C, (float*)D, ldD, (float*)Dt, ldDt);
+  const int regs = lr_regs(C);
+  const bool bf = elem == ELEM_BF16;
+  auto f = regs == 1 ? (bf ? launch_loss_hessian_rows_of<__bf16, 1> : launch_loss_hessian_rows_of<float, 1>)
+         : regs == 4 ? (bf ? launch_loss_hessian_rows_of<__bf16, 4> : launch_loss_hessian_rows_of<float, 4>)
+                     : (bf ? launch_loss_hessian_rows_of<__bf16, 16> : launch_loss_hessian_rows_of<float, 16>);
+  f(ctx.stream, loss, P, Rz, ld, s, rows, C, D, ldD, Dt, ldDt);
 }
 
 __global__ __launch_bounds__(256) void loss_directional_rows_kernel(int loss, const float* P, const float* Z,

@@ -45,6 +45,23 @@ def test_small_launch_forms(dims, batch, loss, prec, tol):
     b.close()
 
 
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
+@pytest.mark.parametrize("loss", ["ce", "mse"])
+@pytest.mark.parametrize("C,batch", [(64, 5), (65, 16), (256, 15), (257, 33), (1024, 17), (1100, 18)])
+def test_loss_rows_of_wide_outputs(C, batch, loss, prec, tol):
+    """Outputs at the edges of what a wavefront keeps of a row and of a workgroup's columns and samples."""
+    wl = wk.tiny(kind="l2", act="gelu", dims=(9, 20, C), batch=batch, loss=loss, prec=prec)
+    prob = oracle_problem(wl)
+    b = binding.from_workload(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    v = np.random.default_rng(C).standard_normal(wl.d)
+    loss_ref, grad_ref = orc.lower_grad(prob, wl.w, wl.lam)
+    grad, cost = b.betty_lower_grad(w, lam, want_loss=True)
+    assert rel_l2(host(grad), grad_ref) < tol and abs(float(cost) - loss_ref) < tol * abs(loss_ref)
+    assert rel_l2(host(b.betty_hvp(w, lam, dev(v))), orc.hvp(prob, wl.w, wl.lam, v)) < tol
+    b.close()
+
+
 def test_recorded_calls_follow_streams_and_batches():
     """A handle without an explicit stream runs on the caller's current stream; recorded sequences
     survive a move to another stream and new batches (labels included), and one argument set does
