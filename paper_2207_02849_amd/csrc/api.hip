@@ -158,6 +158,7 @@ struct betty_handle_s {
   // 1024-512-512-10 36.9 / 35.6, 2048-2048-2048-1000 at 512 181 / 173, 777-301-65-33 at 130 48.3 / 35.3.
   bool fixed_grouping = false;
   bool as_pair = false;                       // choose kernels for single passes as if two shared the launch
+  bool tune_pair_forced = false;              // 64-tiles with a two-way K split for every activation-shaped product
   int tune_linear = -1;                       // one-workgroup kernel for single-layer models: 0 never, 1 wherever it fits, -1 by size
   int tune_samples = -1;                      // sample-space series: 0 never, 1 wherever it exists, -1 by size
   // Finite differences: the passes at w + eps v and w - eps v share their launches, with weight operands
@@ -446,6 +447,10 @@ const float* wnet_theta(betty_handle h, const float* lambda) {
 //    operand rows for the 8192 outputs that two 64-tiles fetch 256 for (121M-parameter model,
 //    batch 512: R-forward link 73 -> 66 us, backward link 76 -> 60 us); with fp32 operands, whose
 //    launches of this size are bound by the matrix cores, 64-tiles are 10 % faster;
+//  * 64-tiles with a two-way K split (eight wavefronts) while every tile has a compute unit of its own and the
+//    reduction is long: four wavefronts leave a SIMD one, with nothing to hide its barriers behind and the whole
+//    epilogue to itself (bf16 gradients of 2048-2048-2048-1000 at 512 117 -> 108 us; 40 models -0.3 ... +8 %; with two tiles a
+//    compute unit 64-tiles hide each other, and fp32 launches lose up to 5 %);
 //  * 128-tiles once there are enough of them to fill the chip several times over;
 //  * otherwise plain 64-tiles.
 int plan_chain(betty_handle h, Elem elem, GemmBatch& b) {
@@ -469,14 +474,15 @@ int plan_chain(betty_handle h, Elem elem, GemmBatch& b) {
   for (int r = 0; r < (h->as_pair && b.n == 1 ? 2 : 1); ++r)
     for (int i = 0; i < b.n; ++i) x.add(elem, b.p[i].g.M, b.p[i].g.N, b.p[i].g.K[0], b.p[i].g.K[1]);
   const bool wide_rows = b.p[0].e.mode == EPI_RFWD_LAST_HESS && b.p[0].g.N > 16;   // its row sums need a whole row per tile
-  if (h->tune_split && !wide_rows) {
+  if (h->tune_split && !h->tune_pair_forced && !wide_rows) {
     const int shorter = elem == ELEM_BF16 ? 1 : 2;        // the same K has twice the steps with fp32 operands
     if (x.t16 <= 256 ? (elem == ELEM_F32 || x.steps < 80)
                      : ((x.t16 <= 512 && x.steps <= 12 * shorter) || (x.t16 <= 1024 && x.steps <= 4 * shorter)))
       return GEMM_16;
   }
-  if (h->tune_split && x.t32 <= 600) return GEMM_32x8;
-  if (x.t128 >= h->tune_tile128_min) return GEMM_128x1;
+  if (h->tune_split && !h->tune_pair_forced && x.t32 <= 600) return GEMM_32x8;
+  if (!h->tune_pair_forced && x.t128 >= h->tune_tile128_min) return GEMM_128x1;
+  if (h->tune_pair_forced || (h->tune_split && !h->tune_rect_forced && x.t64 <= 256 && x.steps >= 16)) return GEMM_64x2;
   if (h->tune_rect_forced || (elem == ELEM_BF16 && x.rect >= 200 && x.t64 <= 1024 && x.steps >= 16)) return GEMM_128x64;
   return GEMM_64x1;
 }
@@ -1641,7 +1647,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
   h->use_pipeline = large && desc->prec == BETTY_PREC_FP32;
   h->fd_paired = !large;
   h->max_Bp = std::max(padup(desc->batch_train), padup(desc->batch_val));
-  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>,linear=<0|1>" (see plan_chain)
+  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,pair=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>,linear=<0|1>" (see plan_chain)
   if (const char* t = getenv("BETTY_TUNE")) {
     int v;
     if (const char* q = strstr(t, "wgrad=")) if (sscanf(q + 6, "%d", &v) == 1 && (v == GEMM_128x1 || v == GEMM_64x1)) h->tune_wgrad_cfg = v;
@@ -1652,6 +1658,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
     if (const char* q = strstr(t, "wgrad128=")) if (sscanf(q + 9, "%d", &v) == 1 && v >= 0) h->tune_wgrad128_min = v;
     if (const char* q = strstr(t, "pipe=")) if (sscanf(q + 5, "%d", &v) == 1) h->use_pipeline = v != 0;
     if (const char* q = strstr(t, "samples=")) if (sscanf(q + 8, "%d", &v) == 1) h->tune_samples = v != 0;
+    if (const char* q = strstr(t, "pair=")) if (sscanf(q + 5, "%d", &v) == 1) h->tune_pair_forced = v == 1;
     if (const char* q = strstr(t, "linear=")) if (sscanf(q + 7, "%d", &v) == 1) h->tune_linear = v != 0;
     if (const char* q = strstr(t, "fd2=")) if (sscanf(q + 4, "%d", &v) == 1) h->fd_paired = v != 0;
   }

@@ -516,7 +516,10 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
   constexpr int KT = NCH * EPC;                    // elements per k-tile
   constexpr int TM = BM / (32 * WM), TN = BN / (32 * WN);   // 32x32 blocks per wavefront
   constexpr int LA = BM * NCH / GT, LB = BN * NCH / GT;
-  static_assert(WPG == 1 ? KG >= 4 : KG == 1, "K is split over groups of one wavefront only");
+  // Two groups of four wavefronts (64-tiles): each takes half of K with LDS buffers of its own and all pass the same
+  // barriers; the padding of the operands makes the number of k-tiles even.
+  constexpr bool PAIR = KG == 2;
+  static_assert(WPG == 1 ? KG >= 4 : WPG == 4 ? KG <= 2 : KG == 1, "K groups: one wavefront each, or two of four");
   static_assert(WPG == 1 || WPG == 4 || WPG == 8, "a K group is one wavefront, 2 x 2 or 4 x 2 wavefronts");
   static_assert(BM % (32 * WM) == 0 && BN % (32 * WN) == 0 && (BM * NCH) % GT == 0 && (BN * NCH) % GT == 0, "tile");
   extern __shared__ u32x4 smem[];
@@ -528,9 +531,9 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
   const int wm = WPG >= 4 ? wave >> 1 : 0, wn = WPG >= 4 ? wave & 1 : 0;
   // Unsplit launches keep two LDS operand buffers and alternate between them, so the stores of
   // one k-tile overlap the multiplication of the previous one and a k-tile costs one barrier.
-  constexpr bool DB = KG == 1;
+  constexpr bool DB = KG == 1 || PAIR;
   constexpr int LBUF = (BM + BN) * ROW;            // one operand buffer, in chunks
-  u32x4* sA = smem + kg * LBUF;
+  u32x4* sA = smem + kg * (PAIR ? 2 * LBUF : LBUF);
   u32x4* sB = sA + BM * ROW;
   // a one-wavefront group owns its LDS region alone: no workgroup barrier inside the k loop
 #define BETTY_GROUP_SYNC() do { if constexpr (WPG == 1) __builtin_amdgcn_wave_barrier(); else __syncthreads(); } while (0)
@@ -560,7 +563,8 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
 
   const int sp = g.split;                          // (see GemmArgs::split)
   constexpr bool BSPLIT = MODE == EPI_WGRAD_SCALED;
-  const int T0 = (g.K[0] + KT - 1) / KT << sp, T1 = (g.K[1] + KT - 1) / KT << sp, TT = T0 + T1;
+  constexpr int KR = PAIR ? 2 : 1;                 // k-tiles come in whole multiples of the groups
+  const int T0 = (g.K[0] + KR * KT - 1) / (KR * KT) * KR << sp, T1 = (g.K[1] + KR * KT - 1) / (KR * KT) * KR << sp, TT = T0 + T1;
   const int NI = (TT + KG - 1) / KG;               // iterations of every group (same barrier count)
   const int tb = kg * NI;
   const int te = tb + NI < TT ? tb + NI : TT;
@@ -580,8 +584,8 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
   // per lane), so the epilogue's arithmetic and stores run on four wavefronts instead of one.
   constexpr bool SPLIT_EPI = WPG == 1;
   const Epilogue& e = batch.p[pi].e;
-  EpiRegs<16> pre[SPLIT_EPI ? 1 : TM * TN];
-  EpiRegs<4> pre4;
+  EpiRegs<16> pre[SPLIT_EPI || PAIR ? 1 : TM * TN];
+  EpiRegs<4> pre4, pre4b;
   // A wavefront's loads return in the order issued, so a workgroup that requests its epilogue
   // inputs first starts its k loop only once they are there, and one that requests them last waits
   // for them after it: either way it streams and multiplies one after the other, and workgroups
@@ -593,6 +597,10 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
   const bool early = !STAGGER || ((blockIdx.x >> 3) & 1) == 0;
   if constexpr (SPLIT_EPI) {
     if (kg < 4) epi_prefetch<MODE, 4>(e, g.M, g.N, m0 + 8 * kg + 4 * (lane >> 5), n0 + (lane & 31), pre4);
+  } else if constexpr (PAIR) {
+    // ... and of two groups' halves each group finishes two register quads of its four blocks
+    epi_prefetch<MODE, 4>(e, g.M, g.N, m0 + wm * 32 + 16 * kg + 4 * (lane >> 5), n0 + wn * 32 + (lane & 31), pre4);
+    epi_prefetch<MODE, 4>(e, g.M, g.N, m0 + wm * 32 + 16 * kg + 8 + 4 * (lane >> 5), n0 + wn * 32 + (lane & 31), pre4b);
   } else if constexpr (PREFETCH) {
     if (kg == 0 && early) {
 #pragma unroll
@@ -605,7 +613,7 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
   // Two register sets hold the global loads of the next two k-tiles, so two tiles' worth of
   // loads are in flight while a third is multiplied out of LDS (four sets in the long-loop form
   // of the unsplit activation-shaped launches, see below).
-  constexpr bool LONG_LOOP = KG == 1 && MODE < EPI_WGRAD;
+  constexpr bool LONG_LOOP = DB && MODE < EPI_WGRAD;
   u32x4 ra0[LA], rb0[LB], ra1[LA], rb1[LB];
   u32x4 ra2[LONG_LOOP ? LA : 1], rb2[LONG_LOOP ? LB : 1], ra3[LONG_LOOP ? LA : 1], rb3[LONG_LOOP ? LB : 1];
   // operand bases of both pairs are read from the kernel arguments once, not per k-tile
@@ -630,7 +638,7 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
   // still has a tile (t_ < te).
 #define BETTY_STAGE(RA_, RB_, t_, first_, always_, dist_, buf_)                                      \
   {                                                                                                  \
-    const bool live_ = KG == 1 || (t_) < te;                                                         \
+    const bool live_ = DB || (t_) < te;                                                         \
     u32x4* const sA_ = sA + (DB ? (buf_) * LBUF : 0);                                                \
     u32x4* const sB_ = sB + (DB ? (buf_) * LBUF : 0);                                                \
     if (!DB && !(first_)) BETTY_GROUP_SYNC();                                                        \
@@ -703,7 +711,7 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
     // stay inside the k-range, then a short tail.  K-split launches run a handful of tiles per
     // group; they keep the compact loop (less code to fetch for a kernel that lives a few us).
     int it = 0;
-    if constexpr (KG == 1) {
+    if constexpr (DB) {
       if (n_full > 3) {                               // first pair peeled: no barrier before the first store
         BETTY_STAGE(ra0, rb0, tb, true, true, 2, 0)
         BETTY_STAGE(ra1, rb1, tb + 1, false, true, 2, 1)
@@ -742,6 +750,23 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
     float sum = 0.f;
     epi_finish<T, MODE, 4>(e, g.M, g.N, m0 + 8 * kg + 4 * (lane >> 5), n0 + (lane & 31), q4, pre4, sum);
     epi_store_sum<MODE>(e, kg, sum);
+    return;
+  }
+
+  if constexpr (PAIR) {
+    __syncthreads();
+    float* red = (float*)smem + (wave * 8) * 64 + lane;      // [group][wavefront][8 registers][lane]
+#pragma unroll
+    for (int r = 0; r < 8; ++r) red[(kg * 32 + r) * 64] = kg ? acc[0][r] : acc[0][8 + r];
+    __syncthreads();
+    float q4[4], q4b[4], sum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      q4[r] = (kg ? acc[0][8 + r] : acc[0][r]) + red[((1 - kg) * 32 + r) * 64];
+      q4b[r] = (kg ? acc[0][12 + r] : acc[0][4 + r]) + red[((1 - kg) * 32 + 4 + r) * 64];
+    }
+    epi_finish<T, MODE, 4>(e, g.M, g.N, m0 + wm * 32 + 16 * kg + 4 * (lane >> 5), n0 + wn * 32 + (lane & 31), q4, pre4, sum);
+    epi_finish<T, MODE, 4>(e, g.M, g.N, m0 + wm * 32 + 16 * kg + 8 + 4 * (lane >> 5), n0 + wn * 32 + (lane & 31), q4b, pre4b, sum);
     return;
   }
 
@@ -1291,7 +1316,7 @@ static int max_problems(int mode) { return mode >= EPI_WGRAD ? MAX_PROBLEMS : mo
 
 template <typename T, int BT, int WPG, int KG>
 constexpr size_t lds_bytes() {
-  constexpr size_t operands = (size_t)(KG == 1 ? 2 : KG) * 2 * BT * (GEMM_NCH + 1) * 16;
+  constexpr size_t operands = (size_t)(KG <= 2 ? 2 * KG : KG) * 2 * BT * (GEMM_NCH + 1) * 16;
   constexpr size_t reduce = WPG == 1 ? (size_t)KG * BT * BT * 4 : 0;
   return operands > reduce ? operands : reduce;
 }
@@ -1458,6 +1483,7 @@ static void launch_elem(int cfg, int mode, int total, hipStream_t st, const Gemm
       else if (mode == EPI_BWD) launch_one<T, 32, 1, 4, EPI_BWD>(total, st, b, err);
       else err = hipErrorInvalidValue;
       break;
+    case GEMM_64x2: launch_chain_mode<T, 64, 4, 2>(mode, total, st, b, err); break;
     case GEMM_128x64: launch_rect_mode<T>(mode, total, st, b, err); break;
     default: err = hipErrorInvalidValue; break;
   }

@@ -117,7 +117,7 @@ constexpr int MAX_PROBLEMS = 8;
 constexpr int GEMM_NCH = 8;              // 16-byte chunks per row of a k-tile
 // tile extent x number of K groups per workgroup; a group is 2 x 2 wavefronts, except in 32x8 and 32x4
 // (32-tile, groups of one wavefront) and 16 (16-tile, 4 to 16 groups of one wavefront)
-enum { GEMM_128x1 = 0, GEMM_64x1 = 2, GEMM_32x8 = 4, GEMM_128x64 = 5, GEMM_16 = 6, GEMM_32x4 = 7 };
+enum { GEMM_128x1 = 0, GEMM_64x1 = 2, GEMM_64x2 = 3, GEMM_32x8 = 4, GEMM_128x64 = 5, GEMM_16 = 6, GEMM_32x4 = 7 };
 
 // Assembled on the host and passed to the kernels by value, in a form cut to the kind of launch.
 // Activation-shaped launches have few problems (train and validation batch; a link of the R-backward chain

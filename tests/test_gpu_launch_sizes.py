@@ -46,6 +46,28 @@ def test_small_launch_forms(dims, batch, loss, prec, tol):
 
 
 @pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
+@pytest.mark.parametrize("kind,samples", [("l2", 0), ("reweight", 1)])
+@pytest.mark.parametrize("dims,batch", [
+    ((64, 64, 64, 40), 64),                  # whole tiles, one k-tile a group
+    ((65, 33, 130, 17), 63),                 # ragged rows, columns and K
+    ((1100, 300, 31), 129),                  # the long-loop form in some products, not in others; Hessian in the epilogue
+])
+def test_two_way_split_of_64_tiles(dims, batch, kind, samples, prec, tol, monkeypatch):
+    monkeypatch.setenv("BETTY_TUNE", f"pair=1,samples={samples}")
+    wl = wk.tiny(kind=kind, act="gelu", dims=dims, batch=batch, prec=prec)
+    prob = oracle_problem(wl)
+    b = binding.from_workload(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    v = orc.lower_grad(prob, wl.w, wl.lam)[1]
+    for name, got, ref in (("grad", b.betty_lower_grad(w, lam), v),
+                           ("hvp", b.betty_hvp(w, lam, dev(v)), orc.hvp(prob, wl.w, wl.lam, v)),
+                           ("neumann", b.betty_hypergrad_neumann(w, lam, 2, 0.02),
+                            orc.hypergrad_neumann(prob, wl.w, wl.lam, 2, 0.02))):
+        assert rel_l2(host(got), ref) < tol, name
+    b.close()
+
+
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
 @pytest.mark.parametrize("loss", ["ce", "mse"])
 @pytest.mark.parametrize("C,batch", [(64, 5), (65, 16), (256, 15), (257, 33), (1024, 17), (1100, 18)])
 def test_loss_rows_of_wide_outputs(C, batch, loss, prec, tol):
