@@ -159,6 +159,7 @@ struct betty_handle_s {
   bool fixed_grouping = false;
   bool as_pair = false;                       // choose kernels for single passes as if two shared the launch
   bool tune_pair_forced = false;              // 64-tiles with a two-way K split for every activation-shaped product
+  int tune_narrow = -1;                       // narrow.hip: 0 never, 1 or 2 that first layer wherever it fits, -1 by size
   int tune_linear = -1;                       // one-workgroup kernel for single-layer models: 0 never, 1 wherever it fits, -1 by size
   int tune_samples = -1;                      // sample-space series: 0 never, 1 wherever it exists, -1 by size
   // Finite differences: the passes at w + eps v and w - eps v share their launches, with weight operands
@@ -325,15 +326,47 @@ double samples_saving(betty_handle h, int K, bool dense) {
   }
   return K * step - begin - (prox && K > 1 ? (K - 1) * sums : 0.0);
 }
+// Models with narrow layers take all layers of a few samples in one workgroup (narrow.hip).  Whether the first-order
+// pass (rop = false) or the forward-over-reverse pass does, and from which layer on: 0 = launches per layer, 1, or
+// 2 = layer 1, whose reduction may be long, stays a launch of its own.
+// By the estimated time: a launch takes 4.7 us whatever its width (up to about 256), the fused kernel 6 us, 1.6 us a
+// link, and 1 us per 9 KB of weights, which every workgroup reads on its own and multiplies on one compute unit.
+// (Forward-over-reverse passes at any batch up to 1024: 32-wide, 8 layers 66 us by launches, 29 us; 64-wide fp32, 4 layers
+// 28 / 23 us; 128-wide 28 / 47 us, with bf16 operands 28 / 32 us.  138 models up to 260 wide, whole calls: 13 % faster,
+// at worst 7 % slower.)
+int narrow_first(betty_handle h, bool rop, Elem elem) {
+  const int L = h->L;
+  if (L < 2 || L > NARROW_MAX_L || h->tune_narrow == 0) return 0;
+  const bool bf16 = elem == ELEM_BF16, relu = h->desc.act == BETTY_ACT_RELU;
+  NarrowNet net{};
+  net.L = L;
+  for (int l = 0; l <= L; ++l) net.n[l] = h->dims[l];
+  if (narrow_lds(net, elem, bf16) > 150 * 1024) return 0;
+  if (h->tune_narrow > 0) return L >= 3 ? h->tune_narrow : 1;
+  const bool narrow_out = net.n[L] <= LAST_ROP_MAX_C;
+  const double launch = 4.7, per_kb = 1.0 / 9, es = bf16 ? 2.0 : 4.0, fwd_es = !rop && bf16 && relu ? 4.0 : es;
+  const double launches = launch * (2 * L - (narrow_out ? 2 : rop && net.n[L] <= 32 ? 1 : 0)), pairs = rop ? 2.0 : 1.0;
+  double fused = 6.0, first_link = 0;
+  for (int l = 1; l <= L; ++l) {
+    const double kb = (double)net.n[l - 1] * net.n[l] / 1024.0;
+    const double forward = 1.6 + (l > 1 ? pairs : 1.0) * kb * fwd_es * per_kb;
+    if (l == 1) first_link = forward;
+    fused += forward + (l > 1 ? 1.6 + pairs * kb * es * per_kb : 0.0);
+  }
+  const int first = L >= 3 && fused - first_link + launch < fused ? 2 : 1;
+  return std::min(fused, fused - first_link + (L >= 3 ? launch : first_link)) < 0.92 * launches ? first : 0;
+}
+
 bool has_samples_form(betty_handle h, int K) { return h->desc.hp == BETTY_HP_REWEIGHT_NET || (h->desc.hp == BETTY_HP_PROXIMAL && K > 0); }
 
 bool use_samples(betty_handle h, int K, bool dense) {
-  return h->sets[0].samples && has_samples_form(h, K) && (h->tune_samples == 1 || samples_saving(h, K, dense) > 0);
+  return h->sets[0].samples && has_samples_form(h, K) && (h->tune_samples == 1 || (!narrow_first(h, true, h->sets[0].elem) && samples_saving(h, K, dense) > 0));
 }
 
 // Whether any call with steps takes that form (the estimate is linear in K beyond 1).
 bool plans_samples(betty_handle h) {
   if (h->tune_samples >= 0) return h->tune_samples == 1 && has_samples_form(h, 1);
+  if (narrow_first(h, true, h->desc.prec == BETTY_PREC_BF16_FP32ACC ? ELEM_BF16 : ELEM_F32)) return false;
   for (int K : {1, 1 << 20})
     for (bool dense : {false, true})
       if (has_samples_form(h, K) && samples_saving(h, K, dense) > 0) return true;
@@ -591,11 +624,12 @@ Pass train_pass(betty_handle h, OperandSet& os, const float* w, const float* lam
 Pass val_pass(OperandSet& os, const float* w) { return Pass{&os, 1, w}; }
 
 // a_l, phi'(z_l) (phi''), logits, per-sample loss, output delta
-void forward_and_loss(betty_handle h, const Pass* ps, int n, bool skip_last = false) {
+// (upto: only the activations of the layers up to that one)
+void forward_and_loss(betty_handle h, const Pass* ps, int n, int upto = 0) {
   const int L = h->L;
   const bool hybrid = hybrid_forward(h, *ps[0].os);
   const Elem elem = hybrid ? ELEM_F32 : ps[0].os->elem;     // operands of the forward products
-  for (int l = 1; l <= (skip_last ? L - 1 : L); ++l) {
+  for (int l = 1; l <= (upto > 0 ? upto : L); ++l) {
     const LayerInfo& li = h->layers[l - 1];
     const bool last = l == L;
     GemmBatch b;
@@ -626,7 +660,7 @@ void forward_and_loss(betty_handle h, const Pass* ps, int n, bool skip_last = fa
     }
     launch_gemm_batch(h->ctx, elem, plan_chain(h, elem, b), b, flops);
   }
-  if (skip_last) return;
+  if (upto > 0) return;
   const LayerInfo& lo = h->layers[L - 1];
   LossBatch lb;
   for (int i = 0; i < n; ++i) {
@@ -677,11 +711,67 @@ void backward_chain(betty_handle h, const Pass* ps, int n, int l_from = 0) {
   }
 }
 
+NarrowNet narrow_net(betty_handle h, int first) {
+  NarrowNet net{};
+  net.L = h->L; net.first = first;
+  for (int l = 0; l <= h->L; ++l) {
+    net.n[l] = h->dims[l];
+    net.np[l] = padup(h->dims[l]);
+  }
+  net.act = h->desc.act; net.loss = h->desc.loss;
+  return net;
+}
+
+void narrow_forward_backward(betty_handle h, const Pass* ps, int n, int first) {
+  const int L = h->L;
+  const bool hybrid = hybrid_forward(h, *ps[0].os);
+  if (first > 1) forward_and_loss(h, ps, n, first - 1);
+  NarrowGradArgs a{};
+  a.net = narrow_net(h, first);
+  a.hidden = h->desc.wnet_hidden;
+  double flops = 0;
+  for (int i = 0; i < n; ++i) {
+    OperandSet& os = *ps[i].os;
+    OperandSet& fs = hybrid ? h->sets[1] : os;
+    SideBuf& sb = os.side[ps[i].side];
+    SideBuf& fb = fs.side[ps[i].side];
+    NarrowGradSide& d = a.side[i];
+    d.X = h->at<void>(fb.X);
+    d.A1 = L > 1 ? h->at<void>(fb.A[1]) : nullptr;
+    for (int l = 1; l <= L; ++l) {
+      d.Wf[l - 1] = h->at<void>(fs.Wt[l - 1]);
+      d.Wn[l - 1] = h->at<void>(os.Wn[l - 1]);
+      d.bias[l - 1] = h->desc.has_bias ? ps[i].w + h->layers[l - 1].b_off : nullptr;
+      if (l < L) {
+        d.A[l - 1] = h->at<void>(sb.A[l]); d.At[l - 1] = h->at<void>(sb.At[l]);
+        d.dphi[l - 1] = h->f(sb.dphi[l]);
+        d.e2[l - 1] = ps[i].curvature && sb.e2[l] ? h->f(sb.e2[l]) : nullptr;
+      }
+      d.D[l - 1] = l > 1 ? h->at<void>(sb.D[l]) : nullptr; d.Dt[l - 1] = h->at<void>(sb.Dt[l]);
+      flops += (l > 1 ? 4.0 : first == 1 ? 2.0 : 0.0) * sb.B * h->layers[l - 1].n_in * h->layers[l - 1].n_out;
+    }
+    d.labels = h->at<Labels>(h->labels) + ps[i].side;
+    d.omega_fixed = ps[i].omega_fixed;
+    d.ZL = h->f(sb.ZL); d.P = h->f(sb.P); d.s = h->f(sb.s);
+    d.ell = h->f(ps[i].ell ? ps[i].ell : sb.ell);
+    d.omega = h->f(ps[i].omega ? ps[i].omega : sb.omega); d.dsig = h->f(ps[i].dsig ? ps[i].dsig : sb.dsig);
+    d.B = sb.B; d.Bp = sb.Bp;
+    d.reweight = (ps[i].side == 0 && h->desc.hp == BETTY_HP_REWEIGHT_NET) ? 1 : 0;
+    d.inv_batch = ps[i].sign / (float)sb.B;
+    if (ps[i].theta) a.theta = ps[i].theta;
+  }
+  launch_narrow_grad(h->ctx, ps[0].os->elem, hybrid, a, n, flops);
+}
+
 // Forward pass, loss and backward chain.  A narrow output layer (see LastGradArgs) goes through
 // one vector kernel that produces the logits, the loss quantities and delta_{L-1}.
 void forward_backward(betty_handle h, const Pass* ps, int n) {
   const int L = h->L;
   const LayerInfo& lo = h->layers[L - 1];
+  if (const int first = h->fixed_grouping && ps[0].os->elem == ELEM_BF16 ? 0 : narrow_first(h, false, ps[0].os->elem)) {
+    narrow_forward_backward(h, ps, n, first);
+    return;
+  }
   // (also with the fp32 forward of ReLU networks: the output layer has no mask to protect, and the
   // operand-type copy of a_{L-1} exists either way)
   const bool narrow = L >= 2 && lo.n_out <= LAST_ROP_MAX_C;
@@ -690,7 +780,7 @@ void forward_backward(betty_handle h, const Pass* ps, int n) {
     backward_chain(h, ps, n);
     return;
   }
-  forward_and_loss(h, ps, n, true);
+  forward_and_loss(h, ps, n, L - 1);
   LastGradArgs a{};
   for (int i = 0; i < n; ++i) {
     SideBuf& sb = ps[i].os->side[ps[i].side];
@@ -914,7 +1004,44 @@ void side_wgrad(betty_handle h, OperandSet& os, const WgradSink& sink, int l) {
   h->ctx.stream = main;
 }
 
+// The forward-over-reverse pass of narrow.hip along the direction in os.Vt, os.Vn and vflat; with cvec only the
+// R-forward and the loss's derivative along it.
+void narrow_rop(betty_handle h, OperandSet& os, const float* vflat, int first, float* cvec) {
+  SideBuf& sb = os.side[0];
+  const int L = h->L;
+  if (first > 1) r_forward(h, os, vflat, false, first - 1);
+  NarrowRopArgs a{};
+  a.net = narrow_net(h, first);
+  a.X = h->at<void>(sb.X); a.RA1 = h->at<void>(os.RA[1]);
+  double flops = 0;
+  for (int l = 1; l <= L; ++l) {
+    const LayerInfo& li = h->layers[l - 1];
+    a.Wt[l - 1] = h->at<void>(os.Wt[l - 1]); a.Vt[l - 1] = h->at<void>(os.Vt[l - 1]);
+    a.Wn[l - 1] = h->at<void>(os.Wn[l - 1]); a.Vn[l - 1] = h->at<void>(os.Vn[l - 1]);
+    a.cbias[l - 1] = h->desc.has_bias ? vflat + li.b_off : nullptr;
+    if (l < L) {
+      a.A[l - 1] = h->at<void>(sb.A[l]);
+      a.dphi[l - 1] = h->f(sb.dphi[l]);
+      a.e2[l - 1] = sb.e2[l] ? h->f(sb.e2[l]) : nullptr;
+      a.Rz[l - 1] = sb.e2[l] && !cvec ? h->f(os.Rz[l]) : nullptr;
+      a.RAt[l - 1] = cvec ? nullptr : h->at<void>(os.RAt[l]);
+    }
+    a.D[l - 1] = h->at<void>(sb.D[l]);
+    a.RDt[l - 1] = h->at<void>(os.RDt[l]);
+    flops += (l > 1 ? cvec ? 4.0 : 8.0 : first == 1 ? 2.0 : 0.0) * sb.B * li.n_in * li.n_out;
+  }
+  a.P = h->f(sb.P); a.s = h->f(sb.s); a.Z = h->f(sb.ZL); a.labels = h->at<Labels>(h->labels);
+  a.cvec = cvec;
+  a.B = sb.B; a.Bp = sb.Bp;
+  launch_narrow_rop(h->ctx, os.elem, a, flops);
+}
+
 void hvp_cached(betty_handle h, OperandSet& os, const float* vflat, const WgradSink& sink, bool pipelined = false) {
+  if (const int first = narrow_first(h, true, os.elem)) {
+    narrow_rop(h, os, vflat, first, nullptr);
+    wgrad_batch(h, os, 0, true, sink);
+    return;
+  }
   SideBuf& sb = os.side[0];
   const int L = h->L, B = sb.B, Bp = sb.Bp;
   const bool pipe = pipelined && h->side_stream && L >= 2;
@@ -1011,7 +1138,9 @@ void mixed_reweight_seq(betty_handle h, OperandSet& os, const float* lam, const 
   const LayerInfo& lo = h->layers[L - 1];
   // c_i is linear in the direction, so the scale is applied once, to the final sum over samples
   if (!copies_current) make_shadows(h, os, {Shadows{qflat, nullptr, &os.Vt}});   // else os.Vt already holds qflat
-  if (L >= 2 && lo.n_out <= LAST_ROP_MAX_C) {
+  if (const int first = narrow_first(h, true, os.elem)) {
+    narrow_rop(h, os, qflat, first, h->f(os.cvec));
+  } else if (L >= 2 && lo.n_out <= LAST_ROP_MAX_C) {
     // narrow output layer: the last product and the directional derivative in one vector kernel
     r_forward(h, os, qflat, false, L - 1);
     LastRopArgs a{};
@@ -1647,7 +1776,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
   h->use_pipeline = large && desc->prec == BETTY_PREC_FP32;
   h->fd_paired = !large;
   h->max_Bp = std::max(padup(desc->batch_train), padup(desc->batch_val));
-  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,pair=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>,linear=<0|1>" (see plan_chain)
+  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,pair=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>,linear=<0|1>,narrow=<0|1|2>" (see plan_chain)
   if (const char* t = getenv("BETTY_TUNE")) {
     int v;
     if (const char* q = strstr(t, "wgrad=")) if (sscanf(q + 6, "%d", &v) == 1 && (v == GEMM_128x1 || v == GEMM_64x1)) h->tune_wgrad_cfg = v;
@@ -1659,6 +1788,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
     if (const char* q = strstr(t, "pipe=")) if (sscanf(q + 5, "%d", &v) == 1) h->use_pipeline = v != 0;
     if (const char* q = strstr(t, "samples=")) if (sscanf(q + 8, "%d", &v) == 1) h->tune_samples = v != 0;
     if (const char* q = strstr(t, "pair=")) if (sscanf(q + 5, "%d", &v) == 1) h->tune_pair_forced = v == 1;
+    if (const char* q = strstr(t, "narrow=")) if (sscanf(q + 7, "%d", &v) == 1 && v >= 0 && v <= 2) h->tune_narrow = v;
     if (const char* q = strstr(t, "linear=")) if (sscanf(q + 7, "%d", &v) == 1) h->tune_linear = v != 0;
     if (const char* q = strstr(t, "fd2=")) if (sscanf(q + 4, "%d", &v) == 1) h->fd_paired = v != 0;
   }

@@ -39,36 +39,6 @@ namespace betty {
 // epilogue helpers
 // ------------------------------------------------------------------------------------------
 
-__device__ __forceinline__ void act_eval(int act, float z, float& a, float& d1, float& d2) {
-  if (act == BETTY_ACT_RELU) {
-    const bool pos = z > 0.f;
-    a = pos ? z : 0.f; d1 = pos ? 1.f : 0.f; d2 = 0.f;
-  } else if (act == BETTY_ACT_GELU_ERF) {
-    const float Phi = 0.5f * (1.f + erff(z * 0.70710678118654752f));
-    const float pdf = 0.39894228040143268f * expf(-0.5f * z * z);
-    a = z * Phi; d1 = Phi + z * pdf; d2 = pdf * (2.f - z * z);
-  } else {
-    a = z; d1 = 1.f; d2 = 0.f;
-  }
-}
-
-typedef float f32x4v __attribute__((ext_vector_type(4)));
-
-template <typename T> __device__ __forceinline__ void store1(T* p, float x);
-template <> __device__ __forceinline__ void store1<float>(float* p, float x) { *p = x; }
-template <> __device__ __forceinline__ void store1<__bf16>(__bf16* p, float x) { *p = (__bf16)x; }
-
-// four consecutive elements, p aligned to 4 elements
-template <typename T> __device__ __forceinline__ void store4(T* p, const float (&x)[4]);
-template <> __device__ __forceinline__ void store4<float>(float* p, const float (&x)[4]) {
-  *(float4*)p = make_float4(x[0], x[1], x[2], x[3]);
-}
-template <> __device__ __forceinline__ void store4<__bf16>(__bf16* p, const float (&x)[4]) {
-  typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
-  bf16x4 v = {(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
-  *(bf16x4*)p = v;
-}
-
 // One 32x32 MFMA block as seen by one lane: 16 accumulators = rows rb + 8*(k/4) + k%4 (k = 0..15)
 // of column col, with rb = block row + 4*(lane/32).  M, N = valid extent.
 //
@@ -797,21 +767,6 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
 // l / 16 of A and of B, so one request covers 16 rows x 64 bytes.  One round trip, U to 4 U MFMA
 // instructions, one pass through LDS (partial tiles summed in wavefront order, bit-reproducible),
 // then one output element per thread.
-template <typename T> struct MfmaStep16;
-template <> struct MfmaStep16<__bf16> {
-  static __device__ __forceinline__ void run(const u32x4& a, const u32x4& b, f32x4v& acc) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
-  }
-};
-template <> struct MfmaStep16<float> {
-  static __device__ __forceinline__ void run(const u32x4& a, const u32x4& b, f32x4v& acc) {
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
-  }
-};
-
 constexpr int G16_PITCH = 17;                      // row pitch of a partial tile in LDS (floats)
 
 template <typename T, int U, int MODE>

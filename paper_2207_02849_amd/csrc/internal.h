@@ -181,6 +181,53 @@ template <> struct MfmaChunk<float> {
   }
 };
 
+// The same for a 16 x 16 block and 64 bytes of K: lane l supplies row l % 16 and chunk l / 16 of A and of B; register r of
+// lane l of the result holds C[4*(l/16) + r][l%16].
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+template <typename T> struct MfmaStep16;
+template <> struct MfmaStep16<__bf16> {
+  static __device__ __forceinline__ void run(const u32x4& a, const u32x4& b, f32x4v& acc) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+  }
+};
+template <> struct MfmaStep16<float> {
+  static __device__ __forceinline__ void run(const u32x4& a, const u32x4& b, f32x4v& acc) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+  }
+};
+
+
+__device__ __forceinline__ void act_eval(int act, float z, float& a, float& d1, float& d2) {
+  if (act == BETTY_ACT_RELU) {
+    const bool pos = z > 0.f;
+    a = pos ? z : 0.f; d1 = pos ? 1.f : 0.f; d2 = 0.f;
+  } else if (act == BETTY_ACT_GELU_ERF) {
+    const float Phi = 0.5f * (1.f + erff(z * 0.70710678118654752f));
+    const float pdf = 0.39894228040143268f * expf(-0.5f * z * z);
+    a = z * Phi; d1 = Phi + z * pdf; d2 = pdf * (2.f - z * z);
+  } else {
+    a = z; d1 = 1.f; d2 = 0.f;
+  }
+}
+
+template <typename T> __device__ __forceinline__ void store1(T* p, float x);
+template <> __device__ __forceinline__ void store1<float>(float* p, float x) { *p = x; }
+template <> __device__ __forceinline__ void store1<__bf16>(__bf16* p, float x) { *p = (__bf16)x; }
+
+// four consecutive elements, p aligned to 4 elements
+template <typename T> __device__ __forceinline__ void store4(T* p, const float (&x)[4]);
+template <> __device__ __forceinline__ void store4<float>(float* p, const float (&x)[4]) {
+  *(float4*)p = make_float4(x[0], x[1], x[2], x[3]);
+}
+template <> __device__ __forceinline__ void store4<__bf16>(__bf16* p, const float (&x)[4]) {
+  typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
+  bf16x4 v = {(__bf16)x[0], (__bf16)x[1], (__bf16)x[2], (__bf16)x[3]};
+  *(bf16x4*)p = v;
+}
+
 // The mixed term of finite differences for L2 decay, -2 exp(lam) w q with q = alpha p: the central difference
 // of grad_lambda along q, formed in double and rounded once.
 __device__ __forceinline__ float fd_mixed_l2(float lam, float w, float alpha, float p) {
@@ -342,6 +389,48 @@ void launch_adam(Ctx&, float* x, const float* g, float* m, float* v, float lr, f
 void launch_weighted_loss_sum(Ctx&, const float* s, const float* ell, int rows, const double* partial, int n, float* out);
 void launch_label_noise(Ctx&, const int32_t* y, const uint32_t* words, const int32_t* alt,
                         unsigned long long threshold, int n, int32_t* y_out, uint8_t* mask);
+
+// ---- narrow.hip : all layers of a few samples in one workgroup ----------------------------------------
+// Everything per layer l = 1 .. L is indexed by l - 1 (weights and what leaves layer l); operands as in the workspace.
+constexpr int NARROW_MAX_L = 8, NARROW_ROWS = 16;
+struct NarrowSplit { int ks, per, by_nt; };            // K groups, steps of each; multiplier for division by the tiles (narrow_splits)
+struct NarrowNet {
+  int L, first;                       // the first layer the kernel does itself: 1, or 2 with a_1 (R a_1) formed before
+  int n[NARROW_MAX_L + 1], np[NARROW_MAX_L + 1];       // widths, padded
+  NarrowSplit fwd[NARROW_MAX_L], bwd[NARROW_MAX_L];
+  int act, loss, pitch, ldz;          // elements between rows of the LDS operands; floats between rows of the logits
+};
+// First-order pass: activations, loss, deltas
+struct NarrowGradSide {
+  const void* X;                      // operand type of the forward products
+  const void* A1;                     // ... as is a_1 where first = 2
+  const void* Wf[NARROW_MAX_L];       // W_l^T for the forward products
+  const void* Wn[NARROW_MAX_L];       // W_l for the backward products
+  const float* bias[NARROW_MAX_L];    // or null
+  void* A[NARROW_MAX_L]; void* At[NARROW_MAX_L]; void* D[NARROW_MAX_L]; void* Dt[NARROW_MAX_L];   // (D null for layer 1)
+  float* dphi[NARROW_MAX_L]; float* e2[NARROW_MAX_L];                                               // (e2 null: not asked for)
+  const Labels* labels; const float* omega_fixed;
+  float* ZL; float* P; float* ell; float* s; float* omega; float* dsig;
+  int B, Bp, reweight; float inv_batch;
+};
+struct NarrowGradArgs { NarrowNet net; NarrowGradSide side[2]; int blocks0; const float* theta; int hidden; };
+// Forward-over-reverse pass: R-forward, loss Hessian, R-backward; or (cvec) R-forward and <dl_i/dz, Rz_L,i>
+struct NarrowRopArgs {
+  NarrowNet net;
+  const void* X; const void* RA1;     // (RA1: R a_1 where first = 2)
+  const void* Wt[NARROW_MAX_L]; const void* Vt[NARROW_MAX_L]; const void* Wn[NARROW_MAX_L]; const void* Vn[NARROW_MAX_L];
+  const float* cbias[NARROW_MAX_L];
+  const void* A[NARROW_MAX_L]; const void* D[NARROW_MAX_L];
+  const float* dphi[NARROW_MAX_L]; const float* e2[NARROW_MAX_L]; float* Rz[NARROW_MAX_L];
+  void* RAt[NARROW_MAX_L]; void* RDt[NARROW_MAX_L];
+  const float* P; const float* s; const float* Z; const Labels* labels; float* cvec;
+  int B, Bp;
+};
+static_assert(sizeof(NarrowGradArgs) <= 3072 && sizeof(NarrowRopArgs) <= 3072, "passed by value as kernel arguments");
+// LDS of a workgroup, and the padded row of its operands; `wide`: the forward operands are fp32
+size_t narrow_lds(NarrowNet&, Elem, bool wide);
+void launch_narrow_grad(Ctx&, Elem, bool wide, NarrowGradArgs&, int n_sides, double flops);
+void launch_narrow_rop(Ctx&, Elem, NarrowRopArgs&, double flops);
 
 // ---- linear.hip : a whole hypergradient of a small single-layer model in one workgroup ----------------
 struct LinearArgs {

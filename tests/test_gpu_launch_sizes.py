@@ -46,6 +46,36 @@ def test_small_launch_forms(dims, batch, loss, prec, tol):
 
 
 @pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
+@pytest.mark.parametrize("first", [1, 2])
+@pytest.mark.parametrize("dims,batch,kind,act,loss,bias", [
+    ((5, 16, 16), 16, "l2", "gelu", "ce", True),              # one tile, one workgroup
+    ((33, 17, 15, 1), 17, "l2", "gelu", "mse", True),         # one past, one short; a sample of its own
+    ((40, 130, 129, 9), 40, "reweight", "gelu", "ce", False), # more tiles than wavefronts
+    ((200, 30, 64, 300), 31, "l2", "relu", "ce", True),       # an output wider than the layers, K left over
+    ((9, 20, 40, 33, 20, 12, 30, 8, 5), 50, "reweight", "relu", "ce", True),   # eight layers
+    ((12, 65, 20, 4), 33, "proximal", "gelu", "ce", True),
+])
+def test_narrow_models_in_one_workgroup(dims, batch, kind, act, loss, bias, first, prec, tol, monkeypatch):
+    """All layers of 16 samples in one workgroup, against the oracle and with the launches per layer beside it."""
+    wl = wk.tiny(kind=kind, act=act, dims=dims, batch=batch, loss=loss, prec=prec, has_bias=bias, hidden=40)
+    prob = oracle_problem(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    v = orc.lower_grad(prob, wl.w, wl.lam)[1]
+    refs = dict(grad=v, upper=orc.upper_grad(prob, wl.w)[1], hvp=orc.hvp(prob, wl.w, wl.lam, v),
+                neumann=orc.hypergrad_neumann(prob, wl.w, wl.lam, 2, 0.02))
+    for form in (first, 0):
+        monkeypatch.setenv("BETTY_TUNE", f"narrow={form},samples=0")
+        b = binding.from_workload(wl)
+        got = dict(grad=b.betty_lower_grad(w, lam), upper=b.betty_upper_grad(w), hvp=b.betty_hvp(w, lam, dev(v)),
+                   neumann=b.betty_hypergrad_neumann(w, lam, 2, 0.02))
+        for name, ref in refs.items():
+            assert rel_l2(host(got[name]), ref) < tol, (name, form)
+        if act == "gelu":
+            assert rel_l2(host(b.betty_hypergrad_fd(w, lam, 1, 0.02)), orc.hypergrad_fd(prob, wl.w, wl.lam, 1, 0.02, 0.01)) < 1e-4
+        b.close()
+
+
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
 @pytest.mark.parametrize("kind,samples", [("l2", 0), ("reweight", 1)])
 @pytest.mark.parametrize("dims,batch", [
     ((64, 64, 64, 40), 64),                  # whole tiles, one k-tile a group
