@@ -75,6 +75,8 @@ struct OperandSet {
 
 }  // namespace
 
+namespace { struct Pass; }
+
 struct betty_handle_s {
   betty_problem_desc desc{};
   std::vector<int> dims;
@@ -94,6 +96,7 @@ struct betty_handle_s {
   size_t vec_g = 0, vec_v = 0, vec_p = 0, vec_Hv = 0;
   size_t bias_pm[2] = {0, 0};        // biases of the two perturbed points (flat layout; only the bias slices are used)
   size_t partials = 0, scalars = 0;
+  size_t fd_z1 = 0;          // z_1 of the train batch at w (finite differences)
   size_t sums = 0;           // what the weight-gradient launches sum up beside their results (Epilogue::partial)
   size_t labels = 0;         // Labels[2]: train, validation
   size_t lin_gram = 0;       // (linear.hip)
@@ -157,6 +160,8 @@ struct betty_handle_s {
   // the rule would save is small but for ragged models: a step of 3072-1024-1024-1024-10 at batch 256 72.6 / 72.5 us,
   // 1024-512-512-10 36.9 / 35.6, 2048-2048-2048-1000 at 512 181 / 173, 777-301-65-33 at 130 48.3 / 35.3.
   bool fixed_grouping = false;
+  const Pass* z1_pass = nullptr;       // first-order passes leave z_1 of this pass in fd_z1
+  bool layer1_done = false;                   // a_1 and phi'(z_1) of the passes are there already (finite differences)
   bool as_pair = false;                       // choose kernels for single passes as if two shared the launch
   bool tune_pair_forced = false;              // 64-tiles with a two-way K split for every activation-shaped product
   int tune_narrow = -1;                       // narrow.hip: 0 never, 1 or 2 that first layer wherever it fits, -1 by size
@@ -446,6 +451,7 @@ void plan(betty_handle h) {
   h->ws_product = pl.off;
   size_t n_sums = 4096;      // one per finishing wavefront of at most 64-tiles (16-tiles: at most 1024 of them) and per bias
   for (const LayerInfo& li : h->layers) n_sums += 4 * (size_t)Extent::up(li.n_in, 64) * Extent::up(li.n_out, 64) + li.n_out + 4096;
+  if (h->L >= 2) h->fd_z1 = pl.take((size_t)h->sets[0].side[0].Bp * h->layers[0].n_out_p * 4);
   h->sums = pl.take(2 * n_sums * sizeof(double));      // (conjugate gradient keeps those of two launches)
   if (plans_samples(h)) plan_samples(h, pl, h->sets[0]);
   if (h->desc.loss == BETTY_LOSS_MSE && use_linear(h, false))
@@ -629,13 +635,16 @@ void forward_and_loss(betty_handle h, const Pass* ps, int n, int upto = 0) {
   const int L = h->L;
   const bool hybrid = hybrid_forward(h, *ps[0].os);
   const Elem elem = hybrid ? ELEM_F32 : ps[0].os->elem;     // operands of the forward products
-  for (int l = 1; l <= (upto > 0 ? upto : L); ++l) {
+  for (int l = h->layer1_done ? 2 : 1; l <= (upto > 0 ? upto : L); ++l) {
     const LayerInfo& li = h->layers[l - 1];
     const bool last = l == L;
     GemmBatch b;
     double flops = 0;
-    for (int i = 0; i < n; ++i) {
-      const Pass& ps_i = ps[i];
+    // (finite differences: z_1 of the train batch, whether or not that batch is among the passes)
+    const Pass* z1 = l == 1 ? h->z1_pass : nullptr;
+    const bool extra = z1 && !(ps[0].os == z1->os && ps[0].side == z1->side);
+    for (int i = 0; i < n + (extra ? 1 : 0); ++i) {
+      const Pass& ps_i = i < n ? ps[i] : *z1;
       OperandSet& fs = hybrid ? h->sets[1] : *ps_i.os;
       SideBuf& sb = ps_i.os->side[ps_i.side];
       SideBuf& fb = fs.side[ps_i.side];
@@ -649,6 +658,7 @@ void forward_and_loss(betty_handle h, const Pass* ps, int n, int upto = 0) {
       if (last) {
         e.f0 = h->f(sb.ZL);
       } else {
+        if (z1 && ps_i.side == z1->side) e.f0 = h->f(h->fd_z1);
         e.dphi_out = h->f(sb.dphi[l]);
         e.d2_out = ps_i.curvature && sb.e2[l] ? h->f(sb.e2[l]) : nullptr;
         e.out = h->at<void>(fb.A[l]); e.ld = li.n_out_p;
@@ -658,7 +668,10 @@ void forward_and_loss(betty_handle h, const Pass* ps, int n, int upto = 0) {
       p.e = e;
       flops += 2.0 * sb.B * li.n_in * li.n_out;
     }
-    launch_gemm_batch(h->ctx, elem, plan_chain(h, elem, b), b, flops);
+    b.n -= extra;                                  // (the passes' kernel, and with it their bits, stay what they are without it)
+    const int cfg = plan_chain(h, elem, b);
+    b.n += extra;
+    launch_gemm_batch(h->ctx, elem, cfg, b, flops);
   }
   if (upto > 0) return;
   const LayerInfo& lo = h->layers[L - 1];
@@ -725,7 +738,7 @@ NarrowNet narrow_net(betty_handle h, int first) {
 void narrow_forward_backward(betty_handle h, const Pass* ps, int n, int first) {
   const int L = h->L;
   const bool hybrid = hybrid_forward(h, *ps[0].os);
-  if (first > 1) forward_and_loss(h, ps, n, first - 1);
+  if (first > 1 && !h->layer1_done) forward_and_loss(h, ps, n, first - 1);
   NarrowGradArgs a{};
   a.net = narrow_net(h, first);
   a.hidden = h->desc.wnet_hidden;
@@ -843,6 +856,7 @@ struct WgradSink {
   bool sums_split = false;  // ... its sums over the steps are value and remainder (samples_accumulate)
   const float* eps = nullptr;      // EPI_WGRAD_FD
   OperandSet* minus = nullptr;     // the second perturbed point: its products are added (its deltas carry the sign)
+  bool minus_summed = false;       // ... and layer 1's deltas of both points stand added in the second's place
   bool sum_p = false;
   int* sums = nullptr;             // non-null: the launch leaves its sums in vec partials, their number here
 };
@@ -867,9 +881,10 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
       const void* aT = l == 1 ? h->at<void>(sb.XT) : h->at<void>(sb.At[l - 1]);
       if (k.minus) {
         SideBuf& mb = k.minus->side[side];
-        set_pairs(p.g, aT, Bp, h->at<void>(sb.Dt[l]), Bp, B, l == 1 ? aT : h->at<void>(mb.At[l - 1]), Bp,
+        if (k.minus_summed && l == 1) set_pairs(p.g, aT, Bp, h->at<void>(mb.Dt[1]), Bp, B, nullptr, 0, nullptr, 0, 0);
+        else set_pairs(p.g, aT, Bp, h->at<void>(sb.Dt[l]), Bp, B, l == 1 ? aT : h->at<void>(mb.At[l - 1]), Bp,
                   h->at<void>(mb.Dt[l]), Bp, B);
-        flops += 4.0 * B * li.n_in * li.n_out;
+        flops += (k.minus_summed && l == 1 ? 2.0 : 4.0) * B * li.n_in * li.n_out;
       } else if (!rop) {
         set_pairs(p.g, aT, Bp, h->at<void>(sb.Dt[l]), Bp, B, nullptr, 0, nullptr, 0, 0);
         flops += 2.0 * B * li.n_in * li.n_out;
@@ -913,9 +928,10 @@ void wgrad_batch(betty_handle h, OperandSet& os, int side, bool rop, const Wgrad
       if (h->desc.has_bias) {
         BiasJob& j = b.bias[b.n_bias++];
         j = BiasJob{};
-        j.Mt2 = k.minus ? h->at<void>(k.minus->side[side].Dt[l]) : nullptr;
+        const bool summed = k.minus_summed && l == 1;
+        j.Mt2 = k.minus && !summed ? h->at<void>(k.minus->side[side].Dt[l]) : nullptr;
         j.eps = k.eps; j.sum_p = k.sum_p;
-        j.Mt = rop ? h->at<void>(os.RDt[l]) : h->at<void>(sb.Dt[l]);
+        j.Mt = rop ? h->at<void>(os.RDt[l]) : h->at<void>(summed ? k.minus->side[side].Dt[l] : sb.Dt[l]);
         j.ld = Bp; j.rows = li.n_out; j.k = B; j.mode = k.mode;
         if (k.sums_split) { j.Mt = h->at<void>(os.sumRD[l]); j.ld = 2 * Bp; j.k = (B + 63) / 64 * 128; }
         j.C = k.C ? k.C + li.b_off : nullptr;
@@ -2073,10 +2089,11 @@ betty_status betty_hypergrad_chain3(betty_handle hp, betty_handle hf, const floa
 }
 
 // The two points w +- eps q, q = scale v, as operands: both at once, or the one of `signs` (1 = plus, 2 = minus).
+// (layer1: as the others; otherwise its place for W_1^T takes the direction's V_1^T, or nothing where signs = 2)
 static void make_perturbed_operands(betty_handle h, const float* w, const float* v, float* eps, float scale, int signs,
-                                    int sums, float eps_scale) {
+                                    int sums, float eps_scale, bool layer1) {
   OperandSet* os[2] = {&fd_operands(h), &h->fd_minus};
-  for (int i0 = 0; i0 < h->L; i0 += MAX_PROBLEMS) {
+  for (int i0 = !layer1 && signs == 2 ? 1 : 0; i0 < h->L; i0 += MAX_PROBLEMS) {
     PerturbBatch b;
     b.n = std::min(MAX_PROBLEMS, h->L - i0);
     b.eps = sums ? nullptr : eps; b.scale = scale; b.signs = signs;
@@ -2087,6 +2104,7 @@ static void make_perturbed_operands(betty_handle h, const float* w, const float*
       j = PerturbJob{};
       j.w = w + li.w_off; j.v = v + li.w_off; j.rows = li.n_in; j.cols = li.n_out;
       j.ld = li.n_out_p; j.ldT = li.n_in_p;
+      if (!layer1 && i0 + k == 0) { j.w = nullptr; j.outT[0] = h->f(os[0]->Wt[0]); continue; }
       if (h->desc.has_bias) { j.b = w + li.b_off; j.bv = v + li.b_off; }
       for (int s = 0; s < 2; ++s) {
         j.out[s] = i0 + k > 0 ? h->f(os[s]->Wn[i0 + k]) : nullptr; j.outT[s] = h->f(os[s]->Wt[i0 + k]);
@@ -2111,6 +2129,14 @@ static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, f
   float* v = h->f(h->vec_v); float* p = h->f(h->vec_p); float* eps = h->f(h->scalars) + 1;
   int sums = 0;
   make_weight_operands(h, os, w);
+  // Layer 1 is linear in the perturbation: z_1 at w +- eps v is X W_1 + b_1 +- eps (X V_1 + c_1).  The first term is
+  // formed once, the second once for both points, and neither point needs operand copies of its first layer: half the
+  // products of the largest layer and most of the perturbation's traffic (5.3M parameters, 5 differences: 1260 -> 1086 us).
+  // (Not where a narrow model's first-order pass starts at layer 1.)
+  const LayerInfo& l1 = h->layers[0];
+  const bool split = h->L >= 2 && narrow_first(h, false, ELEM_F32) != 1 && (K > 0 || rw);
+  const Pass at_w = train_pass(h, os, w, lambda, false);
+  h->z1_pass = split ? &at_w : nullptr;
   WgradSink init{EPI_WGRAD_INIT, nullptr, nullptr, nullptr, v, K > 0 ? p : nullptr, 0.f, false};
   if (K > 0 || rw) init.sums = &sums;
   const float* omega_bar = nullptr;
@@ -2126,6 +2152,19 @@ static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, f
     wgrad_batch(h, os, 1, false, init);
     omega_bar = h->f(sb.omega_bar);
   }
+  h->z1_pass = nullptr;
+  auto first_layer = [&](const float* dir, float scale) {
+    SideBuf& mb = om.side[0];
+    Epilogue e = blank_epilogue(EPI_FWD_PM, h->desc.act);
+    e.colvec = h->desc.has_bias ? dir + l1.b_off : nullptr;
+    e.alpha = scale;
+    e.e = h->f(h->fd_z1); e.Rz = eps; e.ldf = l1.n_out_p;
+    e.dphi_out = h->f(sb.dphi[1]); e.d2_out = h->f(mb.dphi[1]);
+    e.out = h->at<void>(sb.A[1]); e.outT = h->at<void>(sb.At[1]); e.out2 = h->at<void>(mb.A[1]); e.outT2 = h->at<void>(mb.At[1]);
+    e.ld = l1.n_out_p; e.ldT = sb.Bp;
+    chain_gemm(h, ELEM_F32, h->at<void>(sb.X), l1.n_in_p, h->at<void>(os.Wt[0]), l1.n_in_p, l1.n_in, nullptr, 0, nullptr, 0, 0,
+               sb.B, l1.n_out, e, 2.0 * sb.B * l1.n_in * l1.n_out);
+  };
   Pass ps[2] = {Pass{&os, 0, h->f(h->bias_pm[0])}, Pass{&om, 0, h->f(h->bias_pm[1])}};
   for (Pass& q : ps) q.omega_fixed = omega_bar;
   ps[1].sign = -1.f;
@@ -2135,17 +2174,14 @@ static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, f
     // 5.3M parameters and 5 differences both take the same time (1282 and 1281 us).  Reweighting step 1023-509-251-10 with one difference: 145.3 -> 143.7 us.
     const int in_block = sums <= 4096 ? sums : 0;
     if (!in_block) launch_fd_eps(h->ctx, h->at<double>(h->sums), sums, eps_scale, scale, eps);
-    h->as_pair = true;
-    if (h->fd_paired) {
-      make_perturbed_operands(h, w, dir, eps, scale, 3, in_block, eps_scale);
-      passes(ps, 2);
-    } else {
-      for (int s = 0; s < 2; ++s) {
-        make_perturbed_operands(h, w, dir, eps, scale, 1 << s, in_block, eps_scale);
-        passes(ps + s, 1);
-      }
+    for (int s = 0; s < (h->fd_paired ? 1 : 2); ++s) {
+      make_perturbed_operands(h, w, dir, eps, scale, h->fd_paired ? 3 : 1 << s, in_block, eps_scale, !split);
+      if (split && s == 0) first_layer(dir, scale);
+      h->as_pair = true;
+      h->layer1_done = split;
+      passes(ps + s, h->fd_paired ? 2 : 1);
+      h->as_pair = h->layer1_done = false;
     }
-    h->as_pair = false;
   };
   for (int k = 0; k < K; ++k) {
     both(v, 1.f, [&](const Pass* q, int n) { forward_backward(h, q, n); });
@@ -2153,9 +2189,20 @@ static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, f
     WgradSink step{last && !rw ? EPI_WGRAD_FD_LAST : EPI_WGRAD_FD, dlambda, dl, last && l2 ? w : nullptr, v, p, alpha, false};
     step.eps = eps;
     step.minus = &om;
+    // Both points' gradients of layer 1 have the same left operand, so their deltas may be added (with their opposite
+    // signs: the difference) before the product instead of after it.  A launch of 4 us against half of that product, at
+    // some 70 TFLOP/s: from 2^28 multiplications.
+    step.minus_summed = h->L >= 2 && (double)sb.B * l1.n_in * l1.n_out >= 268435456.0;
     step.sum_p = last;
     sums = 0;
     if (!last || rw) step.sums = &sums;
+    if (step.minus_summed) {
+      AccumulateBatch acc;
+      acc.first = false; acc.last = true;
+      acc.n = 1;
+      acc.j[0] = AccumulateJob{h->at<void>(om.side[0].Dt[1]), h->f(sb.Dt[1]), 1.f, (size_t)l1.n_out_p * sb.Bp};
+      launch_accumulate(h->ctx, ELEM_F32, acc);
+    }
     wgrad_batch(h, os, 0, false, step);
   }
   const float* s = K > 0 ? p : v;

@@ -74,13 +74,16 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
   }
   if (MODE == EPI_GRAM || (MODE == EPI_RBWD && e.mode == EPI_GRAM) || col >= N || rb >= M) return;
   const long long ldx = MODE >= EPI_WGRAD ? e.ldc : e.ldf;
-  if constexpr (MODE == EPI_SAMPLE || MODE == EPI_FWD || MODE == EPI_FWD_LAST || MODE == EPI_RFWD || MODE == EPI_RFWD_LAST)
+  if constexpr (MODE == EPI_SAMPLE || MODE == EPI_FWD || MODE == EPI_FWD_LAST || MODE == EPI_RFWD || MODE == EPI_RFWD_LAST || MODE == EPI_FWD_PM)
     R.colv = e.colvec ? e.colvec[col] : 0.f;
 #pragma unroll
   for (int k = 0; k < NR; ++k) {
     const bool ok = epi_row<NR>(rb, k) < M;
     const int o = epi_offset<NR>(rb, k, ldx, col);
-    if constexpr (MODE == EPI_BWD) {
+    if constexpr (MODE == EPI_FWD_PM) {
+      R.a[k] = ok ? e.e[o] : 0.f;
+      R.b[k] = e.Rz[0];
+    } else if constexpr (MODE == EPI_BWD) {
       R.a[k] = ok ? e.dphi[o] : 0.f;
       R.b[k] = (ok && e.e_io) ? e.e_io[o] : 0.f;
     } else if constexpr (MODE == EPI_RFWD) {
@@ -160,6 +163,32 @@ __device__ __forceinline__ void epi_gram(const Epilogue& e, int M, int rb, int c
   }
 }
 
+// operand-typed copies: row-major element by element, transposed as 4-element vectors; rows beyond M
+// are written as zeros (they are padding of the transposed operand).  Either may be null.
+template <typename T, int NR>
+__device__ __forceinline__ void epi_copies(T* out, T* outT, int ld, int ldT, int M, int rb, int col, const float (&val)[NR]) {
+  if (out) {
+#pragma unroll
+    for (int k = 0; k < NR; ++k)
+      if (epi_row<NR>(rb, k) < M) store1<T>(out + (long long)epi_row<NR>(rb, k) * ld + col, val[k]);
+  }
+  if (outT) {
+    T* o = outT + (long long)col * ldT + rb;
+    float v[NR];
+#pragma unroll
+    for (int k = 0; k < NR; ++k) v[k] = epi_row<NR>(rb, k) < M ? val[k] : 0.f;
+    if constexpr (NR == 1) {
+      store1<T>(o, v[0]);
+    } else {
+#pragma unroll
+      for (int q = 0; q < NR / 4; ++q) {
+        const float quad[4] = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+        if (rb + 8 * q < M) store4<T>(o + 8 * q, quad);
+      }
+    }
+  }
+}
+
 template <typename T, int MODE, int NR>
 __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int rb, int col,
                                            const float (&acc)[NR], const EpiRegs<NR>& R, float& sum) {
@@ -197,6 +226,20 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
   }
   if constexpr (MODE == EPI_RFWD_LAST_HESS) {
     // val is set; fall through to the operand copies
+  } else if constexpr (MODE == EPI_FWD_PM) {
+#pragma unroll
+    for (int sg = 0; sg < 2; ++sg) {
+      float* const dphi = sg ? e.d2_out : e.dphi_out;
+#pragma unroll
+      for (int k = 0; k < NR; ++k) {
+        float d1, d2;
+        const float t = R.b[k] * (e.alpha * (acc[k] + R.colv));
+        act_eval(e.act, R.a[k] + (sg ? -t : t), val[k], d1, d2);
+        if (ok[k]) dphi[of[k]] = d1;
+      }
+      epi_copies<T, NR>((T*)(sg ? e.out2 : e.out), (T*)(sg ? e.outT2 : e.outT), e.ld, e.ldT, M, rb, col, val);
+    }
+    return;
   } else if constexpr (MODE == EPI_FWD) {
     float d1[NR], d2[NR];
 #pragma unroll
@@ -208,6 +251,13 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
 #pragma unroll
       for (int k = 0; k < NR; ++k)
         if (ok[k]) e.d2_out[of[k]] = d2[k];
+    }
+    if constexpr (sizeof(T) == 4) {
+      if (e.f0) {
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+          if (ok[k]) e.f0[of[k]] = acc[k] + R.colv;
+      }
     }
   } else if constexpr (MODE == EPI_SAMPLE) {
 #pragma unroll
@@ -323,50 +373,9 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
   } else {
     return;
   }
-  // operand-typed copies: row-major element by element, transposed as 4-element vectors; rows
-  // beyond M are written as zeros (they are padding of the transposed operand)
-#pragma unroll
-  for (int k = 0; k < NR; ++k)
-    if (!ok[k]) val[k] = 0.f;
-  if (e.out) {
-    T* o = (T*)e.out;
-#pragma unroll
-    for (int k = 0; k < NR; ++k)
-      if (ok[k]) store1<T>(o + (long long)epi_row<NR>(rb, k) * e.ld + col, val[k]);
-  }
-  if (e.outT) {
-    T* o = (T*)e.outT + (long long)col * e.ldT + rb;
-    if constexpr (NR == 1) {
-      store1<T>(o, val[0]);
-    } else {
-#pragma unroll
-      for (int q = 0; q < NR / 4; ++q) {
-        const float quad[4] = {val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
-        if (rb + 8 * q < M) store4<T>(o + 8 * q, quad);
-      }
-    }
-  }
-  if constexpr (MODE == EPI_FWD && sizeof(T) == 4) {
-    // fp32 forward of a bf16 problem: the bf16 operand copies of the activation leave from here too
-    if (e.out2) {
-      __bf16* o = (__bf16*)e.out2;
-#pragma unroll
-      for (int k = 0; k < NR; ++k)
-        if (ok[k]) store1<__bf16>(o + (long long)epi_row<NR>(rb, k) * e.ld + col, val[k]);
-    }
-    if (e.outT2) {
-      __bf16* o = (__bf16*)e.outT2 + (long long)col * e.ldT + rb;
-      if constexpr (NR == 1) {
-        store1<__bf16>(o, val[0]);
-      } else {
-#pragma unroll
-        for (int q = 0; q < NR / 4; ++q) {
-          const float quad[4] = {val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
-          if (rb + 8 * q < M) store4<__bf16>(o + 8 * q, quad);
-        }
-      }
-    }
-  }
+  epi_copies<T, NR>((T*)e.out, (T*)e.outT, e.ld, e.ldT, M, rb, col, val);
+  if constexpr (MODE == EPI_FWD && sizeof(T) == 4)         // fp32 forward of a bf16 problem: the bf16 operand copies of the activation leave from here too
+    epi_copies<__bf16, NR>((__bf16*)e.out2, (__bf16*)e.outT2, e.ld, e.ldT, M, rb, col, val);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1314,6 +1323,10 @@ static void launch_rect_mode(int mode, int total, hipStream_t st, const GemmBatc
 #define BETTY_CASE_R(M_) case M_: launch_rect<T, M_>(total, st, b, err); break;
     BETTY_CASE_R(EPI_FWD) BETTY_CASE_R(EPI_FWD_LAST) BETTY_CASE_R(EPI_BWD) BETTY_CASE_R(EPI_RFWD)
     BETTY_CASE_R(EPI_RFWD_LAST) BETTY_CASE_R(EPI_RBWD) BETTY_CASE_R(EPI_RFWD_LAST_HESS) BETTY_CASE_R(EPI_GRAM) BETTY_CASE_R(EPI_SAMPLE)
+    case EPI_FWD_PM:
+      if constexpr (sizeof(T) == 4) launch_rect<T, EPI_FWD_PM>(total, st, b, err);
+      else err = hipErrorInvalidValue;
+      break;
 #undef BETTY_CASE_R
     default: err = hipErrorInvalidValue; break;
   }
@@ -1325,6 +1338,10 @@ static void launch_chain_mode(int mode, int total, hipStream_t st, const GemmBat
 #define BETTY_CASE(M_) case M_: launch_one<T, BT, WPG, KG, M_>(total, st, b, err); break;
     BETTY_CASE(EPI_FWD) BETTY_CASE(EPI_FWD_LAST) BETTY_CASE(EPI_BWD) BETTY_CASE(EPI_RFWD)
     BETTY_CASE(EPI_RFWD_LAST) BETTY_CASE(EPI_RBWD) BETTY_CASE(EPI_RFWD_LAST_HESS) BETTY_CASE(EPI_GRAM) BETTY_CASE(EPI_SAMPLE)
+    case EPI_FWD_PM:
+      if constexpr (sizeof(T) == 4) launch_one<T, BT, WPG, KG, EPI_FWD_PM>(total, st, b, err);
+      else err = hipErrorInvalidValue;
+      break;
     default: err = hipErrorInvalidValue; break;
   }
 }
@@ -1408,6 +1425,10 @@ static void launch_small_mode(int mode, int total, hipStream_t st, const GemmBat
 #define BETTY_CASE_S(M_) case M_: launch_small<T, M_>(total, st, b); break;
     BETTY_CASE_S(EPI_FWD) BETTY_CASE_S(EPI_FWD_LAST) BETTY_CASE_S(EPI_BWD) BETTY_CASE_S(EPI_RFWD)
     BETTY_CASE_S(EPI_RFWD_LAST) BETTY_CASE_S(EPI_RBWD) BETTY_CASE_S(EPI_RFWD_LAST_HESS) BETTY_CASE_S(EPI_GRAM) BETTY_CASE_S(EPI_SAMPLE)
+    case EPI_FWD_PM:
+      if constexpr (sizeof(T) == 4) launch_small<T, EPI_FWD_PM>(total, st, b);
+      else err = hipErrorInvalidValue;
+      break;
     BETTY_CASE_S(EPI_WGRAD) BETTY_CASE_S(EPI_WGRAD_INIT) BETTY_CASE_S(EPI_WGRAD_NEUMANN)
     BETTY_CASE_S(EPI_WGRAD_NEUMANN_L2) BETTY_CASE_S(EPI_WGRAD_SGD) BETTY_CASE_S(EPI_WGRAD_SCALED)
     BETTY_CASE_S(EPI_WGRAD_FD) BETTY_CASE_S(EPI_WGRAD_FD_LAST) BETTY_CASE_S(EPI_WGRAD_CG)

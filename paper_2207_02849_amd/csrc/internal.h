@@ -40,7 +40,11 @@ struct GemmArgs {
 
 // What happens to a finished accumulator tile.
 enum EpiMode {
-  EPI_FWD = 1,             // z = acc + bias; out = phi(z); dphi_out = phi'(z); d2_out = phi''(z)
+  // Layer 1 at both points of a central difference (finite differences, fp32): t = alpha (acc + colvec), acc = X V_1,
+  // z+- = e +- Rz[0] t with e = z_1 at w and Rz[0] the step on the device; out, outT, dphi_out take the plus point's
+  // phi(z), phi'(z), out2, outT2 (fp32 here), d2_out the minus point's
+  EPI_FWD_PM = 0,
+  EPI_FWD = 1,             // z = acc + bias; out = phi(z); dphi_out = phi'(z); d2_out = phi''(z); with fp32 operands f0 = z if given
   EPI_FWD_LAST,          // f0 = acc + bias                       (logits)
   EPI_BWD,               // out = acc * dphi; e_io = acc * e_io   (delta of the layer below)
   EPI_RFWD,              // f0 = rz = acc + cbias (+ e); out = dphi * rz
@@ -86,7 +90,7 @@ struct Epilogue {
       float* dphi_out; float* d2_out;
       const float* dphi; float* e_io; const float* e; const float* Rz;
       long long ldf;
-      void* out2; void* outT2;           // EPI_FWD only: further copies of `out` in bf16 (same ld, ldT), or null
+      void* out2; void* outT2;           // EPI_FWD: further copies of `out` in bf16 (same ld, ldT), or null; EPI_FWD_PM
     };
     struct {                             // parameter-shaped modes
       float* C; long long ldc;           // fp32 row-major (flat parameter slice)
@@ -263,7 +267,8 @@ struct ConvertBatch {
 void launch_convert_batch(Ctx&, Elem, ConvertBatch&);
 
 // out+, out- = w + e v, w - e v as fp32 GEMM operands (as stored and transposed) with e = eps_scale /
-// (|scale| sqrt(sum of partial)) times scale, and the bias slices as they are; e (without scale) also goes to *eps
+// (|scale| sqrt(sum of partial)) times scale, and the bias slices as they are; e (without scale) also goes to *eps.
+// w null: outT[0] = v, transposed, and nothing else
 struct PerturbJob {
   const float* w; const float* v; int rows, cols;
   float* out[2]; int ld; float* outT[2]; int ldT;

@@ -1152,14 +1152,14 @@ __global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
     const long long row = (long long)min(r0 + ty + 16 * i, j.rows - 1) * j.cols;
     if (quads) {
       const long long at = row + min(c0 + 4 * tx, j.cols - 4);
-      const float4 a = *(const float4*)(j.w + at), d = *(const float4*)(j.v + at);
+      const float4 a = *(const float4*)((j.w ? j.w : j.v) + at), d = *(const float4*)(j.v + at);
       w[i][0] = a.x; w[i][1] = a.y; w[i][2] = a.z; w[i][3] = a.w;
       v[i][0] = d.x; v[i][1] = d.y; v[i][2] = d.z; v[i][3] = d.w;
     } else {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const long long at = row + min(c0 + 4 * tx + k, j.cols - 1);
-        w[i][k] = j.w[at]; v[i][k] = j.v[at];
+        w[i][k] = (j.w ? j.w : j.v)[at]; v[i][k] = j.v[at];
       }
     }
   }
@@ -1169,6 +1169,25 @@ __global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
     if (blockIdx.x == 0 && threadIdx.x == 0) b.eps_out[0] = eps;
   } else {
     eps = b.eps[0];
+  }
+  if (!j.w) {                                      // the direction itself, transposed
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) tile[ty + 16 * i][4 * tx + k] = v[i][k];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int cl = ty + 16 * i, c = c0 + cl, r = r0 + 4 * tx;
+      if (c >= j.cols) continue;
+      float* o = j.outT[0] + (long long)c * j.ldT + r;
+      const float x[4] = {tile[4 * tx][cl], tile[4 * tx + 1][cl], tile[4 * tx + 2][cl], tile[4 * tx + 3][cl]};
+      if (r + 3 < j.rows) *(float4*)o = make_float4(x[0], x[1], x[2], x[3]);
+      else
+#pragma unroll
+        for (int k = 0; k < 4; ++k) if (r + k < j.rows) o[k] = x[k];
+    }
+    return;
   }
   // biases ride along with the first row of tiles
   if (j.b && r0 == 0 && threadIdx.x < 64 && c0 + (int)threadIdx.x < j.cols) {
@@ -1216,11 +1235,11 @@ void launch_perturb(Ctx& ctx, PerturbBatch& b) {
   for (int i = 0; i < b.n; ++i) {
     b.block_begin[i] = blocks;
     blocks += ((b.j[i].cols + 63) / 64) * ((b.j[i].rows + 63) / 64);
-    params += (double)b.j[i].rows * b.j[i].cols;
+    params += (double)b.j[i].rows * b.j[i].cols * (b.j[i].w ? 8.0 + 8.0 * ((b.signs & 1) + (b.signs >> 1)) : 8.0);
   }
   b.block_begin[b.n] = blocks;
   if (blocks <= 0) return;
-  Launch l(ctx, BETTY_K_SHADOW, 0, (8.0 + 8.0 * ((b.signs & 1) + (b.signs >> 1))) * params);
+  Launch l(ctx, BETTY_K_SHADOW, 0, params);
   if (b.eps) perturb_kernel<false><<<blocks, 256, 0, ctx.stream>>>(b);
   else perturb_kernel<true><<<blocks, 256, 0, ctx.stream>>>(b);
 }

@@ -497,3 +497,15 @@ def test_proximal_series_keeps_its_bias_sums_beyond_bf16(B, monkeypatch):
     ref = orc.best_response_neumann(prob, np.zeros(b.d), np.zeros(b.d), u.astype(np.float64), K, alpha)
     assert rel_l2(got, ref) < 2e-5
     b.close()
+
+
+@pytest.mark.parametrize("kind,paired", [("l2", 1), ("l2", 0), ("reweight", 1)])
+def test_finite_differences_of_a_large_first_layer(kind, paired, monkeypatch):
+    """The first layer's deltas of both points are added before their product with the inputs; ragged tiles."""
+    wl = wk.tiny(kind=kind, act="gelu", dims=(1030, 1030, 5), batch=256, hidden=20)
+    prob = oracle_problem(wl)
+    monkeypatch.setenv("BETTY_TUNE", f"fd2={paired}")
+    b = binding.from_workload(wl)
+    got = host(b.betty_hypergrad_fd(dev(wl.w), dev(wl.lam), 2, 0.05, 0.01))
+    assert rel_l2(got, orc.hypergrad_fd(prob, wl.w, wl.lam, 2, 0.05, 0.01)) < (1e-3 if kind == "reweight" else 1e-4)
+    b.close()
