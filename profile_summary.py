@@ -19,7 +19,7 @@ import re
 import sqlite3
 
 HERE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2207_02849_amd")
-KERNEL_SOURCES = ["csrc/gemm.hip", "csrc/kernels.hip", "csrc/api.hip", "csrc/internal.h"]
+KERNEL_SOURCES = ["csrc/gemm.hip", "csrc/kernels.hip", "csrc/linear.hip", "csrc/narrow.hip", "csrc/api.hip", "csrc/internal.h"]
 
 
 def _code_only(text: str) -> str:
