@@ -288,7 +288,7 @@ def main():
             for i in range(4)]
     gemm_tflops = gemm[2] / (gemm[1] * 1e-3) / 1e12 if gemm[1] > 0 else 0.0
     # vector phase of the recurrence: it lives in the epilogue of the weight-gradient launch, so its
-    # rate is quoted over the whole fused launch (20 algorithmic bytes per parameter)
+    # rate is quoted over the whole fused launch (20 algorithmic bytes per parameter, 18 in layer 1)
     vec_gbs = upd[3] / (upd[1] * 1e-3) / 1e9 if upd[1] > 0 else 0.0
     total_ms = sum(v[1] for v in by_kind.values())
     phases = {k: {"launches_per_step": v[0], "ms_per_step": v[1], "share_of_step": v[1] / total_ms}
