@@ -2131,7 +2131,7 @@ static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, f
   make_weight_operands(h, os, w);
   // Layer 1 is linear in the perturbation: z_1 at w +- eps v is X W_1 + b_1 +- eps (X V_1 + c_1).  The first term is
   // formed once, the second once for both points, and neither point needs operand copies of its first layer: half the
-  // products of the largest layer and most of the perturbation's traffic (5.3M parameters, 5 differences: 1260 -> 1086 us).
+  // products of the largest layer and most of the perturbation's traffic (5.3M parameters, 5 differences: 1260 -> 1105 us).
   // (Not where a narrow model's first-order pass starts at layer 1.)
   const LayerInfo& l1 = h->layers[0];
   const bool split = h->L >= 2 && narrow_first(h, false, ELEM_F32) != 1 && (K > 0 || rw);

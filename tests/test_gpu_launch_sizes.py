@@ -507,5 +507,5 @@ def test_finite_differences_of_a_large_first_layer(kind, paired, monkeypatch):
     monkeypatch.setenv("BETTY_TUNE", f"fd2={paired}")
     b = binding.from_workload(wl)
     got = host(b.betty_hypergrad_fd(dev(wl.w), dev(wl.lam), 2, 0.05, 0.01))
-    assert rel_l2(got, orc.hypergrad_fd(prob, wl.w, wl.lam, 2, 0.05, 0.01)) < (1e-3 if kind == "reweight" else 1e-4)
+    assert rel_l2(got, orc.hypergrad_fd(prob, wl.w, wl.lam, 2, 0.05, 0.01)) < 1e-4
     b.close()
