@@ -415,17 +415,50 @@ void plan_samples(betty_handle h, Planner& pl, OperandSet& os) {
   }
 }
 
-// Single-layer models with a decay per parameter and fp32 operands that fit one workgroup (linear.hip): a step
-// there takes longer with every output, a launch hardly.  Ridge 64 - 1, batch 512, K = 20: 163 us by launches, 19 us;
-// softmax 200 - 4, batch 128, K = 5: 52 / 38 us (conjugate gradient 84 / 50); 32 - 16, batch 256, K = 5: 52 / 62 us (conjugate
-// gradient, twice the launches: 83 / 70).  (110 problems with 2 to 16 outputs: even at 13 to 16 outputs for the series
-// of a softmax model, half the time or less up to 5.)
-bool use_linear(betty_handle h, bool cg) {
+// Single-layer models with a decay per parameter and fp32 operands whose data fit one workgroup (linear.hip)
+bool has_linear_form(betty_handle h, bool cg) {
   const LayerInfo& li = h->layers[0];
-  if (h->L != 1 || h->desc.hp != BETTY_HP_L2_DECAY || h->desc.prec != BETTY_PREC_FP32 || h->tune_linear == 0) return false;
-  const bool mse = h->desc.loss == BETTY_LOSS_MSE;
-  return linear_fits(li.n_in + (h->desc.has_bias ? 1 : 0), li.n_out, h->desc.batch_train, h->desc.batch_val, mse, cg) &&
-         (h->tune_linear == 1 || li.n_out <= (mse || cg ? 16 : 12));
+  return h->L == 1 && h->desc.hp == BETTY_HP_L2_DECAY && h->desc.prec == BETTY_PREC_FP32 && h->tune_linear != 0 &&
+         linear_fits(li.n_in + (h->desc.has_bias ? 1 : 0), li.n_out, h->desc.batch_train, h->desc.batch_val,
+                     h->desc.loss == BETTY_LOSS_MSE, cg);
+}
+
+// Whether a call of K steps takes that form, by the estimated microseconds of either.  By launches a call costs little
+// more with every output or sample; in one workgroup a product is multiply-adds on four SIMDs (rows, columns: 256
+// threads each round), sums over chunks of features that one thread forms per sample and output (chunks), and over
+// chunks of samples per parameter (update), each times the outputs, and the beginning costs as much as several steps.  The
+// Gram form of the squared error pays for X^T X by the train batch, once, and its steps not at all by it.
+// Fitted to 6078 calls timed in both forms (up to 1000 features, 16 outputs, 262144 train samples, K = 0 ... 20): estimates within
+// 3 to 4 % (launches) and 6 to 11 % (one workgroup); of the 4911 calls that take this form 5 are more than 3 % slower, the worst
+// 10 %, and 226 of the others would have gained 5 % or more.  (By the number of outputs alone: softmax 401 - 12, batch 64, K = 2
+// 36 -> 67 us, conjugate gradient of 64 - 16, batch 512, K = 1 30 -> 57.)  Ridge 64 - 1, batch 512, K = 20: 163 us by
+// launches, 19 us; softmax 200 - 4, batch 128, K = 5: 52 / 38 us (conjugate gradient 84 / 50).
+bool use_linear(betty_handle h, bool cg, int K) {
+  if (!has_linear_form(h, cg)) return false;
+  if (h->tune_linear == 1) return true;
+  const LayerInfo& li = h->layers[0];
+  const bool mse = h->desc.loss == BETTY_LOSS_MSE, gram = mse && !cg;
+  const int n = li.n_in + (h->desc.has_bias ? 1 : 0), C = li.n_out, train = h->desc.batch_train, val = h->desc.batch_val;
+  auto up = [](int x, int m) { return (x + m - 1) / m; };
+  const double kn = n * 1e-3, B = train, Bv = val, chunks = up(n, 32);
+  const double step = cg ? 11.2 + 5.8 * kn + 2.5e-3 * B + 38e-6 * n * B + 0.07 * C
+                         : 4.75 + 3.6 * kn + 3.5e-3 * B + (mse ? 3e-6 : 10e-6) * n * B + 0.02 * C;
+  const double launches = (cg ? K == 0 ? 21.3 : 13.2 : 18.6) + (cg ? 2.6 : 4.0) * kn + 3e-3 * Bv + K * step;
+  auto rows = [&](int b) { return up(up(n, 32) * up(b, 16) * 16, 256); };
+  auto columns = [&](int b) { return up(up(b, 32) * up(n, 16) * 16, 256); };
+  auto update = [&](int b) { return up(C * n, 1024) * up(b, 32); };
+  double one = (cg ? 7.9 : 7.1) + 1.4 * C * kn;
+  one += mse ? C * (0.155 * (rows(val) + columns(val)) + 0.032 * chunks + 0.04) + 0.09 * update(val)
+             : C * (0.127 * (rows(val) + columns(val)) + 0.016 * chunks + 0.10) + 0.115 * update(val);
+  if (gram) {
+    one += K * (0.1 * C * rows(n) + 0.32) - 2.3;
+    if (K > 0) one += 2.2 + B * (3.6e-3 + 1.57e-5 * 4 * chunks * chunks);
+  } else {
+    one += K * (C * ((mse ? 0.065 : 0.051) * (rows(train) + columns(train)) + 0.025 * chunks + (mse ? 0.14 : 0.26)) + 0.044 * update(train) +
+                (cg ? 2.2 : 0.35));
+    if (!mse) one += 0.28 * C * rows(train);
+  }
+  return one < 0.92 * launches;
 }
 
 OperandSet& fd_operands(betty_handle h) { return h->sets[1].present ? h->sets[1] : h->sets[0]; }
@@ -454,7 +487,7 @@ void plan(betty_handle h) {
   if (h->L >= 2) h->fd_z1 = pl.take((size_t)h->sets[0].side[0].Bp * h->layers[0].n_out_p * 4);
   h->sums = pl.take(2 * n_sums * sizeof(double));      // (conjugate gradient keeps those of two launches)
   if (plans_samples(h)) plan_samples(h, pl, h->sets[0]);
-  if (h->desc.loss == BETTY_LOSS_MSE && use_linear(h, false))
+  if (h->desc.loss == BETTY_LOSS_MSE && has_linear_form(h, false))
     h->lin_gram = pl.take(linear_gram_bytes(h->layers[0].n_in + (h->desc.has_bias ? 1 : 0)));
   h->ws_need = pl.off;
 }
@@ -2025,7 +2058,7 @@ betty_status betty_mixed_vjp(betty_handle h, const float* w, const float* lambda
 betty_status betty_hypergrad_neumann(betty_handle h, const float* w, const float* lambda, int K, float alpha,
                                      float* dlambda) {
   CHECK(check_hyper_args(h, w, lambda, K, alpha, dlambda));
-  if (use_linear(h, false)) { linear_seq(h, w, lambda, K, alpha, dlambda, false); return finish(h); }
+  if (use_linear(h, false, K)) { linear_seq(h, w, lambda, K, alpha, dlambda, false); return finish(h); }
   auto body = [=]() { neumann_seq(h, w, lambda, nullptr, K, alpha, dlambda); };
   return run_cached(h, h->CALL_NEUMANN, call_key({w, lambda, dlambda}, K, {alpha}), body);
 }
@@ -2228,7 +2261,7 @@ betty_status betty_hypergrad_fd(betty_handle h, const float* w, const float* lam
 
 betty_status betty_hypergrad_cg(betty_handle h, const float* w, const float* lambda, int K, float* dlambda) {
   CHECK(check_hyper_args(h, w, lambda, K, 0.f, dlambda));
-  if (use_linear(h, true)) { linear_seq(h, w, lambda, K, 0.f, dlambda, true); return finish(h); }
+  if (use_linear(h, true, K)) { linear_seq(h, w, lambda, K, 0.f, dlambda, true); return finish(h); }
   auto body = [=]() {
     OperandSet& os = h->sets[0];
     const bool l2 = h->desc.hp == BETTY_HP_L2_DECAY, rw = h->desc.hp == BETTY_HP_REWEIGHT_NET;
