@@ -332,46 +332,58 @@ double samples_saving(betty_handle h, int K, bool dense) {
   return K * step - begin - (prox && K > 1 ? (K - 1) * sums : 0.0);
 }
 // Models with narrow layers take all layers of a few samples in one workgroup (narrow.hip).  Whether the first-order
-// pass (rop = false) or the forward-over-reverse pass does, and from which layer on: 0 = launches per layer, 1, or
-// 2 = layer 1, whose reduction may be long, stays a launch of its own.
-// By the estimated time: a launch takes 4.7 us whatever its width (up to about 256), the fused kernel 6 us, 1.6 us a
-// link, and 1 us per 9 KB of weights, which every workgroup reads on its own and multiplies on one compute unit.
-// (Forward-over-reverse passes at any batch up to 1024: 32-wide, 8 layers 66 us by launches, 29 us; 64-wide fp32, 4 layers
-// 28 / 23 us; 128-wide 28 / 47 us, with bf16 operands 28 / 32 us.  138 models up to 260 wide, whole calls: 13 % faster,
-// at worst 7 % slower.)
-int narrow_first(betty_handle h, bool rop, Elem elem) {
+// passes over that many samples together (rop = false) or the forward-over-reverse pass does, and from which layer on: 0 =
+// launches per layer, 1, or 2 = layer 1, whose reduction may be long, stays a launch of its own.
+// By the estimated time: a launch takes 4.7 us whatever its width (up to about 256; 3.6 where 16 samples are all its
+// rows), the fused kernel 6 us, 1.6 us a link, and 1 us per 9 KB of weights: that is the latency of fetching them link by
+// link in every workgroup, far below what a compute unit can read.
+// It holds while every 16 samples have a compute unit of their own; beyond, workgroups share units and the launches fill
+// the chip.  488 models up to 300 wide, fused over launches: forward-over-reverse passes up to 4096 samples 0.74 (of 147 chosen
+// one 4 % slower), 4096 to 8192 0.88 but up to 1.09, 8192 to 16384 1.00, above 1.07 and up to 1.47; first-order passes up
+// to 24576 samples 0.73 (none of 534 slower), above 0.85 but up to 1.10.
+// (Forward-over-reverse passes: 32-wide, 8 layers 66 us by launches, 29 us; 64-wide fp32, 4 layers 28 / 23 us; 128-wide 28 / 47 us, with
+// bf16 operands 28 / 32 us.)
+constexpr int NARROW_MAX_ROP = 4096, NARROW_MAX_GRAD = 24576;
+struct NarrowEstimate { double fused, launches; int first; };
+NarrowEstimate narrow_estimate(betty_handle h, bool rop, Elem elem, int samples) {
   const int L = h->L;
-  if (L < 2 || L > NARROW_MAX_L || h->tune_narrow == 0) return 0;
-  const bool bf16 = elem == ELEM_BF16, relu = h->desc.act == BETTY_ACT_RELU;
-  NarrowNet net{};
-  net.L = L;
-  for (int l = 0; l <= L; ++l) net.n[l] = h->dims[l];
-  if (narrow_lds(net, elem, bf16) > 150 * 1024) return 0;
-  if (h->tune_narrow > 0) return L >= 3 ? h->tune_narrow : 1;
-  const bool narrow_out = net.n[L] <= LAST_ROP_MAX_C;
-  const double launch = 4.7, per_kb = 1.0 / 9, es = bf16 ? 2.0 : 4.0, fwd_es = !rop && bf16 && relu ? 4.0 : es;
-  const double launches = launch * (2 * L - (narrow_out ? 2 : rop && net.n[L] <= 32 ? 1 : 0)), pairs = rop ? 2.0 : 1.0;
+  const bool bf16 = elem == ELEM_BF16, narrow_out = h->dims[L] <= LAST_ROP_MAX_C;
+  const double launch = rop ? std::min(4.7, 3.6 + 0.25 * std::log2(std::max(samples, 16) / 16.0)) : 4.7;
+  const double per_kb = 1.0 / 9, es = bf16 ? 2.0 : 4.0, fwd_es = !rop && bf16 && h->desc.act == BETTY_ACT_RELU ? 4.0 : es;
+  const double launches = launch * (2 * L - (narrow_out ? 2 : rop && h->dims[L] <= 32 ? 1 : 0)), pairs = rop ? 2.0 : 1.0;
   double fused = 6.0, first_link = 0;
   for (int l = 1; l <= L; ++l) {
-    const double kb = (double)net.n[l - 1] * net.n[l] / 1024.0;
+    const double kb = (double)h->dims[l - 1] * h->dims[l] / 1024.0;
     const double forward = 1.6 + (l > 1 ? pairs : 1.0) * kb * fwd_es * per_kb;
     if (l == 1) first_link = forward;
     fused += forward + (l > 1 ? 1.6 + pairs * kb * es * per_kb : 0.0);
   }
-  const int first = L >= 3 && fused - first_link + launch < fused ? 2 : 1;
-  return std::min(fused, fused - first_link + (L >= 3 ? launch : first_link)) < 0.92 * launches ? first : 0;
+  const bool split = L >= 3 && launch < first_link;
+  return NarrowEstimate{split ? fused - first_link + launch : fused, launches, split ? 2 : 1};
 }
+int narrow_first(betty_handle h, bool rop, Elem elem, int samples) {
+  const int L = h->L;
+  if (L < 2 || L > NARROW_MAX_L || h->tune_narrow == 0) return 0;
+  NarrowNet net{};
+  net.L = L;
+  for (int l = 0; l <= L; ++l) net.n[l] = h->dims[l];
+  if (narrow_lds(net, elem, elem == ELEM_BF16) > 150 * 1024) return 0;
+  if (h->tune_narrow > 0) return L >= 3 ? h->tune_narrow : 1;
+  const NarrowEstimate e = narrow_estimate(h, rop, elem, samples);
+  return samples <= (rop ? NARROW_MAX_ROP : NARROW_MAX_GRAD) && e.fused < (rop ? 0.88 : 0.92) * e.launches ? e.first : 0;
+}
+int narrow_rop_first(betty_handle h, Elem elem) { return narrow_first(h, true, elem, h->desc.batch_train); }
 
 bool has_samples_form(betty_handle h, int K) { return h->desc.hp == BETTY_HP_REWEIGHT_NET || (h->desc.hp == BETTY_HP_PROXIMAL && K > 0); }
 
 bool use_samples(betty_handle h, int K, bool dense) {
-  return h->sets[0].samples && has_samples_form(h, K) && (h->tune_samples == 1 || (!narrow_first(h, true, h->sets[0].elem) && samples_saving(h, K, dense) > 0));
+  return h->sets[0].samples && has_samples_form(h, K) && (h->tune_samples == 1 || (!narrow_rop_first(h, h->sets[0].elem) && samples_saving(h, K, dense) > 0));
 }
 
 // Whether any call with steps takes that form (the estimate is linear in K beyond 1).
 bool plans_samples(betty_handle h) {
   if (h->tune_samples >= 0) return h->tune_samples == 1 && has_samples_form(h, 1);
-  if (narrow_first(h, true, h->desc.prec == BETTY_PREC_BF16_FP32ACC ? ELEM_BF16 : ELEM_F32)) return false;
+  if (narrow_rop_first(h, h->desc.prec == BETTY_PREC_BF16_FP32ACC ? ELEM_BF16 : ELEM_F32)) return false;
   for (int K : {1, 1 << 20})
     for (bool dense : {false, true})
       if (has_samples_form(h, K) && samples_saving(h, K, dense) > 0) return true;
@@ -814,7 +826,9 @@ void narrow_forward_backward(betty_handle h, const Pass* ps, int n, int first) {
 void forward_backward(betty_handle h, const Pass* ps, int n) {
   const int L = h->L;
   const LayerInfo& lo = h->layers[L - 1];
-  if (const int first = h->fixed_grouping && ps[0].os->elem == ELEM_BF16 ? 0 : narrow_first(h, false, ps[0].os->elem)) {
+  int samples = 0;
+  for (int i = 0; i < n; ++i) samples += ps[i].os->side[ps[i].side].B * (h->as_pair && n == 1 ? 2 : 1);
+  if (const int first = h->fixed_grouping && ps[0].os->elem == ELEM_BF16 ? 0 : narrow_first(h, false, ps[0].os->elem, samples)) {
     narrow_forward_backward(h, ps, n, first);
     return;
   }
@@ -1086,7 +1100,7 @@ void narrow_rop(betty_handle h, OperandSet& os, const float* vflat, int first, f
 }
 
 void hvp_cached(betty_handle h, OperandSet& os, const float* vflat, const WgradSink& sink, bool pipelined = false) {
-  if (const int first = narrow_first(h, true, os.elem)) {
+  if (const int first = narrow_rop_first(h, os.elem)) {
     narrow_rop(h, os, vflat, first, nullptr);
     wgrad_batch(h, os, 0, true, sink);
     return;
@@ -1187,7 +1201,7 @@ void mixed_reweight_seq(betty_handle h, OperandSet& os, const float* lam, const 
   const LayerInfo& lo = h->layers[L - 1];
   // c_i is linear in the direction, so the scale is applied once, to the final sum over samples
   if (!copies_current) make_shadows(h, os, {Shadows{qflat, nullptr, &os.Vt}});   // else os.Vt already holds qflat
-  if (const int first = narrow_first(h, true, os.elem)) {
+  if (const int first = narrow_rop_first(h, os.elem)) {
     narrow_rop(h, os, qflat, first, h->f(os.cvec));
   } else if (L >= 2 && lo.n_out <= LAST_ROP_MAX_C) {
     // narrow output layer: the last product and the directional derivative in one vector kernel
@@ -2165,9 +2179,11 @@ static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, f
   // Layer 1 is linear in the perturbation: z_1 at w +- eps v is X W_1 + b_1 +- eps (X V_1 + c_1).  The first term is
   // formed once, the second once for both points, and neither point needs operand copies of its first layer: half the
   // products of the largest layer and most of the perturbation's traffic (5.3M parameters, 5 differences: 1260 -> 1105 us).
-  // (Not where a narrow model's first-order pass starts at layer 1.)
+  // (Not where a narrow model's first-order pass starts at layer 1: the one at w, which reweighting never takes so, or
+  // those at the points.)
   const LayerInfo& l1 = h->layers[0];
-  const bool split = h->L >= 2 && narrow_first(h, false, ELEM_F32) != 1 && (K > 0 || rw);
+  auto from_inputs = [&](int samples) { return narrow_first(h, false, ELEM_F32, samples) == 1; };
+  const bool split = h->L >= 2 && (K > 0 || rw) && (rw || !from_inputs(h->desc.batch_val)) && !from_inputs(2 * sb.B);
   const Pass at_w = train_pass(h, os, w, lambda, false);
   h->z1_pass = split ? &at_w : nullptr;
   WgradSink init{EPI_WGRAD_INIT, nullptr, nullptr, nullptr, v, K > 0 ? p : nullptr, 0.f, false};

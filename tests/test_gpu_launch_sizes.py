@@ -8,7 +8,7 @@ import torch
 from oracle import betty_oracle as orc
 from paper_2207_02849_amd import binding
 from paper_2207_02849_amd import workloads as wk
-from tests.util import oracle_problem, rel_l2
+from tests.util import oracle_problem, rel_l2, time_forms
 
 pytestmark = pytest.mark.gpu
 
@@ -73,6 +73,31 @@ def test_narrow_models_in_one_workgroup(dims, batch, kind, act, loss, bias, firs
         if act == "gelu":
             assert rel_l2(host(b.betty_hypergrad_fd(w, lam, 1, 0.02)), orc.hypergrad_fd(prob, wl.w, wl.lam, 1, 0.02, 0.01)) < 1e-4
         b.close()
+
+
+@pytest.mark.parametrize("dims,batch,prec,act", [
+    ((117, 58, 46, 154), 29661, "bf16", "relu"),                     # one workgroup for 16 samples 1.4 times the time of the launches
+    ((9, 67, 67, 41, 26, 153), 13003, "bf16", "relu"),               # ... 1.2
+])
+def test_narrow_models_with_many_samples_go_by_launches(dims, batch, prec, act, monkeypatch):
+    """Beyond a workgroup per compute unit the launches per layer fill the chip, and the rule knows the batch."""
+    rule, launches = time_forms(monkeypatch, lambda b, w: b.betty_hypergrad_neumann(w, w, 9, 1e-4), ("samples=0", "narrow=0,samples=0"), rounds=5,
+                                reps=3, dims=dims, act=act, loss="ce", hp="l2", prec=prec, batch_train=batch, batch_val=batch)
+    assert rule < 1.1 * launches, (rule, launches)        # (first-order passes may be a few percent slower, runs differ by as much)
+
+
+@pytest.mark.parametrize("kind", ["l2", "reweight"])
+@pytest.mark.parametrize("batch,batch_val", [(13000, 50), (40, 24600), (40, 50)])
+def test_finite_differences_of_narrow_models_mix_forms(batch, batch_val, kind):
+    """The pass at w, those at both points and the shared first layer with either form of pass beside the other."""
+    wl, big = (wk.tiny(kind=kind, act="gelu", dims=(20, 12, 16, 12, 3), batch=n, hidden=20, seed=s) for n, s in ((batch, 0), (batch_val, 3)))
+    wl.X_val, wl.y_val = big.X_val, big.y_val
+    prob = oracle_problem(wl)
+    b = binding.from_workload(wl)
+    for K in (0, 1, 2):                                    # (tolerances as in test_finite_difference_forms)
+        assert rel_l2(host(b.betty_hypergrad_fd(dev(wl.w), dev(wl.lam), K, 0.05, 0.01)),
+                      orc.hypergrad_fd(prob, wl.w, wl.lam, K, 0.05, 0.01)) < (1e-3 if kind == "reweight" else 1e-4), K
+    b.close()
 
 
 @pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])

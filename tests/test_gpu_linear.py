@@ -1,6 +1,5 @@
 """The one-workgroup kernel for small single-layer models at the edges of what it takes, against the fp64 oracle."""
 import dataclasses
-import math
 
 import numpy as np
 import pytest
@@ -9,7 +8,7 @@ import torch
 from oracle import betty_oracle as orc
 from paper_2207_02849_amd import binding
 from paper_2207_02849_amd import workloads as wk
-from tests.util import oracle_problem, rel_l2
+from tests.util import oracle_problem, rel_l2, time_forms
 
 pytestmark = pytest.mark.gpu
 
@@ -43,38 +42,6 @@ def test_small_linear_models(dims, batch, batch_val, loss, bias, monkeypatch):
     b.close()
 
 
-def both_forms(monkeypatch, call, tunes, rounds=8, reps=20, **problem):
-    """Best time of `call(handle)` for a handle of each BETTY_TUNE, in turn."""
-    g = torch.Generator(device="cuda")
-    g.manual_seed(0)
-    dims, B, Bv = problem["dims"], problem["batch_train"], problem["batch_val"]
-    randn = lambda *s: torch.randn(*s, generator=g, device="cuda")
-    if problem["loss"] == "ce":
-        labels = dict(zip(("y_tr", "y_val"), ((torch.arange(n, device="cuda") % dims[-1]).int() for n in (B, Bv))))
-    else:
-        labels = dict(t_tr=randn(B, dims[-1]), t_val=randn(Bv, dims[-1]))
-    X = dict(X_tr=randn(B, dims[0]), X_val=randn(Bv, dims[0]))
-    handles, best = [], [math.inf] * len(tunes)
-    for tune in tunes:
-        monkeypatch.setenv("BETTY_TUNE", tune)
-        handles.append(binding.Betty(**problem))
-        handles[-1].set_batches(**X, **labels)
-    w = randn(handles[0].d) / math.sqrt(dims[0])
-    for _ in range(rounds):
-        for i, b in enumerate(handles):
-            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
-            call(b, w)
-            start.record()
-            for _ in range(reps):
-                call(b, w)
-            end.record()
-            end.synchronize()
-            best[i] = min(best[i], start.elapsed_time(end) / reps)
-    for b in handles:
-        b.close()
-    return best
-
-
 @pytest.mark.parametrize("dims,batch,batch_val,loss,bias,method,K", [
     ((400, 12), 64, 64, "ce", True, "neumann", 2),        # one workgroup 1.9 times the time of the launches
     ((64, 12), 512, 512, "ce", False, "neumann", 1),      # ... 1.6
@@ -87,6 +54,6 @@ def test_one_workgroup_only_where_it_is_the_faster_form(dims, batch, batch_val, 
     def call(b, w):
         lam = w                                    # (any values: only the time counts)
         return b.betty_hypergrad_cg(w, lam, K) if method == "cg" else b.betty_hypergrad_neumann(w, lam, K, 0.01)
-    rule, launches = both_forms(monkeypatch, call, ("", "linear=0"), dims=dims, act="none", loss=loss, hp="l2", prec="fp32",
+    rule, launches = time_forms(monkeypatch, call, ("", "linear=0"), dims=dims, act="none", loss=loss, hp="l2", prec="fp32",
                                 has_bias=bias, batch_train=batch, batch_val=batch_val)
     assert rule < 1.15 * launches, (rule, launches)       # (a few percent between runs)

@@ -1,4 +1,6 @@
 """Test helpers: build an oracle Problem from a seeded workload; error metric."""
+import math
+
 import numpy as np
 
 from oracle import betty_oracle as orc
@@ -64,3 +66,37 @@ def spectral_alpha(prob, w, lam, iters=8, seed=0):
         top = np.linalg.norm(Hv)
         v = Hv / top
     return 1.0 / top
+
+
+def time_forms(monkeypatch, call, tunes, rounds=8, reps=20, **problem):
+    """Best time of `call(handle, w)` for a handle of each BETTY_TUNE, in turn (milliseconds)."""
+    import torch
+    from paper_2207_02849_amd import binding
+    g = torch.Generator(device="cuda")
+    g.manual_seed(0)
+    dims, B, Bv = problem["dims"], problem["batch_train"], problem["batch_val"]
+    randn = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    if problem["loss"] == "ce":
+        labels = dict(zip(("y_tr", "y_val"), ((torch.arange(n, device="cuda") % dims[-1]).int() for n in (B, Bv))))
+    else:
+        labels = dict(t_tr=randn(B, dims[-1]), t_val=randn(Bv, dims[-1]))
+    X = dict(X_tr=randn(B, dims[0]), X_val=randn(Bv, dims[0]))
+    handles, best = [], [math.inf] * len(tunes)
+    for tune in tunes:
+        monkeypatch.setenv("BETTY_TUNE", tune)
+        handles.append(binding.Betty(**problem))
+        handles[-1].set_batches(**X, **labels)
+    w = randn(handles[0].d) / math.sqrt(dims[0])
+    for _ in range(rounds):
+        for i, b in enumerate(handles):
+            start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            call(b, w)
+            start.record()
+            for _ in range(reps):
+                call(b, w)
+            end.record()
+            end.synchronize()
+            best[i] = min(best[i], start.elapsed_time(end) / reps)
+    for b in handles:
+        b.close()
+    return best
