@@ -86,6 +86,13 @@ def test_narrow_models_with_many_samples_go_by_launches(dims, batch, prec, act, 
     assert rule < 1.1 * launches, (rule, launches)        # (first-order passes may be a few percent slower, runs differ by as much)
 
 
+@pytest.mark.parametrize("dims,batch,K", [((1006, 9, 80), 65, 9), ((915, 33, 33, 146), 25, 9)])     # 1.25 times the time of the series over samples
+def test_narrow_models_keep_the_series_over_samples_where_it_is_faster(dims, batch, K, monkeypatch):
+    rule, samples = time_forms(monkeypatch, lambda b, w: b.betty_hypergrad_neumann(w, w[:b.n_hyper], K, 1e-4), ("", "narrow=0"), dims=dims,
+                               act="gelu", loss="ce", hp="reweight", prec="fp32" if len(dims) == 3 else "bf16", batch_train=batch, batch_val=batch)
+    assert rule < 1.1 * samples, (rule, samples)
+
+
 @pytest.mark.parametrize("kind", ["l2", "reweight"])
 @pytest.mark.parametrize("batch,batch_val", [(13000, 50), (40, 24600), (40, 50)])
 def test_finite_differences_of_narrow_models_mix_forms(batch, batch_val, kind):
