@@ -1288,14 +1288,9 @@ constexpr size_t lds_bytes() {
 template <typename T, int BT, int WPG, int KG, int MODE>
 static void launch_one(int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
   constexpr size_t lds = lds_bytes<T, BT, WPG, KG>();
-  static bool configured = false;
-  if (!configured) {
-    if (lds > 48 * 1024) {
-      hipError_t e = hipFuncSetAttribute((const void*)gemm_fused_kernel<T, BT, BT, GEMM_NCH, WPG, KG, MODE>,
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) { err = e; return; }
-    }
-    configured = true;
+  if constexpr (lds > 48 * 1024) {
+    static PerDevice allowed;
+    if (const hipError_t e = allow_lds(allowed, (const void*)gemm_fused_kernel<T, BT, BT, GEMM_NCH, WPG, KG, MODE>, lds); e != hipSuccess) { err = e; return; }
   }
   gemm_fused_kernel<T, BT, BT, GEMM_NCH, WPG, KG, MODE><<<total, 64 * WPG * KG, lds, st>>>(kernel_args<MODE>(b));
 }
@@ -1307,13 +1302,8 @@ static void launch_one(int total, hipStream_t st, const GemmBatch& b, hipError_t
 template <typename T, int MODE>
 static void launch_rect(int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
   constexpr size_t lds = (size_t)2 * (128 + 64) * (GEMM_NCH + 1) * 16;
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute((const void*)gemm_fused_kernel<T, 128, 64, GEMM_NCH, 8, 1, MODE>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) { err = e; return; }
-    configured = true;
-  }
+  static PerDevice allowed;
+  if (const hipError_t e = allow_lds(allowed, (const void*)gemm_fused_kernel<T, 128, 64, GEMM_NCH, 8, 1, MODE>, lds); e != hipSuccess) { err = e; return; }
   gemm_fused_kernel<T, 128, 64, GEMM_NCH, 8, 1, MODE><<<total, 512, lds, st>>>(kernel_args<MODE>(b));
 }
 
@@ -1361,13 +1351,8 @@ static void launch_wgrad_mode(int mode, int total, hipStream_t st, const GemmBat
 
 template <int MODE, int LAM>
 static void launch_wgrad128_one(int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
-  static bool configured = false;
-  if (!configured) {
-    hipError_t e = hipFuncSetAttribute((const void*)wgrad128_kernel<MODE, LAM>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)WG_LDS);
-    if (e != hipSuccess) { err = e; return; }
-    configured = true;
-  }
+  static PerDevice allowed;
+  if (const hipError_t e = allow_lds(allowed, (const void*)wgrad128_kernel<MODE, LAM>, WG_LDS); e != hipSuccess) { err = e; return; }
   wgrad128_kernel<MODE, LAM><<<total - b.gemm_blocks + b.walkers, 256, WG_LDS, st>>>(kernel_args<MODE>(b));
 }
 

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "betty_hip.h"
+#include "per_device.h"
 
 namespace betty {
 
@@ -158,6 +159,18 @@ struct Launch {   // RAII bracket around one kernel launch
   Launch(Ctx& ctx, int kind, double flops = 0, double bytes = 0) : c(ctx) { c.begin(kind, flops, bytes); }
   ~Launch() { c.end(); }
 };
+
+// Allows a kernel that much dynamic LDS on the current device (the limit is kept per kernel and device).
+inline hipError_t allow_lds(PerDevice& allowed, const void* kernel, size_t bytes) {
+  int device = 0;
+  hipError_t e = hipGetDevice(&device);
+  if (e == hipSuccess)
+    allowed.once(device, [&]() {
+      e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+      return e == hipSuccess;
+    });
+  return e;
+}
 
 // One 16-byte chunk of K for a 32 x 32 MFMA block: 8 bf16 (one v_mfma_f32_32x32x16_bf16) or 4 floats
 // (four v_mfma_f32_32x32x2_f32).  Lane l supplies row l % 32 of A and of B; lanes 0-31 hold the

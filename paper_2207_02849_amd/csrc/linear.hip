@@ -333,12 +333,9 @@ template <bool CG, bool GRAM>
 static void launch_linear(Ctx& ctx, const LinearArgs& a) {
   const int n = a.n_in + a.bias, B = GRAM ? lin_up(n) * LIN_CH : a.B[0];
   const size_t lds = lin_lds_floats(n, a.C, B > a.B[1] ? B : a.B[1], CG) * 4;
-  static bool configured = false;
-  if (!configured) {
-    const hipError_t e = hipFuncSetAttribute((const void*)linear_hypergrad_kernel<CG, GRAM>, hipFuncAttributeMaxDynamicSharedMemorySize, LIN_LDS);
-    if (e != hipSuccess) { if (ctx.first_error == hipSuccess) ctx.first_error = e; return; }
-    configured = true;
-  }
+  static PerDevice allowed;
+  const hipError_t e = allow_lds(allowed, (const void*)linear_hypergrad_kernel<CG, GRAM>, LIN_LDS);
+  if (e != hipSuccess) { if (ctx.first_error == hipSuccess) ctx.first_error = e; return; }
   if (GRAM && a.K > 0) {
     const int tiles = lin_up(n) * LIN_CH / 16;
     Launch l(ctx, BETTY_K_GEMM, 2.0 * a.B[0] * n * n);

@@ -470,12 +470,9 @@ static void narrow_splits(NarrowNet& net, int ks_fwd, int ks_bwd) {
 }
 
 template <typename K, typename A>
-static void narrow_launch(Ctx& ctx, K kernel, bool& configured, int blocks, size_t lds, const A& a) {
-  if (!configured) {
-    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)NARROW_LDS);
-    if (e != hipSuccess) { if (ctx.first_error == hipSuccess) ctx.first_error = e; return; }
-    configured = true;
-  }
+static void narrow_launch(Ctx& ctx, K kernel, PerDevice& allowed, int blocks, size_t lds, const A& a) {
+  const hipError_t e = allow_lds(allowed, (const void*)kernel, NARROW_LDS);
+  if (e != hipSuccess) { if (ctx.first_error == hipSuccess) ctx.first_error = e; return; }
   kernel<<<blocks, NT, lds, ctx.stream>>>(a);
 }
 
@@ -485,10 +482,10 @@ void launch_narrow_grad(Ctx& ctx, Elem elem, bool wide, NarrowGradArgs& a, int n
   const size_t lds = narrow_lds(a.net, elem, wide);
   Launch l(ctx, BETTY_K_GEMM, flops);
   narrow_splits(a.net, elem == ELEM_F32 || wide ? 16 : 32, elem == ELEM_F32 ? 16 : 32);
-  static bool configured[3] = {};
-  if (elem == ELEM_F32) narrow_launch(ctx, narrow_grad_kernel<float, float>, configured[0], blocks, lds, a);
-  else if (wide) narrow_launch(ctx, narrow_grad_kernel<__bf16, float>, configured[1], blocks, lds, a);
-  else narrow_launch(ctx, narrow_grad_kernel<__bf16, __bf16>, configured[2], blocks, lds, a);
+  static PerDevice allowed[3];
+  if (elem == ELEM_F32) narrow_launch(ctx, narrow_grad_kernel<float, float>, allowed[0], blocks, lds, a);
+  else if (wide) narrow_launch(ctx, narrow_grad_kernel<__bf16, float>, allowed[1], blocks, lds, a);
+  else narrow_launch(ctx, narrow_grad_kernel<__bf16, __bf16>, allowed[2], blocks, lds, a);
 }
 
 void launch_narrow_rop(Ctx& ctx, Elem elem, NarrowRopArgs& a, double flops) {
@@ -496,9 +493,9 @@ void launch_narrow_rop(Ctx& ctx, Elem elem, NarrowRopArgs& a, double flops) {
   const size_t lds = narrow_lds(a.net, elem, false);
   Launch l(ctx, BETTY_K_GEMM_RFWD, flops);
   narrow_splits(a.net, elem == ELEM_F32 ? 16 : 32, elem == ELEM_F32 ? 16 : 32);
-  static bool configured[2] = {};
-  if (elem == ELEM_F32) narrow_launch(ctx, narrow_rop_kernel<float>, configured[0], blocks, lds, a);
-  else narrow_launch(ctx, narrow_rop_kernel<__bf16>, configured[1], blocks, lds, a);
+  static PerDevice allowed[2];
+  if (elem == ELEM_F32) narrow_launch(ctx, narrow_rop_kernel<float>, allowed[0], blocks, lds, a);
+  else narrow_launch(ctx, narrow_rop_kernel<__bf16>, allowed[1], blocks, lds, a);
 }
 
 }  // namespace betty

@@ -3,6 +3,7 @@ rejects bad problem descriptions on the host without touching a device."""
 import ctypes as C
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -111,3 +112,41 @@ def test_calls_before_bind_fail_cleanly():
     assert lib.betty_apply_label_noise(h, None, None, None, 1.5, 4, None, None) == binding.EINVAL
     assert lib.betty_apply_label_noise(h, None, None, None, 0.5, -1, None, None) == binding.EINVAL
     lib.betty_destroy(h)
+
+
+def test_settings_of_a_kernel_are_made_once_a_device(tmp_path):
+    """Limits of LDS belong to a kernel and a device: set on the first call on each, again after a failure, from any thread.
+    (The header has no HIP in it.)"""
+    src = tmp_path / "once.cpp"
+    src.write_text("""
+#include "per_device.h"
+#include <cstdio>
+#include <thread>
+#include <vector>
+int main() {
+  betty::PerDevice p;
+  int calls = 0;
+  auto ok = [&]() { ++calls; return true; };
+  for (int rep = 0; rep < 3; ++rep)
+    for (int d : {0, 1, 7, 63}) if (!p.once(d, ok)) return 1;
+  if (calls != 4) return 2;
+  for (int rep = 0; rep < 2; ++rep) if (p.once(5, []() { return false; })) return 3;
+  if (!p.once(5, ok) || !p.once(5, ok) || calls != 5) return 4;
+  for (int rep = 0; rep < 2; ++rep) if (!p.once(64, ok) || !p.once(-1, ok)) return 5;
+  if (calls != 9) return 6;
+  betty::PerDevice q;
+  std::atomic<int> n[64] = {};
+  std::vector<std::thread> ts;
+  for (int t = 0; t < 4; ++t)
+    ts.emplace_back([&]() { for (int rep = 0; rep < 100; ++rep) for (int d = 0; d < 64; ++d) q.once(d, [&]() { ++n[d]; return true; }); });
+  for (auto& t : ts) t.join();
+  for (auto& c : n) if (c < 1 || c > 4) return 7;
+  return 0;
+}
+""")
+    exe = str(tmp_path / "once")
+    csrc = os.path.join(ROOT, "paper_2207_02849_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-pthread", "-I", csrc, str(src), "-o", exe], check=True)
+    assert subprocess.run([exe]).returncode == 0
+    launchers = "".join(open(os.path.join(csrc, f)).read() for f in os.listdir(csrc) if f.endswith(".hip"))
+    assert "hipFuncSetAttribute" not in launchers       # everyone goes through allow_lds
