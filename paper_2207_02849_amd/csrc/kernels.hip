@@ -64,8 +64,8 @@ template <> __device__ __forceinline__ void store_quad<__bf16>(__bf16* p, float 
 // requested before the first is used (positions are clamped into the matrix instead of being
 // predicated; a load inside control flow is waited for before the next one starts).  A 784 x 10 matrix:
 // 8 us with predicated loads, 3.6 us; 5.3M parameters: 13.6 us = 4.6 TB/s either way.
-template <typename T>
-__global__ __launch_bounds__(256) void convert_batch_kernel(ConvertBatch b) {
+template <typename T, int N>
+__global__ __launch_bounds__(256) void convert_batch_kernel(ConvertBatchT<N> b) {
   __shared__ float tile[64][65];
   int bid = blockIdx.x, ji = 0;
   while (ji + 1 < b.n && bid >= b.block_begin[ji + 1]) ++ji;
@@ -158,8 +158,18 @@ void launch_convert_batch(Ctx& ctx, Elem elem, ConvertBatch& b) {
   b.block_begin[b.n] = blocks;
   if (blocks <= 0) return;
   Launch l(ctx, BETTY_K_SHADOW, 0, bytes);
-  if (elem == ELEM_BF16) convert_batch_kernel<__bf16><<<blocks, 256, 0, ctx.stream>>>(b);
-  else convert_batch_kernel<float><<<blocks, 256, 0, ctx.stream>>>(b);
+  if (b.n > FEW_CONVERTS) {
+    if (elem == ELEM_BF16) convert_batch_kernel<__bf16><<<blocks, 256, 0, ctx.stream>>>(b);
+    else convert_batch_kernel<float><<<blocks, 256, 0, ctx.stream>>>(b);
+    return;
+  }
+  ConvertBatchT<FEW_CONVERTS> few;
+  few.n = b.n; few.table = b.table;
+  for (int i = 0; i <= b.n; ++i) few.block_begin[i] = b.block_begin[i];
+  for (int i = 0; i < b.n; ++i) few.j[i] = b.j[i];
+  for (int i = 0; i < 2; ++i) few.labels[i] = b.labels[i];
+  if (elem == ELEM_BF16) convert_batch_kernel<__bf16><<<blocks, 256, 0, ctx.stream>>>(few);
+  else convert_batch_kernel<float><<<blocks, 256, 0, ctx.stream>>>(few);
 }
 
 // (a workgroup's 2048 elements are a whole number of 64-element groups, so the result may take the place of the

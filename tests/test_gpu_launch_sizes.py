@@ -146,6 +146,26 @@ def test_loss_rows_of_wide_outputs(C, batch, loss, prec, tol):
     b.close()
 
 
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
+@pytest.mark.parametrize("layers", [2, 4, 5, 8, 9])
+def test_operand_conversions_at_the_edges_of_a_launch(layers, prec, tol):
+    """Four matrices are the most of the short form of a conversion, sixteen those of a launch: a gradient converts one a
+    layer, a product two."""
+    wl = wk.tiny(kind="l2", act="gelu", dims=(21, 18) + (14, 17) * (layers // 2 - 1) + (13,) * (layers % 2) + (5,), batch=20, prec=prec)
+    assert len(wl.dims) == layers + 1
+    prob = oracle_problem(wl)
+    b = binding.from_workload(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    v = orc.lower_grad(prob, wl.w, wl.lam)[1]
+    for matrices, call, ref in ((layers, lambda: b.betty_lower_grad(w, lam), v),
+                                (2 * layers, lambda: b.betty_hvp(w, lam, dev(v)), orc.hvp(prob, wl.w, wl.lam, v))):
+        b.profile(True)
+        assert rel_l2(host(call()), ref) < tol
+        assert sum(r[0] == "shadow" for r in b.profile_records()) == -(-matrices // 16)
+        b.profile(False)
+    b.close()
+
+
 def test_recorded_calls_follow_streams_and_batches():
     """A handle without an explicit stream runs on the caller's current stream; recorded sequences
     survive a move to another stream and new batches (labels included), and one argument set does
