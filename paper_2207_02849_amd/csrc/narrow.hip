@@ -18,6 +18,25 @@ constexpr int NW = 8, NT = 64 * NW, NROWS = NARROW_ROWS;
 template <typename T> constexpr int narrow_ks() { return 64 / (int)sizeof(T); }     // elements of K per step
 template <typename T> __device__ __forceinline__ T narrow_cast(float x) { return (T)x; }
 
+// Accumulators of a 16-tile.  In fp32 the four MFMA instructions of a step have one each, added at the end.  One chain
+// of K additions, where the kernels of whole batches add up partial sums of a few steps, left results 7 to 18 % further off
+// fp64 than theirs (70 models: first-order passes, products, series, differences; up to 2.2 times with a long first
+// layer), two 0 to 7 %; with four they are 2 to 8 % nearer, and a call takes 1 % longer.
+template <typename T> struct NarrowAcc {
+  f32x4v a = {0.f, 0.f, 0.f, 0.f};
+  __device__ __forceinline__ void step(const u32x4& x, const u32x4& y) { MfmaStep16<T>::run(x, y, a); }
+  __device__ __forceinline__ f32x4v total() const { return a; }
+};
+template <> struct NarrowAcc<float> {
+  f32x4v a[4] = {};
+  __device__ __forceinline__ void step(const u32x4& x, const u32x4& y) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      a[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[i]), __uint_as_float(y[i]), a[i], 0, 0, 0);
+  }
+  __device__ __forceinline__ f32x4v total() const { return (a[0] + a[1]) + (a[2] + a[3]); }
+};
+
 // A barrier for what is exchanged through LDS: loads and stores of memory stay in flight across it (nothing that goes
 // to memory is read by another thread of the launch).  __syncthreads() waits for every store: a microsecond a link.
 __device__ __forceinline__ void narrow_barrier() {
@@ -36,7 +55,7 @@ __device__ __forceinline__ void narrow_load(const T* P, int s, int n, u32x4 (&f)
 
 // acc += A B^T over the steps [s0, s1); A, B in memory at this lane's row and chunk
 template <typename T, int U>
-__device__ __forceinline__ void narrow_mac(const T* A, const T* B, int s0, int s1, f32x4v& acc) {
+__device__ __forceinline__ void narrow_mac(const T* A, const T* B, int s0, int s1, NarrowAcc<T>& acc) {
   for (int s = s0; s < s1; s += U) {
     const int n = min(U, s1 - s);
     u32x4 a[U], b[U];
@@ -44,24 +63,24 @@ __device__ __forceinline__ void narrow_mac(const T* A, const T* B, int s0, int s
     narrow_load<T, U>(B, s, n, b);
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (u < n) MfmaStep16<T>::run(a[u], b[u], acc);
+      if (u < n) acc.step(a[u], b[u]);
   }
 }
 // ... with A in LDS and the first U steps of B already in w
 template <typename T, int U>
-__device__ __forceinline__ void narrow_mac_lds(const T* A, const T* B, int s0, int s1, u32x4 (&w)[U], f32x4v& acc) {
+__device__ __forceinline__ void narrow_mac_lds(const T* A, const T* B, int s0, int s1, u32x4 (&w)[U], NarrowAcc<T>& acc) {
   constexpr int KS = narrow_ks<T>();
   const int n0 = min(U, s1 - s0);
 #pragma unroll
   for (int u = 0; u < U; ++u)
-    if (u < n0) MfmaStep16<T>::run(*(const u32x4*)(A + (s0 + u) * KS), w[u], acc);
+    if (u < n0) acc.step(*(const u32x4*)(A + (s0 + u) * KS), w[u]);
   for (int s = s0 + U; s < s1; s += U) {
     const int n = min(U, s1 - s);
     u32x4 b[U];
     narrow_load<T, U>(B, s, n, b);
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (u < n) MfmaStep16<T>::run(*(const u32x4*)(A + (s + u) * KS), b[u], acc);
+      if (u < n) acc.step(*(const u32x4*)(A + (s + u) * KS), b[u]);
   }
 }
 
@@ -88,18 +107,19 @@ __device__ __forceinline__ void narrow_link_of(const NarrowLink<T>& k, const T* 
     const int kp = ks > 1 ? wave * k.split.by_nt >> 8 : 0, tile = ks > 1 ? wave - kp * nt : base + wave;
     const bool active = kp < ks && tile < nt;
     const int s0 = kp * k.split.per, s1 = min(S, s0 + k.split.per), col = tile * 16 + fr, row = 4 * (lane >> 4);
-    f32x4v acc = {0.f, 0.f, 0.f, 0.f};
+    NarrowAcc<T> sums;
     u32x4 w[U];
     if (active) {
       const long long b = (long long)(tile * 16 + fr) * k.ldb + fc;
       if (k.lds >= 0) narrow_load<T, U>(k.B0 + b, s0, min(U, s1 - s0), w);
       pre(min(col, k.N - 1), row);
-      if (k.A1) narrow_mac<T, U>(k.A1 + (long long)(i0 + fr) * k.lda + fc, k.B1 + b, s0, s1, acc);
-      if (k.A2) narrow_mac<T, U>(k.A2 + (long long)(i0 + fr) * k.lda + fc, k.B2 + b, s0, s1, acc);
+      if (k.A1) narrow_mac<T, U>(k.A1 + (long long)(i0 + fr) * k.lda + fc, k.B1 + b, s0, s1, sums);
+      if (k.A2) narrow_mac<T, U>(k.A2 + (long long)(i0 + fr) * k.lda + fc, k.B2 + b, s0, s1, sums);
     }
     if (base == 0) narrow_barrier();
     if (active && k.lds >= 0)
-      narrow_mac_lds<T, U>(bufs + k.lds * NROWS * pitch + fr * pitch + fc, k.B0 + (long long)(tile * 16 + fr) * k.ldb + fc, s0, s1, w, acc);
+      narrow_mac_lds<T, U>(bufs + k.lds * NROWS * pitch + fr * pitch + fc, k.B0 + (long long)(tile * 16 + fr) * k.ldb + fc, s0, s1, w, sums);
+    f32x4v acc = sums.total();
     if (ks > 1) {
       if (active && kp > 0) *(f32x4v*)(red + ((kp - 1) * nt + tile) * 256 + lane * 4) = acc;
       narrow_barrier();

@@ -75,6 +75,26 @@ def test_narrow_models_in_one_workgroup(dims, batch, kind, act, loss, bias, firs
         b.close()
 
 
+def test_narrow_models_are_as_exact_as_launches(monkeypatch):
+    """fp32 sums of all layers in one workgroup: no further off fp64 than those of the launches, on the geometric mean (one
+    accumulator for a whole sum: 1.2 times as far; single results scatter by half as much)."""
+    errors = {1: [], 0: []}
+    for seed, dims in enumerate([(600, 24, 24, 5), (300, 40, 40, 10), (500, 17, 33, 3), (64, 64, 64, 64, 8), (200, 30, 30, 30, 30, 4), (100, 90, 20, 60)] * 2):
+        wl = wk.tiny(kind="l2", act="gelu", dims=dims, batch=100 + 31 * seed, prec="fp32", seed=seed)
+        prob = oracle_problem(wl)
+        v = np.random.default_rng(seed).standard_normal(wl.d).astype(np.float32)
+        refs = orc.lower_grad(prob, wl.w, wl.lam)[1], orc.hvp(prob, wl.w, wl.lam, v.astype(np.float64))
+        for form in errors:
+            monkeypatch.setenv("BETTY_TUNE", f"narrow={form}")
+            b = binding.from_workload(wl)
+            w, lam = dev(wl.w), dev(wl.lam)
+            errors[form] += [rel_l2(host(got), ref) for got, ref in zip((b.betty_lower_grad(w, lam), b.betty_hvp(w, lam, dev(v))), refs)]
+            b.close()
+    ratio = np.exp(np.mean(np.log(errors[1])) - np.mean(np.log(errors[0])))
+    print(f"{ratio:.3f}", flush=True)
+    assert ratio < 1.05, ratio
+
+
 @pytest.mark.parametrize("dims,batch,prec,act", [
     ((117, 58, 46, 154), 29661, "bf16", "relu"),                     # one workgroup for 16 samples 1.4 times the time of the launches
     ((9, 67, 67, 41, 26, 153), 13003, "bf16", "relu"),               # ... 1.2
