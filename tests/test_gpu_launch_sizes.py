@@ -31,7 +31,8 @@ def host(t):
     ((40, 9), 257, "mse"),                   # ... and inside one
     ((70, 530, 260), 100, "ce"),             # 16-, 32- and 64-tiles side by side
 ])
-def test_small_launch_forms(dims, batch, loss, prec, tol):
+def test_small_launch_forms(dims, batch, loss, prec, tol, monkeypatch):
+    monkeypatch.setenv("BETTY_TUNE", "narrow=0")
     wl = wk.tiny(kind="l2", act="gelu" if len(dims) > 2 else "none", dims=dims, batch=batch, loss=loss, prec=prec)
     prob = oracle_problem(wl)
     b = binding.from_workload(wl)
@@ -135,25 +136,32 @@ def test_finite_differences_of_narrow_models_mix_forms(batch, batch_val, kind):
     ((1100, 300, 31), 129),                  # the long-loop form in some products, not in others; Hessian in the epilogue
 ])
 def test_two_way_split_of_64_tiles(dims, batch, kind, samples, prec, tol, monkeypatch):
-    monkeypatch.setenv("BETTY_TUNE", f"pair=1,samples={samples}")
+    """Against the oracle, and other bits than those of unsplit 64-tiles: the sums along K are grouped by halves (a bf16
+    series whose sums fit one k-tile has the same)."""
     wl = wk.tiny(kind=kind, act="gelu", dims=dims, batch=batch, prec=prec)
     prob = oracle_problem(wl)
-    b = binding.from_workload(wl)
     w, lam = dev(wl.w), dev(wl.lam)
     v = orc.lower_grad(prob, wl.w, wl.lam)[1]
-    for name, got, ref in (("grad", b.betty_lower_grad(w, lam), v),
-                           ("hvp", b.betty_hvp(w, lam, dev(v)), orc.hvp(prob, wl.w, wl.lam, v)),
-                           ("neumann", b.betty_hypergrad_neumann(w, lam, 2, 0.02),
-                            orc.hypergrad_neumann(prob, wl.w, wl.lam, 2, 0.02))):
-        assert rel_l2(host(got), ref) < tol, name
-    b.close()
+    refs = dict(grad=v, hvp=orc.hvp(prob, wl.w, wl.lam, v), neumann=orc.hypergrad_neumann(prob, wl.w, wl.lam, 2, 0.02))
+    got = {}
+    for form in ("pair=1", "blocks=1"):
+        monkeypatch.setenv("BETTY_TUNE", f"{form},narrow=0,samples={samples}")
+        b = binding.from_workload(wl)
+        got[form] = dict(grad=host(b.betty_lower_grad(w, lam)), hvp=host(b.betty_hvp(w, lam, dev(v))),
+                         neumann=host(b.betty_hypergrad_neumann(w, lam, 2, 0.02)))
+        for name, ref in refs.items():
+            assert rel_l2(got[form][name], ref) < tol, (name, form)
+        b.close()
+    for name in ("grad", "hvp"):
+        assert not np.array_equal(got["pair=1"][name], got["blocks=1"][name]), name
 
 
 @pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
 @pytest.mark.parametrize("loss", ["ce", "mse"])
 @pytest.mark.parametrize("C,batch", [(64, 5), (65, 16), (256, 15), (257, 33), (1024, 17), (1100, 18)])
-def test_loss_rows_of_wide_outputs(C, batch, loss, prec, tol):
+def test_loss_rows_of_wide_outputs(C, batch, loss, prec, tol, monkeypatch):
     """Outputs at the edges of what a wavefront keeps of a row and of a workgroup's columns and samples."""
+    monkeypatch.setenv("BETTY_TUNE", "narrow=0")
     wl = wk.tiny(kind="l2", act="gelu", dims=(9, 20, C), batch=batch, loss=loss, prec=prec)
     prob = oracle_problem(wl)
     b = binding.from_workload(wl)
@@ -162,7 +170,9 @@ def test_loss_rows_of_wide_outputs(C, batch, loss, prec, tol):
     loss_ref, grad_ref = orc.lower_grad(prob, wl.w, wl.lam)
     grad, cost = b.betty_lower_grad(w, lam, want_loss=True)
     assert rel_l2(host(grad), grad_ref) < tol and abs(float(cost) - loss_ref) < tol * abs(loss_ref)
+    b.profile(True)
     assert rel_l2(host(b.betty_hvp(w, lam, dev(v))), orc.hvp(prob, wl.w, wl.lam, v)) < tol
+    assert sum(r[0] == "loss" for r in b.profile_records()) == 2       # the rows of the loss and those of its Hessian
     b.close()
 
 
@@ -297,17 +307,28 @@ def test_stream_of_a_handle_kept_from_before_a_call():
     kept.synchronize()                            # the stream outlives the handle
 
 
-DEEP = (24, 20, 20, 20, 20, 20, 20, 4)               # steps of more than ten launches: recorded when they repeat
+DEEP = (24, 20, 20, 20, 20, 20, 20, 4)               # ten launches a call and more, layer by layer: recorded when they repeat
+
+
+def launches(b, call):
+    b.profile(True)
+    call()
+    n = len(b.profile_records())
+    b.profile(False)
+    return n
 
 
 @pytest.mark.parametrize("dims,act,repeats", [((64, 32, 4), "relu", 2), (DEEP, "gelu", 2), (DEEP, "gelu", 3)])
-def test_steps_whose_arguments_keep_changing(dims, act, repeats):
+def test_steps_whose_arguments_keep_changing(dims, act, repeats, monkeypatch):
     """Two or three steps with each learning rate cost what steps with as many learning rates cost (next to
     nothing is recorded that will not be replayed), and each uses the scalars it was given."""
+    monkeypatch.setenv("BETTY_TUNE", "narrow=0")
     wl = wk.tiny(kind="l2", act=act, dims=dims, batch=64, prec="fp32")
     prob = oracle_problem(wl)
     b = binding.from_workload(wl)
     w, lam, mom = dev(wl.w), dev(wl.lam), torch.zeros(wl.d, device="cuda")
+    n = launches(b, lambda: b.betty_lower_sgd_step(w.clone(), lam, mom.clone(), 0.0, 0.0))
+    assert n >= 10 if dims == DEEP else n < 10, n
     w64, m64 = wl.w.astype(np.float64), np.zeros(wl.d)
     for k in range(8):
         lr, wd = 0.02 / (1 + k // repeats), 0.01 * (k // repeats)
@@ -326,16 +347,17 @@ def test_steps_whose_arguments_keep_changing(dims, act, repeats):
         torch.cuda.synchronize()
         return time.perf_counter() - t0
 
-    both = [(loop(1), loop(repeats)) for _ in range(10)]
+    both = [(loop(1), loop(repeats)) for _ in range(30)]     # (the host's speed changes now and then: both see the fast times)
     one, many = (min(t) for t in zip(*both))
     assert many < 1.25 * one, (one, many)         # (recording every second step: 1.6 times)
     b.close()
 
 
 @pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
-def test_short_calls_that_are_recorded(prec, tol):
+def test_short_calls_that_are_recorded(prec, tol, monkeypatch):
     """Gradients, products and steps of a deep small model are replayed from the third call on: every call
     against the oracle, with other batches registered and another stream in between."""
+    monkeypatch.setenv("BETTY_TUNE", "narrow=0")
     wl, wl2 = (wk.tiny(kind="reweight", act="gelu", dims=DEEP, batch=33, prec=prec, hidden=9, seed=s) for s in (0, 1))
     wl2.w, wl2.lam = wl.w, wl.lam
     batches = [dict(X_tr=dev(x.X_tr), X_val=dev(x.X_val), y_tr=torch.as_tensor(x.y_tr).int().cuda(),
@@ -348,6 +370,9 @@ def test_short_calls_that_are_recorded(prec, tol):
     vd, qd, Hv, m = dev(v), dev(q), torch.empty_like(w), torch.empty_like(lam)
     grad, gval = torch.empty_like(w), torch.empty_like(w)
     other, lib = torch.cuda.Stream(), b.lib
+    for call in (lambda: b.betty_hvp(w, lam, vd, out=Hv), lambda: b.betty_lower_grad(w, lam), lambda: b.betty_upper_grad(w),
+                 lambda: b.betty_mixed_vjp(w, lam, qd), lambda: b.betty_lower_sgd_step(w2.clone(), lam, mom.clone(), 0.0, 0.0)):
+        assert launches(b, call) >= 10
     w64, m64 = wl.w.astype(np.float64), np.zeros(wl.d)
     for rep in range(7):
         prob = probs[rep % 2]
@@ -422,8 +447,9 @@ def test_series_in_sample_space(kind, dims, batch, act, prec, tol, monkeypatch):
     prob = oracle_problem(wl)
     u = orc.lower_grad(prob, wl.w, wl.lam)[1].astype(np.float32)
     err = {}
-    for form in (0, 1):
-        monkeypatch.setenv("BETTY_TUNE", f"samples={form}")
+    for form in (0, 1, 2):
+        # (2: first-order passes with all layers in one workgroup, where the model has up to eight)
+        monkeypatch.setenv("BETTY_TUNE", f"samples={min(form, 1)},narrow={form // 2}")
         b = binding.from_workload(wl)
         w, lam = dev(wl.w), dev(wl.lam)
         for K in (0, 1, 4):
@@ -433,7 +459,7 @@ def test_series_in_sample_space(kind, dims, batch, act, prec, tol, monkeypatch):
                        orc.best_response_neumann(prob, wl.w, wl.lam, u.astype(np.float64), K, 0.05)))
         b.close()
     for K in (0, 1, 4):
-        assert err[1, K] < max(tol, 1.5 * err[0, K]), (K, err)
+        assert max(err[1, K], err[2, K]) < max(tol, 1.5 * err[0, K]), (K, err)
 
 
 @pytest.mark.parametrize("kind,dims,batch", [
@@ -467,7 +493,7 @@ def test_finite_difference_forms(kind, dims, batch, paired, monkeypatch):
     """Both points of a central difference in shared launches, and one after the other."""
     wl = wk.tiny(kind=kind, act="gelu" if len(dims) > 2 else "none", dims=dims, batch=batch, hidden=20, prox_rho=0.3)
     prob = oracle_problem(wl)
-    monkeypatch.setenv("BETTY_TUNE", f"fd2={paired}")
+    monkeypatch.setenv("BETTY_TUNE", f"fd2={paired},narrow=0")
     b = binding.from_workload(wl)
     w, lam = dev(wl.w), dev(wl.lam)
     for K in (0, 1, 3):

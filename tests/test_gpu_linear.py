@@ -13,18 +13,20 @@ from tests.util import oracle_problem, rel_l2, time_forms
 pytestmark = pytest.mark.gpu
 
 
-# (features and bias in chunks of 32, batches in chunks of 32 and groups of 16 lanes, 1024 threads)
-@pytest.mark.parametrize("dims,batch,batch_val,loss,bias", [
-    ((1, 1), 1, 1, "mse", True),
-    ((31, 2), 33, 15, "ce", True),            # 32 entries with the bias
-    ((32, 3), 32, 64, "ce", True),            # the bias opens a chunk of its own
-    ((64, 1), 512, 256, "mse", False),        # every thread holds data of the validation batch's columns
-    ((32, 12), 1024, 1000, "ce", False),      # every thread holds a row; the largest softmax model
-    ((1000, 2), 16, 17, "ce", False),         # ... a column
-    ((175, 4), 700, 30, "mse", True),         # G at its largest, a train batch the registers could not hold
-    ((128, 16), 100, 101, "mse", True),       # operand rows end where the bias begins
+# (features and bias in chunks of 32, batches in chunks of 32 and groups of 16 lanes, 1024 threads; whether the series and
+# conjugate gradient fit)
+@pytest.mark.parametrize("dims,batch,batch_val,loss,bias,fits", [
+    ((1, 1), 1, 1, "mse", True, (True, True)),
+    ((31, 2), 33, 15, "ce", True, (True, True)),            # 32 entries with the bias
+    ((32, 3), 32, 64, "ce", True, (True, True)),            # the bias opens a chunk of its own
+    ((64, 1), 512, 256, "mse", False, (True, True)),        # every thread holds data of the validation batch's columns
+    ((32, 12), 1024, 1000, "ce", False, (True, True)),      # every thread holds a row; the largest softmax model
+    ((1000, 2), 16, 17, "ce", False, (True, True)),         # ... a column
+    ((159, 4), 700, 30, "mse", True, (True, False)),        # G at its largest, a train batch the registers could not hold
+    ((160, 4), 700, 30, "mse", True, (False, False)),       # ... one more
+    ((128, 16), 100, 101, "mse", True, (True, True)),       # operand rows end where the bias begins
 ])
-def test_small_linear_models(dims, batch, batch_val, loss, bias, monkeypatch):
+def test_small_linear_models(dims, batch, batch_val, loss, bias, fits, monkeypatch):
     monkeypatch.setenv("BETTY_TUNE", "linear=1")
     wl = wk.tiny(kind="l2", act="none", dims=dims, batch=max(batch, batch_val), loss=loss, prec="fp32")
     cut = {f: getattr(wl, f)[:n] for f, n in (("X_tr", batch), ("y_tr", batch), ("t_tr", batch), ("X_val", batch_val),
@@ -39,6 +41,12 @@ def test_small_linear_models(dims, batch, batch_val, loss, bias, monkeypatch):
         assert rel_l2(got, orc.hypergrad_neumann(prob, wl.w, wl.lam, K, 0.05)) < 1e-5, ("neumann", K)
         got = b.betty_hypergrad_cg(w, lam, K).cpu().numpy()
         assert rel_l2(got, orc.hypergrad_cg(prob, wl.w, wl.lam, K)) < 1e-4, ("cg", K)
+    for call, fit in zip((lambda: b.betty_hypergrad_neumann(w, lam, 4, 0.05), lambda: b.betty_hypergrad_cg(w, lam, 4)), fits):
+        b.profile(True)
+        call()
+        kinds = [r[0] for r in b.profile_records()]
+        assert (len(kinds) <= 2 and "shadow" not in kinds) == fit, kinds      # (X^T X and the rest, or launches from the conversion on)
+        b.profile(False)
     b.close()
 
 
