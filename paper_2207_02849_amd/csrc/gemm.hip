@@ -166,23 +166,23 @@ __device__ __forceinline__ void epi_gram(const Epilogue& e, int M, int rb, int c
 // operand-typed copies: row-major element by element, transposed as 4-element vectors; rows beyond M
 // are written as zeros (they are padding of the transposed operand).  Either may be null.
 template <typename T, int NR>
-__device__ __forceinline__ void epi_copies(T* out, T* outT, int ld, int ldT, int M, int rb, int col, const float (&val)[NR]) {
+__device__ __forceinline__ void epi_copies(T* out, T* outT, int ld, int ldT, int M, int rb, int col, const bool (&ok)[NR], float (&val)[NR]) {
+#pragma unroll
+  for (int k = 0; k < NR; ++k)
+    if (!ok[k]) val[k] = 0.f;
   if (out) {
 #pragma unroll
     for (int k = 0; k < NR; ++k)
-      if (epi_row<NR>(rb, k) < M) store1<T>(out + (long long)epi_row<NR>(rb, k) * ld + col, val[k]);
+      if (ok[k]) store1<T>(out + (long long)epi_row<NR>(rb, k) * ld + col, val[k]);
   }
   if (outT) {
     T* o = outT + (long long)col * ldT + rb;
-    float v[NR];
-#pragma unroll
-    for (int k = 0; k < NR; ++k) v[k] = epi_row<NR>(rb, k) < M ? val[k] : 0.f;
     if constexpr (NR == 1) {
-      store1<T>(o, v[0]);
+      store1<T>(o, val[0]);
     } else {
 #pragma unroll
       for (int q = 0; q < NR / 4; ++q) {
-        const float quad[4] = {v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+        const float quad[4] = {val[4 * q], val[4 * q + 1], val[4 * q + 2], val[4 * q + 3]};
         if (rb + 8 * q < M) store4<T>(o + 8 * q, quad);
       }
     }
@@ -237,7 +237,7 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
         act_eval(e.act, R.a[k] + (sg ? -t : t), val[k], d1, d2);
         if (ok[k]) dphi[of[k]] = d1;
       }
-      epi_copies<T, NR>((T*)(sg ? e.out2 : e.out), (T*)(sg ? e.outT2 : e.outT), e.ld, e.ldT, M, rb, col, val);
+      epi_copies<T, NR>((T*)(sg ? e.out2 : e.out), (T*)(sg ? e.outT2 : e.outT), e.ld, e.ldT, M, rb, col, ok, val);
     }
     return;
   } else if constexpr (MODE == EPI_FWD) {
@@ -373,9 +373,9 @@ __device__ __forceinline__ void epi_finish(const Epilogue& e, int M, int N, int 
   } else {
     return;
   }
-  epi_copies<T, NR>((T*)e.out, (T*)e.outT, e.ld, e.ldT, M, rb, col, val);
+  epi_copies<T, NR>((T*)e.out, (T*)e.outT, e.ld, e.ldT, M, rb, col, ok, val);
   if constexpr (MODE == EPI_FWD && sizeof(T) == 4)         // fp32 forward of a bf16 problem: the bf16 operand copies of the activation leave from here too
-    epi_copies<__bf16, NR>((__bf16*)e.out2, (__bf16*)e.outT2, e.ld, e.ldT, M, rb, col, val);
+    epi_copies<__bf16, NR>((__bf16*)e.out2, (__bf16*)e.outT2, e.ld, e.ldT, M, rb, col, ok, val);
 }
 
 // ------------------------------------------------------------------------------------------
