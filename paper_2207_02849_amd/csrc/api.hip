@@ -545,7 +545,8 @@ const float* wnet_theta(betty_handle h, const float* lambda) {
 //    reduction is long: four wavefronts leave a SIMD one, with nothing to hide its barriers behind and the whole
 //    epilogue to itself (bf16 gradients of 2048-2048-2048-1000 at 512 117 -> 108 us; 40 models -0.3 ... +8 %; with two tiles a
 //    compute unit 64-tiles hide each other, and fp32 launches lose up to 5 %);
-//  * 128-tiles once there are enough of them to fill the chip several times over;
+//  * 128-tiles once there are enough of them to fill the chip several times over (not for layer 1 at both points of a
+//    difference, whose epilogue does not fit their registers: 168-812-26 with 23949 samples 1620 -> 2020 us a call);
 //  * otherwise plain 64-tiles.
 int plan_chain(betty_handle h, Elem elem, GemmBatch& b) {
   if (h->fixed_grouping && elem == ELEM_BF16) {
@@ -575,7 +576,7 @@ int plan_chain(betty_handle h, Elem elem, GemmBatch& b) {
       return GEMM_16;
   }
   if (h->tune_split && !h->tune_pair_forced && x.t32 <= 600) return GEMM_32x8;
-  if (!h->tune_pair_forced && x.t128 >= h->tune_tile128_min) return GEMM_128x1;
+  if (!h->tune_pair_forced && x.t128 >= h->tune_tile128_min && b.p[0].e.mode != EPI_FWD_PM) return GEMM_128x1;
   if (h->tune_pair_forced || (h->tune_split && !h->tune_rect_forced && x.t64 <= 256 && x.steps >= 16)) return GEMM_64x2;
   if (h->tune_rect_forced || (elem == ELEM_BF16 && x.rect >= 200 && x.t64 <= 1024 && x.steps >= 16)) return GEMM_128x64;
   return GEMM_64x1;

@@ -1329,7 +1329,7 @@ static void launch_chain_mode(int mode, int total, hipStream_t st, const GemmBat
     BETTY_CASE(EPI_FWD) BETTY_CASE(EPI_FWD_LAST) BETTY_CASE(EPI_BWD) BETTY_CASE(EPI_RFWD)
     BETTY_CASE(EPI_RFWD_LAST) BETTY_CASE(EPI_RBWD) BETTY_CASE(EPI_RFWD_LAST_HESS) BETTY_CASE(EPI_GRAM) BETTY_CASE(EPI_SAMPLE)
     case EPI_FWD_PM:
-      if constexpr (sizeof(T) == 4) launch_one<T, BT, WPG, KG, EPI_FWD_PM>(total, st, b, err);
+      if constexpr (sizeof(T) == 4 && BT < 128) launch_one<T, BT, WPG, KG, EPI_FWD_PM>(total, st, b, err);
       else err = hipErrorInvalidValue;
       break;
     default: err = hipErrorInvalidValue; break;

@@ -55,3 +55,12 @@ def test_forward_kernels_leave_four_wavefronts_a_simd():
     assert len(forward) == 8
     crowded = {k: m[".vgpr_count"] for k, m in forward.items() if m[".vgpr_count"] > 128 or m[".vgpr_spill_count"]}
     assert not crowded, crowded
+
+
+@pytest.mark.skipif(not os.path.exists(build.LIB), reason="not built")
+def test_no_kernel_keeps_arrays_in_scratch():
+    """(An epilogue too large for its tile's registers had 1344 bytes a lane there: up to 1.25 times the time of a call.)"""
+    kernels = built_kernels()
+    assert len(kernels) > 300
+    scratch = {k: m[".private_segment_fixed_size"] for k, m in kernels.items() if m[".private_segment_fixed_size"] or m[".vgpr_spill_count"]}
+    assert not scratch, scratch
