@@ -166,6 +166,7 @@ struct betty_handle_s {
   bool tune_pair_forced = false;              // 64-tiles with a two-way K split for every activation-shaped product
   int tune_narrow = -1;                       // narrow.hip: 0 never, 1 or 2 that first layer wherever it fits, -1 by size
   int tune_linear = -1;                       // one-workgroup kernel for single-layer models: 0 never, 1 wherever it fits, -1 by size
+  int tune_layer1 = -1;                       // finite differences, layer 1 of both points from one product: 0 never, 1 wherever it can be, -1 by size
   int tune_samples = -1;                      // sample-space series: 0 never, 1 wherever it exists, -1 by size
   // Finite differences: the passes at w + eps v and w - eps v share their launches, with weight operands
   // for both points; above 32M parameters, where either alone fills the chip, they follow each other on one
@@ -724,9 +725,19 @@ void forward_and_loss(betty_handle h, const Pass* ps, int n, int upto = 0) {
       p.e = e;
       flops += 2.0 * sb.B * li.n_in * li.n_out;
     }
-    b.n -= extra;                                  // (the passes' kernel, and with it their bits, stay what they are without it)
+    if (extra) --b.n;
     const int cfg = plan_chain(h, elem, b);
-    b.n += extra;
+    if (extra) {
+      // z_1 of that batch rides along where its product takes the passes' kernel anyway, whose choice (and with it the
+      // passes' bits) it does not change; otherwise it takes a launch with the kernel of its own size
+      GemmBatch own;
+      own.n = 1;
+      own.p[0] = b.p[b.n];
+      const int own_cfg = plan_chain(h, elem, own);
+      const double own_flops = 2.0 * own.p[0].g.M * li.n_in * li.n_out;
+      if (own_cfg == cfg) ++b.n;
+      else { launch_gemm_batch(h->ctx, elem, own_cfg, own, own_flops); flops -= own_flops; }
+    }
     launch_gemm_batch(h->ctx, elem, cfg, b, flops);
   }
   if (upto > 0) return;
@@ -1850,7 +1861,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
   h->use_pipeline = large && desc->prec == BETTY_PREC_FP32;
   h->fd_paired = !large;
   h->max_Bp = std::max(padup(desc->batch_train), padup(desc->batch_val));
-  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,pair=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>,linear=<0|1>,narrow=<0|1|2>" (see plan_chain)
+  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,pair=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>,linear=<0|1>,narrow=<0|1|2>,layer1=<0|1>" (see plan_chain)
   if (const char* t = getenv("BETTY_TUNE")) {
     int v;
     if (const char* q = strstr(t, "wgrad=")) if (sscanf(q + 6, "%d", &v) == 1 && (v == GEMM_128x1 || v == GEMM_64x1)) h->tune_wgrad_cfg = v;
@@ -1863,6 +1874,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
     if (const char* q = strstr(t, "samples=")) if (sscanf(q + 8, "%d", &v) == 1) h->tune_samples = v != 0;
     if (const char* q = strstr(t, "pair=")) if (sscanf(q + 5, "%d", &v) == 1) h->tune_pair_forced = v == 1;
     if (const char* q = strstr(t, "narrow=")) if (sscanf(q + 7, "%d", &v) == 1 && v >= 0 && v <= 2) h->tune_narrow = v;
+    if (const char* q = strstr(t, "layer1=")) if (sscanf(q + 7, "%d", &v) == 1) h->tune_layer1 = v != 0;
     if (const char* q = strstr(t, "linear=")) if (sscanf(q + 7, "%d", &v) == 1) h->tune_linear = v != 0;
     if (const char* q = strstr(t, "fd2=")) if (sscanf(q + 4, "%d", &v) == 1) h->fd_paired = v != 0;
   }
@@ -2190,11 +2202,19 @@ static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, f
   // Layer 1 is linear in the perturbation: z_1 at w +- eps v is X W_1 + b_1 +- eps (X V_1 + c_1).  The first term is
   // formed once, the second once for both points, and neither point needs operand copies of its first layer: half the
   // products of the largest layer and most of the perturbation's traffic (5.3M parameters, 5 differences: 1260 -> 1105 us).
+  // z_1 is written once and read at every difference, and but for reweighting, whose pass at w goes over the train batch
+  // anyway, it is a product more, the only one that a single difference would save.  So from 128 inputs and 2^25
+  // multiplications of that layer for reweighting, and from three differences and 2^28 otherwise: of 1674 calls timed in both
+  // forms 302, 4.4 % faster, 10 of them more than 1.5 % slower, at most 2.6 % (with two differences 7 of 27 are slower, up to
+  // 8 %).  (At any size: 15-1200-86, batch 976, K = 1 104 -> 124 us.)
   // (Not where a narrow model's first-order pass starts at layer 1: the one at w, which reweighting never takes so, or
   // those at the points.)
   const LayerInfo& l1 = h->layers[0];
+  const double products = (double)sb.B * l1.n_in * l1.n_out;
+  const bool shared = h->tune_layer1 >= 0 ? h->tune_layer1 == 1
+                                          : l1.n_in >= 128 && (rw ? products >= 33554432.0 : K > 2 && products >= 268435456.0);
   auto from_inputs = [&](int samples) { return narrow_first(h, false, ELEM_F32, samples) == 1; };
-  const bool split = h->L >= 2 && (K > 0 || rw) && (rw || !from_inputs(h->desc.batch_val)) && !from_inputs(2 * sb.B);
+  const bool split = shared && h->L >= 2 && (K > 0 || rw) && (rw || !from_inputs(h->desc.batch_val)) && !from_inputs(2 * sb.B);
   const Pass at_w = train_pass(h, os, w, lambda, false);
   h->z1_pass = split ? &at_w : nullptr;
   WgradSink init{EPI_WGRAD_INIT, nullptr, nullptr, nullptr, v, K > 0 ? p : nullptr, 0.f, false};
@@ -2252,7 +2272,7 @@ static void fd_seq(betty_handle h, const float* w, const float* lambda, int K, f
     // Both points' gradients of layer 1 have the same left operand, so their deltas may be added (with their opposite
     // signs: the difference) before the product instead of after it.  A launch of 4 us against half of that product, at
     // some 70 TFLOP/s: from 2^28 multiplications.
-    step.minus_summed = h->L >= 2 && (double)sb.B * l1.n_in * l1.n_out >= 268435456.0;
+    step.minus_summed = h->L >= 2 && products >= 268435456.0;
     step.sum_p = last;
     sums = 0;
     if (!last || rw) step.sums = &sums;

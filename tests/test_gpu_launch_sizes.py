@@ -116,8 +116,9 @@ def test_narrow_models_keep_the_series_over_samples_where_it_is_faster(dims, bat
 
 @pytest.mark.parametrize("kind", ["l2", "reweight"])
 @pytest.mark.parametrize("batch,batch_val", [(13000, 50), (40, 24600), (40, 50)])
-def test_finite_differences_of_narrow_models_mix_forms(batch, batch_val, kind):
+def test_finite_differences_of_narrow_models_mix_forms(batch, batch_val, kind, monkeypatch):
     """The pass at w, those at both points and the shared first layer with either form of pass beside the other."""
+    monkeypatch.setenv("BETTY_TUNE", "layer1=1")
     wl, big = (wk.tiny(kind=kind, act="gelu", dims=(20, 12, 16, 12, 3), batch=n, hidden=20, seed=s) for n, s in ((batch, 0), (batch_val, 3)))
     wl.X_val, wl.y_val = big.X_val, big.y_val
     prob = oracle_problem(wl)
@@ -481,6 +482,7 @@ def test_conjugate_gradient_steps(kind, dims, batch):
     b.close()
 
 
+@pytest.mark.parametrize("layer1", (0, 1))
 @pytest.mark.parametrize("paired", (0, 1))
 @pytest.mark.parametrize("kind,dims,batch", [
     ("l2", (65, 3), 40),                     # one layer; rows that allow no 16-byte accesses, a second tile of one row
@@ -489,11 +491,12 @@ def test_conjugate_gradient_steps(kind, dims, batch):
     ("proximal", (33, 66, 10), 31),
     ("reweight", (33, 66, 10), 65),
 ])
-def test_finite_difference_forms(kind, dims, batch, paired, monkeypatch):
-    """Both points of a central difference in shared launches, and one after the other."""
+def test_finite_difference_forms(kind, dims, batch, paired, layer1, monkeypatch):
+    """Both points of a central difference in shared launches, and one after the other; layer 1 of both from one product
+    or from their own weights."""
     wl = wk.tiny(kind=kind, act="gelu" if len(dims) > 2 else "none", dims=dims, batch=batch, hidden=20, prox_rho=0.3)
     prob = oracle_problem(wl)
-    monkeypatch.setenv("BETTY_TUNE", f"fd2={paired},narrow=0")
+    monkeypatch.setenv("BETTY_TUNE", f"fd2={paired},layer1={layer1},narrow=0")
     b = binding.from_workload(wl)
     w, lam = dev(wl.w), dev(wl.lam)
     for K in (0, 1, 3):
@@ -594,6 +597,31 @@ def test_proximal_series_keeps_its_bias_sums_beyond_bf16(B, monkeypatch):
     got = host(b.betty_best_response_neumann(w, w, dev(u), K, alpha))
     ref = orc.best_response_neumann(prob, np.zeros(b.d), np.zeros(b.d), u.astype(np.float64), K, alpha)
     assert rel_l2(got, ref) < 2e-5
+    b.close()
+
+
+@pytest.mark.parametrize("dims,batch,batch_val,kind,K", [
+    ((15, 1200, 86), 976, 40, "l2", 1),               # layer 1 of both points from one product: 1.2 times the time of its own
+    ((168, 812, 26), 23949, 144, "reweight", 1),      # ... 1.25
+    ((1011, 97, 3), 788, 203, "l2", 1),               # ... 1.16
+])
+def test_finite_differences_share_the_first_layer_only_where_it_is_faster(dims, batch, batch_val, kind, K, monkeypatch):
+    rule, own = time_forms(monkeypatch, lambda b, w: b.betty_hypergrad_fd(w, w[:b.n_hyper], K, 1e-4), ("narrow=0", "narrow=0,layer1=0"), reps=10, dims=dims,
+                           act="gelu", loss="ce", hp=kind, prec="fp32", batch_train=batch, batch_val=batch_val)
+    assert rule < 1.08 * own, (rule, own)
+
+
+@pytest.mark.parametrize("rows,tune", [(1000, "tile128=1"), (40, "pair=1"), (129, "blocks=1"), (129, "")])
+def test_first_layer_at_both_points_in_every_tile(rows, tune, monkeypatch):
+    """Large launches take 64-tiles there, also where a plain forward product takes 128-tiles; z_1 at w with a kernel of its
+    own size beside a validation batch of another."""
+    wl, big = (wk.tiny(kind="l2", act="gelu", dims=(140, 150, 20), batch=n, hidden=20, seed=s) for n, s in ((rows, 0), (9, 3)))
+    wl.X_val, wl.y_val = big.X_val, big.y_val
+    prob = oracle_problem(wl)
+    monkeypatch.setenv("BETTY_TUNE", f"layer1=1,narrow=0,{tune}")
+    b = binding.from_workload(wl)
+    for K in (1, 2):
+        assert rel_l2(host(b.betty_hypergrad_fd(dev(wl.w), dev(wl.lam), K, 0.05, 0.01)), orc.hypergrad_fd(prob, wl.w, wl.lam, K, 0.05, 0.01)) < 1e-4
     b.close()
 
 
