@@ -3,6 +3,7 @@
 // approximate implicit differentiation followed by the mixed second-order VJP).
 #include <algorithm>
 #include <atomic>
+#include <climits>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -335,22 +336,26 @@ double samples_saving(betty_handle h, int K, bool dense) {
 // Models with narrow layers take all layers of a few samples in one workgroup (narrow.hip).  Whether the first-order
 // passes over that many samples together (rop = false) or the forward-over-reverse pass does, and from which layer on: 0 =
 // launches per layer, 1, or 2 = layer 1, whose reduction may be long, stays a launch of its own.
-// By the estimated time: a launch takes 4.7 us whatever its width (up to about 256; 3.6 where 16 samples are all its
-// rows), the fused kernel 6 us, 1.6 us a link, and 1 us per 9 KB of weights: that is the latency of fetching them link by
-// link in every workgroup, far below what a compute unit can read.
-// It holds while every 16 samples have a compute unit of their own; beyond, workgroups share units and the launches fill
-// the chip.  488 models up to 300 wide, fused over launches: forward-over-reverse passes up to 4096 samples 0.74 (of 147 chosen
-// one 4 % slower), 4096 to 8192 0.88 but up to 1.09, 8192 to 16384 1.00, above 1.07 and up to 1.47; first-order passes up
-// to 24576 samples 0.73 (none of 534 slower), above 0.85 but up to 1.10.
+// By the estimated time: a launch takes 4.7 us whatever its width (up to about 256), the fused kernel 6 us, 1.6 us a
+// link, and 1 us per 9 KB of weights: that is the latency of fetching them link by link in every workgroup, far below what a
+// compute unit can read.  Calls over fused, up to 4096 samples: forward-over-reverse passes 0.77 (353 models chosen of 619, 8 more
+// than 2.5 % slower, those of few rows), first-order passes 0.73 (none slower).
+// Beyond, workgroups share compute units and the launches fill the chip, soonest where the output is wide (a narrow one has
+// kernels of its own that cost the launches more).  Forward-over-reverse with more than 16 outputs: 4096 to 8192 samples 0.97, up
+// to 1.09, then 1.07 ... 1.36, up to 1.47; up to 16 outputs: fp32 0.80 ... 0.86 up to 32768 samples, bf16 0.85 up to 8192, 0.96 up to
+// 12288, then 1.0 and more, up to 1.22.  First-order with more than 16 outputs: 1.0 from 24576 samples on, up to 1.15; up to
+// 16 outputs: 0.75 ... 0.79 up to 65536, none slower.
 // (Forward-over-reverse passes: 32-wide, 8 layers 66 us by launches, 29 us; 64-wide fp32, 4 layers 28 / 23 us; 128-wide 28 / 47 us, with
 // bf16 operands 28 / 32 us.)
-constexpr int NARROW_MAX_ROP = 4096, NARROW_MAX_GRAD = 24576;
+int narrow_max_samples(betty_handle h, bool rop, Elem elem) {
+  if (h->dims[h->L] > LAST_ROP_MAX_C) return rop ? 4096 : 24576;
+  return !rop ? INT_MAX : elem == ELEM_BF16 ? 12288 : 32768;
+}
 struct NarrowEstimate { double fused, launches; int first; };
-NarrowEstimate narrow_estimate(betty_handle h, bool rop, Elem elem, int samples) {
+NarrowEstimate narrow_estimate(betty_handle h, bool rop, Elem elem) {
   const int L = h->L;
   const bool bf16 = elem == ELEM_BF16, narrow_out = h->dims[L] <= LAST_ROP_MAX_C;
-  const double launch = rop ? std::min(4.7, 3.6 + 0.25 * std::log2(std::max(samples, 16) / 16.0)) : 4.7;
-  const double per_kb = 1.0 / 9, es = bf16 ? 2.0 : 4.0, fwd_es = !rop && bf16 && h->desc.act == BETTY_ACT_RELU ? 4.0 : es;
+  const double launch = 4.7, per_kb = 1.0 / 9, es = bf16 ? 2.0 : 4.0, fwd_es = !rop && bf16 && h->desc.act == BETTY_ACT_RELU ? 4.0 : es;
   const double launches = launch * (2 * L - (narrow_out ? 2 : rop && h->dims[L] <= 32 ? 1 : 0)), pairs = rop ? 2.0 : 1.0;
   double fused = 6.0, first_link = 0;
   for (int l = 1; l <= L; ++l) {
@@ -370,20 +375,21 @@ int narrow_first(betty_handle h, bool rop, Elem elem, int samples) {
   for (int l = 0; l <= L; ++l) net.n[l] = h->dims[l];
   if (narrow_lds(net, elem, elem == ELEM_BF16) > 150 * 1024) return 0;
   if (h->tune_narrow > 0) return L >= 3 ? h->tune_narrow : 1;
-  const NarrowEstimate e = narrow_estimate(h, rop, elem, samples);
-  return samples <= (rop ? NARROW_MAX_ROP : NARROW_MAX_GRAD) && e.fused < (rop ? 0.88 : 0.92) * e.launches ? e.first : 0;
+  const NarrowEstimate e = narrow_estimate(h, rop, elem);
+  return samples <= narrow_max_samples(h, rop, elem) && e.fused < 0.92 * e.launches ? e.first : 0;
 }
 int narrow_rop_first(betty_handle h, Elem elem) { return narrow_first(h, true, elem, h->desc.batch_train); }
 
-// What the fused pass takes off a step of the recurrence over parameters, which samples_saving counts by launches: half the
-// estimate (measured: 0.8 of it on average, less for two layers), as the saving in sample space is underestimated with it.
-// (154 models with narrow layers, series of 1, 3 and 9 steps over launches only: 0.758; narrow layers always 0.757, but a
-// model with one wide and two narrow widths up to 1.26 times as long: 915-33-33-146, batch 25, K = 9 208 -> 264 us.)
+// What the fused pass takes off a step of the recurrence over parameters, which samples_saving counts by launches: half of
+// the estimate less 2 us, as it is 0.8 of it on average, nothing with two layers or few rows, and the saving in sample space is
+// underestimated where it is.  (371 models with narrow layers, series of 1, 3 and 9 steps over launches only: 0.800, the better
+// form of every call 0.798, 9 of 2226 calls more than 3 % slower; narrow layers always: up to 1.26, 915-33-33-146, batch 25,
+// K = 9 208 -> 264 us.)
 double narrow_saving(betty_handle h) {
   const Elem elem = h->sets[0].elem;
   if (!narrow_rop_first(h, elem)) return 0.0;
-  const NarrowEstimate e = narrow_estimate(h, true, elem, h->desc.batch_train);
-  return 0.5 * std::max(0.0, e.launches - e.fused);
+  const NarrowEstimate e = narrow_estimate(h, true, elem);
+  return std::max(0.0, 0.5 * (e.launches - e.fused) - 2.0);
 }
 
 bool has_samples_form(betty_handle h, int K) { return h->desc.hp == BETTY_HP_REWEIGHT_NET || (h->desc.hp == BETTY_HP_PROXIMAL && K > 0); }

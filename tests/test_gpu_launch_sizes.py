@@ -97,6 +97,7 @@ def test_narrow_models_are_as_exact_as_launches(monkeypatch):
 
 
 @pytest.mark.parametrize("dims,batch,prec,act", [
+    ((44, 40, 40, 40, 10), 60000, "bf16", "gelu"),
     ((117, 58, 46, 154), 29661, "bf16", "relu"),                     # one workgroup for 16 samples 1.4 times the time of the launches
     ((9, 67, 67, 41, 26, 153), 13003, "bf16", "relu"),               # ... 1.2
 ])
@@ -119,7 +120,7 @@ def test_narrow_models_keep_the_series_over_samples_where_it_is_faster(dims, bat
 def test_finite_differences_of_narrow_models_mix_forms(batch, batch_val, kind, monkeypatch):
     """The pass at w, those at both points and the shared first layer with either form of pass beside the other."""
     monkeypatch.setenv("BETTY_TUNE", "layer1=1")
-    wl, big = (wk.tiny(kind=kind, act="gelu", dims=(20, 12, 16, 12, 3), batch=n, hidden=20, seed=s) for n, s in ((batch, 0), (batch_val, 3)))
+    wl, big = (wk.tiny(kind=kind, act="gelu", dims=(20, 12, 16, 12, 20), batch=n, hidden=20, seed=s) for n, s in ((batch, 0), (batch_val, 3)))
     wl.X_val, wl.y_val = big.X_val, big.y_val
     prob = oracle_problem(wl)
     b = binding.from_workload(wl)
