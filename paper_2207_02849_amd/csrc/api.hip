@@ -457,15 +457,17 @@ bool has_linear_form(betty_handle h, bool cg) {
 // threads each round), sums over chunks of features that one thread forms per sample and output (chunks), and over
 // chunks of samples per parameter (update), each times the outputs, and the beginning costs as much as several steps.  The
 // Gram form of the squared error pays for X^T X by the train batch, once, and its steps not at all by it.
-// Fitted to 6078 calls timed in both forms (up to 1000 features, 16 outputs, 262144 train samples, K = 0 ... 20): estimates within
-// 3 to 4 % (launches) and 6 to 11 % (one workgroup); of the 4911 calls that take this form 5 are more than 3 % slower, the worst
-// 10 %, and 226 of the others would have gained 5 % or more.  (By the number of outputs alone: softmax 401 - 12, batch 64, K = 2
+// Fitted to 6078 calls timed in both forms (up to 1000 features, 16 outputs, 262144 train samples, K = 0 ... 20): estimates
+// within 3 to 4 % (launches) and 6 to 10 % (one workgroup); 26 of the calls that take this form are more than 3 % slower, the worst
+// 12 %, and 87 of the others would have been more than 3 % faster, up to 16 % (single steps of squared errors with 10^5
+// samples and more 29 %).  (By the number of outputs alone: softmax 401 - 12, batch 64, K = 2
 // 36 -> 67 us, conjugate gradient of 64 - 16, batch 512, K = 1 30 -> 57.)  Ridge 64 - 1, batch 512, K = 20: 163 us by
 // launches, 19 us; softmax 200 - 4, batch 128, K = 5: 52 / 38 us (conjugate gradient 84 / 50).
 bool use_linear(betty_handle h, bool cg, int K) {
   if (!has_linear_form(h, cg)) return false;
   if (h->tune_linear == 1) return true;
   const LayerInfo& li = h->layers[0];
+  if (li.n_out > 16) return false;                          // (as far as it was timed)
   const bool mse = h->desc.loss == BETTY_LOSS_MSE, gram = mse && !cg;
   const int n = li.n_in + (h->desc.has_bias ? 1 : 0), C = li.n_out, train = h->desc.batch_train, val = h->desc.batch_val;
   auto up = [](int x, int m) { return (x + m - 1) / m; };
@@ -477,17 +479,17 @@ bool use_linear(betty_handle h, bool cg, int K) {
   auto columns = [&](int b) { return up(up(b, 32) * up(n, 16) * 16, 256); };
   auto update = [&](int b) { return up(C * n, 1024) * up(b, 32); };
   double one = (cg ? 7.9 : 7.1) + 1.4 * C * kn;
-  one += mse ? C * (0.155 * (rows(val) + columns(val)) + 0.032 * chunks + 0.04) + 0.09 * update(val)
+  one += mse ? C * (0.15 * (rows(val) + columns(val)) + 0.022 * chunks + 0.03) + 0.09 * update(val)
              : C * (0.127 * (rows(val) + columns(val)) + 0.016 * chunks + 0.10) + 0.115 * update(val);
   if (gram) {
     one += K * (0.1 * C * rows(n) + 0.32) - 2.3;
-    if (K > 0) one += 2.2 + B * (3.6e-3 + 1.57e-5 * 4 * chunks * chunks);
+    if (K > 0) one += 2.2 + B * ((train <= 131072 ? 3.3e-3 : 4.2e-3) + 1.57e-5 * 4 * chunks * chunks);
   } else {
-    one += K * (C * ((mse ? 0.065 : 0.051) * (rows(train) + columns(train)) + 0.025 * chunks + (mse ? 0.14 : 0.26)) + 0.044 * update(train) +
+    one += K * (C * ((mse ? 0.062 : 0.051) * (rows(train) + columns(train)) + (mse ? 0.02 : 0.025) * chunks + (mse ? 0.14 : 0.26)) + 0.044 * update(train) +
                 (cg ? 2.2 : 0.35));
     if (!mse) one += 0.28 * C * rows(train);
   }
-  return one < 0.92 * launches;
+  return one < 0.97 * launches;
 }
 
 OperandSet& fd_operands(betty_handle h) { return h->sets[1].present ? h->sets[1] : h->sets[0]; }
