@@ -76,7 +76,12 @@ struct OperandSet {
 
 }  // namespace
 
-namespace { struct Pass; }
+namespace {
+struct Pass;
+// Which form the forward-over-reverse pass takes (main operand set): 0 = launches, or the first layer of narrow.hip's kernels;
+// microseconds that a pass is shorter than by launches
+struct NarrowForm { int first = 0; bool staged = false; double saving = 0.0; };
+}
 
 struct betty_handle_s {
   betty_problem_desc desc{};
@@ -161,6 +166,7 @@ struct betty_handle_s {
   // the rule would save is small but for ragged models: a step of 3072-1024-1024-1024-10 at batch 256 72.6 / 72.5 us,
   // 1024-512-512-10 36.9 / 35.6, 2048-2048-2048-1000 at 512 181 / 173, 777-301-65-33 at 130 48.3 / 35.3.
   bool fixed_grouping = false;
+  NarrowForm rop_form;
   const Pass* z1_pass = nullptr;       // first-order passes leave z_1 of this pass in fd_z1
   bool layer1_done = false;                   // a_1 and phi'(z_1) of the passes are there already (finite differences)
   bool as_pair = false;                       // choose kernels for single passes as if two shared the launch
@@ -374,23 +380,57 @@ int narrow_first(betty_handle h, bool rop, Elem elem, int samples) {
   net.L = L;
   for (int l = 0; l <= L; ++l) net.n[l] = h->dims[l];
   if (narrow_lds(net, elem, elem == ELEM_BF16) > 150 * 1024) return 0;
+  if (h->tune_narrow > 2) return 0;
   if (h->tune_narrow > 0) return L >= 3 ? h->tune_narrow : 1;
   const NarrowEstimate e = narrow_estimate(h, rop, elem);
   return samples <= narrow_max_samples(h, rop, elem) && e.fused < 0.92 * e.launches ? e.first : 0;
 }
-int narrow_rop_first(betty_handle h, Elem elem) { return narrow_first(h, true, elem, h->desc.batch_train); }
-
-// What the fused pass takes off a step of the recurrence over parameters, which samples_saving counts by launches: half of
-// the estimate less 2 us, as it is 0.8 of it on average, nothing with two layers or few rows, and the saving in sample space is
-// underestimated where it is.  (371 models with narrow layers, series of 1, 3 and 9 steps over launches only: 0.800, the better
-// form of every call 0.798, 9 of 2226 calls more than 3 % slower; narrow layers always: up to 1.26, 915-33-33-146, batch 25,
-// K = 9 208 -> 264 us.)
-double narrow_saving(betty_handle h) {
-  const Elem elem = h->sets[0].elem;
-  if (!narrow_rop_first(h, elem)) return 0.0;
-  const NarrowEstimate e = narrow_estimate(h, true, elem);
-  return std::max(0.0, 0.5 * (e.launches - e.fused) - 2.0);
+NarrowNet narrow_net(betty_handle h, int first);
+// The forward-over-reverse pass with all weights in LDS (staged_rop_kernel), from layer `first` on: its estimated time, or
+// infinity where it does not fit (which does not depend on the pointers).  4 us, 0.6 us a link, the products with operands of the
+// direction alone by the steps of a wavefront (bf16 0.75 us, fp32 1 us) and those that one 16-tile makes one after the other beyond
+// four, 0.04 us a KB of weights, 3.3 us for layer 1 by itself.  Taken below 0.8 of the launches' estimate.  1100 models (2 to 8
+// layers, up to 320 wide, 8 to 1500 inputs, batch 16 to 3000; product and weight gradients): 700 of them 22.37 ms in all, 22.31 with
+// the better form of each, 28.51 by launches, none more than 3 % slower than launches; the other 400, up to 160 wide, 10.4 ms, 14.1 by
+// launches, 11.9 with the better of launches and narrow_rop_kernel.  Up to 4096 samples: a workgroup has a compute unit's LDS to itself.
+double staged_estimate(betty_handle h, Elem elem, int first) {
+  if (h->L < 2 || h->L > NARROW_MAX_L || first > (h->L >= 3 ? 2 : 1)) return INFINITY;
+  NarrowRopArgs r{};
+  StagedArgs a;
+  r.net = narrow_net(h, first);
+  narrow_lds(r.net, elem, false);
+  if (!staged_plan(r, elem, h->desc.act == BETTY_ACT_GELU_ERF, a)) return INFINITY;
+  int steps = 0, longest = 0;
+  for (int u = 0; u < a.units; ++u) {
+    const StagedPart& p = a.part[a.unit[u] & 15];
+    const int n = p.steps * p.products;
+    steps += n;
+    longest = std::max(longest, n);
+  }
+  return 4.0 + 0.6 * (a.n_fwd + a.n_bwd) + (elem == ELEM_BF16 ? 0.75 : 1.0) * steps / 16 + 0.2 * std::max(0, longest - 4) + 0.04 * a.groups +
+         (first > 1 ? 3.3 : 0.0);
 }
+NarrowForm choose_rop_form(betty_handle h, Elem elem) {
+  const double launches = narrow_estimate(h, true, elem).launches;
+  const double one = h->tune_narrow >= 0 && h->tune_narrow < 3 ? INFINITY : staged_estimate(h, elem, 1);
+  const double two = h->tune_narrow >= 0 && h->tune_narrow < 3 ? INFINITY : staged_estimate(h, elem, 2);
+  const NarrowForm staged{two < one ? 2 : 1, true, launches - std::min(one, two)};
+  if (h->tune_narrow >= 3) {
+    if (h->L >= 3 && h->tune_narrow == 4) return std::isfinite(two) ? NarrowForm{2, true, 0.0} : NarrowForm{};
+    return std::isfinite(one) ? NarrowForm{1, true, 0.0} : NarrowForm{};
+  }
+  NarrowForm f{narrow_first(h, true, elem, h->desc.batch_train), false, 0.0};
+  // Half of the estimate less 2 us: it is 0.8 of it on average, nothing with two layers or few rows, and the saving in sample space
+  // is underestimated where this is.  (371 models with narrow layers, series of 1, 3 and 9 steps over launches only: 0.800, the
+  // better form of every call 0.798, 9 of 2226 calls more than 3 % slower; narrow layers always: up to 1.26, 915-33-33-146,
+  // batch 25, K = 9 208 -> 264 us.)
+  if (f.first) f.saving = std::max(0.0, 0.5 * (launches - narrow_estimate(h, true, elem).fused) - 2.0);
+  return h->desc.batch_train <= 4096 && staged.saving > std::max(0.2 * launches, f.saving) ? staged : f;
+}
+int narrow_rop_first(betty_handle h) { return h->rop_form.first; }
+
+// What the fused pass takes off a step of the recurrence over parameters, which samples_saving counts by launches
+double narrow_saving(betty_handle h) { return h->rop_form.saving; }
 
 bool has_samples_form(betty_handle h, int K) { return h->desc.hp == BETTY_HP_REWEIGHT_NET || (h->desc.hp == BETTY_HP_PROXIMAL && K > 0); }
 
@@ -497,6 +537,7 @@ OperandSet& fd_operands(betty_handle h) { return h->sets[1].present ? h->sets[1]
 void plan(betty_handle h) {
   Planner pl;
   const Elem main_elem = h->desc.prec == BETTY_PREC_BF16_FP32ACC ? ELEM_BF16 : ELEM_F32;
+  h->rop_form = choose_rop_form(h, main_elem);
   plan_set(h, pl, h->sets[0], main_elem, true, SET_FULL);
   if (main_elem == ELEM_BF16) plan_set(h, pl, h->sets[1], ELEM_F32, false, SET_FIRST_ORDER);
   const size_t vb = h->d * 4;
@@ -1126,11 +1167,15 @@ void narrow_rop(betty_handle h, OperandSet& os, const float* vflat, int first, f
   a.P = h->f(sb.P); a.s = h->f(sb.s); a.Z = h->f(sb.ZL); a.labels = h->at<Labels>(h->labels);
   a.cvec = cvec;
   a.B = sb.B; a.Bp = sb.Bp;
-  launch_narrow_rop(h->ctx, os.elem, a, flops);
+  StagedArgs staged;
+  narrow_lds(a.net, os.elem, false);
+  const bool curvature = sb.e2[1] != 0;
+  if (h->rop_form.staged && staged_plan(a, os.elem, curvature, staged)) launch_staged_rop(h->ctx, os.elem, curvature, staged, flops);
+  else launch_narrow_rop(h->ctx, os.elem, a, flops);
 }
 
 void hvp_cached(betty_handle h, OperandSet& os, const float* vflat, const WgradSink& sink, bool pipelined = false) {
-  if (const int first = narrow_rop_first(h, os.elem)) {
+  if (const int first = narrow_rop_first(h)) {
     narrow_rop(h, os, vflat, first, nullptr);
     wgrad_batch(h, os, 0, true, sink);
     return;
@@ -1231,7 +1276,7 @@ void mixed_reweight_seq(betty_handle h, OperandSet& os, const float* lam, const 
   const LayerInfo& lo = h->layers[L - 1];
   // c_i is linear in the direction, so the scale is applied once, to the final sum over samples
   if (!copies_current) make_shadows(h, os, {Shadows{qflat, nullptr, &os.Vt}});   // else os.Vt already holds qflat
-  if (const int first = narrow_rop_first(h, os.elem)) {
+  if (const int first = narrow_rop_first(h)) {
     narrow_rop(h, os, qflat, first, h->f(os.cvec));
   } else if (L >= 2 && lo.n_out <= LAST_ROP_MAX_C) {
     // narrow output layer: the last product and the directional derivative in one vector kernel
@@ -1869,7 +1914,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
   h->use_pipeline = large && desc->prec == BETTY_PREC_FP32;
   h->fd_paired = !large;
   h->max_Bp = std::max(padup(desc->batch_train), padup(desc->batch_val));
-  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,pair=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>,linear=<0|1>,narrow=<0|1|2>,layer1=<0|1>" (see plan_chain)
+  // tuning overrides for experiments: BETTY_TUNE="wgrad=<cfg>,wgrad128=<n>,tile128=<n>,blocks=1,pair=1,rect=<n>,pipe=<0|1>,fd2=<0|1>,samples=<0|1>,linear=<0|1>,narrow=<0..4>,layer1=<0|1>" (see plan_chain)
   if (const char* t = getenv("BETTY_TUNE")) {
     int v;
     if (const char* q = strstr(t, "wgrad=")) if (sscanf(q + 6, "%d", &v) == 1 && (v == GEMM_128x1 || v == GEMM_64x1)) h->tune_wgrad_cfg = v;
@@ -1881,7 +1926,7 @@ betty_status betty_create(const betty_problem_desc* desc, betty_handle* out) {
     if (const char* q = strstr(t, "pipe=")) if (sscanf(q + 5, "%d", &v) == 1) h->use_pipeline = v != 0;
     if (const char* q = strstr(t, "samples=")) if (sscanf(q + 8, "%d", &v) == 1) h->tune_samples = v != 0;
     if (const char* q = strstr(t, "pair=")) if (sscanf(q + 5, "%d", &v) == 1) h->tune_pair_forced = v == 1;
-    if (const char* q = strstr(t, "narrow=")) if (sscanf(q + 7, "%d", &v) == 1 && v >= 0 && v <= 2) h->tune_narrow = v;
+    if (const char* q = strstr(t, "narrow=")) if (sscanf(q + 7, "%d", &v) == 1 && v >= 0 && v <= 4) h->tune_narrow = v;
     if (const char* q = strstr(t, "layer1=")) if (sscanf(q + 7, "%d", &v) == 1) h->tune_layer1 = v != 0;
     if (const char* q = strstr(t, "linear=")) if (sscanf(q + 7, "%d", &v) == 1) h->tune_linear = v != 0;
     if (const char* q = strstr(t, "fd2=")) if (sscanf(q + 4, "%d", &v) == 1) h->fd_paired = v != 0;

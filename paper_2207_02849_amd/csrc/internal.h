@@ -447,6 +447,33 @@ struct NarrowRopArgs {
   const float* P; const float* s; const float* Z; const Labels* labels; float* cvec;
   int B, Bp;
 };
+// The same pass with the weights of all links in LDS from the start (staged_rop_kernel).  Places in LDS are bytes, -1: absent.
+constexpr int STAGED_PARTS = 2 * NARROW_MAX_L, STAGED_UNITS = 128;
+// products that do not wait for the chain: 16-tiles of A W^T
+struct StagedPart {
+  const void* A[2]; const void* W[2]; // rows of ld elements; one product, or the sum of two
+  const float* bias;                  // or null
+  const float* dphi; const float* e2; const float* Rz;    // of the layer whose quantity leaves (some address where not used)
+  int ld, steps, N, ldf;
+  int products, S, D, E;              // where the sums, phi' and phi'' go
+  int finish;                         // what S is: 0 the sum (+ bias), 1 sum phi', 2 sum phi' + phi'' Rz
+};
+struct StagedWeights { const void* src; int ld, rows, cpr, at; unsigned inv; int group0; };   // cpr: 16-byte chunks a row, one of them room between rows; inv: 2^32 / cpr
+struct StagedLink { void* outT; int w, wpitch, steps, N, F, D, T, E; };        // weights in LDS, summand, phi', what the backward link adds, phi''
+struct StagedArgs {
+  unsigned short unit[STAGED_UNITS];  // part and 16-tile (<< 4) of a unit
+  int units, groups, n_w, n_fwd, n_bwd;
+  int B, Bp, C, pitch, buf, zl, ldz, loss, ldp;
+  const float* P; const float* s; const float* Z; const Labels* labels; float* cvec; void* RDt;
+  StagedWeights w[STAGED_PARTS];      // those of the forward links, then of the backward links, in groups of 64 chunks
+  StagedPart part[STAGED_PARTS];
+  StagedLink fwd[NARROW_MAX_L], bwd[NARROW_MAX_L];
+  int bytes;                          // of LDS
+};
+static_assert(sizeof(StagedArgs) <= 3840, "passed by value as kernel arguments");
+// false: it does not fit (which does not depend on the pointers)
+bool staged_plan(const NarrowRopArgs&, Elem, bool curvature, StagedArgs&);
+void launch_staged_rop(Ctx&, Elem, bool curvature, const StagedArgs&, double flops);
 static_assert(sizeof(NarrowGradArgs) <= 3072 && sizeof(NarrowRopArgs) <= 3072, "passed by value as kernel arguments");
 // LDS of a workgroup, and the padded row of its operands; `wide`: the forward operands are fp32
 size_t narrow_lds(NarrowNet&, Elem, bool wide);

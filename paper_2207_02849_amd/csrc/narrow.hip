@@ -462,6 +462,250 @@ __global__ __launch_bounds__(NT) void narrow_rop_kernel(NarrowRopArgs) {
 }
 
 // ------------------------------------------------------------------------------------------
+// The forward-over-reverse pass with everything a link needs in LDS before the chain begins.  narrow_rop_kernel fetches
+// weights, direction products and elementwise factors link by link, a memory latency or two (1.6 us) in every link.
+// Of these only the weights' product with the link before is in the chain.  So 16 wavefronts first form all products with
+// operands of the direction alone (units: the 16-tiles of all links) and leave them with phi' and phi'' in LDS as they stand in the accumulators;
+// forward and backward weights go straight to LDS meanwhile.  A link is then LDS reads, MFMA and one barrier.  LDS bounds the width:
+// the weights in both orientations and 3 or 4 floats an element of every hidden layer.
+//
+// Bound by the instructions that a wavefront issues one after the other, at 4 cycles and more each: 13-64-64-1, fp32, 200
+// samples (13 workgroups) 8.2 us, of which 1 us arguments and requests, 3.4 us the products along the direction, 1.8 us
+// three forward links, 0.4 us the loss Hessian, 1.3 us two backward links; the launches per layer take 13.5 us,
+// narrow_rop_kernel as much.  What counted: no loads or stores under conditions, 32-bit offsets from scalar bases, padding that
+// is zero in memory instead of masks, small loops (first version, 3600 instructions: 12.5 us).  Eight 32-wide layers, bf16, 100 samples:
+// product and weight gradient 30.7 -> 16.9 us.  Requesting a wavefront's next 16-tile ahead: 14.0 -> 14.5 us a step.
+// ------------------------------------------------------------------------------------------
+
+constexpr int SW = 16, ST = 64 * SW;                      // wavefronts, threads
+constexpr int STAGED_LDS = 159 * 1024;
+
+// Requests every 64-byte line of the argument block at once.  They are read all through the kernel, and each line's first
+// scalar load would wait for memory where it stands.
+template <typename A> __device__ __forceinline__ void warm_args() {
+  const unsigned* p = (const unsigned*)__builtin_amdgcn_kernarg_segment_ptr();
+  constexpr int N = (int)(sizeof(A) + 63) / 64;
+  static_assert(N <= 60, "lines");
+  auto at = [&](int i) { return p[(i < N ? i : N - 1) * 16]; };
+#define BETTY_W5(i_) "s"(at(i_)), "s"(at(i_ + 1)), "s"(at(i_ + 2)), "s"(at(i_ + 3)), "s"(at(i_ + 4))
+  asm volatile("" :: BETTY_W5(0), BETTY_W5(5), BETTY_W5(10), BETTY_W5(15), BETTY_W5(20), BETTY_W5(25));
+  if constexpr (N > 30) asm volatile("" :: BETTY_W5(30), BETTY_W5(35), BETTY_W5(40), BETTY_W5(45), BETTY_W5(50), BETTY_W5(55));
+#undef BETTY_W5
+}
+
+// elements of a matrix as the base, which stays in scalar registers, and 32 bits of offset
+template <typename V, typename T> __device__ __forceinline__ V at32(const void* base, unsigned i) {
+  return *(const V*)((const char*)base + i * (unsigned)sizeof(T));
+}
+
+// sums of U steps of A W^T from memory, all requested at once
+template <typename T, int U>
+__device__ __forceinline__ void staged_mac(const void* A, const void* W, unsigned a0, unsigned w0, NarrowAcc<T>& sums) {
+  constexpr int KS = narrow_ks<T>();
+  u32x4 a[U], w[U];
+#pragma unroll
+  for (int v = 0; v < U; ++v) { a[v] = at32<u32x4, T>(A, a0 + v * KS); w[v] = at32<u32x4, T>(W, w0 + v * KS); }
+#pragma unroll
+  for (int v = 0; v < U; ++v) sums.step(a[v], w[v]);
+}
+// ... from LDS
+template <typename T, int U>
+__device__ __forceinline__ void staged_mac_lds(const T* x, const T* w, NarrowAcc<T>& sums) {
+  constexpr int KS = narrow_ks<T>();
+  u32x4 a[U], b[U];
+#pragma unroll
+  for (int v = 0; v < U; ++v) { a[v] = *(const u32x4*)(x + v * KS); b[v] = *(const u32x4*)(w + v * KS); }
+#pragma unroll
+  for (int v = 0; v < U; ++v) sums.step(a[v], b[v]);
+}
+
+// CURV: phi'' is not zero
+template <typename T, bool CURV>
+__global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
+  const StagedArgs& a = *narrow_args<StagedArgs>();
+  extern __shared__ u32x4 narrow_smem[];
+  char* const lds = (char*)narrow_smem;
+  constexpr int KS = narrow_ks<T>(), EPC = 16 / (int)sizeof(T);
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int i0 = (int)blockIdx.x * NROWS, B = a.B, pitch = a.pitch, C = a.C;
+  const int fr = lane & 15, fc = (lane >> 4) * EPC, row = 4 * (lane >> 4);
+  T* const buf0 = (T*)(lds + a.buf);
+  float* const zl = (float*)(lds + a.zl);
+  const int ldz = a.ldz, Bp = a.Bp, n_fwd = a.n_fwd, n_bwd = a.n_bwd;
+  auto buf = [&](int i) { return buf0 + i * NROWS * pitch; };
+  auto slot = [&](int off, int tile) { return (f32x4v*)(lds + off + tile * 1024) + lane; };
+  warm_args<StagedArgs>();
+
+  // All weights of the chain, straight to LDS.  A layer's rows are those of its outputs, a row K rounded up to a step (the
+  // operands are zero there) and a chunk of room, which spreads the rows over the banks.
+  {
+    int q = 0;
+    for (int g = wave; g < a.groups; g += SW) {
+      while (q + 1 < a.n_w && g >= a.w[q + 1].group0) ++q;
+      const StagedWeights& w = a.w[q];
+      const int y = (g - w.group0) * 64 + lane, r = __umulhi(y, w.inv), c = y - r * w.cpr;
+      const unsigned o = min(r, w.rows - 1) * w.ld + min(c, w.cpr - 2) * EPC;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const char*)w.src + o * (unsigned)sizeof(T)),
+                                       (__attribute__((address_space(3))) void*)(lds + g * 1024), 16, 0, 0);
+    }
+  }
+  const int is = i0 + wave;                                // the sample whose loss Hessian this wavefront applies
+  const float* const prow = a.P + (long long)is * a.ldp;
+  const float p0 = prow[lane], s0 = a.s[is];
+
+  // Products with operands of the direction alone.  phi' and phi'' are zero beyond the batch and beyond the layer's width, and so
+  // is everything that leaves a link there.
+  for (int u = wave; u < a.units; u += SW) {
+    const int id = a.unit[u], tile = id >> 4, col = tile * 16 + fr;
+    const StagedPart& p = a.part[id & 15];
+    const unsigned a0 = (i0 + fr) * p.ld + fc, w0 = col * p.ld + fc, f0 = (i0 + row) * p.ldf + col;
+    const float* const bp = p.bias ? p.bias : p.dphi;
+    const float bias = bp[p.bias ? min(col, p.N - 1) : 0];
+    f32x4v d = {}, e = {}, rz = {};
+    if (p.D >= 0) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        d[k] = at32<float, float>(p.dphi, f0 + k * p.ldf);
+        if (CURV) e[k] = at32<float, float>(p.e2, f0 + k * p.ldf);
+      }
+      if (CURV && p.finish) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) rz[k] = at32<float, float>(p.Rz, f0 + k * p.ldf);
+      }
+    }
+    NarrowAcc<T> sums;
+    for (int m = 0; m < p.products; ++m) {
+      const void* const A = p.A[m];
+      const void* const W = p.W[m];
+      int s = 0;
+      for (; s + 8 <= p.steps; s += 8) staged_mac<T, 8>(A, W, a0 + s * KS, w0 + s * KS, sums);
+      if (p.steps & 4) { staged_mac<T, 4>(A, W, a0 + s * KS, w0 + s * KS, sums); s += 4; }
+      if (p.steps & 2) { staged_mac<T, 2>(A, W, a0 + s * KS, w0 + s * KS, sums); s += 2; }
+      if (p.steps & 1) staged_mac<T, 1>(A, W, a0 + s * KS, w0 + s * KS, sums);
+    }
+    f32x4v acc = sums.total();
+    if (p.finish) acc = CURV ? acc * d + e * rz : acc * d;
+    else if (p.bias) acc += bias;
+    *slot(p.S, tile) = acc;
+    if (p.D >= 0) *slot(p.D, tile) = d;
+    if (CURV && p.E >= 0) *slot(p.E, tile) = e;
+  }
+  __syncthreads();
+
+  // sums += the operand in LDS times the weights of a link
+  auto mac = [&](const T* A, const StagedLink& k, int tile, NarrowAcc<T>& sums) {
+    const T* x = A + fr * pitch + fc;
+    const T* w = (const T*)(lds + k.w) + min(tile * 16 + fr, k.N - 1) * k.wpitch + fc;
+    for (int s = k.steps >> 2; s > 0; --s, x += 4 * KS, w += 4 * KS) staged_mac_lds<T, 4>(x, w, sums);
+    if (k.steps & 2) { staged_mac_lds<T, 2>(x, w, sums); x += 2 * KS; w += 2 * KS; }
+    if (k.steps & 1) staged_mac_lds<T, 1>(x, w, sums);
+  };
+
+  auto tiles = [&](int n) { return (n + KS - 1) / KS * (KS / 16); };
+  // a hidden layer's R z: R a as the next operand and for the weight gradients, phi'' R z beside what the backward link adds
+  auto hidden = [&](const StagedLink& k, int tile, int to, const f32x4v& z) {
+    const f32x4v d = *slot(k.D, tile);
+    if (n_bwd > 0) {
+      if (CURV) *slot(k.T, tile) = *slot(k.T, tile) * d + *slot(k.E, tile) * z;
+      else *slot(k.T, tile) *= d;
+    }
+    const int col = tile * 16 + fr;
+    T* const o = buf(to) + row * pitch + col;
+    const float v[4] = {d[0] * z[0], d[1] * z[1], d[2] * z[2], d[3] * z[3]};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) o[r * pitch] = narrow_cast<T>(v[r]);
+    if (col < k.N && k.outT) store4<T>((T*)k.outT + (col * Bp + i0 + row), v);
+  };
+  StagedLink k = a.fwd[0];
+  for (int tile = wave; tile < tiles(k.N); tile += SW) hidden(k, tile, 1, *slot(k.F, tile));
+  for (int i = 1; i < n_fwd - 1; ++i) {
+    k = a.fwd[i];
+    narrow_barrier();
+    for (int tile = wave; tile < tiles(k.N); tile += SW) {
+      const f32x4v f = *slot(k.F, tile);
+      NarrowAcc<T> sums;
+      mac(buf(i & 1), k, tile, sums);
+      hidden(k, tile, (i + 1) & 1, f + sums.total());
+    }
+  }
+  k = a.fwd[n_fwd - 1];
+  narrow_barrier();
+  for (int tile = wave; tile < tiles(k.N); tile += SW) {
+    const f32x4v f = *slot(k.F, tile);
+    NarrowAcc<T> sums;
+    mac(buf((n_fwd - 1) & 1), k, tile, sums);
+    const f32x4v z = f + sums.total();
+    const int col = tile * 16 + fr;
+    if (col < C) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) zl[(row + r) * ldz + col] = z[r];
+    }
+  }
+  narrow_barrier();
+
+  // loss Hessian (or the loss's derivative along Rz): a wavefront per sample
+  {
+    const bool ok = is < B, ce = a.loss == BETTY_LOSS_SOFTMAX_CE;
+    const float* z = zl + wave * ldz;
+    auto p = [&](int c) { return c < 64 ? p0 : prow[c]; };
+    if (a.cvec) {
+      const int iv = min(is, B - 1);
+      const Labels lab = *a.labels;
+      float acc = 0.f;
+      if (ce) {
+        for (int c = lane; c < C; c += 64) acc += p(c) * z[c];
+        acc = narrow_wave_sum(acc);
+        acc -= z[min(max(lab.y[iv], 0), C - 1)];
+      } else {
+        const float* zz = a.Z + (long long)iv * a.ldp;
+        const float* tg = lab.target + (long long)iv * C;
+        for (int c = lane; c < C; c += 64) acc += 2.f * (zz[c] - tg[c]) * z[c];
+        acc = narrow_wave_sum(acc);
+      }
+      if (ok && lane == 0) a.cvec[is] = acc;
+      return;
+    }
+    float dot = 0.f;
+    if (ce) {
+      for (int c = lane; c < C; c += 64) dot += p(c) * z[c];
+      dot = narrow_wave_sum(dot);
+    }
+    for (int c = lane; c < (C + KS - 1) / KS * KS; c += 64) {
+      float v = 0.f;
+      if (ok && c < C) v = ce ? s0 * (p(c) * z[c] - p(c) * dot) : s0 * 2.f * z[c];
+      buf(0)[wave * pitch + c] = narrow_cast<T>(v);
+    }
+  }
+  narrow_barrier();
+  for (int x = t; x < C * 4; x += ST) {                              // transposed copy
+    const int c = x >> 2, r = 4 * (x & 3);
+    const T* b = buf(0) + r * pitch + c;
+    const float q[4] = {(float)b[0], (float)b[pitch], (float)b[2 * pitch], (float)b[3 * pitch]};
+    store4<T>((T*)a.RDt + (long long)c * a.Bp + i0 + r, q);
+  }
+
+  for (int i = 0; i < n_bwd; ++i) {
+    k = a.bwd[i];
+    const bool last = i + 1 == n_bwd;
+    for (int tile = wave; tile < tiles(k.N); tile += SW) {
+      const f32x4v d = *slot(k.D, tile), tt = *slot(k.T, tile);
+      NarrowAcc<T> sums;
+      mac(buf(i & 1), k, tile, sums);
+      const f32x4v x = sums.total() * d + tt;
+      const int col = tile * 16 + fr;
+      const float v[4] = {x[0], x[1], x[2], x[3]};
+      if (!last) {
+        T* const o = buf((i + 1) & 1) + row * pitch + col;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r * pitch] = narrow_cast<T>(v[r]);
+      }
+      if (col < k.N) store4<T>((T*)k.outT + (col * Bp + i0 + row), v);
+    }
+    if (!last) narrow_barrier();
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 
 constexpr size_t NARROW_LDS = 150 * 1024;
 
@@ -516,6 +760,92 @@ void launch_narrow_rop(Ctx& ctx, Elem elem, NarrowRopArgs& a, double flops) {
   static PerDevice allowed[2];
   if (elem == ELEM_F32) narrow_launch(ctx, narrow_rop_kernel<float>, allowed[0], blocks, lds, a);
   else narrow_launch(ctx, narrow_rop_kernel<__bf16>, allowed[1], blocks, lds, a);
+}
+
+bool staged_plan(const NarrowRopArgs& r, Elem elem, bool curvature, StagedArgs& a) {
+  a = StagedArgs{};
+  const NarrowNet& net = r.net;
+  const int KS = elem == ELEM_F32 ? 16 : 32, EPC = elem == ELEM_F32 ? 4 : 8, L = net.L, first = net.first;
+  const bool backward = !r.cvec;
+  auto steps = [&](int n) { return (n + KS - 1) / KS; };
+  auto tiles = [&](int n) { return steps(n) * (KS / 16); };
+  int width = 16, place[2][NARROW_MAX_L + 1] = {};
+  long long at = 0;
+  for (int back = 0; back < 2; ++back)
+    for (int l = back ? 2 : first + 1; l <= L && (!back || backward); ++l) {
+      const int K = back ? net.n[l] : net.n[l - 1];
+      StagedWeights& w = a.w[a.n_w++];
+      w.src = back ? r.Wn[l - 1] : r.Wt[l - 1];
+      w.ld = net.np[back ? l : l - 1]; w.rows = back ? net.n[l - 1] : net.n[l];
+      w.cpr = steps(K) * KS / EPC + 1;
+      w.inv = (unsigned)((1ULL << 32) / w.cpr + 1);      // (exact below 2^16 chunks)
+      w.group0 = a.groups;
+      w.at = place[back][l] = 1024 * a.groups;
+      a.groups += (w.rows * w.cpr + 63) / 64;
+      at = 1024LL * a.groups;
+      if (at > STAGED_LDS) return false;
+    }
+  auto take = [&](long long bytes) { const long long o = at; at += (bytes + 15) / 16 * 16; return at > STAGED_LDS ? -1 : (int)o; };
+  int F[NARROW_MAX_L + 1], D[NARROW_MAX_L + 1], T[NARROW_MAX_L + 1], E[NARROW_MAX_L + 1];
+  for (int l = 1; l <= L; ++l) {
+    const long long n = 1024LL * tiles(net.n[l]);
+    const bool inner = l >= first, hidden = l < L;
+    F[l] = inner ? take(n) : -1;
+    D[l] = hidden && (inner || backward) ? take(n) : -1;
+    T[l] = hidden && backward ? take(n) : -1;
+    E[l] = hidden && backward && curvature && inner ? take(n) : -1;
+    if (inner) width = width > net.n[l] ? width : net.n[l];
+  }
+  a.pitch = (width + 31) / 32 * 32 + EPC;                // (an odd number of chunks a row, as in narrow_lds)
+  a.buf = take(2LL * NROWS * a.pitch * (16 / EPC));
+  a.zl = take(4LL * NROWS * net.ldz);
+  if (at > STAGED_LDS) return false;
+  a.bytes = (int)at;
+  int n = 0;
+  auto part = [&](const void* A, const void* W, int K, int N, int ld, int out, int S, int D, int E, int fin) -> StagedPart& {
+    StagedPart& p = a.part[n];
+    for (int tile = 0; tile < tiles(N); ++tile, ++a.units)
+      if (a.units < STAGED_UNITS) a.unit[a.units] = (unsigned short)(tile << 4 | n);
+    ++n;
+    const float* any = r.P;
+    p = StagedPart{{A, A}, {W, W}, nullptr, any, any, any, ld, steps(K), N, net.np[out], 1, S, D, E, fin};
+    if (out < L && r.dphi[out - 1]) p.dphi = p.e2 = p.Rz = r.dphi[out - 1];
+    if (E >= 0 || fin == 2) p.e2 = r.e2[out - 1];
+    if (fin == 2) p.Rz = r.Rz[out - 1];
+    return p;
+  };
+  for (int l = first; l <= L; ++l) {
+    StagedPart& p = part(l == 1 ? r.X : r.A[l - 2], r.Vt[l - 1], net.n[l - 1], net.n[l], net.np[l - 1], l, F[l], D[l], E[l], 0);
+    p.bias = r.cbias[l - 1];
+    if (l == 2 && first == 2) { p.A[1] = r.RA1; p.W[1] = r.Wt[1]; p.products = 2; }
+    StagedLink& k = a.fwd[a.n_fwd++];
+    k = StagedLink{l < L ? r.RAt[l - 1] : nullptr, place[0][l], 0, steps(net.n[l - 1]), net.n[l], F[l], D[l], T[l], E[l]};
+    k.wpitch = (k.steps * KS / EPC + 1) * EPC;
+  }
+  for (int l = L; l >= 2 && backward; --l) {
+    const bool whole = l - 1 < first;                    // R z of the layer that leaves is in memory already
+    part(r.D[l - 1], r.Vn[l - 1], net.n[l], net.n[l - 1], net.np[l], l - 1, T[l - 1], whole ? D[l - 1] : -1, -1, whole ? curvature ? 2 : 1 : 0);
+    StagedLink& k = a.bwd[a.n_bwd++];
+    k = StagedLink{r.RDt[l - 2], place[1][l], 0, steps(net.n[l]), net.n[l - 1], -1, D[l - 1], T[l - 1], -1};
+    k.wpitch = (k.steps * KS / EPC + 1) * EPC;
+  }
+  if (a.units > STAGED_UNITS) return false;
+  a.B = r.B; a.Bp = r.Bp; a.C = net.n[L]; a.ldz = net.ldz; a.loss = net.loss; a.ldp = net.np[L];
+  a.P = r.P; a.s = r.s; a.Z = r.Z; a.labels = r.labels; a.cvec = r.cvec; a.RDt = r.RDt[L - 1];
+  return true;
+}
+
+void launch_staged_rop(Ctx& ctx, Elem elem, bool curvature, const StagedArgs& a, double flops) {
+  const int blocks = (a.B + NROWS - 1) / NROWS;
+  Launch l(ctx, BETTY_K_GEMM_RFWD, flops);
+  static PerDevice allowed[4];
+  auto go = [&](auto kernel, PerDevice& ok) {
+    const hipError_t e = allow_lds(ok, (const void*)kernel, STAGED_LDS);
+    if (e != hipSuccess) { if (ctx.first_error == hipSuccess) ctx.first_error = e; return; }
+    kernel<<<blocks, ST, a.bytes, ctx.stream>>>(a);
+  };
+  if (elem == ELEM_F32) curvature ? go(staged_rop_kernel<float, true>, allowed[0]) : go(staged_rop_kernel<float, false>, allowed[1]);
+  else curvature ? go(staged_rop_kernel<__bf16, true>, allowed[2]) : go(staged_rop_kernel<__bf16, false>, allowed[3]);
 }
 
 }  // namespace betty

@@ -76,6 +76,57 @@ def test_narrow_models_in_one_workgroup(dims, batch, kind, act, loss, bias, firs
         b.close()
 
 
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
+@pytest.mark.parametrize("first", [1, 2])
+@pytest.mark.parametrize("dims,batch,kind,act,loss,bias", [
+    ((5, 16, 16), 16, "l2", "gelu", "ce", True),              # one tile, one workgroup
+    ((33, 17, 15, 1), 17, "l2", "gelu", "mse", True),         # one past, one short; a sample of its own
+    ((40, 100, 33, 9), 40, "reweight", "gelu", "ce", False),  # more tiles than wavefronts
+    ((130, 30, 64, 70), 31, "l2", "relu", "ce", True),        # an output wider than a wavefront, K left over
+    ((9, 20, 40, 33, 20, 12, 30, 8, 5), 50, "reweight", "relu", "ce", True),   # eight layers
+    ((12, 65, 20, 4), 33, "proximal", "gelu", "mse", True),
+    ((1030, 8, 3), 20, "reweight", "gelu", "mse", True),      # many steps of K in one tile
+])
+def test_narrow_models_with_weights_in_lds(dims, batch, kind, act, loss, bias, first, prec, tol, monkeypatch):
+    """The forward-over-reverse pass with everything in LDS before the chain begins, against the oracle; and that this is the
+    form that ran: one launch where the others make one a layer."""
+    wl = wk.tiny(kind=kind, act=act, dims=dims, batch=batch, loss=loss, prec=prec, has_bias=bias, hidden=40)
+    prob = oracle_problem(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    v = orc.lower_grad(prob, wl.w, wl.lam)[1]
+    refs = dict(hvp=orc.hvp(prob, wl.w, wl.lam, v), mixed=orc.mixed_vjp(prob, wl.w, wl.lam, v),
+                neumann=orc.hypergrad_neumann(prob, wl.w, wl.lam, 2, 0.02))
+    monkeypatch.setenv("BETTY_TUNE", f"narrow={first + 2},samples=0")
+    b = binding.from_workload(wl)
+    for _ in range(2):                                        # (a second call finds what the first left in the workspace)
+        got = dict(hvp=b.betty_hvp(w, lam, dev(v)), mixed=b.betty_mixed_vjp(w, lam, dev(v)), neumann=b.betty_hypergrad_neumann(w, lam, 2, 0.02))
+        for name, ref in refs.items():
+            assert rel_l2(host(got[name]), ref) < tol, name
+    b.profile(True)
+    b.betty_hvp(w, lam, dev(v))
+    kinds = [r[0] for r in b.profile_records()]
+    assert kinds.count("gemm_rfwd") == (2 if first == 2 and len(dims) > 3 else 1) and "gemm_rbwd" not in kinds, kinds
+    b.close()
+
+
+def test_narrow_models_with_weights_in_lds_are_as_exact_as_launches(monkeypatch):
+    """(as test_narrow_models_are_as_exact_as_launches)"""
+    errors = {3: [], 0: []}
+    for seed, dims in enumerate([(300, 24, 24, 5), (200, 40, 40, 10), (100, 17, 33, 3), (64, 64, 64, 8), (200, 30, 30, 30, 30, 4), (100, 80, 20, 40)] * 2):
+        wl = wk.tiny(kind="l2", act="gelu", dims=dims, batch=100 + 31 * seed, prec="fp32", seed=seed)
+        prob = oracle_problem(wl)
+        v = np.random.default_rng(seed).standard_normal(wl.d).astype(np.float32)
+        ref = orc.hvp(prob, wl.w, wl.lam, v.astype(np.float64))
+        for form in errors:
+            monkeypatch.setenv("BETTY_TUNE", f"narrow={form}")
+            b = binding.from_workload(wl)
+            errors[form].append(rel_l2(host(b.betty_hvp(dev(wl.w), dev(wl.lam), dev(v))), ref))
+            b.close()
+    ratio = np.exp(np.mean(np.log(errors[3])) - np.mean(np.log(errors[0])))
+    print(f"{ratio:.3f}", flush=True)
+    assert ratio < 1.05, ratio
+
+
 def test_narrow_models_are_as_exact_as_launches(monkeypatch):
     """fp32 sums of all layers in one workgroup: no further off fp64 than those of the launches, on the geometric mean (one
     accumulator for a whole sum: 1.2 times as far; single results scatter by half as much)."""
