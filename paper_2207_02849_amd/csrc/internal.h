@@ -245,6 +245,27 @@ template <> __device__ __forceinline__ void store4<__bf16>(__bf16* p, const floa
   *(bf16x4*)p = v;
 }
 
+// A barrier for what is exchanged through LDS: loads and stores of memory stay in flight across it (where nothing that goes to memory is
+// read by another thread of the launch).  __syncthreads() waits for all of them, one to two microseconds.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Requests N 64-byte lines of the kernel arguments at once, from byte `at` on.  They are read all through a kernel, and the first scalar
+// load from each would wait for memory where it stands, one after the other.
+template <int N> __device__ __forceinline__ void warm_lines(int at) {
+  static_assert(N <= 60, "lines");
+  const unsigned* p = (const unsigned*)((const char*)__builtin_amdgcn_kernarg_segment_ptr() + at);
+  auto line = [&](int i) { return p[(i < N ? i : N - 1) * 16]; };
+#define BETTY_W5(i_) "s"(line(i_)), "s"(line(i_ + 1)), "s"(line(i_ + 2)), "s"(line(i_ + 3)), "s"(line(i_ + 4))
+  if constexpr (N <= 5) asm volatile("" :: BETTY_W5(0));
+  else asm volatile("" :: BETTY_W5(0), BETTY_W5(5), BETTY_W5(10), BETTY_W5(15), BETTY_W5(20), BETTY_W5(25));
+  if constexpr (N > 30) asm volatile("" :: BETTY_W5(30), BETTY_W5(35), BETTY_W5(40), BETTY_W5(45), BETTY_W5(50), BETTY_W5(55));
+#undef BETTY_W5
+}
+
 // The mixed term of finite differences for L2 decay, -2 exp(lam) w q with q = alpha p: the central difference
 // of grad_lambda along q, formed in double and rounded once.
 __device__ __forceinline__ float fd_mixed_l2(float lam, float w, float alpha, float p) {

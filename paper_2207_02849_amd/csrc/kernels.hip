@@ -64,8 +64,9 @@ template <> __device__ __forceinline__ void store_quad<__bf16>(__bf16* p, float 
 // requested before the first is used (positions are clamped into the matrix instead of being
 // predicated; a load inside control flow is waited for before the next one starts).  A 784 x 10 matrix:
 // 8 us with predicated loads, 3.6 us; 5.3M parameters: 13.6 us = 4.6 TB/s either way.
-template <typename T, int N>
-__global__ __launch_bounds__(256) void convert_batch_kernel(ConvertBatchT<N> b) {
+template <typename T, int N, int NT>
+__global__ __launch_bounds__(NT) void convert_batch_kernel(ConvertBatchT<N> b) {
+  constexpr int Q = 1024 / NT, QS = NT / 16, E = 4096 / NT, ES = NT / 64;      // quads, elements a thread; their distance in rows
   __shared__ float tile[64][65];
   int bid = blockIdx.x, ji = 0;
   while (ji + 1 < b.n && bid >= b.block_begin[ji + 1]) ++ji;
@@ -84,13 +85,13 @@ __global__ __launch_bounds__(256) void convert_batch_kernel(ConvertBatchT<N> b) 
   if (quads) {
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     const int c = c0 + 4 * tx;
-    float4 v[4];
+    float4 v[Q];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      v[i] = *(const float4*)(j.src + (long long)min(r0 + ty + 16 * i, j.rows - 1) * j.lds + min(c, j.cols - 4));
+    for (int i = 0; i < Q; ++i)
+      v[i] = *(const float4*)(j.src + (long long)min(r0 + ty + QS * i, j.rows - 1) * j.lds + min(c, j.cols - 4));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int rl = ty + 16 * i, r = r0 + rl;
+    for (int i = 0; i < Q; ++i) {
+      const int rl = ty + QS * i, r = r0 + rl;
       if (r < j.rows && c < j.cols) {
         if (out) store_quad<T>(out + (long long)r * j.ld + c, v[i].x, v[i].y, v[i].z, v[i].w);
         if (j.out32) store_quad<float>(j.out32 + (long long)r * j.ld + c, v[i].x, v[i].y, v[i].z, v[i].w);
@@ -100,8 +101,8 @@ __global__ __launch_bounds__(256) void convert_batch_kernel(ConvertBatchT<N> b) 
     if (!outT && !j.outT32) return;
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int cl = ty + 16 * i, cc = c0 + cl, r = r0 + 4 * tx;
+    for (int i = 0; i < Q; ++i) {
+      const int cl = ty + QS * i, cc = c0 + cl, r = r0 + 4 * tx;
       if (cc >= j.cols || r >= j.rows) continue;
       const float v0 = tile[4 * tx][cl], v1 = tile[4 * tx + 1][cl], v2 = tile[4 * tx + 2][cl], v3 = tile[4 * tx + 3][cl];
       T* o = outT ? outT + (long long)cc * j.ldT + r : nullptr;
@@ -120,29 +121,39 @@ __global__ __launch_bounds__(256) void convert_batch_kernel(ConvertBatchT<N> b) 
     return;
   }
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  float v[16];
+  float v[E];
 #pragma unroll
-  for (int i = 0; i < 16; ++i)
-    v[i] = j.src[(long long)min(r0 + ty + 4 * i, j.rows - 1) * j.lds + min(c0 + tx, j.cols - 1)];
+  for (int i = 0; i < E; ++i)
+    v[i] = j.src[(long long)min(r0 + ty + ES * i, j.rows - 1) * j.lds + min(c0 + tx, j.cols - 1)];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int r = r0 + ty + 4 * i, c = c0 + tx;
+  for (int i = 0; i < E; ++i) {
+    const int r = r0 + ty + ES * i, c = c0 + tx;
     if (r < j.rows && c < j.cols) {
       if (out) out[(long long)r * j.ld + c] = from_float<T>(v[i]);
       if (j.out32) j.out32[(long long)r * j.ld + c] = v[i];
     }
-    tile[ty + 4 * i][tx] = v[i];
+    tile[ty + ES * i][tx] = v[i];
   }
   if (!outT && !j.outT32) return;
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int c = c0 + ty + 4 * i, r = r0 + tx;
+  for (int i = 0; i < E; ++i) {
+    const int c = c0 + ty + ES * i, r = r0 + tx;
     if (r < j.rows && c < j.cols) {
-      if (outT) outT[(long long)c * j.ldT + r] = from_float<T>(tile[tx][ty + 4 * i]);
-      if (j.outT32) j.outT32[(long long)c * j.ldT + r] = tile[tx][ty + 4 * i];
+      if (outT) outT[(long long)c * j.ldT + r] = from_float<T>(tile[tx][ty + ES * i]);
+      if (j.outT32) j.outT32[(long long)c * j.ldT + r] = tile[tx][ty + ES * i];
     }
   }
+}
+
+// 1024 threads a tile while a compute unit has four tiles at most: a thread's address arithmetic and stores, one after the other, are what
+// such a launch waits for (steps of 1023-509-251-10, three conversions: 135.1 -> 130.1 us; product of 777-301-65-33 60.6 -> 59.5);
+// beyond, 256, whose four loads a thread keep more bytes in flight.
+constexpr int CONVERT_WIDE = 1024;
+template <typename T, int N>
+static void launch_convert(Ctx& ctx, bool wide, int blocks, const ConvertBatchT<N>& b) {
+  if (wide) convert_batch_kernel<T, N, 1024><<<blocks, 1024, 0, ctx.stream>>>(b);
+  else convert_batch_kernel<T, N, 256><<<blocks, 256, 0, ctx.stream>>>(b);
 }
 
 void launch_convert_batch(Ctx& ctx, Elem elem, ConvertBatch& b) {
@@ -158,9 +169,10 @@ void launch_convert_batch(Ctx& ctx, Elem elem, ConvertBatch& b) {
   b.block_begin[b.n] = blocks;
   if (blocks <= 0) return;
   Launch l(ctx, BETTY_K_SHADOW, 0, bytes);
+  const bool wide = blocks <= CONVERT_WIDE;
   if (b.n > FEW_CONVERTS) {
-    if (elem == ELEM_BF16) convert_batch_kernel<__bf16><<<blocks, 256, 0, ctx.stream>>>(b);
-    else convert_batch_kernel<float><<<blocks, 256, 0, ctx.stream>>>(b);
+    if (elem == ELEM_BF16) launch_convert<__bf16>(ctx, wide, blocks, b);
+    else launch_convert<float>(ctx, wide, blocks, b);
     return;
   }
   ConvertBatchT<FEW_CONVERTS> few;
@@ -168,8 +180,8 @@ void launch_convert_batch(Ctx& ctx, Elem elem, ConvertBatch& b) {
   for (int i = 0; i <= b.n; ++i) few.block_begin[i] = b.block_begin[i];
   for (int i = 0; i < b.n; ++i) few.j[i] = b.j[i];
   for (int i = 0; i < 2; ++i) few.labels[i] = b.labels[i];
-  if (elem == ELEM_BF16) convert_batch_kernel<__bf16><<<blocks, 256, 0, ctx.stream>>>(few);
-  else convert_batch_kernel<float><<<blocks, 256, 0, ctx.stream>>>(few);
+  if (elem == ELEM_BF16) launch_convert<__bf16>(ctx, wide, blocks, few);
+  else launch_convert<float>(ctx, wide, blocks, few);
 }
 
 // (a workgroup's 2048 elements are a whole number of 64-element groups, so the result may take the place of the
@@ -433,204 +445,174 @@ __global__ __launch_bounds__(256) void loss_directional_rows_kernel(int loss, co
 // last layer of the R-op passes for narrow outputs (see LastRopArgs)
 // ------------------------------------------------------------------------------------------
 
-// Workgroup = 16 wavefronts, 4 samples.  Both small products run as zero-padded 32 x 32 MFMA
-// blocks (rows = the 4 samples; only lanes that own a real operand row load anything):
-//  phase 1  Rz_L block (4 x C): K = n_in sliced over the wavefronts in chunk pairs, partial blocks
-//           combined through LDS in wavefront order;
+// Workgroup = 16 wavefronts, 4 samples.  Both small products run as 16 x 16 MFMA blocks whose rows 4 g + s all hold sample s, so
+// that every group of 16 lanes has every sample's results and takes one of them on:
+//  phase 1  Rz_L block (4 x C): K = n_in sliced over the wavefronts, partial blocks combined through LDS in wavefront order;
 //  phase 2  (one wavefront) loss Hessian per sample with 16-lane butterflies -> R delta_L, kept in
 //           LDS in operand type next to delta_L;
-//  phase 3  each wavefront takes 32 columns j at a time: (R delta_L W^T + delta_L V^T) is one
-//           chunk pair of K = 16 classes, then the elementwise part and both output copies.
-// SAMPLES: the direction's products come in as AS and DS.  A form of its own, since 16 wavefronts leave a
-// lane 128 registers and the two forms together need more (bf16: 4 spilled, 8.1 us a launch on
-// configuration 4 against 7.5 us).
+//  phase 3  each wavefront takes 16 columns j at a time: R delta_L W^T + delta_L V^T has K = 16 + 16 classes, then the
+//           elementwise part, a sample and column a lane, and both output copies.
+// SAMPLES: the direction's products come in as AS and DS (a form of its own: fewer registers).
+// Deltas and everything beside them are zero beyond the batch and the layers' widths.
+// Bound by the one memory round trip and by what the L1 of a compute unit takes in meanwhile.  784-256-10, fp32, batch 128: 4.9 ->
+// 2.6 us from first instruction to last (a call of K = 5 119 -> 105 us): 32 x 32 blocks spent 2 us on padding in the matrix cores, and
+// loads for rows that hold nothing cost as much as real ones.  3072-1024-1024-1024-10, bf16, batch 256: 5.4 -> 3.6 us.
 template <typename T, bool SAMPLES>
 __global__ __launch_bounds__(1024) void last_layer_rop_kernel(LastRopArgs a) {
-  constexpr int S = 4, CP = LAST_ROP_MAX_C, EPC = 16 / (int)sizeof(T), NW = 16, U = sizeof(T) == 4 ? 2 : 4;
+  constexpr int S = 4, CP = LAST_ROP_MAX_C, EPC = 16 / (int)sizeof(T), KS = 4 * EPC, NW = 16, U = 2, NB = 2, HALF = CP / EPC;
   __shared__ float part[NW][S * CP];
-  __shared__ __attribute__((aligned(16))) T rdT[32][CP], dlT[32][CP];   // rows >= S stay zero
-  const int t = threadIdx.x, lane = t & 63, ks = t >> 6;
-  const int row = lane & 31, half = lane >> 5;
+  __shared__ __attribute__((aligned(16))) T cat[S][2 * CP];                    // R delta_L, delta_L
+  const int t = threadIdx.x, lane = t & 63, ks = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int fr = lane & 15, q = lane >> 4;
   // blockIdx.y splits the columns j of phase 3; every split repeats phases 1-2 for its samples
   // (cheap), the first one writes R delta_L
   const int i0 = blockIdx.x * S;
-  const int jsplit = ((a.n_in + gridDim.y - 1) / gridDim.y + 31) / 32 * 32;
-  const int j_begin = blockIdx.y * jsplit, j_end = min(a.n_in, j_begin + jsplit);
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  for (int x = t; x < 32 * CP; x += 64 * NW) { (&rdT[0][0])[x] = from_float<T>(0.f); (&dlT[0][0])[x] = from_float<T>(0.f); }
+  const int jsplit = ((a.n_in + gridDim.y - 1) / gridDim.y + 15) / 16 * 16;
+  const int j_begin = blockIdx.y * jsplit, j_end = a.cvec ? 0 : min(a.n_in, j_begin + jsplit);     // (the directional form has no phase 3)
 
-  // Everything phases 2 and 3 read from memory is independent of phase 1: request it now, so the
-  // kernel pays one memory round trip instead of three.  (The launcher sizes the column splits so
-  // that a wavefront has at most one block of 32 columns.)
-  const int jb = j_begin + ks * 32;
-  const bool jb_ok = jb < j_end && !a.cvec;                 // the directional form has no phase 3
-  const int j = jb + lane;
-  const bool j_ok = jb_ok && lane < 32 && j < j_end;
-  u32x4 w3[CP / (2 * EPC)], v3[CP / (2 * EPC)];
-  float dphi3[S], e23[S], rz3[S], ds3[S];
+  // operands of phase 1, the first U steps of this wavefront
+  const int steps = (a.n_in + KS - 1) / KS, per = (steps + NW - 1) / NW;
+  const int s_begin = min(ks * per, steps), s_end = min(steps, s_begin + per);
+  // (Lanes of rows that hold nothing load nothing: what a compute unit's L1 takes in, 16 cycles for 64 lanes' 16 bytes, is
+  // what a launch waits for here.)
+  const T* const ra = (const T*)a.RA + (long long)(i0 + (fr & 3)) * a.lda + q * EPC;
+  const T* const av = (const T*)a.A + (long long)(i0 + (fr & 3)) * a.lda + q * EPC;
+  const T* const w = (const T*)a.Wt + (long long)fr * a.ldt + q * EPC;
+  const T* const v = (const T*)a.Vt + (long long)fr * a.ldt + q * EPC;
+  u32x4 r8[U] = {}, a8[U] = {}, w8[U] = {}, v8[U] = {};
+  auto request = [&](int s) {
+    if (fr < S) {
 #pragma unroll
-  for (int p = 0; p < CP / (2 * EPC); ++p) { w3[p] = zero; v3[p] = zero; }
-#pragma unroll
-  for (int ss = 0; ss < S; ++ss) { dphi3[ss] = 0.f; e23[ss] = 0.f; rz3[ss] = 0.f; ds3[ss] = 0.f; }
-  if (jb_ok) {
-    const int jr = jb + row;                                // < n_in_p: rows beyond n_in are zero padding
-    const T* wr = (const T*)a.Wn + (long long)jr * a.ldn + half * EPC;
-#pragma unroll
-    for (int p = 0; p < CP / (2 * EPC); ++p) w3[p] = *(const u32x4*)(wr + p * 2 * EPC);
-    if constexpr (!SAMPLES) {
-      const T* vr = (const T*)a.Vn + (long long)jr * a.ldn + half * EPC;
-#pragma unroll
-      for (int p = 0; p < CP / (2 * EPC); ++p) v3[p] = *(const u32x4*)(vr + p * 2 * EPC);
+      for (int u = 0; u < U; ++u)
+        if (s + u < s_end) {
+          r8[u] = *(const u32x4*)(ra + (s + u) * KS);
+          if constexpr (!SAMPLES) a8[u] = *(const u32x4*)(av + (s + u) * KS);
+        }
     }
-  }
-  if (j_ok) {
+    if (fr < a.C) {
 #pragma unroll
-    for (int ss = 0; ss < S; ++ss)
-      if (i0 + ss < a.B) {
-        const long long f = (long long)(i0 + ss) * a.ldf + j;
-        dphi3[ss] = a.dphi[f];
-        if (a.e2) { e23[ss] = a.e2[f]; rz3[ss] = a.Rz[f]; }
-        if constexpr (SAMPLES) ds3[ss] = a.DS[f];
-      }
+      for (int u = 0; u < U; ++u)
+        if (s + u < s_end) {
+          w8[u] = *(const u32x4*)(w + (s + u) * KS);
+          if constexpr (!SAMPLES) v8[u] = *(const u32x4*)(v + (s + u) * KS);
+        }
+    }
+  };
+  request(s_begin);
+
+  // Everything phases 2 and 3 read from memory is independent of phase 1: requested beside its operands and not waited for at its
+  // barrier, so the kernel pays one memory round trip (1 to 2 us) instead of three.  (The launcher sizes the column splits so that a wavefront has at most NB blocks of 16 columns.)
+  u32x4 w3[NB] = {}, v3[NB] = {};
+  float dphi3[NB], e23[NB], rz3[NB], ds3[NB];
+#pragma unroll
+  for (int n = 0; n < NB; ++n) {
+    const int jb = j_begin + (ks + NW * n) * 16;
+    dphi3[n] = e23[n] = rz3[n] = ds3[n] = 0.f;
+    if (jb >= j_end) break;
+    const long long wo = (long long)(jb + fr) * a.ldn;
+    if constexpr (sizeof(T) == 2) {
+      // one step of 32: chunks 0 and 1 are W with R delta_L, 2 and 3 V with delta_L
+      const T* x = (const T*)(!SAMPLES && q >= HALF ? a.Vn : a.Wn) + wo + (q & 1) * EPC;
+      w3[n] = *(const u32x4*)x;
+    } else {
+      w3[n] = *(const u32x4*)((const T*)a.Wn + wo + q * EPC);
+      if constexpr (!SAMPLES) v3[n] = *(const u32x4*)((const T*)a.Vn + wo + q * EPC);
+    }
+    const long long f = (long long)(i0 + q) * a.ldf + jb + fr;
+    dphi3[n] = a.dphi[f];
+    if (a.e2) { e23[n] = a.e2[f]; rz3[n] = a.Rz[f]; }
+    if constexpr (SAMPLES) ds3[n] = a.DS[f];
   }
   float p2 = 0.f, s2 = 0.f, cb2 = 0.f;
   Labels lab{};
-  if (ks == 0 && a.cvec) lab = *a.labels;
   T d2 = from_float<T>(0.f);
   if (ks == 0) {
-    const int s = lane >> 4, c = lane & 15, i = i0 + s;
-    if (c < a.C && i < a.B) {
-      if (a.loss == BETTY_LOSS_SOFTMAX_CE) p2 = a.P[(long long)i * a.ldp + c];
-      if constexpr (SAMPLES) cb2 = a.AS[(long long)i * a.ldas + c];
-      else if (a.cbias) cb2 = a.cbias[c];
-      if (!a.cvec) {
-        s2 = a.s[i];
-        d2 = ((const T*)a.DL)[(long long)i * a.ldd + c];
-      }
+    const int i = i0 + q;
+    if (a.loss == BETTY_LOSS_SOFTMAX_CE) p2 = a.P[(long long)i * a.ldp + fr];
+    if constexpr (SAMPLES) cb2 = a.AS[(long long)i * a.ldas + fr];
+    else if (a.cbias) cb2 = a.cbias[min(fr, a.C - 1)];
+    if (a.cvec) {
+      lab = *a.labels;
+    } else {
+      s2 = a.s[i];
+      d2 = ((const T*)a.DL)[(long long)i * a.ldd + fr];
     }
   }
 
   // ---- phase 1
-  {
-    f32x16 acc;
+  f32x4v acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s = s_begin; s < s_end; s += U) {
+    if (s > s_begin) request(s);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    const bool a_ok = row < S && i0 + row < a.B, b_ok = row < a.C;
-    const int pairs = a.n_in_p / (2 * EPC), per = (pairs + NW - 1) / NW;
-    const int p_begin = ks * per, p_end = min(pairs, p_begin + per);
-    const T* ra = (const T*)a.RA + (long long)(i0 + row) * a.lda + half * EPC;
-    const T* av = (const T*)a.A + (long long)(i0 + row) * a.lda + half * EPC;
-    const T* w = (const T*)a.Wt + (long long)row * a.ldt + half * EPC;
-    const T* v = (const T*)a.Vt + (long long)row * a.ldt + half * EPC;
-    for (int p0 = p_begin; p0 < p_end; p0 += U) {
-      u32x4 r8[U], a8[U], w8[U], v8[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) { r8[u] = zero; a8[u] = zero; w8[u] = zero; v8[u] = zero; }
-      if (a_ok) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (p0 + u < p_end) {
-            r8[u] = *(const u32x4*)(ra + (p0 + u) * 2 * EPC);
-            if constexpr (!SAMPLES) a8[u] = *(const u32x4*)(av + (p0 + u) * 2 * EPC);
-          }
-      }
-      if (b_ok) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (p0 + u < p_end) {
-            w8[u] = *(const u32x4*)(w + (p0 + u) * 2 * EPC);
-            if constexpr (!SAMPLES) v8[u] = *(const u32x4*)(v + (p0 + u) * 2 * EPC);
-          }
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {                         // all-zero chunks add nothing
-        MfmaChunk<T>::run(r8[u], w8[u], acc);
-        if constexpr (!SAMPLES) MfmaChunk<T>::run(a8[u], v8[u], acc);
-      }
-    }
-    // registers 0..3 of lanes 0..15 hold samples 0..3 of class `lane`
-    if (lane < CP) {
-#pragma unroll
-      for (int r = 0; r < S; ++r) part[ks][r * CP + lane] = acc[r];
+    for (int u = 0; u < U; ++u) {
+      if (s + u >= s_end) break;
+      MfmaStep16<T>::run(r8[u], w8[u], acc);
+      if constexpr (!SAMPLES) MfmaStep16<T>::run(a8[u], v8[u], acc);
     }
   }
-  __syncthreads();
+  if (lane < CP) {
+#pragma unroll
+    for (int r = 0; r < S; ++r) part[ks][r * CP + lane] = acc[r];
+  }
+  lds_barrier();
 
-  // ---- phase 2
+  // ---- phase 2: 16 lanes per sample (lane % 16 = class)
   if (ks == 0) {
-    const int s = lane >> 4, c = lane & 15, i = i0 + s;
+    const int i = i0 + q;
     float rz = 0.f;
 #pragma unroll
-    for (int q = 0; q < NW; ++q) rz += part[q][lane];
-    const bool ok = c < a.C && i < a.B;
+    for (int k = 0; k < NW; ++k) rz += part[k][lane];
+    const bool ok = fr < a.C && i < a.B;
     rz = ok ? rz + cb2 : 0.f;
     if (a.cvec) {                                           // directional form: one number per sample
       float term = 0.f;
       if (ok) {
         if (a.loss == BETTY_LOSS_SOFTMAX_CE) {
           const int yy = min(max(lab.y[i], 0), a.C - 1);
-          term = p2 * rz - (c == yy ? rz : 0.f);
+          term = p2 * rz - (fr == yy ? rz : 0.f);
         } else {
-          term = 2.f * (a.Z[(long long)i * a.ldp + c] - lab.target[(long long)i * a.C + c]) * rz;
+          term = 2.f * (a.Z[(long long)i * a.ldp + fr] - lab.target[(long long)i * a.C + fr]) * rz;
         }
       }
 #pragma unroll
       for (int o = 8; o > 0; o >>= 1) term += __shfl_xor(term, o, 64);
-      if (c == 0 && i < a.B) a.cvec[i] = term;
+      if (fr == 0 && i < a.B) a.cvec[i] = term;
     } else {
-      const float si = s2;
       float val;
       if (a.loss == BETTY_LOSS_SOFTMAX_CE) {
-        const float p = p2;
-        float dot = p * rz;
+        float dot = p2 * rz;
 #pragma unroll
         for (int o = 8; o > 0; o >>= 1) dot += __shfl_xor(dot, o, 64);
-        val = si * (p * rz - p * dot);
+        val = s2 * (p2 * rz - p2 * dot);
       } else {
-        val = si * 2.f * rz;
+        val = s2 * 2.f * rz;
       }
-      const T vt = from_float<T>(val);
-      if (ok) {
-        rdT[s][c] = vt;
-        dlT[s][c] = d2;
-        if (blockIdx.y == 0) {
-          ((T*)a.RDL)[(long long)i * a.ldd + c] = vt;
-          ((T*)a.RDLt)[(long long)c * a.ldRDLt + i] = vt;
-        }
+      const T vt = from_float<T>(ok ? val : 0.f);
+      cat[q][fr] = vt;
+      cat[q][CP + fr] = SAMPLES ? from_float<T>(0.f) : d2;
+      if (ok && blockIdx.y == 0) {
+        ((T*)a.RDL)[(long long)i * a.ldd + fr] = vt;
+        ((T*)a.RDLt)[(long long)fr * a.ldRDLt + i] = vt;
       }
     }
   }
-  __syncthreads();                                          // (every wavefront reaches this, in both forms)
+  lds_barrier();                                            // (every wavefront reaches this, in both forms)
 
   // ---- phase 3
-  if (jb_ok) {
-    f32x16 acc;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-    for (int p = 0; p < CP / (2 * EPC); ++p) {
-      const u32x4 r8 = *(const u32x4*)(&rdT[row][p * 2 * EPC + half * EPC]);
-      const u32x4 d8 = *(const u32x4*)(&dlT[row][p * 2 * EPC + half * EPC]);
-      MfmaChunk<T>::run(r8, w3[p], acc);
-      if constexpr (!SAMPLES) MfmaChunk<T>::run(d8, v3[p], acc);
-    }
-    // registers 0..3 of lanes 0..31: samples i0..i0+3 of column jb + lane
-    if (j_ok) {
-      float out[S];
-#pragma unroll
-      for (int ss = 0; ss < S; ++ss) {
-        const int ii = i0 + ss;
-        float o = 0.f;
-        if (ii < a.B) {
-          o = (SAMPLES ? acc[ss] + ds3[ss] : acc[ss]) * dphi3[ss] + e23[ss] * rz3[ss];
-          if (a.RD) ((T*)a.RD)[(long long)ii * a.ldRD + j] = from_float<T>(o);
-        }
-        out[ss] = o;                                       // rows beyond the batch: zero padding
-      }
-      T* ot = (T*)a.RDt + (long long)j * a.ldRDt + i0;
-#pragma unroll
-      for (int ss = 0; ss < S; ++ss) ot[ss] = from_float<T>(out[ss]);
-    }
+  for (int n = 0; n < NB; ++n) {
+    const int jb = j_begin + (ks + NW * n) * 16, j = jb + fr, i = i0 + q;
+    if (jb >= j_end) continue;
+    f32x4v o4 = {0.f, 0.f, 0.f, 0.f};
+    const T* c = &cat[fr & 3][q * EPC];
+    MfmaStep16<T>::run(*(const u32x4*)c, w3[n], o4);
+    if constexpr (sizeof(T) == 4 && !SAMPLES) MfmaStep16<T>::run(*(const u32x4*)(c + CP), v3[n], o4);
+    // register s of every lane: sample s of column j; this lane takes sample q
+    float o = q == 0 ? o4[0] : q == 1 ? o4[1] : q == 2 ? o4[2] : o4[3];
+    o = i < a.B ? (SAMPLES ? o + ds3[n] : o) * dphi3[n] + e23[n] * rz3[n] : 0.f;     // rows beyond the batch: zero padding
+    if (j >= j_end) continue;
+    if (a.RD && i < a.B) ((T*)a.RD)[(long long)i * a.ldRD + j] = from_float<T>(o);
+    ((T*)a.RDt)[(long long)j * a.ldRDt + i] = from_float<T>(o);
   }
 }
 
@@ -638,7 +620,7 @@ void launch_last_layer_rop(Ctx& ctx, Elem elem, const LastRopArgs& a) {
   if (a.B <= 0) return;
   Launch l(ctx, BETTY_K_LAST_LAYER, 8.0 * a.B * a.n_in * a.C, 0);      // two pairs in each of two products
   const int blocks = (a.B + 3) / 4;
-  // column splits: at most one block of 32 columns per wavefront (16 x 32 per workgroup), and
+  // column splits: at most two blocks of 16 columns per wavefront (512 columns per workgroup), and
   // enough workgroups to occupy the chip
   const int splits = a.cvec ? 1 : std::max((a.n_in + 511) / 512, std::max(1, std::min(256 / blocks, (a.n_in + 31) / 32)));
   const dim3 grid(blocks, splits);
@@ -651,95 +633,83 @@ void launch_last_layer_rop(Ctx& ctx, Elem elem, const LastRopArgs& a) {
   }
 }
 
-// Same layout as last_layer_rop_kernel (16 wavefronts, 4 samples, zero-padded MFMA blocks);
+// Same layout as last_layer_rop_kernel (16 wavefronts, 4 samples, 16 x 16 MFMA blocks);
 // blockIdx.z selects the batch.
 template <typename T>
 __global__ __launch_bounds__(1024) void last_layer_grad_kernel(LastGradArgs a) {
-  constexpr int S = 4, CP = LAST_ROP_MAX_C, EPC = 16 / (int)sizeof(T), NW = 16, U = sizeof(T) == 4 ? 2 : 4;
+  constexpr int S = 4, CP = LAST_ROP_MAX_C, EPC = 16 / (int)sizeof(T), KS = 4 * EPC, NW = 16, U = 2, NB = 2, HALF = CP / EPC;
   __shared__ float part[NW][S * CP];
-  __shared__ __attribute__((aligned(16))) T dlT[32][CP];   // rows >= S stay zero
+  __shared__ __attribute__((aligned(16))) T dlT[S][2 * CP];                    // (bf16: a step of 32, whose second half is zero)
   const LastGradSide& sd = a.side[blockIdx.z];
-  const int t = threadIdx.x, lane = t & 63, ks = t >> 6;
-  const int row = lane & 31, half = lane >> 5;
+  const int t = threadIdx.x, lane = t & 63, ks = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int fr = lane & 15, g = lane >> 4;
   const int i0 = blockIdx.x * S;
   if (i0 >= sd.B) return;                                   // the two batches may differ in size
-  const int jsplit = ((a.n_in + gridDim.y - 1) / gridDim.y + 31) / 32 * 32;
+  const int jsplit = ((a.n_in + gridDim.y - 1) / gridDim.y + 15) / 16 * 16;
   const int j_begin = blockIdx.y * jsplit, j_end = min(a.n_in, j_begin + jsplit);
-  const u32x4 zero = {0u, 0u, 0u, 0u};
-  for (int x = t; x < 32 * CP; x += 64 * NW) (&dlT[0][0])[x] = from_float<T>(0.f);
+
+  // operands of phase 1, the first U steps of this wavefront
+  const int steps = (a.n_in + KS - 1) / KS, per = (steps + NW - 1) / NW;
+  const int s_begin = min(ks * per, steps), s_end = min(steps, s_begin + per);
+  const T* const av = (const T*)sd.A + (long long)(i0 + (fr & 3)) * sd.lda + g * EPC;
+  const T* const w = (const T*)sd.Wt + (long long)fr * a.ldt + g * EPC;
+  u32x4 a8[U] = {}, w8[U] = {};
+  auto request = [&](int s) {
+    if (fr < S) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (s + u < s_end) a8[u] = *(const u32x4*)(av + (s + u) * KS);
+    }
+    if (fr < a.C) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (s + u < s_end) w8[u] = *(const u32x4*)(w + (s + u) * KS);
+    }
+  };
+  request(s_begin);
 
   // inputs of phase 3 that do not depend on the earlier phases
-  const int jb = j_begin + ks * 32;
-  const bool jb_ok = jb < j_end;
-  const int j = jb + lane;
-  const bool j_ok = jb_ok && lane < 32 && j < j_end;
-  u32x4 w3[CP / (2 * EPC)];
-  float dphi3[S], e23[S];
+  u32x4 w3[NB] = {};
+  float dphi3[NB], e23[NB];
 #pragma unroll
-  for (int p = 0; p < CP / (2 * EPC); ++p) w3[p] = zero;
-#pragma unroll
-  for (int ss = 0; ss < S; ++ss) { dphi3[ss] = 0.f; e23[ss] = 0.f; }
-  if (jb_ok) {
-    const T* wr = (const T*)sd.Wn + (long long)(jb + row) * a.ldn + half * EPC;
-#pragma unroll
-    for (int p = 0; p < CP / (2 * EPC); ++p) w3[p] = *(const u32x4*)(wr + p * 2 * EPC);
-  }
-  if (j_ok) {
-#pragma unroll
-    for (int ss = 0; ss < S; ++ss)
-      if (i0 + ss < sd.B) {
-        const long long f = (long long)(i0 + ss) * sd.ldf + j;
-        dphi3[ss] = sd.dphi[f];
-        if (sd.e2) e23[ss] = sd.e2[f];
-      }
+  for (int n = 0; n < NB; ++n) {
+    const int jb = j_begin + (ks + NW * n) * 16;
+    dphi3[n] = e23[n] = 0.f;
+    if (jb >= j_end) break;
+    if (g < HALF) w3[n] = *(const u32x4*)((const T*)sd.Wn + (long long)(jb + fr) * a.ldn + g * EPC);
+    const long long f = (long long)(i0 + g) * sd.ldf + jb + fr;
+    dphi3[n] = sd.dphi[f];
+    if (sd.e2) e23[n] = sd.e2[f];
   }
 
   // ... and the label (or target) and bias of phase 2
   float t2 = 0.f, bias2 = 0.f;
   int y2 = 0;
   if (ks == 0) {
-    const int i = i0 + (lane >> 4), c = lane & 15;
+    const int i = i0 + g;
     const Labels lab = *sd.labels;
     if (i < sd.B) {
       if (a.loss == BETTY_LOSS_SOFTMAX_CE) y2 = lab.y[i];
-      else if (c < a.C) t2 = lab.target[(long long)i * a.C + c];
-      if (c < a.C && sd.bias) bias2 = sd.bias[c];
+      else if (fr < a.C) t2 = lab.target[(long long)i * a.C + fr];
+      if (fr < a.C && sd.bias) bias2 = sd.bias[fr];
     }
   }
 
   // ---- phase 1: logits block (4 x C), K = n_in sliced over the wavefronts
-  {
-    f32x16 acc;
+  f32x4v acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s = s_begin; s < s_end; s += U) {
+    if (s > s_begin) request(s);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    const bool a_ok = row < S && i0 + row < sd.B, b_ok = row < a.C;
-    const int pairs = a.n_in_p / (2 * EPC), per = (pairs + NW - 1) / NW;
-    const int p_begin = ks * per, p_end = min(pairs, p_begin + per);
-    const T* av = (const T*)sd.A + (long long)(i0 + row) * sd.lda + half * EPC;
-    const T* w = (const T*)sd.Wt + (long long)row * a.ldt + half * EPC;
-    for (int p0 = p_begin; p0 < p_end; p0 += U) {
-      u32x4 a8[U], w8[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) { a8[u] = zero; w8[u] = zero; }
-      if (a_ok) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (p0 + u < p_end) a8[u] = *(const u32x4*)(av + (p0 + u) * 2 * EPC);
-      }
-      if (b_ok) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-          if (p0 + u < p_end) w8[u] = *(const u32x4*)(w + (p0 + u) * 2 * EPC);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) MfmaChunk<T>::run(a8[u], w8[u], acc);
-    }
-    if (lane < CP) {
-#pragma unroll
-      for (int r = 0; r < S; ++r) part[ks][r * CP + lane] = acc[r];
+    for (int u = 0; u < U; ++u) {
+      if (s + u >= s_end) break;
+      MfmaStep16<T>::run(a8[u], w8[u], acc);
     }
   }
-  __syncthreads();
+  if (lane < CP) {
+#pragma unroll
+    for (int r = 0; r < S; ++r) part[ks][r * CP + lane] = acc[r];
+  }
+  lds_barrier();
 
   // ---- phase 2: 16 lanes per sample (lane % 16 = class)
   if (ks == 0) {
@@ -787,7 +757,8 @@ __global__ __launch_bounds__(1024) void last_layer_grad_kernel(LastGradArgs a) {
     }
     const float sc = omega * sd.inv_batch;
     const T dv = from_float<T>(sc * dz);
-    if (ok) dlT[s][c] = dv;
+    dlT[s][c] = ok ? dv : from_float<T>(0.f);
+    dlT[s][CP + c] = from_float<T>(0.f);
     if (blockIdx.y == 0) {
       if (iok && c == 0) { sd.ell[i] = ell; sd.s[i] = sc; sd.omega[i] = omega; }
       if (ok) {
@@ -798,35 +769,22 @@ __global__ __launch_bounds__(1024) void last_layer_grad_kernel(LastGradArgs a) {
       }
     }
   }
-  __syncthreads();
+  lds_barrier();
 
-  // ---- phase 3: delta_{L-1} for 32 columns per wavefront
-  if (jb_ok) {
-    f32x16 acc;
+  // ---- phase 3: delta_{L-1}, 16 columns a block; rows 4 g + s of a block all hold sample s, and a lane takes sample g on
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll
-    for (int p = 0; p < CP / (2 * EPC); ++p) {
-      const u32x4 d8 = *(const u32x4*)(&dlT[row][p * 2 * EPC + half * EPC]);
-      MfmaChunk<T>::run(d8, w3[p], acc);
-    }
-    if (j_ok) {
-      float out[S];
-#pragma unroll
-      for (int ss = 0; ss < S; ++ss) {
-        const int ii = i0 + ss;
-        float o = 0.f;
-        if (ii < sd.B) {
-          o = acc[ss] * dphi3[ss];
-          if (sd.D) ((T*)sd.D)[(long long)ii * sd.ldD + j] = from_float<T>(o);
-          if (sd.e2) sd.e2[(long long)ii * sd.ldf + j] = acc[ss] * e23[ss];
-        }
-        out[ss] = o;
-      }
-      T* ot = (T*)sd.Dt + (long long)j * sd.ldDt + i0;
-#pragma unroll
-      for (int ss = 0; ss < S; ++ss) ot[ss] = from_float<T>(out[ss]);
-    }
+  for (int n = 0; n < NB; ++n) {
+    const int jb = j_begin + (ks + NW * n) * 16, j = jb + fr, i = i0 + g;
+    if (jb >= j_end) break;
+    f32x4v o4 = {0.f, 0.f, 0.f, 0.f};
+    MfmaStep16<T>::run(*(const u32x4*)&dlT[fr & 3][g * EPC], w3[n], o4);
+    const float o = g == 0 ? o4[0] : g == 1 ? o4[1] : g == 2 ? o4[2] : o4[3];
+    if (j >= j_end) continue;
+    const bool iok = i < sd.B;
+    const float dl = iok ? o * dphi3[n] : 0.f;              // rows beyond the batch: zero padding
+    if (iok && sd.D) ((T*)sd.D)[(long long)i * sd.ldD + j] = from_float<T>(dl);
+    if (iok && sd.e2) sd.e2[(long long)i * sd.ldf + j] = o * e23[n];
+    ((T*)sd.Dt)[(long long)j * sd.ldDt + i] = from_float<T>(dl);
   }
 }
 

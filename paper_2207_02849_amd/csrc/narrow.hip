@@ -37,14 +37,6 @@ template <> struct NarrowAcc<float> {
   __device__ __forceinline__ f32x4v total() const { return (a[0] + a[1]) + (a[2] + a[3]); }
 };
 
-// A barrier for what is exchanged through LDS: loads and stores of memory stay in flight across it (nothing that goes
-// to memory is read by another thread of the launch).  __syncthreads() waits for every store: a microsecond a link.
-__device__ __forceinline__ void narrow_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // U steps of an operand row at this lane's chunk (beyond n they repeat the last one and are not multiplied)
 template <typename T, int U>
 __device__ __forceinline__ void narrow_load(const T* P, int s, int n, u32x4 (&f)[U]) {
@@ -116,13 +108,13 @@ __device__ __forceinline__ void narrow_link_of(const NarrowLink<T>& k, const T* 
       if (k.A1) narrow_mac<T, U>(k.A1 + (long long)(i0 + fr) * k.lda + fc, k.B1 + b, s0, s1, sums);
       if (k.A2) narrow_mac<T, U>(k.A2 + (long long)(i0 + fr) * k.lda + fc, k.B2 + b, s0, s1, sums);
     }
-    if (base == 0) narrow_barrier();
+    if (base == 0) lds_barrier();
     if (active && k.lds >= 0)
       narrow_mac_lds<T, U>(bufs + k.lds * NROWS * pitch + fr * pitch + fc, k.B0 + (long long)(tile * 16 + fr) * k.ldb + fc, s0, s1, w, sums);
     f32x4v acc = sums.total();
     if (ks > 1) {
       if (active && kp > 0) *(f32x4v*)(red + ((kp - 1) * nt + tile) * 256 + lane * 4) = acc;
-      narrow_barrier();
+      lds_barrier();
       if (active && kp == 0)
         for (int q = 1; q < ks; ++q) acc += *(const f32x4v*)(red + ((q - 1) * nt + tile) * 256 + lane * 4);
     }
@@ -222,7 +214,7 @@ __global__ __launch_bounds__(NT) void narrow_grad_kernel(NarrowGradArgs) {
         if (col < N) store4<T>(At + (long long)col * sd.Bp + i0 + row, v);
       });
   }
-  narrow_barrier();
+  lds_barrier();
 
   // loss, sample weight and output delta: a wavefront per sample, two samples each
   for (int row = wave; row < NROWS; row += NW) {
@@ -281,7 +273,7 @@ __global__ __launch_bounds__(NT) void narrow_grad_kernel(NarrowGradArgs) {
       D[c] = narrow_cast<T>(dv);
     }
   }
-  narrow_barrier();
+  lds_barrier();
   narrow_store_t<T>(dbuf(0), pitch, (T*)sd.Dt[L - 1], sd.Bp, i0, C);
 
   int from = 0;
@@ -379,7 +371,7 @@ __global__ __launch_bounds__(NT) void narrow_rop_kernel(NarrowRopArgs) {
         if (!last && col < N && RAt) store4<T>(RAt + (long long)col * a.Bp + i0 + row, v);
       });
   }
-  narrow_barrier();
+  lds_barrier();
 
   // loss Hessian (or the loss's derivative along Rz): a wavefront per sample
   for (int row = wave; row < NROWS; row += NW) {
@@ -417,7 +409,7 @@ __global__ __launch_bounds__(NT) void narrow_rop_kernel(NarrowRopArgs) {
     }
   }
   if (a.cvec) return;
-  narrow_barrier();
+  lds_barrier();
   narrow_store_t<T>(buf(0), pitch, (T*)a.RDt[L - 1], a.Bp, i0, C);
 
   int from = 0;
@@ -480,19 +472,6 @@ __global__ __launch_bounds__(NT) void narrow_rop_kernel(NarrowRopArgs) {
 constexpr int SW = 16, ST = 64 * SW;                      // wavefronts, threads
 constexpr int STAGED_LDS = 159 * 1024;
 
-// Requests every 64-byte line of the argument block at once.  They are read all through the kernel, and each line's first
-// scalar load would wait for memory where it stands.
-template <typename A> __device__ __forceinline__ void warm_args() {
-  const unsigned* p = (const unsigned*)__builtin_amdgcn_kernarg_segment_ptr();
-  constexpr int N = (int)(sizeof(A) + 63) / 64;
-  static_assert(N <= 60, "lines");
-  auto at = [&](int i) { return p[(i < N ? i : N - 1) * 16]; };
-#define BETTY_W5(i_) "s"(at(i_)), "s"(at(i_ + 1)), "s"(at(i_ + 2)), "s"(at(i_ + 3)), "s"(at(i_ + 4))
-  asm volatile("" :: BETTY_W5(0), BETTY_W5(5), BETTY_W5(10), BETTY_W5(15), BETTY_W5(20), BETTY_W5(25));
-  if constexpr (N > 30) asm volatile("" :: BETTY_W5(30), BETTY_W5(35), BETTY_W5(40), BETTY_W5(45), BETTY_W5(50), BETTY_W5(55));
-#undef BETTY_W5
-}
-
 // elements of a matrix as the base, which stays in scalar registers, and 32 bits of offset
 template <typename V, typename T> __device__ __forceinline__ V at32(const void* base, unsigned i) {
   return *(const V*)((const char*)base + i * (unsigned)sizeof(T));
@@ -534,7 +513,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
   const int ldz = a.ldz, Bp = a.Bp, n_fwd = a.n_fwd, n_bwd = a.n_bwd;
   auto buf = [&](int i) { return buf0 + i * NROWS * pitch; };
   auto slot = [&](int off, int tile) { return (f32x4v*)(lds + off + tile * 1024) + lane; };
-  warm_args<StagedArgs>();
+  warm_lines<(sizeof(StagedArgs) + 63) / 64>(0);
 
   // All weights of the chain, straight to LDS.  A layer's rows are those of its outputs, a row K rounded up to a step (the
   // operands are zero there) and a chunk of room, which spreads the rows over the banks.
@@ -620,7 +599,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
   for (int tile = wave; tile < tiles(k.N); tile += SW) hidden(k, tile, 1, *slot(k.F, tile));
   for (int i = 1; i < n_fwd - 1; ++i) {
     k = a.fwd[i];
-    narrow_barrier();
+    lds_barrier();
     for (int tile = wave; tile < tiles(k.N); tile += SW) {
       const f32x4v f = *slot(k.F, tile);
       NarrowAcc<T> sums;
@@ -629,7 +608,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
     }
   }
   k = a.fwd[n_fwd - 1];
-  narrow_barrier();
+  lds_barrier();
   for (int tile = wave; tile < tiles(k.N); tile += SW) {
     const f32x4v f = *slot(k.F, tile);
     NarrowAcc<T> sums;
@@ -641,7 +620,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
       for (int r = 0; r < 4; ++r) zl[(row + r) * ldz + col] = z[r];
     }
   }
-  narrow_barrier();
+  lds_barrier();
 
   // loss Hessian (or the loss's derivative along Rz): a wavefront per sample
   {
@@ -676,7 +655,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
       buf(0)[wave * pitch + c] = narrow_cast<T>(v);
     }
   }
-  narrow_barrier();
+  lds_barrier();
   for (int x = t; x < C * 4; x += ST) {                              // transposed copy
     const int c = x >> 2, r = 4 * (x & 3);
     const T* b = buf(0) + r * pitch + c;
@@ -701,7 +680,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
       }
       if (col < k.N) store4<T>((T*)k.outT + (col * Bp + i0 + row), v);
     }
-    if (!last) narrow_barrier();
+    if (!last) lds_barrier();
   }
 }
 
