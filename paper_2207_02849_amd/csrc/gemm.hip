@@ -775,7 +775,9 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
 // every operand row) at once, directly in fragment layout: lane l holds row l % 16 and 16-byte chunk
 // l / 16 of A and of B, so one request covers 16 rows x 64 bytes.  One round trip, U to 4 U MFMA
 // instructions, one pass through LDS (partial tiles summed in wavefront order, bit-reproducible),
-// then one output element per thread.
+// then one output element per thread.  What a compute unit's L1 takes in is the next limit (about 40 cycles for a wavefront's
+// 16 rows x 64 bytes): rows and steps that nothing is multiplied with are not requested (conjugate gradient of 784-10, batch 512: 168 ->
+// 159.5 us a call, where six of 16 columns are padding).
 constexpr int G16_PITCH = 17;                      // row pitch of a partial tile in LDS (floats)
 
 template <typename T, int U, int MODE>
@@ -814,17 +816,19 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
   const T* B0 = (const T*)g.B[0] + (long long)(n0 + fr) * g.ldb[0] + fc;
   const T* A1 = (const T*)g.A[1] + (long long)(m0 + fr) * g.lda[1] + fc;
   const T* B1 = (const T*)g.B[1] + (long long)(n0 + fr) * g.ldb[1] + fc;
+  const bool a_ok = m0 + fr < g.M, b_ok = n0 + fr < g.N;
   f32x4v acc = {0.f, 0.f, 0.f, 0.f};
   for (int s = s_begin; s < s_end; s += U) {
-    u32x4 a[U], b[U];
+    u32x4 a[U] = {}, b[U] = {};
 #pragma unroll
-    for (int u = 0; u < U; ++u) {                  // (steps beyond the range repeat the last one and are not multiplied)
-      const int q = min(s + u, s_end - 1);
+    for (int u = 0; u < U; ++u) {                  // (what nothing is multiplied with is not loaded: steps beyond the range, rows beyond the output)
+      const int q = s + u;
+      if (q >= s_end) break;
       const bool second = q >= S0;
       const int qs = second ? q - S0 : q, qo = sp ? (qs >> 2 << 1) | (qs & 1) : qs;   // two steps of value, two of remainder
       const bool bs = MODE == EPI_WGRAD_SCALED && second;
-      a[u] = *(const u32x4*)((second ? A1 : A0) + (long long)(bs ? qo : qs) * KS);
-      b[u] = *(const u32x4*)((second ? B1 : B0) + (long long)(bs ? qs : qo) * KS);
+      if (a_ok) a[u] = *(const u32x4*)((second ? A1 : A0) + (long long)(bs ? qo : qs) * KS);
+      if (b_ok) b[u] = *(const u32x4*)((second ? B1 : B0) + (long long)(bs ? qs : qo) * KS);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
