@@ -765,26 +765,28 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
 }
 
 // ------------------------------------------------------------------------------------------
-// small launches: 16 x 16 tiles, operands straight from memory into MFMA fragments
+// small launches: 16 x 16 tiles, operands in whole lines to LDS
 // ------------------------------------------------------------------------------------------
 //
-// A launch whose output has few tiles is bound by latency, not by any throughput: what counts is how
-// many dependent memory round trips, barriers and instructions lie between its start and its last
-// store (an empty kernel in a graph costs 1.75 us, one load-add-store per thread 1.85 us).  Here a
-// workgroup owns one 16 x 16 tile; its wavefronts split K, and each requests U steps (64 bytes of
-// every operand row) at once, directly in fragment layout: lane l holds row l % 16 and 16-byte chunk
-// l / 16 of A and of B, so one request covers 16 rows x 64 bytes.  One round trip, U to 4 U MFMA
-// instructions, one pass through LDS (partial tiles summed in wavefront order, bit-reproducible),
-// then one output element per thread.  What a compute unit's L1 takes in is the next limit (about 40 cycles for a wavefront's
-// 16 rows x 64 bytes): rows and steps that nothing is multiplied with are not requested (conjugate gradient of 784-10, batch 512: 168 ->
-// 159.5 us a call, where six of 16 columns are padding).
+// A launch whose output has few tiles is bound by dependent memory round trips (an empty kernel in a graph costs 1.75 us, one
+// load-add-store per thread 1.85 us) and then by what the L1 of a compute unit takes in: 4 cycles a 128-byte line of a load,
+// whether the load wants all of it or half.  16 rows x 64 bytes, a step of K in MFMA fragments, cost 65 cycles, 8 rows x 128 bytes 32.
+// So a workgroup owns one 16 x 16 tile, its wavefronts split K, and each requests U pairs of steps (128 bytes of every operand row) at
+// once, whole lines straight to LDS, and reads the fragments there: lane l holds row l % 16 and 16-byte chunk
+// l / 16 of A and of B.  The chunks of row r stand in the order c ^ (r % 8), so that the rows spread over the banks.  Rows and
+// pairs that nothing is multiplied with are not requested.  One round trip, 2 U to 8 U MFMA instructions, one pass through LDS
+// (partial tiles summed in wavefront order, bit-reproducible), then one output element per thread.  Against steps
+// straight into fragments: classifier 784-256-10, fp32, batch 128, K = 5 102.6 -> 95.9 us; conjugate gradient of 784-10, batch 512 159.5 -> 150.3;
+// finite-difference step of 1023-509-251-10, batch 100 127.7 -> 121.2; with short K too (13-64-64-1 167.5 -> 165.4).
 constexpr int G16_PITCH = 17;                      // row pitch of a partial tile in LDS (floats)
 
-template <typename T, int U, int MODE>
+// HALVES: at most two pairs, a step for each of four wavefronts
+template <typename T, int U, bool HALVES, int MODE>
 __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::type batch) {
-  constexpr int EPC = 16 / (int)sizeof(T), KS = 4 * EPC;   // elements per chunk, per step
-  extern __shared__ float part[];
+  constexpr int EPC = 16 / (int)sizeof(T), PK = 8 * EPC;   // elements per chunk, per pair of steps
+  extern __shared__ u32x4 smem[];
   const int t = threadIdx.x, lane = t & 63, kg = __builtin_amdgcn_readfirstlane(t >> 6), KG = blockDim.x >> 6;
+  float* const part = (float*)((char*)smem + KG * U * 4096);
   int bid = blockIdx.x;
   if constexpr (MODE >= EPI_WGRAD) {
     if (bid >= batch.gemm_blocks) {
@@ -807,32 +809,54 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
   EpiRegs<1> pre;
   if (t < 256) epi_prefetch<MODE, 1>(e, g.M, g.N, row, col, pre);
 
+  // pairs of steps: 128 bytes of K
   const bool sp = g.split;
-  const int S0 = sp ? (g.K[0] + 63) / 64 * 4 : (g.K[0] + KS - 1) / KS;
-  const int S = S0 + (sp ? (g.K[1] + 63) / 64 * 4 : (g.K[1] + KS - 1) / KS);
-  const int per = (S + KG - 1) / KG, s_begin = kg * per, s_end = min(S, s_begin + per);
-  const int fr = lane & 15, fc = (lane >> 4) * EPC;
-  const T* A0 = (const T*)g.A[0] + (long long)(m0 + fr) * g.lda[0] + fc;
-  const T* B0 = (const T*)g.B[0] + (long long)(n0 + fr) * g.ldb[0] + fc;
-  const T* A1 = (const T*)g.A[1] + (long long)(m0 + fr) * g.lda[1] + fc;
-  const T* B1 = (const T*)g.B[1] + (long long)(n0 + fr) * g.ldb[1] + fc;
-  const bool a_ok = m0 + fr < g.M, b_ok = n0 + fr < g.N;
+  const int P0 = sp ? (g.K[0] + 63) / 64 * 2 : (g.K[0] + PK - 1) / PK;
+  const int PT = P0 + (sp ? (g.K[1] + 63) / 64 * 2 : (g.K[1] + PK - 1) / PK);
+  const int per = HALVES ? 1 : (PT + KG - 1) / KG, p_begin = HALVES ? kg >> 1 : kg * per, p_end = min(PT, p_begin + per);
+  // a lane's row and 16-byte chunk of a load of 8 rows x 128 bytes, chunks of a row in an order of its own (see below)
+  const int lr = lane >> 3, lc = ((lane & 7) ^ lr) * EPC;
+  const T* const A0 = (const T*)g.A[0] + (long long)(m0 + lr) * g.lda[0] + lc;
+  const T* const B0 = (const T*)g.B[0] + (long long)(n0 + lr) * g.ldb[0] + lc;
+  const T* const A1 = (const T*)g.A[1] + (long long)(m0 + lr) * g.lda[1] + lc;
+  const T* const B1 = (const T*)g.B[1] + (long long)(n0 + lr) * g.ldb[1] + lc;
+  const bool k_ok = !HALVES || lc / (4 * EPC) == (kg & 1);
+  const bool a_ok[2] = {k_ok && m0 + lr < g.M, k_ok && m0 + lr + 8 < g.M}, b_ok[2] = {k_ok && n0 + lr < g.N, k_ok && n0 + lr + 8 < g.N};
+  char* const mine = (char*)smem + kg * U * 4096;              // this wavefront's operands: 16 rows of A, 16 of B a pair
+  auto request = [&](const T* x, int ld, const bool (&ok)[2], char* to) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (ok[h])
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(x + (long long)(8 * h) * ld),
+                                         (__attribute__((address_space(3))) void*)(to + 1024 * h), 16, 0, 0);
+  };
+  const int fr = lane & 15, f0 = fr * 128 + (((lane >> 4) ^ fr) & 7) * 16, f1 = fr * 128 + ((((lane >> 4) + 4) ^ fr) & 7) * 16;
   f32x4v acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s = s_begin; s < s_end; s += U) {
-    u32x4 a[U] = {}, b[U] = {};
+  for (int p = p_begin; p < p_end; p += U) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {                  // (what nothing is multiplied with is not loaded: steps beyond the range, rows beyond the output)
-      const int q = s + u;
-      if (q >= s_end) break;
-      const bool second = q >= S0;
-      const int qs = second ? q - S0 : q, qo = sp ? (qs >> 2 << 1) | (qs & 1) : qs;   // two steps of value, two of remainder
+    for (int u = 0; u < U; ++u) {                  // (what nothing is multiplied with is not loaded: pairs beyond the range, rows beyond the output)
+      const int q = p + u;
+      if (q >= p_end) break;
+      const bool second = q >= P0;
+      const int qs = second ? q - P0 : q, qo = sp ? qs >> 1 : qs;            // a pair of value, one of remainder
       const bool bs = MODE == EPI_WGRAD_SCALED && second;
-      if (a_ok) a[u] = *(const u32x4*)((second ? A1 : A0) + (long long)(bs ? qo : qs) * KS);
-      if (b_ok) b[u] = *(const u32x4*)((second ? B1 : B0) + (long long)(bs ? qs : qo) * KS);
+      request((second ? A1 : A0) + (long long)(bs ? qo : qs) * PK, second ? g.lda[1] : g.lda[0], a_ok, mine + u * 4096);
+      request((second ? B1 : B0) + (long long)(bs ? qs : qo) * PK, second ? g.ldb[1] : g.ldb[0], b_ok, mine + u * 4096 + 2048);
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (s + u < s_end) MfmaStep16<T>::run(a[u], b[u], acc);
+    for (int u = 0; u < U; ++u) {
+      if (p + u >= p_end) break;
+      const char* const x = mine + u * 4096;
+      if constexpr (HALVES) {
+        const int f = kg & 1 ? f1 : f0;
+        MfmaStep16<T>::run(*(const u32x4*)(x + f), *(const u32x4*)(x + 2048 + f), acc);
+        continue;
+      }
+      MfmaStep16<T>::run(*(const u32x4*)(x + f0), *(const u32x4*)(x + 2048 + f0), acc);
+      MfmaStep16<T>::run(*(const u32x4*)(x + f1), *(const u32x4*)(x + 2048 + f1), acc);
+    }
+    if (p + U < p_end) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (read before they are overwritten)
   }
   // register r of lane l is element [4 (l / 16) + r][l % 16]
 #pragma unroll
@@ -1379,43 +1403,43 @@ static void launch_wgrad128(int mode, int total, hipStream_t st, const GemmBatch
   }
 }
 
-// gemm16_kernel: K steps per wavefront and round (U) and wavefronts (KG) for S steps in all
+// gemm16_kernel: pairs of steps per wavefront and round (U) and wavefronts (KG) for S pairs in all
 struct Small { int u, kg; };
 static Small small_shape(int S) {
-  int u = 1;
-  while (u < 8 && (S + u - 1) / u > 16) u *= 2;
-  const int per = std::max(u, (S + 15) / 16);
+  const int u = S > 16 ? 2 : 1, per = std::max(u, (S + 15) / 16);
   return Small{u, std::min(16, std::max(4, (S + per - 1) / per))};
 }
 template <typename T>
-static int batch_steps(const GemmBatch& b) {
-  constexpr int KS = 64 / (int)sizeof(T);
+static int batch_pairs(const GemmBatch& b) {
+  constexpr int PK = 128 / (int)sizeof(T);
   int S = 1;
-  for (int i = 0; i < b.n; ++i) S = std::max(S, ((b.p[i].g.K[0] + KS - 1) / KS + (b.p[i].g.K[1] + KS - 1) / KS) << b.p[i].g.split);
+  for (int i = 0; i < b.n; ++i) S = std::max(S, ((b.p[i].g.K[0] + PK - 1) / PK + (b.p[i].g.K[1] + PK - 1) / PK) << b.p[i].g.split);
   return S;
 }
 
+template <typename T, int U, bool HALVES, int MODE>
+static void launch_small_one(int total, int kg, hipStream_t st, const GemmBatch& b, hipError_t& err) {
+  static PerDevice allowed;
+  if (const hipError_t e = allow_lds(allowed, (const void*)gemm16_kernel<T, U, HALVES, MODE>, 16 * (U * 4096 + 16 * G16_PITCH * 4)); e != hipSuccess) { err = e; return; }
+  gemm16_kernel<T, U, HALVES, MODE><<<total, 64 * kg, (size_t)kg * (U * 4096 + 16 * G16_PITCH * 4), st>>>(kernel_args<MODE>(b));
+}
 template <typename T, int MODE>
-static void launch_small(int total, hipStream_t st, const GemmBatch& b) {
-  const Small sh = small_shape(batch_steps<T>(b));
-  const dim3 block(64 * sh.kg);
-  const size_t lds = (size_t)sh.kg * 16 * G16_PITCH * 4;
-  switch (sh.u) {
-    case 1: gemm16_kernel<T, 1, MODE><<<total, block, lds, st>>>(kernel_args<MODE>(b)); break;
-    case 2: gemm16_kernel<T, 2, MODE><<<total, block, lds, st>>>(kernel_args<MODE>(b)); break;
-    case 4: gemm16_kernel<T, 4, MODE><<<total, block, lds, st>>>(kernel_args<MODE>(b)); break;
-    default: gemm16_kernel<T, 8, MODE><<<total, block, lds, st>>>(kernel_args<MODE>(b)); break;
-  }
+static void launch_small(int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
+  const int pairs = batch_pairs<T>(b);
+  const Small sh = small_shape(pairs);
+  if (pairs <= 2) launch_small_one<T, 1, true, MODE>(total, sh.kg, st, b, err);
+  else if (sh.u == 1) launch_small_one<T, 1, false, MODE>(total, sh.kg, st, b, err);
+  else launch_small_one<T, 2, false, MODE>(total, sh.kg, st, b, err);
 }
 
 template <typename T>
 static void launch_small_mode(int mode, int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
   switch (mode) {
-#define BETTY_CASE_S(M_) case M_: launch_small<T, M_>(total, st, b); break;
+#define BETTY_CASE_S(M_) case M_: launch_small<T, M_>(total, st, b, err); break;
     BETTY_CASE_S(EPI_FWD) BETTY_CASE_S(EPI_FWD_LAST) BETTY_CASE_S(EPI_BWD) BETTY_CASE_S(EPI_RFWD)
     BETTY_CASE_S(EPI_RFWD_LAST) BETTY_CASE_S(EPI_RBWD) BETTY_CASE_S(EPI_RFWD_LAST_HESS) BETTY_CASE_S(EPI_GRAM) BETTY_CASE_S(EPI_SAMPLE)
     case EPI_FWD_PM:
-      if constexpr (sizeof(T) == 4) launch_small<T, EPI_FWD_PM>(total, st, b);
+      if constexpr (sizeof(T) == 4) launch_small<T, EPI_FWD_PM>(total, st, b, err);
       else err = hipErrorInvalidValue;
       break;
     BETTY_CASE_S(EPI_WGRAD) BETTY_CASE_S(EPI_WGRAD_INIT) BETTY_CASE_S(EPI_WGRAD_NEUMANN)
@@ -1473,7 +1497,7 @@ static int gemm_cfg_waves(int cfg) { return cfg == GEMM_32x8 ? 8 : 4; }
 int launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& b, double flops, double bytes, double* partial) {
   const int bt = gemm_cfg_tile(cfg);
   const int rows_per_block = cfg != GEMM_16 ? gemm_cfg_waves(cfg)
-                           : small_shape(elem == ELEM_BF16 ? batch_steps<__bf16>(b) : batch_steps<float>(b)).kg;
+                           : small_shape(elem == ELEM_BF16 ? batch_pairs<__bf16>(b) : batch_pairs<float>(b)).kg;
   int blocks = 0;
   for (int i = 0; i < b.n; ++i) {
     b.block_begin[i] = blocks;
