@@ -100,6 +100,7 @@ struct betty_handle_s {
   OperandSet sets[2];        // [0]: element type of desc.prec; [1]: fp32 set for finite differences when prec is bf16
   OperandSet fd_minus;       // fp32, train side only: the evaluation at w - eps v, which runs beside the one at w + eps v
   size_t vec_g = 0, vec_v = 0, vec_p = 0, vec_Hv = 0;
+  size_t vec_r = 0;          // second place of the residual (cg_update_kernel)
   size_t bias_pm[2] = {0, 0};        // biases of the two perturbed points (flat layout; only the bias slices are used)
   size_t partials = 0, scalars = 0;
   size_t fd_z1 = 0;          // z_1 of the train batch at w (finite differences)
@@ -558,6 +559,7 @@ void plan(betty_handle h) {
   for (const LayerInfo& li : h->layers) n_sums += 4 * (size_t)Extent::up(li.n_in, 64) * Extent::up(li.n_out, 64) + li.n_out + 4096;
   if (h->L >= 2) h->fd_z1 = pl.take((size_t)h->sets[0].side[0].Bp * h->layers[0].n_out_p * 4);
   h->sums = pl.take(2 * n_sums * sizeof(double));      // (conjugate gradient keeps those of two launches)
+  if (h->d <= CG_ONE && h->L <= MAX_PROBLEMS) h->vec_r = pl.take(vb);
   if (plans_samples(h)) plan_samples(h, pl, h->sets[0]);
   if (h->desc.loss == BETTY_LOSS_MSE && has_linear_form(h, false))
     h->lin_gram = pl.take(linear_gram_bytes(h->layers[0].n_in + (h->desc.has_bias ? 1 : 0)));
@@ -2384,6 +2386,21 @@ betty_status betty_hypergrad_cg(betty_handle h, const float* w, const float* lam
       WgradSink hd{EPI_WGRAD_CG, Hd, dl, d, nullptr, nullptr, 0.f, false};
       hd.sums = &n_sums;
       hvp_cached(h, os, d, hd);
+      if (h->vec_r && !last) {
+        CgUpdate u;
+        u.n = h->L;
+        u.q = q; u.r = r; u.r_out = r == h->f(h->vec_g) ? h->f(h->vec_r) : h->f(h->vec_g); u.d = d; u.Hd = Hd; u.params = (int)h->d;
+        u.dHd = h->at<double>(h->sums) + begin; u.n_dHd = n_sums - begin;
+        u.rs_partial = first ? h->at<double>(h->sums) : nullptr; u.n_rs = n_rs; u.rs = rs; u.rs_new = rs_new;
+        for (int i = 0; i < h->L; ++i) {
+          const LayerInfo& li = h->layers[i];
+          u.j[i] = CgUpdateJob{(long long)li.w_off, h->desc.has_bias ? (long long)li.b_off : -1LL, li.n_in, li.n_out,
+                               i > 0 ? h->at<void>(os.Vn[i]) : nullptr, li.n_out_p, h->at<void>(os.Vt[i]), li.n_in_p};
+        }
+        launch_cg_update(h->ctx, os.elem, u);
+        r = u.r_out;
+        continue;
+      }
       CgStep c{q, r, d, Hd, h->d, h->at<double>(h->sums) + begin, n_sums - begin, first ? h->at<double>(h->sums) : nullptr, n_rs, rs, partials};
       if (last && !rw) { c.lam = dl; c.w = l2 ? w : nullptr; c.out = dlambda; }
       const int n_partial = launch_cg_step(h->ctx, c);

@@ -424,6 +424,16 @@ struct CgStep {
 struct CgDirJob { const float* r; float* d; int rows, cols; void* out; int ld; void* outT; int ldT; const float* br; float* bd; };
 struct CgDirBatch { int n = 0; int block_begin[MAX_PROBLEMS + 1]; CgDirJob j[MAX_PROBLEMS]; const double* partials; int n_partial; const float* rs; float* rs_new; };
 int launch_cg_step(Ctx&, const CgStep&);       // returns the number of partial sums
+// Both at once for up to CG_ONE parameters: every workgroup forms all of the new residual for <r, r>; the residual goes to
+// another place, since others are still reading it.  at, bias: offsets into the flat vectors (bias -1: none)
+constexpr size_t CG_ONE = 16384;
+struct CgUpdateJob { long long at, bias; int rows, cols; void* out; int ld; void* outT; int ldT; };
+struct CgUpdate {
+  int n = 0; int block_begin[MAX_PROBLEMS + 1]; CgUpdateJob j[MAX_PROBLEMS];
+  float* q; const float* r; float* r_out; float* d; const float* Hd; int params;
+  const double* dHd; int n_dHd; const double* rs_partial; int n_rs; const float* rs; float* rs_new;
+};
+void launch_cg_update(Ctx&, Elem, CgUpdate&);
 void launch_cg_dir(Ctx&, Elem, CgDirBatch&);
 void launch_adam(Ctx&, float* x, const float* g, float* m, float* v, float lr, float beta1, float beta2, float eps,
                  float bias1, float bias2, size_t n);

@@ -1097,6 +1097,101 @@ void launch_cg_dir(Ctx& ctx, Elem elem, CgDirBatch& b) {
   else cg_dir_kernel<float><<<blocks, 256, 0, ctx.stream>>>(b);
 }
 
+// cg_step and cg_dir in one launch.  Few parameters: a workgroup reads both vectors for the sum, 64 KB of 8 000 parameters,
+// sooner than another launch would start (784 x 10, batch 512, K = 8: 152 -> 130 us a call).
+template <typename T>
+__global__ __launch_bounds__(1024) void cg_update_kernel(CgUpdate b) {
+  __shared__ float tile[64][65];
+  __shared__ double red[16], red2[16], red3[16];
+  const int t = threadIdx.x;
+  int bid = blockIdx.x, ji = 0;
+  while (ji + 1 < b.n && bid >= b.block_begin[ji + 1]) ++ji;
+  const CgUpdateJob& j = b.j[ji];
+  bid -= b.block_begin[ji];
+  const int tiles_x = (j.cols + 63) / 64, c0 = (bid % tiles_x) * 64, r0 = (bid / tiles_x) * 64;
+  // the tile's own elements: four rows 16 apart of one column
+  const int tx = t & 63, ty = t >> 6, c = min(c0 + tx, j.cols - 1);
+  float r[4], h[4], d[4], q[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const long long at = j.at + (long long)min(r0 + ty + 16 * i, j.rows - 1) * j.cols + c;
+    r[i] = b.r[at]; h[i] = b.Hd[at]; d[i] = b.d[at]; q[i] = b.rs_partial ? 0.f : b.q[at];
+  }
+  // all of the residual (the vectors stand at multiples of 256 bytes); at most CG_ONE / 4096 quads a thread
+  constexpr int QUADS = CG_ONE / 4096;
+  const int quads = b.params >> 2;
+  float4 fr[QUADS], fh[QUADS];
+#pragma unroll
+  for (int i = 0; i < QUADS; ++i) {
+    if (i * 1024 >= quads) break;
+    const int x = min(t + 1024 * i, quads - 1);
+    fr[i] = ((const float4*)b.r)[x]; fh[i] = ((const float4*)b.Hd)[x];
+  }
+  const int rest = 4 * quads + t;
+  const bool has_rest = rest < b.params;
+  const float rr = has_rest ? b.r[rest] : 0.f, rh = has_rest ? b.Hd[rest] : 0.f;
+  const float den = (float)sum_partials<1024>(b.dHd, b.n_dHd, red);
+  const float num = b.rs_partial ? (float)sum_partials<1024>(b.rs_partial, b.n_rs, red2) : *b.rs;
+  const float a = (num != 0.f && den != 0.f) ? num / den : 0.f;
+  double acc = 0.0;
+#pragma unroll
+  for (int i = 0; i < QUADS; ++i) {
+    if (i * 1024 >= quads) break;
+    const float x0 = fr[i].x - a * fh[i].x, x1 = fr[i].y - a * fh[i].y, x2 = fr[i].z - a * fh[i].z, x3 = fr[i].w - a * fh[i].w;
+    if (t + 1024 * i < quads) acc += (double)(x0 * x0 + x1 * x1 + x2 * x2 + x3 * x3);
+  }
+  const float xr = rr - a * rh;
+  if (has_rest) acc += (double)(xr * xr);
+  acc = wave_sum(acc);
+  if ((t & 63) == 0) red3[t >> 6] = acc;
+  __syncthreads();
+  double sum = 0.0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) sum += red3[k];
+  const float rs_new = (float)sum, beta = num != 0.f ? rs_new / num : 0.f;
+  if (blockIdx.x == 0 && t == 0) *b.rs_new = rs_new;
+  if (j.bias >= 0 && r0 == 0 && t < 64 && c0 + t < j.cols) {          // biases: with the first row of tiles
+    const long long at = j.bias + c0 + t;
+    const float db = b.d[at], rb = b.r[at] - a * b.Hd[at];
+    b.q[at] = (b.rs_partial ? 0.f : b.q[at]) + a * db;
+    b.r_out[at] = rb;
+    b.d[at] = rb + beta * db;
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int rl = ty + 16 * i, row = r0 + rl;
+    const float rn = r[i] - a * h[i], x = rn + beta * d[i];
+    tile[rl][tx] = x;
+    if (row >= j.rows || c0 + tx >= j.cols) continue;
+    const long long at = j.at + (long long)row * j.cols + c;
+    b.q[at] = q[i] + a * d[i];
+    b.r_out[at] = rn;
+    b.d[at] = x;
+    if (j.out) ((T*)j.out)[(long long)row * j.ld + c] = from_float<T>(x);
+  }
+  __syncthreads();
+  const int cl = t >> 4, r4 = 4 * (t & 15), cc = c0 + cl, row = r0 + r4;
+  if (cc >= j.cols || row >= j.rows) return;
+  T* const o = (T*)j.outT + (long long)cc * j.ldT + row;
+  const float x[4] = {tile[r4][cl], tile[r4 + 1][cl], tile[r4 + 2][cl], tile[r4 + 3][cl]};
+  if (row + 3 < j.rows) store_quad<T>(o, x[0], x[1], x[2], x[3]);
+  else
+#pragma unroll
+    for (int k = 0; k < 4; ++k) if (row + k < j.rows) o[k] = from_float<T>(x[k]);
+}
+void launch_cg_update(Ctx& ctx, Elem elem, CgUpdate& b) {
+  int blocks = 0;
+  for (int i = 0; i < b.n; ++i) {
+    b.block_begin[i] = blocks;
+    blocks += ((b.j[i].cols + 63) / 64) * ((b.j[i].rows + 63) / 64);
+  }
+  b.block_begin[b.n] = blocks;
+  if (blocks <= 0) return;
+  Launch l(ctx, BETTY_K_VECTOR, 0, (24.0 + 2.0 * elem_size(elem)) * b.params);
+  if (elem == ELEM_BF16) cg_update_kernel<__bf16><<<blocks, 1024, 0, ctx.stream>>>(b);
+  else cg_update_kernel<float><<<blocks, 1024, 0, ctx.stream>>>(b);
+}
+
 // The two perturbed points of a central difference, straight into GEMM operands: w and v are read once,
 // 24 bytes a parameter against 48 for two passes of perturbation and conversion each.  64 x 64 tiles as in
 // convert_batch_kernel, all loads of a tile in flight together.  EPS: the step comes out of the partial sums

@@ -76,6 +76,32 @@ def test_narrow_models_in_one_workgroup(dims, batch, kind, act, loss, bias, firs
         b.close()
 
 
+@pytest.mark.parametrize("dims,batch,bias,one", [
+    ((5, 3), 20, True, True),                # fewer parameters than a wavefront, a remainder of quads
+    ((64, 64), 100, False, True),            # exactly one tile
+    ((65, 63), 90, True, True),              # one row past, one column short; biases
+    ((128, 128), 200, False, True),          # the most parameters: every quad of every thread
+    ((127, 129), 200, True, False),          # one more: two launches a step
+    ((33, 20, 9), 60, True, True),           # two layers, whose second has a row-major copy
+])
+def test_conjugate_gradient_of_few_parameters(dims, batch, bias, one, monkeypatch):
+    """Step and direction in one launch: against the oracle, and the number of launches."""
+    monkeypatch.setenv("BETTY_TUNE", "linear=0,narrow=0")
+    wl = wk.tiny(kind="l2", act="none" if len(dims) == 2 else "gelu", dims=dims, batch=batch, prec="fp32", has_bias=bias)
+    wl.lam = wl.lam + 5.0                    # a definite problem
+    prob = oracle_problem(wl)
+    b = binding.from_workload(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    for K in (1, 2, 4):
+        ref = orc.hypergrad_cg(prob, wl.w, wl.lam, K)
+        for _ in range(3):                   # (the third is a replay)
+            assert rel_l2(host(b.betty_hypergrad_cg(w, lam, K)), ref) < 1e-4, K
+    b.profile(True)
+    b.betty_hypergrad_cg(w, lam, 4)
+    assert sum(r[0] == "vector" for r in b.profile_records()) == (4 if one else 7)
+    b.close()
+
+
 @pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
 @pytest.mark.parametrize("first", [1, 2])
 @pytest.mark.parametrize("dims,batch,kind,act,loss,bias", [
