@@ -1197,10 +1197,11 @@ void launch_cg_update(Ctx& ctx, Elem elem, CgUpdate& b) {
 // convert_batch_kernel, all loads of a tile in flight together.  EPS: the step comes out of the partial sums
 // of |v|^2 in every block, in the same order, beside the loads of the tile, instead of a launch between
 // (see fd_seq).
-template <bool EPS>
-__global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
+template <bool EPS, int NT>
+__global__ __launch_bounds__(NT) void perturb_kernel(PerturbBatch b) {
+  constexpr int Q = 1024 / NT, QS = NT / 16;       // quads a thread, their distance in rows
   __shared__ float tile[64][65];
-  __shared__ double red[4];
+  __shared__ double red[NT / 64];
   int bid = blockIdx.x, ji = 0;
   while (ji + 1 < b.n && bid >= b.block_begin[ji + 1]) ++ji;
   const PerturbJob& j = b.j[ji];
@@ -1209,10 +1210,10 @@ __global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
   const int c0 = (bid % tiles_x) * 64, r0 = (bid / tiles_x) * 64;
   const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
   const bool quads = j.cols % 4 == 0 && ((uintptr_t)j.w & 15) == 0 && ((uintptr_t)j.v & 15) == 0;
-  float w[4][4], v[4][4];
+  float w[Q][4], v[Q][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const long long row = (long long)min(r0 + ty + 16 * i, j.rows - 1) * j.cols;
+  for (int i = 0; i < Q; ++i) {
+    const long long row = (long long)min(r0 + ty + QS * i, j.rows - 1) * j.cols;
     if (quads) {
       const long long at = row + min(c0 + 4 * tx, j.cols - 4);
       const float4 a = *(const float4*)((j.w ? j.w : j.v) + at), d = *(const float4*)(j.v + at);
@@ -1228,20 +1229,20 @@ __global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
   }
   float eps;
   if constexpr (EPS) {
-    eps = fd_step(sum_partials<256>(b.partial, b.n_partial, red), b.eps_scale, b.scale);
+    eps = fd_step(sum_partials<NT>(b.partial, b.n_partial, red), b.eps_scale, b.scale);
     if (blockIdx.x == 0 && threadIdx.x == 0) b.eps_out[0] = eps;
   } else {
     eps = b.eps[0];
   }
   if (!j.w) {                                      // the direction itself, transposed
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < Q; ++i)
 #pragma unroll
-      for (int k = 0; k < 4; ++k) tile[ty + 16 * i][4 * tx + k] = v[i][k];
+      for (int k = 0; k < 4; ++k) tile[ty + QS * i][4 * tx + k] = v[i][k];
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int cl = ty + 16 * i, c = c0 + cl, r = r0 + 4 * tx;
+    for (int i = 0; i < Q; ++i) {
+      const int cl = ty + QS * i, c = c0 + cl, r = r0 + 4 * tx;
       if (c >= j.cols) continue;
       float* o = j.outT[0] + (long long)c * j.ldT + r;
       const float x[4] = {tile[4 * tx][cl], tile[4 * tx + 1][cl], tile[4 * tx + 2][cl], tile[4 * tx + 3][cl]};
@@ -1265,8 +1266,8 @@ __global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
     const float e = sg ? -eps : eps;
     if (sg && (b.signs & 1)) __syncthreads();       // the tile of the other sign is read out
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int rl = ty + 16 * i, r = r0 + rl, c = c0 + 4 * tx;
+    for (int i = 0; i < Q; ++i) {
+      const int rl = ty + QS * i, r = r0 + rl, c = c0 + 4 * tx;
       float x[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) { x[k] = w[i][k] + e * (b.scale * v[i][k]); tile[rl][4 * tx + k] = x[k]; }
@@ -1280,8 +1281,8 @@ __global__ __launch_bounds__(256) void perturb_kernel(PerturbBatch b) {
     }
     __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int cl = ty + 16 * i, c = c0 + cl, r = r0 + 4 * tx;
+    for (int i = 0; i < Q; ++i) {
+      const int cl = ty + QS * i, c = c0 + cl, r = r0 + 4 * tx;
       if (c >= j.cols) continue;
       float* o = j.outT[sg] + (long long)c * j.ldT + r;
       const float x[4] = {tile[4 * tx][cl], tile[4 * tx + 1][cl], tile[4 * tx + 2][cl], tile[4 * tx + 3][cl]};
@@ -1303,8 +1304,14 @@ void launch_perturb(Ctx& ctx, PerturbBatch& b) {
   b.block_begin[b.n] = blocks;
   if (blocks <= 0) return;
   Launch l(ctx, BETTY_K_SHADOW, 0, params);
-  if (b.eps) perturb_kernel<false><<<blocks, 256, 0, ctx.stream>>>(b);
-  else perturb_kernel<true><<<blocks, 256, 0, ctx.stream>>>(b);
+  const bool wide = blocks <= CONVERT_WIDE;
+  if (b.eps) {
+    if (wide) perturb_kernel<false, 1024><<<blocks, 1024, 0, ctx.stream>>>(b);
+    else perturb_kernel<false, 256><<<blocks, 256, 0, ctx.stream>>>(b);
+  } else {
+    if (wide) perturb_kernel<true, 1024><<<blocks, 1024, 0, ctx.stream>>>(b);
+    else perturb_kernel<true, 256><<<blocks, 256, 0, ctx.stream>>>(b);
+  }
 }
 
 __global__ __launch_bounds__(256) void label_noise_kernel(const int32_t* y, const uint32_t* words, const int32_t* alt,
