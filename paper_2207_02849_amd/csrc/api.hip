@@ -503,7 +503,8 @@ bool has_linear_form(betty_handle h, bool cg) {
 // 12 %, and 87 of the others would have been more than 3 % faster, up to 16 % (single steps of squared errors with 10^5
 // samples and more 29 %).  (By the number of outputs alone: softmax 401 - 12, batch 64, K = 2
 // 36 -> 67 us, conjugate gradient of 64 - 16, batch 512, K = 1 30 -> 57.)  Ridge 64 - 1, batch 512, K = 20: 163 us by
-// launches, 19 us; softmax 200 - 4, batch 128, K = 5: 52 / 38 us (conjugate gradient 84 / 50).
+// launches, 19 us; softmax 200 - 4, batch 128, K = 5: 52 / 38 us (conjugate gradient 84 / 50).  Since its vector launches are one
+// and 16-tiles faster: 5259 calls 0.3 % behind the better form on average, at most 17 %.
 bool use_linear(betty_handle h, bool cg, int K) {
   if (!has_linear_form(h, cg)) return false;
   if (h->tune_linear == 1) return true;
@@ -580,7 +581,8 @@ const float* wnet_theta(betty_handle h, const float* lambda) {
 
 // Kernel configuration of an activation-shaped GEMM (M = batch), from its extent.  The lines come from
 // timing every configuration on 1 400 shapes (batch 32 ... 1024, widths 8 ... 4096, K 64 ... 8192, both
-// element types, one and two problems a launch); the rule stays within 0.6 % of the best on average.
+// element types, one and two problems a launch); the rule stays within 0.6 % of the best on average.  (With 16-tiles
+// in whole lines: 710 models, the lines between 16- and 32-tiles moved either way -0.2 ... +1.6 %.)
 //  * 16-tiles while every tile has a compute unit of its own (256 of them; bf16 up to 80 steps, where
 //    32-tiles with their half as large operand traffic draw level), with short K also beyond:
 //    such a launch is bound by latency.  fp32 128 x 256 x 784: 8.9 us on 32-tiles, 6.0 us; bf16

@@ -1098,7 +1098,7 @@ void launch_cg_dir(Ctx& ctx, Elem elem, CgDirBatch& b) {
 }
 
 // cg_step and cg_dir in one launch.  Few parameters: a workgroup reads both vectors for the sum, 64 KB of 8 000 parameters,
-// sooner than another launch would start (784 x 10, batch 512, K = 8: 152 -> 130 us a call).
+// sooner than another launch would start (784 x 10, batch 512, K = 8: 152 -> 132 us a call).
 template <typename T>
 __global__ __launch_bounds__(1024) void cg_update_kernel(CgUpdate b) {
   __shared__ float tile[64][65];
