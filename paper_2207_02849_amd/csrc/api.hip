@@ -524,7 +524,7 @@ bool use_linear(betty_handle h, bool cg, int K) {
   one += mse ? C * (0.15 * (rows(val) + columns(val)) + 0.022 * chunks + 0.03) + 0.09 * update(val)
              : C * (0.127 * (rows(val) + columns(val)) + 0.016 * chunks + 0.10) + 0.115 * update(val);
   if (gram) {
-    one += K * (0.1 * C * rows(n) + 0.32) - 2.3;
+    one += K * (n <= 64 ? 0.33 : 0.1 * C * rows(n) + 0.32) - 2.3;
     if (K > 0) one += 2.2 + B * ((train <= 131072 ? 3.3e-3 : 4.2e-3) + 1.57e-5 * 4 * chunks * chunks);
   } else {
     one += K * (C * ((mse ? 0.062 : 0.051) * (rows(train) + columns(train)) + (mse ? 0.02 : 0.025) * chunks + (mse ? 0.14 : 0.26)) + 0.044 * update(train) +

@@ -65,3 +65,21 @@ def test_one_workgroup_only_where_it_is_the_faster_form(dims, batch, batch_val, 
     rule, launches = time_forms(monkeypatch, call, ("", "linear=0"), dims=dims, act="none", loss=loss, hp="l2", prec="fp32",
                                 has_bias=bias, batch_train=batch, batch_val=batch_val)
     assert rule < 1.15 * launches, (rule, launches)       # (a few percent between runs)
+
+
+@pytest.mark.parametrize("dims,batch,bias", [
+    ((31, 1), 40, True),                                  # 32 entries: half the registers
+    ((32, 2), 40, True),                                  # one more
+    ((63, 16), 100, True),                                # 64 entries, an output for every wavefront
+    ((64, 17), 33, False),                                # ... and one for a second turn
+])
+def test_squared_errors_of_few_features(dims, batch, bias, monkeypatch):
+    """A wavefront takes an output through all steps by itself; no steps, one, many."""
+    wl = wk.tiny(kind="l2", act="none", dims=dims, batch=batch, loss="mse", has_bias=bias)
+    prob = oracle_problem(wl)
+    monkeypatch.setenv("BETTY_TUNE", "linear=1")
+    b = binding.from_workload(wl)
+    for K in (0, 1, 20):
+        got = b.betty_hypergrad_neumann(torch.as_tensor(wl.w).cuda(), torch.as_tensor(wl.lam).cuda(), K, 0.02).cpu().numpy()
+        assert rel_l2(got, orc.hypergrad_neumann(prob, wl.w, wl.lam, K, 0.02)) < 1e-5, K
+    b.close()
