@@ -778,6 +778,9 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
 // (partial tiles summed in wavefront order, bit-reproducible), then one output element per thread.  Against steps
 // straight into fragments: classifier 784-256-10, fp32, batch 128, K = 5 102.6 -> 95.9 us; conjugate gradient of 784-10, batch 512 159.5 -> 150.3;
 // finite-difference step of 1023-509-251-10, batch 100 127.7 -> 121.2; with short K too (13-64-64-1 167.5 -> 165.4).
+// The two steps of a pair have a sum each, as two wavefronts would: fp32 products of K = 100 were 1.22 times as far off fp64 with one
+// chain, calls of 90 GELU models 1.027 +- 0.004 times; with two, and MfmaSum16 in the narrow-output kernels, 0.92 times.  A call takes
+// 0.2 % longer (0.5 at most).
 constexpr int G16_PITCH = 17;                      // row pitch of a partial tile in LDS (floats)
 
 // HALVES: at most two pairs, a step for each of four wavefronts
@@ -831,7 +834,7 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
                                          (__attribute__((address_space(3))) void*)(to + 1024 * h), 16, 0, 0);
   };
   const int fr = lane & 15, f0 = fr * 128 + (((lane >> 4) ^ fr) & 7) * 16, f1 = fr * 128 + ((((lane >> 4) + 4) ^ fr) & 7) * 16;
-  f32x4v acc = {0.f, 0.f, 0.f, 0.f};
+  f32x4v acc = {0.f, 0.f, 0.f, 0.f}, odd = {0.f, 0.f, 0.f, 0.f};
   for (int p = p_begin; p < p_end; p += U) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {                  // (what nothing is multiplied with is not loaded: pairs beyond the range, rows beyond the output)
@@ -854,10 +857,11 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
         continue;
       }
       MfmaStep16<T>::run(*(const u32x4*)(x + f0), *(const u32x4*)(x + 2048 + f0), acc);
-      MfmaStep16<T>::run(*(const u32x4*)(x + f1), *(const u32x4*)(x + 2048 + f1), acc);
+      MfmaStep16<T>::run(*(const u32x4*)(x + f1), *(const u32x4*)(x + 2048 + f1), odd);
     }
     if (p + U < p_end) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (read before they are overwritten)
   }
+  if constexpr (!HALVES) acc += odd;
   // register r of lane l is element [4 (l / 16) + r][l % 16]
 #pragma unroll
   for (int r = 0; r < 4; ++r) part[(kg * 16 + 4 * (lane >> 4) + r) * G16_PITCH + fr] = acc[r];

@@ -540,16 +540,17 @@ __global__ __launch_bounds__(1024) void last_layer_rop_kernel(LastRopArgs a) {
   }
 
   // ---- phase 1
-  f32x4v acc = {0.f, 0.f, 0.f, 0.f};
+  MfmaSum16<T> sums;
   for (int s = s_begin; s < s_end; s += U) {
     if (s > s_begin) request(s);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s + u >= s_end) break;
-      MfmaStep16<T>::run(r8[u], w8[u], acc);
-      if constexpr (!SAMPLES) MfmaStep16<T>::run(a8[u], v8[u], acc);
+      sums.step(r8[u], w8[u]);
+      if constexpr (!SAMPLES) sums.step(a8[u], v8[u]);
     }
   }
+  const f32x4v acc = sums.total();
   if (lane < CP) {
 #pragma unroll
     for (int r = 0; r < S; ++r) part[ks][r * CP + lane] = acc[r];
@@ -696,15 +697,16 @@ __global__ __launch_bounds__(1024) void last_layer_grad_kernel(LastGradArgs a) {
   }
 
   // ---- phase 1: logits block (4 x C), K = n_in sliced over the wavefronts
-  f32x4v acc = {0.f, 0.f, 0.f, 0.f};
+  MfmaSum16<T> sums;
   for (int s = s_begin; s < s_end; s += U) {
     if (s > s_begin) request(s);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s + u >= s_end) break;
-      MfmaStep16<T>::run(a8[u], w8[u], acc);
+      sums.step(a8[u], w8[u]);
     }
   }
+  const f32x4v acc = sums.total();
   if (lane < CP) {
 #pragma unroll
     for (int r = 0; r < S; ++r) part[ks][r * CP + lane] = acc[r];

@@ -18,25 +18,6 @@ constexpr int NW = 8, NT = 64 * NW, NROWS = NARROW_ROWS;
 template <typename T> constexpr int narrow_ks() { return 64 / (int)sizeof(T); }     // elements of K per step
 template <typename T> __device__ __forceinline__ T narrow_cast(float x) { return (T)x; }
 
-// Accumulators of a 16-tile.  In fp32 the four MFMA instructions of a step have one each, added at the end.  One chain
-// of K additions, where the kernels of whole batches add up partial sums of a few steps, left results 7 to 18 % further off
-// fp64 than theirs (70 models: first-order passes, products, series, differences; up to 2.2 times with a long first
-// layer), two 0 to 7 %; with four they are 2 to 8 % nearer, and a call takes 1 % longer.
-template <typename T> struct NarrowAcc {
-  f32x4v a = {0.f, 0.f, 0.f, 0.f};
-  __device__ __forceinline__ void step(const u32x4& x, const u32x4& y) { MfmaStep16<T>::run(x, y, a); }
-  __device__ __forceinline__ f32x4v total() const { return a; }
-};
-template <> struct NarrowAcc<float> {
-  f32x4v a[4] = {};
-  __device__ __forceinline__ void step(const u32x4& x, const u32x4& y) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      a[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x[i]), __uint_as_float(y[i]), a[i], 0, 0, 0);
-  }
-  __device__ __forceinline__ f32x4v total() const { return (a[0] + a[1]) + (a[2] + a[3]); }
-};
-
 // U steps of an operand row at this lane's chunk (beyond n they repeat the last one and are not multiplied)
 template <typename T, int U>
 __device__ __forceinline__ void narrow_load(const T* P, int s, int n, u32x4 (&f)[U]) {
@@ -47,7 +28,7 @@ __device__ __forceinline__ void narrow_load(const T* P, int s, int n, u32x4 (&f)
 
 // acc += A B^T over the steps [s0, s1); A, B in memory at this lane's row and chunk
 template <typename T, int U>
-__device__ __forceinline__ void narrow_mac(const T* A, const T* B, int s0, int s1, NarrowAcc<T>& acc) {
+__device__ __forceinline__ void narrow_mac(const T* A, const T* B, int s0, int s1, MfmaSum16<T>& acc) {
   for (int s = s0; s < s1; s += U) {
     const int n = min(U, s1 - s);
     u32x4 a[U], b[U];
@@ -60,7 +41,7 @@ __device__ __forceinline__ void narrow_mac(const T* A, const T* B, int s0, int s
 }
 // ... with A in LDS and the first U steps of B already in w
 template <typename T, int U>
-__device__ __forceinline__ void narrow_mac_lds(const T* A, const T* B, int s0, int s1, u32x4 (&w)[U], NarrowAcc<T>& acc) {
+__device__ __forceinline__ void narrow_mac_lds(const T* A, const T* B, int s0, int s1, u32x4 (&w)[U], MfmaSum16<T>& acc) {
   constexpr int KS = narrow_ks<T>();
   const int n0 = min(U, s1 - s0);
 #pragma unroll
@@ -99,7 +80,7 @@ __device__ __forceinline__ void narrow_link_of(const NarrowLink<T>& k, const T* 
     const int kp = ks > 1 ? wave * k.split.by_nt >> 8 : 0, tile = ks > 1 ? wave - kp * nt : base + wave;
     const bool active = kp < ks && tile < nt;
     const int s0 = kp * k.split.per, s1 = min(S, s0 + k.split.per), col = tile * 16 + fr, row = 4 * (lane >> 4);
-    NarrowAcc<T> sums;
+    MfmaSum16<T> sums;
     u32x4 w[U];
     if (active) {
       const long long b = (long long)(tile * 16 + fr) * k.ldb + fc;
@@ -479,7 +460,7 @@ template <typename V, typename T> __device__ __forceinline__ V at32(const void* 
 
 // sums of U steps of A W^T from memory, all requested at once
 template <typename T, int U>
-__device__ __forceinline__ void staged_mac(const void* A, const void* W, unsigned a0, unsigned w0, NarrowAcc<T>& sums) {
+__device__ __forceinline__ void staged_mac(const void* A, const void* W, unsigned a0, unsigned w0, MfmaSum16<T>& sums) {
   constexpr int KS = narrow_ks<T>();
   u32x4 a[U], w[U];
 #pragma unroll
@@ -489,7 +470,7 @@ __device__ __forceinline__ void staged_mac(const void* A, const void* W, unsigne
 }
 // ... from LDS
 template <typename T, int U>
-__device__ __forceinline__ void staged_mac_lds(const T* x, const T* w, NarrowAcc<T>& sums) {
+__device__ __forceinline__ void staged_mac_lds(const T* x, const T* w, MfmaSum16<T>& sums) {
   constexpr int KS = narrow_ks<T>();
   u32x4 a[U], b[U];
 #pragma unroll
@@ -552,7 +533,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
         for (int k = 0; k < 4; ++k) rz[k] = at32<float, float>(p.Rz, f0 + k * p.ldf);
       }
     }
-    NarrowAcc<T> sums;
+    MfmaSum16<T> sums;
     for (int m = 0; m < p.products; ++m) {
       const void* const A = p.A[m];
       const void* const W = p.W[m];
@@ -572,7 +553,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
   __syncthreads();
 
   // sums += the operand in LDS times the weights of a link
-  auto mac = [&](const T* A, const StagedLink& k, int tile, NarrowAcc<T>& sums) {
+  auto mac = [&](const T* A, const StagedLink& k, int tile, MfmaSum16<T>& sums) {
     const T* x = A + fr * pitch + fc;
     const T* w = (const T*)(lds + k.w) + min(tile * 16 + fr, k.N - 1) * k.wpitch + fc;
     for (int s = k.steps >> 2; s > 0; --s, x += 4 * KS, w += 4 * KS) staged_mac_lds<T, 4>(x, w, sums);
@@ -602,7 +583,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
     lds_barrier();
     for (int tile = wave; tile < tiles(k.N); tile += SW) {
       const f32x4v f = *slot(k.F, tile);
-      NarrowAcc<T> sums;
+      MfmaSum16<T> sums;
       mac(buf(i & 1), k, tile, sums);
       hidden(k, tile, (i + 1) & 1, f + sums.total());
     }
@@ -611,7 +592,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
   lds_barrier();
   for (int tile = wave; tile < tiles(k.N); tile += SW) {
     const f32x4v f = *slot(k.F, tile);
-    NarrowAcc<T> sums;
+    MfmaSum16<T> sums;
     mac(buf((n_fwd - 1) & 1), k, tile, sums);
     const f32x4v z = f + sums.total();
     const int col = tile * 16 + fr;
@@ -668,7 +649,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
     const bool last = i + 1 == n_bwd;
     for (int tile = wave; tile < tiles(k.N); tile += SW) {
       const f32x4v d = *slot(k.D, tile), tt = *slot(k.T, tile);
-      NarrowAcc<T> sums;
+      MfmaSum16<T> sums;
       mac(buf(i & 1), k, tile, sums);
       const f32x4v x = sums.total() * d + tt;
       const int col = tile * 16 + fr;

@@ -46,6 +46,52 @@ def test_small_launch_forms(dims, batch, loss, prec, tol, monkeypatch):
     b.close()
 
 
+def partial_sums(x, V, K):
+    """x V of fp32 matrices as fp32 sums: K products one after the other (each multiply-add rounded once), the partial sums in order."""
+    f32 = lambda y: y.astype(np.float32).astype(np.float64)
+    total = 0.0
+    for k in range(0, x.shape[1], K):
+        part = 0.0
+        for i in range(k, min(x.shape[1], k + K)):
+            part = f32(part + x[:, i, None] * V[:, i])
+        total = f32(total + part)
+    return total
+
+
+@pytest.mark.parametrize("kernel,n,K", [
+    ("tile", 100, 16), ("tile", 250, 16),                   # 16-tiles, up to 16 steps: a partial sum a step of 16 products
+    ("rop", 100, 8), ("rop", 250, 16), ("grad", 100, 8), ("grad", 250, 16),      # outputs of up to 16 columns: n / 16 rounded up to 8
+])
+def test_fp32_sums_of_small_launches(kernel, n, K, monkeypatch):
+    """One product of a single sample, read off the gradient's first row (x_0 = 1, squared errors): no further off fp64 than
+    partial sums of K products.  (Chains of twice that leave it 1.09 to 1.17 times as far; the ratio scatters by 2 %.)"""
+    monkeypatch.setenv("BETTY_TUNE", "linear=0,narrow=0")
+    C, N = (64, 60) if kernel == "tile" else (16, 240)
+    rng = np.random.default_rng(n)
+    x = np.abs(rng.standard_normal((N, n))).astype(np.float32)
+    x[:, 0] = 1.0
+    V = rng.standard_normal((N, n, C)).astype(np.float32)
+    dims = (n, C) if kernel == "tile" else (n, n, C)
+    b = binding.Betty(dims, act="none" if kernel == "tile" else "relu", loss="mse", hp="l2", prec="fp32", has_bias=False, batch_train=1, batch_val=1)
+    lam = torch.full((b.d,), -80.0, device="cuda")          # no decay to speak of
+    w, v = torch.zeros(b.d, device="cuda"), torch.zeros(b.d, device="cuda")
+    if kernel != "tile":
+        w[:n * n] = torch.eye(n, device="cuda").flatten()   # a_1 = x, exactly
+    got = []
+    for i in range(N):
+        X, t = dev(x[i:i + 1]), torch.zeros(1, C, device="cuda")
+        b.set_batches(X, X, t_tr=t, t_val=t)
+        (w if kernel == "grad" else v)[-n * C:] = dev(V[i].ravel())
+        g = b.betty_lower_grad(w, lam) if kernel == "grad" else b.betty_hvp(w, lam, v)
+        got.append(host(g)[-n * C:][:C] / 2)
+    b.close()
+    x, V = x.astype(np.float64), V.astype(np.float64)
+    exact = np.einsum("in,inc->ic", x, V)
+    ratio = np.linalg.norm(np.array(got) - exact) / np.linalg.norm(partial_sums(x, V, K) - exact)
+    print(f"{ratio:.3f}", flush=True)
+    assert ratio < 1.05, ratio
+
+
 @pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
 @pytest.mark.parametrize("first", [1, 2])
 @pytest.mark.parametrize("dims,batch,kind,act,loss,bias", [
