@@ -62,7 +62,7 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
   if constexpr (MODE == EPI_RFWD_LAST_HESS) {
     // every lane of the block takes part in the row sums later: lanes outside the valid extent hold zeros
     const bool colok = col < N;
-    R.colv = (colok && e.colvec) ? e.colvec[col] : 0.f;
+    if constexpr (NR > 1) R.colv = (colok && e.colvec) ? e.colvec[col] : 0.f;
 #pragma unroll
     for (int k = 0; k < NR; ++k) {
       const int row = epi_row<NR>(rb, k);
@@ -70,12 +70,13 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
       R.a[k] = (ok && e.dphi) ? e.dphi[epi_offset<NR>(rb, k, e.ldf, col)] : 0.f;
       R.b[k] = ok ? e.e[row] : 0.f;
     }
+    if constexpr (NR == 1) R.colv = (colok && e.colvec) ? e.colvec[col] : 0.f;      // (last: see below)
     return;
   }
   if (MODE == EPI_GRAM || (MODE == EPI_RBWD && e.mode == EPI_GRAM) || col >= N || rb >= M) return;
   const long long ldx = MODE >= EPI_WGRAD ? e.ldc : e.ldf;
-  if constexpr (MODE == EPI_SAMPLE || MODE == EPI_FWD || MODE == EPI_FWD_LAST || MODE == EPI_RFWD || MODE == EPI_RFWD_LAST || MODE == EPI_FWD_PM)
-    R.colv = e.colvec ? e.colvec[col] : 0.f;
+  constexpr bool COLUMN = MODE == EPI_SAMPLE || MODE == EPI_FWD || MODE == EPI_FWD_LAST || MODE == EPI_RFWD || MODE == EPI_RFWD_LAST || MODE == EPI_FWD_PM;
+  if constexpr (COLUMN && NR > 1) R.colv = e.colvec ? e.colvec[col] : 0.f;
 #pragma unroll
   for (int k = 0; k < NR; ++k) {
     const bool ok = epi_row<NR>(rb, k) < M;
@@ -130,6 +131,9 @@ __device__ __forceinline__ void epi_prefetch(const Epilogue& e, int M, int N, in
       R.d[k] = (ok && e.x) ? e.x[o] : 0.f;
     }
   }
+  // (One element a lane: last.  The offset above is 64 bits wide on the way, with col's register and the one behind it, and was made to wait for
+  // this value where it is loaded into that one.)
+  if constexpr (COLUMN && NR == 1) R.colv = e.colvec ? e.colvec[col] : 0.f;
 }
 
 // the sums of a launch (Epilogue::partial): one number per finishing wavefront
@@ -774,22 +778,33 @@ __global__ __launch_bounds__(64 * WPG * KG, (BM == 128 && KG == 1) ? 2 : 1) void
 // So a workgroup owns one 16 x 16 tile, its wavefronts split K, and each requests U pairs of steps (128 bytes of every operand row) at
 // once, whole lines straight to LDS, and reads the fragments there: lane l holds row l % 16 and 16-byte chunk
 // l / 16 of A and of B.  The chunks of row r stand in the order c ^ (r % 8), so that the rows spread over the banks.  Rows and
-// pairs that nothing is multiplied with are not requested.  One round trip, 2 U to 8 U MFMA instructions, one pass through LDS
+// pairs that nothing is multiplied with are not requested.  One round trip up to 32 pairs (fp32 K = 1024, bf16 2048), as many again for each
+// further 32; 2 U to 8 U MFMA instructions, one pass through LDS
 // (partial tiles summed in wavefront order, bit-reproducible), then one output element per thread.  Against steps
 // straight into fragments: classifier 784-256-10, fp32, batch 128, K = 5 102.6 -> 95.9 us; conjugate gradient of 784-10, batch 512 159.5 -> 150.3;
-// finite-difference step of 1023-509-251-10, batch 100 127.7 -> 121.2; with short K too (13-64-64-1 167.5 -> 165.4).
+// finite-difference step of 1023-509-251-10, batch 100 127.7 -> 121.2; a step of the series of n-48-48, batch 128, n = 1024, 2048, 4096:
+// fp32 18.7 / 23.3 / 35.0 -> 16.5 / 19.7 / 27.5, bf16 16.0 / 18.4 / 20.7 -> 14.8 / 16.1 / 20.4.
+// Short K goes straight into fragments, a step a wavefront (DIRECT): the way through LDS costs a launch more than the lines it saves.  Steps of eight
+// layers, 32, 64, 128 wide, batch 256, by pairs and by steps: bf16 51.5 / 52.8 / 63.4 -> 46.3 / 49.4 / 60.7, fp32 54.0 / 56.7 -> 49.2 / 52.3
+// (before there were pairs 48.9 / 52.0 / 61.8 and 52.1 / 54.4).  Of each, 1 to 2 us are the inputs of the epilogue that one wavefront's were
+// waiting for (epi_prefetch), 2 us the partial tiles read four at a time.  The line: bf16 up to 10 steps (160-wide 65.3 us by steps, 66.1 by
+// pairs; 192-wide 77.7 / 73.9 at batch 512), fp32 up to 12 (96-wide 68.0 / 70.1; 128-wide, 16 steps, 62.5 / 57.4 at batch 16).
 // The two steps of a pair have a sum each, as two wavefronts would: fp32 products of K = 100 were 1.22 times as far off fp64 with one
 // chain, calls of 90 GELU models 1.027 +- 0.004 times; with two, and MfmaSum16 in the narrow-output kernels, 0.92 times.  A call takes
 // 0.2 % longer (0.5 at most).
 constexpr int G16_PITCH = 17;                      // row pitch of a partial tile in LDS (floats)
 
-// HALVES: at most two pairs, a step for each of four wavefronts
-template <typename T, int U, bool HALVES, int MODE>
+// steps of K, 64 bytes of every operand row, and pairs of them (split: 64 elements, value and remainder)
+__host__ __device__ __forceinline__ int small_steps(bool split, int K, int KS) { return split ? (K + 63) / 64 * 4 : (K + KS - 1) / KS; }
+__host__ __device__ __forceinline__ int small_pairs(bool split, int K, int PK) { return split ? (K + 63) / 64 * 2 : (K + PK - 1) / PK; }
+
+// DIRECT: a step a wavefront, straight into fragments
+template <typename T, int U, bool DIRECT, int MODE>
 __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::type batch) {
-  constexpr int EPC = 16 / (int)sizeof(T), PK = 8 * EPC;   // elements per chunk, per pair of steps
+  constexpr int EPC = 16 / (int)sizeof(T), KS = 4 * EPC, PK = 2 * KS;      // elements per chunk, per step, per pair of steps
   extern __shared__ u32x4 smem[];
   const int t = threadIdx.x, lane = t & 63, kg = __builtin_amdgcn_readfirstlane(t >> 6), KG = blockDim.x >> 6;
-  float* const part = (float*)((char*)smem + KG * U * 4096);
+  float* const part = (float*)((char*)smem + (DIRECT ? 0 : KG * U * 4096));
   int bid = blockIdx.x;
   if constexpr (MODE >= EPI_WGRAD) {
     if (bid >= batch.gemm_blocks) {
@@ -812,63 +827,77 @@ __global__ __launch_bounds__(1024) void gemm16_kernel(typename BatchOf<MODE>::ty
   EpiRegs<1> pre;
   if (t < 256) epi_prefetch<MODE, 1>(e, g.M, g.N, row, col, pre);
 
-  // pairs of steps: 128 bytes of K
   const bool sp = g.split;
-  const int P0 = sp ? (g.K[0] + 63) / 64 * 2 : (g.K[0] + PK - 1) / PK;
-  const int PT = P0 + (sp ? (g.K[1] + 63) / 64 * 2 : (g.K[1] + PK - 1) / PK);
-  const int per = HALVES ? 1 : (PT + KG - 1) / KG, p_begin = HALVES ? kg >> 1 : kg * per, p_end = min(PT, p_begin + per);
-  // a lane's row and 16-byte chunk of a load of 8 rows x 128 bytes, chunks of a row in an order of its own (see below)
-  const int lr = lane >> 3, lc = ((lane & 7) ^ lr) * EPC;
-  const T* const A0 = (const T*)g.A[0] + (long long)(m0 + lr) * g.lda[0] + lc;
-  const T* const B0 = (const T*)g.B[0] + (long long)(n0 + lr) * g.ldb[0] + lc;
-  const T* const A1 = (const T*)g.A[1] + (long long)(m0 + lr) * g.lda[1] + lc;
-  const T* const B1 = (const T*)g.B[1] + (long long)(n0 + lr) * g.ldb[1] + lc;
-  const bool k_ok = !HALVES || lc / (4 * EPC) == (kg & 1);
-  const bool a_ok[2] = {k_ok && m0 + lr < g.M, k_ok && m0 + lr + 8 < g.M}, b_ok[2] = {k_ok && n0 + lr < g.N, k_ok && n0 + lr + 8 < g.N};
-  char* const mine = (char*)smem + kg * U * 4096;              // this wavefront's operands: 16 rows of A, 16 of B a pair
-  auto request = [&](const T* x, int ld, const bool (&ok)[2], char* to) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-      if (ok[h])
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(x + (long long)(8 * h) * ld),
-                                         (__attribute__((address_space(3))) void*)(to + 1024 * h), 16, 0, 0);
-  };
-  const int fr = lane & 15, f0 = fr * 128 + (((lane >> 4) ^ fr) & 7) * 16, f1 = fr * 128 + ((((lane >> 4) + 4) ^ fr) & 7) * 16;
-  f32x4v acc = {0.f, 0.f, 0.f, 0.f}, odd = {0.f, 0.f, 0.f, 0.f};
-  for (int p = p_begin; p < p_end; p += U) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {                  // (what nothing is multiplied with is not loaded: pairs beyond the range, rows beyond the output)
-      const int q = p + u;
-      if (q >= p_end) break;
-      const bool second = q >= P0;
-      const int qs = second ? q - P0 : q, qo = sp ? qs >> 1 : qs;            // a pair of value, one of remainder
-      const bool bs = MODE == EPI_WGRAD_SCALED && second;
-      request((second ? A1 : A0) + (long long)(bs ? qo : qs) * PK, second ? g.lda[1] : g.lda[0], a_ok, mine + u * 4096);
-      request((second ? B1 : B0) + (long long)(bs ? qs : qo) * PK, second ? g.ldb[1] : g.ldb[0], b_ok, mine + u * 4096 + 2048);
+  const int fr = lane & 15;
+  f32x4v acc = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (DIRECT) {
+    const int S0 = small_steps(sp, g.K[0], KS), S = S0 + small_steps(sp, g.K[1], KS);
+    const bool second = kg >= S0, bs = MODE == EPI_WGRAD_SCALED && second;
+    const int qs = second ? kg - S0 : kg, qo = sp ? (qs >> 2 << 1) | (qs & 1) : qs;     // two steps of value, two of remainder
+    const int ld_a = second ? g.lda[1] : g.lda[0], ld_b = second ? g.ldb[1] : g.ldb[0], fc = (lane >> 4) * EPC;
+    u32x4 x = {}, y = {};
+    if (kg < S) {
+      if (m0 + fr < g.M) x = *(const u32x4*)((const T*)(second ? g.A[1] : g.A[0]) + (long long)(m0 + fr) * ld_a + (bs ? qo : qs) * KS + fc);
+      if (n0 + fr < g.N) y = *(const u32x4*)((const T*)(second ? g.B[1] : g.B[0]) + (long long)(n0 + fr) * ld_b + (bs ? qs : qo) * KS + fc);
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    MfmaStep16<T>::run(x, y, acc);                             // (beyond the steps: zeros)
+  } else {
+    f32x4v odd = {0.f, 0.f, 0.f, 0.f};
+    const int P0 = small_pairs(sp, g.K[0], PK), PT = P0 + small_pairs(sp, g.K[1], PK);
+    const int per = (PT + KG - 1) / KG, p_begin = kg * per, p_end = min(PT, p_begin + per);
+    // a lane's row and 16-byte chunk of a load of 8 rows x 128 bytes, chunks of a row in an order of its own (see below)
+    const int lr = lane >> 3, lc = ((lane & 7) ^ lr) * EPC;
+    const T* const A0 = (const T*)g.A[0] + (long long)(m0 + lr) * g.lda[0] + lc;
+    const T* const B0 = (const T*)g.B[0] + (long long)(n0 + lr) * g.ldb[0] + lc;
+    const T* const A1 = (const T*)g.A[1] + (long long)(m0 + lr) * g.lda[1] + lc;
+    const T* const B1 = (const T*)g.B[1] + (long long)(n0 + lr) * g.ldb[1] + lc;
+    const bool a_ok[2] = {m0 + lr < g.M, m0 + lr + 8 < g.M}, b_ok[2] = {n0 + lr < g.N, n0 + lr + 8 < g.N};
+    char* const mine = (char*)smem + kg * U * 4096;            // this wavefront's operands: 16 rows of A, 16 of B a pair
+    auto request = [&](const T* x, int ld, const bool (&ok)[2], char* to) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (p + u >= p_end) break;
-      const char* const x = mine + u * 4096;
-      if constexpr (HALVES) {
-        const int f = kg & 1 ? f1 : f0;
-        MfmaStep16<T>::run(*(const u32x4*)(x + f), *(const u32x4*)(x + 2048 + f), acc);
-        continue;
+      for (int h = 0; h < 2; ++h)
+        if (ok[h])
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(x + (long long)(8 * h) * ld),
+                                           (__attribute__((address_space(3))) void*)(to + 1024 * h), 16, 0, 0);
+    };
+    const int f0 = fr * 128 + (((lane >> 4) ^ fr) & 7) * 16, f1 = fr * 128 + ((((lane >> 4) + 4) ^ fr) & 7) * 16;
+    for (int p = p_begin; p < p_end; p += U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {                // (what nothing is multiplied with is not loaded: pairs beyond the range, rows beyond the output)
+        const int q = p + u;
+        if (q >= p_end) break;
+        const bool second = q >= P0;
+        const int qs = second ? q - P0 : q, qo = sp ? qs >> 1 : qs;          // a pair of value, one of remainder
+        const bool bs = MODE == EPI_WGRAD_SCALED && second;
+        request((second ? A1 : A0) + (long long)(bs ? qo : qs) * PK, second ? g.lda[1] : g.lda[0], a_ok, mine + u * 4096);
+        request((second ? B1 : B0) + (long long)(bs ? qs : qo) * PK, second ? g.ldb[1] : g.ldb[0], b_ok, mine + u * 4096 + 2048);
       }
-      MfmaStep16<T>::run(*(const u32x4*)(x + f0), *(const u32x4*)(x + 2048 + f0), acc);
-      MfmaStep16<T>::run(*(const u32x4*)(x + f1), *(const u32x4*)(x + 2048 + f1), odd);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (p + u >= p_end) break;
+        const char* const x = mine + u * 4096;
+        MfmaStep16<T>::run(*(const u32x4*)(x + f0), *(const u32x4*)(x + 2048 + f0), acc);
+        MfmaStep16<T>::run(*(const u32x4*)(x + f1), *(const u32x4*)(x + 2048 + f1), odd);
+      }
+      if (p + U < p_end) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // (read before they are overwritten)
     }
-    if (p + U < p_end) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // (read before they are overwritten)
+    acc += odd;
   }
-  if constexpr (!HALVES) acc += odd;
   // register r of lane l is element [4 (l / 16) + r][l % 16]
 #pragma unroll
   for (int r = 0; r < 4; ++r) part[(kg * 16 + 4 * (lane >> 4) + r) * G16_PITCH + fr] = acc[r];
   __syncthreads();
   if (t >= 256) return;
   float v[1] = {0.f};
-  for (int k = 0; k < KG; ++k) v[0] += part[(k * 16 + (t >> 4)) * G16_PITCH + (t & 15)];
+  const float* const mine = part + (t >> 4) * G16_PITCH + (t & 15);
+  for (int k = 0; k < KG; k += 4) {                  // (a multiple of four wavefronts, whose tiles' elements are read together)
+    float x[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = mine[(k + i) * 16 * G16_PITCH];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[0] += x[i];
+  }
   float sum = 0.f;
   epi_finish<T, MODE, 1>(e, g.M, g.N, row, col, v, pre, sum);
   epi_store_sum<MODE>(e, kg, sum);
@@ -1407,33 +1436,34 @@ static void launch_wgrad128(int mode, int total, hipStream_t st, const GemmBatch
   }
 }
 
-// gemm16_kernel: pairs of steps per wavefront and round (U) and wavefronts (KG) for S pairs in all
+// gemm16_kernel: wavefronts (kg), pairs of steps per wavefront and round (u; 0: a step a wavefront)
 struct Small { int u, kg; };
-static Small small_shape(int S) {
-  const int u = S > 16 ? 2 : 1, per = std::max(u, (S + 15) / 16);
-  return Small{u, std::min(16, std::max(4, (S + per - 1) / per))};
-}
 template <typename T>
-static int batch_pairs(const GemmBatch& b) {
-  constexpr int PK = 128 / (int)sizeof(T);
-  int S = 1;
-  for (int i = 0; i < b.n; ++i) S = std::max(S, ((b.p[i].g.K[0] + PK - 1) / PK + (b.p[i].g.K[1] + PK - 1) / PK) << b.p[i].g.split);
-  return S;
+static Small small_shape(const GemmBatch& b) {
+  constexpr int KS = 64 / (int)sizeof(T), DIRECT = sizeof(T) == 2 ? 10 : 12;
+  int S = 1, P = 1;
+  for (int i = 0; i < b.n; ++i) {
+    const GemmArgs& g = b.p[i].g;
+    S = std::max(S, small_steps(g.split, g.K[0], KS) + small_steps(g.split, g.K[1], KS));
+    P = std::max(P, small_pairs(g.split, g.K[0], 2 * KS) + small_pairs(g.split, g.K[1], 2 * KS));
+  }
+  if (S <= DIRECT) return Small{0, (S + 3) / 4 * 4};
+  const int u = P > 16 ? 2 : 1, per = std::max(u, (P + 15) / 16);
+  return Small{u, ((P + per - 1) / per + 3) / 4 * 4};
 }
 
-template <typename T, int U, bool HALVES, int MODE>
+template <typename T, int U, int MODE>
 static void launch_small_one(int total, int kg, hipStream_t st, const GemmBatch& b, hipError_t& err) {
   static PerDevice allowed;
-  if (const hipError_t e = allow_lds(allowed, (const void*)gemm16_kernel<T, U, HALVES, MODE>, 16 * (U * 4096 + 16 * G16_PITCH * 4)); e != hipSuccess) { err = e; return; }
-  gemm16_kernel<T, U, HALVES, MODE><<<total, 64 * kg, (size_t)kg * (U * 4096 + 16 * G16_PITCH * 4), st>>>(kernel_args<MODE>(b));
+  if (const hipError_t e = allow_lds(allowed, (const void*)gemm16_kernel<T, U, false, MODE>, 16 * (U * 4096 + 16 * G16_PITCH * 4)); e != hipSuccess) { err = e; return; }
+  gemm16_kernel<T, U, false, MODE><<<total, 64 * kg, (size_t)kg * (U * 4096 + 16 * G16_PITCH * 4), st>>>(kernel_args<MODE>(b));
 }
 template <typename T, int MODE>
 static void launch_small(int total, hipStream_t st, const GemmBatch& b, hipError_t& err) {
-  const int pairs = batch_pairs<T>(b);
-  const Small sh = small_shape(pairs);
-  if (pairs <= 2) launch_small_one<T, 1, true, MODE>(total, sh.kg, st, b, err);
-  else if (sh.u == 1) launch_small_one<T, 1, false, MODE>(total, sh.kg, st, b, err);
-  else launch_small_one<T, 2, false, MODE>(total, sh.kg, st, b, err);
+  const Small sh = small_shape<T>(b);
+  if (sh.u == 0) gemm16_kernel<T, 1, true, MODE><<<total, 64 * sh.kg, (size_t)sh.kg * 16 * G16_PITCH * 4, st>>>(kernel_args<MODE>(b));
+  else if (sh.u == 1) launch_small_one<T, 1, MODE>(total, sh.kg, st, b, err);
+  else launch_small_one<T, 2, MODE>(total, sh.kg, st, b, err);
 }
 
 template <typename T>
@@ -1501,7 +1531,7 @@ static int gemm_cfg_waves(int cfg) { return cfg == GEMM_32x8 ? 8 : 4; }
 int launch_gemm_batch(Ctx& ctx, Elem elem, int cfg, GemmBatch& b, double flops, double bytes, double* partial) {
   const int bt = gemm_cfg_tile(cfg);
   const int rows_per_block = cfg != GEMM_16 ? gemm_cfg_waves(cfg)
-                           : small_shape(elem == ELEM_BF16 ? batch_pairs<__bf16>(b) : batch_pairs<float>(b)).kg;
+                           : (elem == ELEM_BF16 ? small_shape<__bf16>(b) : small_shape<float>(b)).kg;
   int blocks = 0;
   for (int i = 0; i < b.n; ++i) {
     b.block_begin[i] = blocks;

@@ -30,6 +30,10 @@ def host(t):
     ((40, 24), 65, "ce"),                    # one layer, rows of the loss Hessian wider than a 16-tile
     ((40, 9), 257, "mse"),                   # ... and inside one
     ((70, 530, 260), 100, "ce"),             # 16-, 32- and 64-tiles side by side
+    ((160, 160, 48), 33, "ce"),              # the most steps straight into fragments with bf16 operands (two products of five)
+    ((161, 161, 48), 33, "ce"),              # ... and one product of six
+    ((96, 96, 48), 20, "ce"),                # ... in fp32 (two of six)
+    ((97, 97, 48), 20, "ce"),                # ... two of seven, an odd number of steps in pairs
 ])
 def test_small_launch_forms(dims, batch, loss, prec, tol, monkeypatch):
     monkeypatch.setenv("BETTY_TUNE", "narrow=0")
@@ -59,7 +63,7 @@ def partial_sums(x, V, K):
 
 
 @pytest.mark.parametrize("kernel,n,K", [
-    ("tile", 100, 16), ("tile", 250, 16),                   # 16-tiles, up to 16 steps: a partial sum a step of 16 products
+    ("tile", 100, 16), ("tile", 192, 16), ("tile", 193, 16), ("tile", 250, 16),      # 16-tiles: a partial sum a step of 16 products
     ("rop", 100, 8), ("rop", 250, 16), ("grad", 100, 8), ("grad", 250, 16),      # outputs of up to 16 columns: n / 16 rounded up to 8
 ])
 def test_fp32_sums_of_small_launches(kernel, n, K, monkeypatch):
