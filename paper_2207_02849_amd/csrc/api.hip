@@ -343,27 +343,31 @@ double samples_saving(betty_handle h, int K, bool dense) {
 // Models with narrow layers take all layers of a few samples in one workgroup (narrow.hip).  Whether the first-order
 // passes over that many samples together (rop = false) or the forward-over-reverse pass does, and from which layer on: 0 =
 // launches per layer, 1, or 2 = layer 1, whose reduction may be long, stays a launch of its own.
-// By the estimated time: a launch takes 4.7 us whatever its width (up to about 256), the fused kernel 6 us, 1.6 us a
-// link, and 1 us per 9 KB of weights: that is the latency of fetching them link by link in every workgroup, far below what a
-// compute unit can read.  Calls over fused, up to 4096 samples: forward-over-reverse passes 0.77 (353 models chosen of 619, 8 more
-// than 2.5 % slower, those of few rows), first-order passes 0.73 (none slower).
+// By the estimated time: a launch taken as 4.7 us whatever its width (up to about 256; now nearer 4, but a lower price leaves more of the fused
+// form's gain than it saves), the fused kernel 6 us, 1.6 us a link, and 1 us per 9 KB of weights: that is the latency of fetching them link by link
+// in every workgroup, far below what a compute unit can read.  Chosen forms over launches, up to 4096 samples: first-order passes of 500 models
+// 17.8 ms in all, 17.3 with the better form of each, 21.0 by launches, 2 more than 3 % slower, up to 1.11 times; forward-over-reverse passes beside
+// the form in LDS below (choose_rop_form).
 // Beyond, workgroups share compute units and the launches fill the chip, soonest where the output is wide (a narrow one has
-// kernels of its own that cost the launches more).  Forward-over-reverse with more than 16 outputs: 4096 to 8192 samples 0.97, up
-// to 1.09, then 1.07 ... 1.36, up to 1.47; up to 16 outputs: fp32 0.80 ... 0.86 up to 32768 samples, bf16 0.85 up to 8192, 0.96 up to
-// 12288, then 1.0 and more, up to 1.22.  First-order with more than 16 outputs: 1.0 from 24576 samples on, up to 1.15; up to
-// 16 outputs: 0.75 ... 0.79 up to 65536, none slower.
+// kernels of its own that cost the launches more).  Fused over launches, 400 models of each kind of pass: forward-over-reverse with more than 16
+// outputs 0.91 up to 8192 samples, 1.05 ... 1.6 beyond; up to 16 outputs, bf16 0.91 up to 8192, 0.99 ... 1.04 up to 12288, 1.1 ... 1.25 beyond, fp32
+// 0.91 ... 0.94 up to 8192, 0.96 ... 1.03 up to 24576, 1.07 beyond.  First-order with more than 16 outputs 0.64 ... 0.95 up to 32768, 1.05 beyond;
+// up to 16 outputs 0.70 ... 0.94 up to 66000, 1.13 times at most.
 // (Forward-over-reverse passes: 32-wide, 8 layers 66 us by launches, 29 us; 64-wide fp32, 4 layers 28 / 23 us; 128-wide 28 / 47 us, with
 // bf16 operands 28 / 32 us.)
 int narrow_max_samples(betty_handle h, bool rop, Elem elem) {
   if (h->dims[h->L] > LAST_ROP_MAX_C) return rop ? 4096 : 24576;
   return !rop ? INT_MAX : elem == ELEM_BF16 ? 12288 : 32768;
 }
+int launches_per_layer(betty_handle h, bool rop) {
+  return 2 * h->L - (h->dims[h->L] <= LAST_ROP_MAX_C ? 2 : rop && h->dims[h->L] <= 32 ? 1 : 0);
+}
 struct NarrowEstimate { double fused, launches; int first; };
 NarrowEstimate narrow_estimate(betty_handle h, bool rop, Elem elem) {
   const int L = h->L;
-  const bool bf16 = elem == ELEM_BF16, narrow_out = h->dims[L] <= LAST_ROP_MAX_C;
+  const bool bf16 = elem == ELEM_BF16;
   const double launch = 4.7, per_kb = 1.0 / 9, es = bf16 ? 2.0 : 4.0, fwd_es = !rop && bf16 && h->desc.act == BETTY_ACT_RELU ? 4.0 : es;
-  const double launches = launch * (2 * L - (narrow_out ? 2 : rop && h->dims[L] <= 32 ? 1 : 0)), pairs = rop ? 2.0 : 1.0;
+  const double launches = launch * launches_per_layer(h, rop), pairs = rop ? 2.0 : 1.0;
   double fused = 6.0, first_link = 0;
   for (int l = 1; l <= L; ++l) {
     const double kb = (double)h->dims[l - 1] * h->dims[l] / 1024.0;
@@ -390,10 +394,7 @@ NarrowNet narrow_net(betty_handle h, int first);
 // The forward-over-reverse pass with all weights in LDS (staged_rop_kernel), from layer `first` on: its estimated time, or
 // infinity where it does not fit (which does not depend on the pointers).  4 us, 0.6 us a link, the products with operands of the
 // direction alone by the steps of a wavefront (bf16 0.75 us, fp32 1 us) and those that one 16-tile makes one after the other beyond
-// four, 0.04 us a KB of weights, 3.3 us for layer 1 by itself.  Taken below 0.8 of the launches' estimate.  1100 models (2 to 8
-// layers, up to 320 wide, 8 to 1500 inputs, batch 16 to 3000; product and weight gradients): 700 of them 22.37 ms in all, 22.31 with
-// the better form of each, 28.51 by launches, none more than 3 % slower than launches; the other 400, up to 160 wide, 10.4 ms, 14.1 by
-// launches, 11.9 with the better of launches and narrow_rop_kernel.  Up to 4096 samples: a workgroup has a compute unit's LDS to itself.
+// four, 0.04 us a KB of weights, 3.3 us for layer 1 by itself.
 double staged_estimate(betty_handle h, Elem elem, int first) {
   if (h->L < 2 || h->L > NARROW_MAX_L || first > (h->L >= 3 ? 2 : 1)) return INFINITY;
   NarrowRopArgs r{};
@@ -411,11 +412,20 @@ double staged_estimate(betty_handle h, Elem elem, int first) {
   return 4.0 + 0.6 * (a.n_fwd + a.n_bwd) + (elem == ELEM_BF16 ? 0.75 : 1.0) * steps / 16 + 0.2 * std::max(0, longest - 4) + 0.04 * a.groups +
          (first > 1 ? 3.3 : 0.0);
 }
+// The form of the forward-over-reverse pass: the one in LDS where it takes less than 0.94 of 4.0 us a launch.  Steps of the series of
+// 1500 models (2 to 8 layers, up to 320 wide, 8 to 1500 inputs, batch 16 to 3000): 40.4 ms by the rule, 40.1 with the better form of each, 53.1 by
+// launches; 11 of them more than 3 % slower than launches, one 1.18 times, the others up to 1.13.  Up to 4096 samples: a workgroup has a
+// compute unit's LDS to itself.
+// What it saves beside the series over samples, whose estimate counts launches: 3.2 us a launch, those of up to 32 outputs 2 or 3 us more.  Calls of
+// 2600 reweighting and proximal models: 0.25 % behind the better of samples and parameters, 8 of those that take this pass more than 3 %, up to
+// 1.09 times (at 4.7 us a launch 21 of them, up to 1.4 times: 511-12-34, batch 50, fp32, K = 9 127 us, on parameters 181).
 NarrowForm choose_rop_form(betty_handle h, Elem elem) {
-  const double launches = narrow_estimate(h, true, elem).launches;
+  const int C = h->dims[h->L];
+  const double n = launches_per_layer(h, true);
   const double one = h->tune_narrow >= 0 && h->tune_narrow < 3 ? INFINITY : staged_estimate(h, elem, 1);
   const double two = h->tune_narrow >= 0 && h->tune_narrow < 3 ? INFINITY : staged_estimate(h, elem, 2);
-  const NarrowForm staged{two < one ? 2 : 1, true, launches - std::min(one, two)};
+  const double time = std::min(one, two), gain = 4.0 * n - time;
+  const NarrowForm staged{two < one ? 2 : 1, true, std::max(0.0, 3.2 * n + (C <= LAST_ROP_MAX_C ? 3.0 : C <= 32 ? 2.0 : 0.0) - time)};
   if (h->tune_narrow >= 3) {
     if (h->L >= 3 && h->tune_narrow == 4) return std::isfinite(two) ? NarrowForm{2, true, 0.0} : NarrowForm{};
     return std::isfinite(one) ? NarrowForm{1, true, 0.0} : NarrowForm{};
@@ -425,8 +435,9 @@ NarrowForm choose_rop_form(betty_handle h, Elem elem) {
   // is underestimated where this is.  (371 models with narrow layers, series of 1, 3 and 9 steps over launches only: 0.800, the
   // better form of every call 0.798, 9 of 2226 calls more than 3 % slower; narrow layers always: up to 1.26, 915-33-33-146,
   // batch 25, K = 9 208 -> 264 us.)
-  if (f.first) f.saving = std::max(0.0, 0.5 * (launches - narrow_estimate(h, true, elem).fused) - 2.0);
-  return h->desc.batch_train <= 4096 && staged.saving > std::max(0.2 * launches, f.saving) ? staged : f;
+  const NarrowEstimate e = narrow_estimate(h, true, elem);
+  if (f.first) f.saving = std::max(0.0, 0.5 * (e.launches - e.fused) - 2.0);
+  return h->desc.batch_train <= 4096 && gain > std::max(0.06 * 4.0 * n, f.saving) ? staged : f;
 }
 int narrow_rop_first(betty_handle h) { return h->rop_form.first; }
 

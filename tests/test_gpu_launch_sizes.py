@@ -242,6 +242,15 @@ def test_narrow_models_keep_the_series_over_samples_where_it_is_faster(dims, bat
     assert rule < 1.1 * samples, (rule, samples)
 
 
+@pytest.mark.parametrize("dims,batch,batch_val,K", [                                     # on parameters:
+    ((232, 56, 46), 124, 350, 9), ((413, 14, 38), 331, 78, 20), ((511, 12, 34), 50, 60, 9),      # 1.20, 1.13, 1.4 times the time
+])
+def test_series_over_samples_beside_passes_with_weights_in_lds(dims, batch, batch_val, K, monkeypatch):
+    rule, samples = time_forms(monkeypatch, lambda b, w: b.betty_hypergrad_neumann(w, w[:b.n_hyper], K, 1e-4), ("", "samples=1"), dims=dims,
+                               act="relu", loss="ce", hp="reweight", prec="fp32", batch_train=batch, batch_val=batch_val)
+    assert rule < 1.05 * samples, (rule, samples)
+
+
 @pytest.mark.parametrize("kind", ["l2", "reweight"])
 @pytest.mark.parametrize("batch,batch_val", [(13000, 50), (40, 24600), (40, 50)])
 def test_finite_differences_of_narrow_models_mix_forms(batch, batch_val, kind, monkeypatch):
