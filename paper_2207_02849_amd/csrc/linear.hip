@@ -208,18 +208,26 @@ __global__ __launch_bounds__(LIN_T) void linear_hypergrad_kernel(LinearArgs a) {
   const int B = a.B[0];
   // Squared errors of up to 64 features: the outputs do not meet in G, so a wavefront takes one through all steps by itself, a feature
   // a lane and G's columns (the rows, as it is symmetric) in its registers: no barrier between the steps (64 - 1, batch 512, K = 20:
-  // 19.6 -> 17.5 us a call; with the vector through v_readlane instead of LDS 22.4).
-  const bool own = GRAM && n <= 64;
+  // 19.6 -> 16.5 us a call; with the vector through v_readlane instead of LDS 22.4).  All 16 wavefronts' loads of G had taken 1.5 us beside one
+  // output: 7 - 1, K = 1 7.9 us without this form, 9.7, 8.1 with loads where there is an output.  A single step of more than 32 features stays with
+  // the form below (32 - 3 with a bias, K = 1: 9.6, 10.0 us).
+  const bool own = GRAM && n <= 64 && (n <= LIN_CH || a.K > 1);
   if (own) {
-    const int k = t & 63, kc = min(k, NP - 1);
+    const int k = t & 63, kc = min(k, NP - 1), wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    if (wave < C) {                                // (a wavefront without an output would keep the compute unit's L1 busy for nothing)
+      int nl = n;
+      asm("" : "+v"(nl));                          // (compared a lane: of a comparison of scalars the compiler makes branches that wait for each load)
 #pragma unroll
-    for (int j = 0; j < LIN_CH; ++j) {
-      const float x = a.G[min(j, n - 1) * NP + kc], y = a.G[min(j + LIN_CH, n - 1) * NP + kc];
-      xr[j] = j < n ? x : 0.f;
-      xc[j] = j + LIN_CH < n ? y : 0.f;
+      for (int j = 0; j < LIN_CH; ++j) xr[j] = a.G[min(j, n - 1) * NP + kc];
+      if (n > LIN_CH) {
+#pragma unroll
+        for (int j = 0; j < LIN_CH; ++j) xc[j] = a.G[min(j + LIN_CH, n - 1) * NP + kc];
+      }
+#pragma unroll
+      for (int j = 0; j < LIN_CH; ++j) { xr[j] = j < nl ? xr[j] : 0.f; xc[j] = j + LIN_CH < nl ? xc[j] : 0.f; }
     }
     __syncthreads();
-    for (int c = __builtin_amdgcn_readfirstlane(t >> 6); c < C; c += LIN_T / 64) {
+    for (int c = wave; c < C; c += LIN_T / 64) {
       const float g = k < n ? gv[c * NP + k] : 0.f, e = k < n ? el[c * NP + k] : 0.f;
       float* const v = sv + c * NP;
       float sk = g;
