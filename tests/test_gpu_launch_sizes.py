@@ -126,6 +126,7 @@ def test_narrow_models_in_one_workgroup(dims, batch, kind, act, loss, bias, firs
         b.close()
 
 
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
 @pytest.mark.parametrize("dims,batch,bias,one", [
     ((5, 3), 20, True, True),                # fewer parameters than a wavefront, a remainder of quads
     ((64, 64), 100, False, True),            # exactly one tile
@@ -134,10 +135,10 @@ def test_narrow_models_in_one_workgroup(dims, batch, kind, act, loss, bias, firs
     ((127, 129), 200, True, False),          # one more: two launches a step
     ((33, 20, 9), 60, True, True),           # two layers, whose second has a row-major copy
 ])
-def test_conjugate_gradient_of_few_parameters(dims, batch, bias, one, monkeypatch):
+def test_conjugate_gradient_of_few_parameters(dims, batch, bias, one, prec, tol, monkeypatch):
     """Step and direction in one launch: against the oracle, and the number of launches."""
     monkeypatch.setenv("BETTY_TUNE", "linear=0,narrow=0")
-    wl = wk.tiny(kind="l2", act="none" if len(dims) == 2 else "gelu", dims=dims, batch=batch, prec="fp32", has_bias=bias)
+    wl = wk.tiny(kind="l2", act="none" if len(dims) == 2 else "gelu", dims=dims, batch=batch, prec=prec, has_bias=bias)
     wl.lam = wl.lam + 5.0                    # a definite problem
     prob = oracle_problem(wl)
     b = binding.from_workload(wl)
@@ -145,7 +146,7 @@ def test_conjugate_gradient_of_few_parameters(dims, batch, bias, one, monkeypatc
     for K in (1, 2, 4):
         ref = orc.hypergrad_cg(prob, wl.w, wl.lam, K)
         for _ in range(3):                   # (the third is a replay)
-            assert rel_l2(host(b.betty_hypergrad_cg(w, lam, K)), ref) < 1e-4, K
+            assert rel_l2(host(b.betty_hypergrad_cg(w, lam, K)), ref) < tol, K
     b.profile(True)
     b.betty_hypergrad_cg(w, lam, 4)
     assert sum(r[0] == "vector" for r in b.profile_records()) == (4 if one else 7)
@@ -157,7 +158,8 @@ def test_conjugate_gradient_of_few_parameters(dims, batch, bias, one, monkeypatc
 @pytest.mark.parametrize("dims,batch,kind,act,loss,bias", [
     ((5, 16, 16), 16, "l2", "gelu", "ce", True),              # one tile, one workgroup
     ((33, 17, 15, 1), 17, "l2", "gelu", "mse", True),         # one past, one short; a sample of its own
-    ((40, 100, 33, 9), 40, "reweight", "gelu", "ce", False),  # more tiles than wavefronts
+    ((40, 100, 33, 9), 40, "reweight", "gelu", "ce", False),  # more products with the direction (21) than wavefronts
+    ((20, 300, 10), 40, "l2", "gelu", "ce", True),            # more tiles in a link (19, 20) than wavefronts, LDS nearly full
     ((130, 30, 64, 70), 31, "l2", "relu", "ce", True),        # an output wider than a wavefront, K left over
     ((9, 20, 40, 33, 20, 12, 30, 8, 5), 50, "reweight", "relu", "ce", True),   # eight layers
     ((12, 65, 20, 4), 33, "proximal", "gelu", "mse", True),
@@ -240,6 +242,30 @@ def test_narrow_models_keep_the_series_over_samples_where_it_is_faster(dims, bat
     rule, samples = time_forms(monkeypatch, lambda b, w: b.betty_hypergrad_neumann(w, w[:b.n_hyper], K, 1e-4), ("", "narrow=0"), dims=dims,
                                act="gelu", loss="ce", hp="reweight", prec="fp32" if len(dims) == 3 else "bf16", batch_train=batch, batch_val=batch)
     assert rule < 1.1 * samples, (rule, samples)
+
+
+@pytest.mark.parametrize("prec,tol", [("fp32", 1e-4), ("bf16", 2e-2)])
+@pytest.mark.parametrize("dims,batch,kind,samples", [
+    ((12, 257, 3), 521, "reweight", 0),      # one column in the second block
+    ((20, 300, 7), 530, "l2", 0),
+    ((12, 512, 16), 521, "reweight", 1),     # both blocks whole; the series over samples
+])
+def test_narrow_outputs_with_a_second_block_of_columns(dims, batch, kind, samples, prec, tol, monkeypatch):
+    """With more than 512 samples a workgroup takes all columns of a hidden layer beyond 256, a wavefront two blocks of 16."""
+    monkeypatch.setenv("BETTY_TUNE", f"narrow=0,samples={samples}")
+    wl = wk.tiny(kind=kind, act="gelu", dims=dims, batch=batch, prec=prec, hidden=40)
+    prob = oracle_problem(wl)
+    b = binding.from_workload(wl)
+    w, lam = dev(wl.w), dev(wl.lam)
+    v = np.random.default_rng(3).standard_normal(wl.d)
+    for name, got, ref in (("grad", b.betty_lower_grad(w, lam), orc.lower_grad(prob, wl.w, wl.lam)[1]),
+                           ("hvp", b.betty_hvp(w, lam, dev(v)), orc.hvp(prob, wl.w, wl.lam, v)),
+                           ("neumann", b.betty_hypergrad_neumann(w, lam, 2, 0.02), orc.hypergrad_neumann(prob, wl.w, wl.lam, 2, 0.02))):
+        assert rel_l2(host(got), ref) < tol, name
+    b.profile(True)
+    b.betty_hypergrad_neumann(w, lam, 2, 0.02)
+    assert [r[0] for r in b.profile_records()].count("last_layer") >= 3        # gradient, two products
+    b.close()
 
 
 @pytest.mark.parametrize("dims,batch,batch_val,K", [                                     # on parameters:
