@@ -950,7 +950,7 @@ void forward_backward(betty_handle h, const Pass* ps, int n) {
   }
   a.ldt = lo.n_in_p; a.ldn = lo.n_out_p;
   a.hidden = h->desc.wnet_hidden;
-  a.n_in = lo.n_in; a.n_in_p = lo.n_in_p; a.C = lo.n_out; a.loss = h->desc.loss;
+  a.n_in = lo.n_in; a.C = lo.n_out; a.loss = h->desc.loss;
   launch_last_layer_grad(h->ctx, ps[0].os->elem, a);
   backward_chain(h, ps, n, L - 1);
 }
@@ -1216,7 +1216,7 @@ void hvp_cached(betty_handle h, OperandSet& os, const float* vflat, const WgradS
     a.Rz = h->f(os.Rz[L - 1]); a.ldf = lo.n_in_p;
     a.RDL = h->at<void>(os.RD[L]); a.RDLt = h->at<void>(os.RDt[L]); a.ldRDLt = Bp;
     a.RD = L > 2 ? h->at<void>(os.RD[L - 1]) : nullptr; a.ldRD = lo.n_in_p; a.RDt = h->at<void>(os.RDt[L - 1]); a.ldRDt = Bp;
-    a.B = B; a.n_in = lo.n_in; a.n_in_p = lo.n_in_p; a.C = lo.n_out; a.loss = h->desc.loss;
+    a.B = B; a.n_in = lo.n_in; a.C = lo.n_out; a.loss = h->desc.loss;
     launch_last_layer_rop(h->ctx, os.elem, a);
     if (pipe) { side_wgrad(h, os, sink, L); side_wgrad(h, os, sink, L - 1); }
   } else {
@@ -1301,7 +1301,7 @@ void mixed_reweight_seq(betty_handle h, OperandSet& os, const float* lam, const 
     a.Wt = h->at<void>(os.Wt[L - 1]); a.Vt = h->at<void>(os.Vt[L - 1]); a.ldt = lo.n_in_p;
     a.cbias = h->desc.has_bias ? qflat + lo.b_off : nullptr;
     a.P = h->f(sb.P); a.ldp = lo.n_out_p;
-    a.B = sb.B; a.n_in = lo.n_in; a.n_in_p = lo.n_in_p; a.C = lo.n_out; a.loss = h->desc.loss;
+    a.B = sb.B; a.n_in = lo.n_in; a.C = lo.n_out; a.loss = h->desc.loss;
     a.cvec = h->f(os.cvec); a.labels = h->at<Labels>(h->labels); a.Z = h->f(sb.ZL);
     launch_last_layer_rop(h->ctx, os.elem, a);
   } else {
@@ -1626,7 +1626,7 @@ LastRopArgs samples_last_args(betty_handle h, OperandSet& os, const std::vector<
   a.Wn = h->at<void>(os.Wn[L - 1]); a.ldn = lo.n_out_p;
   a.AS = h->f(AS[L]); a.ldas = lo.n_out_p;
   a.P = h->f(sb.P); a.ldp = lo.n_out_p;
-  a.B = sb.B; a.n_in = lo.n_in; a.n_in_p = lo.n_in_p; a.C = lo.n_out; a.loss = h->desc.loss;
+  a.B = sb.B; a.n_in = lo.n_in; a.C = lo.n_out; a.loss = h->desc.loss;
   return a;
 }
 

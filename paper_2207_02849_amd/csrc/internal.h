@@ -271,15 +271,14 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// Requests N 64-byte lines of the kernel arguments at once, from byte `at` on.  They are read all through a kernel, and the first scalar
+// Requests the first N 64-byte lines of the kernel arguments at once.  They are read all through a kernel, and the first scalar
 // load from each would wait for memory where it stands, one after the other.
-template <int N> __device__ __forceinline__ void warm_lines(int at) {
+template <int N> __device__ __forceinline__ void warm_lines() {
   static_assert(N <= 60, "lines");
-  const unsigned* p = (const unsigned*)((const char*)__builtin_amdgcn_kernarg_segment_ptr() + at);
+  const unsigned* p = (const unsigned*)__builtin_amdgcn_kernarg_segment_ptr();
   auto line = [&](int i) { return p[(i < N ? i : N - 1) * 16]; };
 #define BETTY_W5(i_) "s"(line(i_)), "s"(line(i_ + 1)), "s"(line(i_ + 2)), "s"(line(i_ + 3)), "s"(line(i_ + 4))
-  if constexpr (N <= 5) asm volatile("" :: BETTY_W5(0));
-  else asm volatile("" :: BETTY_W5(0), BETTY_W5(5), BETTY_W5(10), BETTY_W5(15), BETTY_W5(20), BETTY_W5(25));
+  asm volatile("" :: BETTY_W5(0), BETTY_W5(5), BETTY_W5(10), BETTY_W5(15), BETTY_W5(20), BETTY_W5(25));
   if constexpr (N > 30) asm volatile("" :: BETTY_W5(30), BETTY_W5(35), BETTY_W5(40), BETTY_W5(45), BETTY_W5(50), BETTY_W5(55));
 #undef BETTY_W5
 }
@@ -376,7 +375,7 @@ struct LastRopArgs {
   const float* dphi; const float* e2; const float* Rz; int ldf;   // layer L-1, fp32 [B][ldf]; e2 may be null
   void* RDL; void* RDLt; int ldRDLt;                    // out: R delta_L [B][ldd] and [n_out_p][ldRDLt]
   void* RD; int ldRD; void* RDt; int ldRDt;             // out: R delta_{L-1} [B][ldRD] (or null) and [n_in_p][ldRDt]
-  int B, n_in, n_in_p, C, loss;
+  int B, n_in, C, loss;
   // Directional form (cvec non-null): only c_i = <dl_i/dz, Rz_L,i> per sample leaves the kernel
   // (the per-sample directional derivative of the loss, for the reweighting mixed term);
   // labels / (Z, targets) give dl/dz for cross-entropy / squared error.
@@ -407,7 +406,7 @@ struct LastGradArgs {
   LastGradSide side[2]; int n_sides;
   int ldt, ldn;
   const float* theta; int hidden;                     // weight net (sides with reweight set)
-  int n_in, n_in_p, C, loss;
+  int n_in, C, loss;
 };
 void launch_last_layer_grad(Ctx&, Elem, const LastGradArgs&);
 
@@ -507,7 +506,7 @@ struct StagedPart {
   int products, S, D, E;              // where the sums, phi' and phi'' go
   int finish;                         // what S is: 0 the sum (+ bias), 1 sum phi', 2 sum phi' + phi'' Rz
 };
-struct StagedWeights { const void* src; int ld, rows, cpr, at; unsigned inv; int group0; };   // cpr: 16-byte chunks a row, one of them room between rows; inv: 2^32 / cpr
+struct StagedWeights { const void* src; int ld, rows, cpr; unsigned inv; int group0; };   // cpr: 16-byte chunks a row, one of them room between rows; inv: 2^32 / cpr
 struct StagedLink { void* outT; int w, wpitch, steps, N, F, D, T, E; };        // weights in LDS, summand, phi', what the backward link adds, phi''
 struct StagedArgs {
   unsigned short unit[STAGED_UNITS];  // part and 16-tile (<< 4) of a unit

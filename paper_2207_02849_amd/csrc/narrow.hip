@@ -494,7 +494,7 @@ __global__ __launch_bounds__(ST) void staged_rop_kernel(StagedArgs) {
   const int ldz = a.ldz, Bp = a.Bp, n_fwd = a.n_fwd, n_bwd = a.n_bwd;
   auto buf = [&](int i) { return buf0 + i * NROWS * pitch; };
   auto slot = [&](int off, int tile) { return (f32x4v*)(lds + off + tile * 1024) + lane; };
-  warm_lines<(sizeof(StagedArgs) + 63) / 64>(0);
+  warm_lines<(sizeof(StagedArgs) + 63) / 64>();
 
   // All weights of the chain, straight to LDS.  A layer's rows are those of its outputs, a row K rounded up to a step (the
   // operands are zero there) and a chunk of room, which spreads the rows over the banks.
@@ -740,7 +740,7 @@ bool staged_plan(const NarrowRopArgs& r, Elem elem, bool curvature, StagedArgs& 
       w.cpr = steps(K) * KS / EPC + 1;
       w.inv = (unsigned)((1ULL << 32) / w.cpr + 1);      // (exact below 2^16 chunks)
       w.group0 = a.groups;
-      w.at = place[back][l] = 1024 * a.groups;
+      place[back][l] = 1024 * a.groups;
       a.groups += (w.rows * w.cpr + 63) / 64;
       at = 1024LL * a.groups;
       if (at > STAGED_LDS) return false;
