@@ -514,8 +514,9 @@ bool has_linear_form(betty_handle h, bool cg) {
 // 12 %, and 87 of the others would have been more than 3 % faster, up to 16 % (single steps of squared errors with 10^5
 // samples and more 29 %).  (By the number of outputs alone: softmax 401 - 12, batch 64, K = 2
 // 36 -> 67 us, conjugate gradient of 64 - 16, batch 512, K = 1 30 -> 57.)  Ridge 64 - 1, batch 512, K = 20: 163 us by
-// launches, 19 us; softmax 200 - 4, batch 128, K = 5: 52 / 38 us (conjugate gradient 84 / 50).  Since its vector launches are one
-// and 16-tiles faster: 5259 calls 0.3 % behind the better form on average, at most 17 %.
+// launches, 16.5 us; softmax 200 - 4, batch 128, K = 5: 52 / 38 us (conjugate gradient 84 / 50).  A step of up to 64 features takes 0.25 us with one
+// output, 0.65 with 16, counted as 0.33.  With launches as they are now 674 calls: 0.4 % behind the better form on average, 6 of them more
+// than 3 %, at most 11.5 %.
 bool use_linear(betty_handle h, bool cg, int K) {
   if (!has_linear_form(h, cg)) return false;
   if (h->tune_linear == 1) return true;
