@@ -88,6 +88,10 @@ def test_squared_errors_of_few_features(dims, batch, bias, monkeypatch):
 def test_squared_errors_of_few_features_take_no_longer_than_many(monkeypatch):
     """A single step: what the form of up to 64 features sets up is no more than what it saves (9.7 against 8.9 us when every
     wavefront did, beside one output)."""
-    few, many = (time_forms(monkeypatch, lambda b, w: b.betty_hypergrad_neumann(w, w, 1, 1e-4), ("linear=1",), dims=(n, 1), act="none", loss="mse",
-                            hp="l2", prec="fp32", has_bias=True, batch_train=200, batch_val=100)[0] for n in (7, 64))
-    assert few < many, (few, many)
+    call = lambda b, w: b.betty_hypergrad_neumann(w, w, 1, 1e-4)
+    ratios = []
+    for _ in range(9):                                    # (close together: the card's speed changes now and then)
+        few, many = (time_forms(monkeypatch, call, ("linear=1",), rounds=3, dims=(n, 1), act="none", loss="mse", hp="l2", prec="fp32",
+                                has_bias=True, batch_train=200, batch_val=100)[0] for n in (7, 64))
+        ratios.append(few / many)
+    assert np.median(ratios) < 1.0, ratios
